@@ -686,122 +686,276 @@ __global__ void k_csr_to_dense(int64_t n, const int64_t *__restrict__ rowptr, co
     for (int64_t e = rowptr[i]; e < rowptr[i + 1]; e++) D[i * n + col[e]] = val[e];
 }
 
-// Blocked Gauss-Jordan inversion of an SPD matrix (no pivoting: every
-// leading block of an SPD matrix and every Schur complement stay SPD).  For
-// the pivot block K = [k0, k0+b):  P = D_KK,  R_K: = P^{-1} D_K: (with P^{-1}
-// itself in the K columns),  S_:K = D_:K (old), then
-//   D_ij <- R_{i-k0, j}                                  for i in K,
-//   D_ij <- [j not in K] D_ij - sum_t S_it R_tj          otherwise.
-constexpr int GJB = 64;  // pivot block
+// Blocked symmetric Gauss-Jordan (sweep) inversion of an SPD matrix, in
+// place (no pivoting: every leading block of an SPD matrix and every Schur
+// complement stay SPD).  Sweeping the pivot block K: P = D_KK,
+//   D_Kj <- R_j = P^{-1} D_Kj,  D_iK <- -D_iK P^{-1},  D_KK <- P^{-1},
+//   D_ij <- D_ij - D_iK R_j                            otherwise.
+// Between two swept or two unswept blocks the matrix stays symmetric, between
+// a swept and an unswept one antisymmetric, so only the tiles on and below the
+// diagonal are kept: half the operations and half the bytes of a full
+// sweep.  Each step is two launches: a panel (S = D_:K and R for every tile
+// row, the new row and column K), then the update of all other tiles on the
+// FP64 matrix cores; the block of the next pivot tile inverts it right after
+// updating it, beside the other tiles' updates, so the 64 scalar steps of a
+// pivot are not a launch of their own.
+// Bounds: the update moves 8 n^2 bytes a step (n = 3118: 78 MB, resident in
+// the last-level cache) and does 32 n^2 multiply-adds; on small n the pivot's
+// serial chain (64 steps of LDS, barrier, reciprocal).  Measured a step:
+// n = 3118 update 36 and panel 10 us (a full sweep with the pivot as its own
+// launch: 103 + 59 + 18 + 5), n = 517 27 and 8 us (19 + 54 + 16 + 5).
+constexpr int GJB = 64;  // pivot block and tile size
 
-// P^{-1} by scalar Gauss-Jordan in LDS (one workgroup, b <= 64).  The block
-// is padded to 64 x 64 with the identity (its inverse is then diag(P^{-1}, I)),
-// each of the 1024 threads owns four fixed entries, and the block is
-// double-buffered so that one barrier per pivot suffices.
-__global__ void __launch_bounds__(1024) k_bgj_pivot(const double *__restrict__ D, int64_t n, int64_t k0, int b,
-                                                    double *__restrict__ Pinv, int *__restrict__ bad) {
-    __shared__ double A[2][GJB][GJB + 1];
-    const int tid = threadIdx.x;
+// P^{-1} of the symmetric 64 x 64 block in A, one workgroup of 256 threads.
+// Thread (ti, tj) keeps the entries (ti + 16 a, tj + 16 b) in registers; each
+// of the 64 scalar Gauss-Jordan steps shares its pivot row and column through
+// double-buffered LDS (one barrier a step).  rc: 4 * 64 doubles.
+__device__ __forceinline__ void invert_pivot(const double (*__restrict__ A)[GJB + 1], double *__restrict__ rc,
+                                    double *__restrict__ Pinv, int *__restrict__ bad) {
+    const int tid = threadIdx.x, ti = tid >> 4, tj = tid & 15;
+    double v[4][4];
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
-        int t = tid + 1024 * q, i = t >> 6, j = t & 63;
-        A[0][i][j] = (i < b && j < b) ? D[(k0 + i) * n + k0 + j] : (i == j ? 1.0 : 0.0);
+    for (int a = 0; a < 4; a++)
+#pragma unroll
+        for (int c = 0; c < 4; c++) v[a][c] = A[ti + 16 * a][tj + 16 * c];
+    bool neg = false;
+#pragma unroll
+    for (int ka = 0; ka < 4; ka++)
+#pragma unroll 1
+        for (int kk = 0; kk < 16; kk++) {
+            const int k = 16 * ka + kk;
+            double *row = rc + (k & 1) * 2 * GJB, *col = row + GJB;
+            // the owners hand out row and column k and clear them: with
+            // f_k = -1/p and r_k = 1 the one update below serves every entry
+            if (ti == kk)
+#pragma unroll
+                for (int c = 0; c < 4; c++) {
+                    row[tj + 16 * c] = v[ka][c];
+                    if (c != ka || tj != kk) v[ka][c] = 0.0;
+                }
+            if (tj == kk)
+#pragma unroll
+                for (int a = 0; a < 4; a++) {
+                    if (a != ka || ti != kk) col[ti + 16 * a] = v[a][ka];
+                    v[a][ka] = 0.0;
+                }
+            __syncthreads();
+            double p = row[k];
+            if (!(p > 0.0)) {
+                neg = true;
+                p = 1.0;  // keep going; the caller reports the failure
+            }
+            // 1/p: hardware estimate and two Newton steps
+            double ip = __builtin_amdgcn_rcp(p);
+            ip = fma(fma(-p, ip, 1.0), ip, ip);
+            ip = fma(fma(-p, ip, 1.0), ip, ip);
+            double r[4], f[4];
+#pragma unroll
+            for (int c = 0; c < 4; c++) r[c] = c == ka && tj == kk ? 1.0 : row[tj + 16 * c];
+#pragma unroll
+            for (int a = 0; a < 4; a++) f[a] = a == ka && ti == kk ? -ip : col[ti + 16 * a] * ip;
+#pragma unroll
+            for (int a = 0; a < 4; a++)
+#pragma unroll
+                for (int c = 0; c < 4; c++) v[a][c] = fma(-f[a], r[c], v[a][c]);
+        }
+    if (neg && tid == 0) *bad = 1;
+#pragma unroll
+    for (int a = 0; a < 4; a++)
+#pragma unroll
+        for (int c = 0; c < 4; c++) Pinv[(ti + 16 * a) * GJB + tj + 16 * c] = v[a][c];
+}
+
+// The first pivot block (padded to 64 x 64 with the identity: its inverse is
+// then diag(P^{-1}, I)).
+__global__ void __launch_bounds__(256) k_bgj_pivot(const double *__restrict__ D, int64_t n,
+                                                   double *__restrict__ Pinv, int *__restrict__ bad) {
+    __shared__ double A[GJB][GJB + 1], rc[4 * GJB];
+    double d[16];
+#pragma unroll
+    for (int q = 0; q < 16; q++) {
+        const int t = threadIdx.x + 256 * q, i = t / GJB, j = t % GJB;
+        // the lower triangle holds the matrix
+        const int lo = i < j ? i : j, hi = i < j ? j : i;
+        d[q] = hi < n ? D[(int64_t)hi * n + lo] : (i == j ? 1.0 : 0.0);
+    }
+#pragma unroll
+    for (int q = 0; q < 16; q++) {
+        const int t = threadIdx.x + 256 * q;
+        A[t / GJB][t % GJB] = d[q];
     }
     __syncthreads();
-    int cur = 0;
-    for (int k = 0; k < b; k++, cur ^= 1) {
-        double p = A[cur][k][k];
-        if (!(p > 0.0)) {
-            if (tid == 0) *bad = 1;
-            p = 1.0;  // keep going; the caller reports the failure
-        }
-        const double ip = 1.0 / p;
-#pragma unroll
-        for (int q = 0; q < 4; q++) {
-            int t = tid + 1024 * q, i = t >> 6, j = t & 63;
-            double v;
-            if (i == k) v = (j == k) ? ip : A[cur][k][j] * ip;
-            else if (j == k) v = -A[cur][i][k] * ip;
-            else v = A[cur][i][j] - A[cur][i][k] * ip * A[cur][k][j];
-            A[cur ^ 1][i][j] = v;
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-        int t = tid + 1024 * q, i = t >> 6, j = t & 63;
-        if (i < b && j < b) Pinv[i * GJB + j] = A[cur][i][j];
-    }
+    invert_pivot(A, rc, Pinv, bad);
 }
 
-// R (b x n): one thread per entry, blockIdx.y = row r of the pivot block.
-__global__ void k_bgj_panel_R(const double *__restrict__ D, int64_t n, int64_t k0, int b,
-                              const double *__restrict__ Pinv, double *__restrict__ R) {
-    int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int r = blockIdx.y;
-    if (j >= n || r >= b) return;
-    double v;
-    if (j >= k0 && j < k0 + b) {
-        v = Pinv[r * GJB + (j - k0)];
-    } else {
-        v = 0.0;
-        for (int t = 0; t < b; t++) v += Pinv[r * GJB + t] * D[(k0 + t) * n + j];
-    }
-    R[(int64_t)r * n + j] = v;
-}
-
-// S (n x GJB): the old column block, one thread per entry.
-__global__ void k_bgj_panel_S(const double *__restrict__ D, int64_t n, int64_t k0, int b, double *__restrict__ S) {
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n * GJB) return;
-    int64_t j = t / GJB;
-    int c = (int)(t - j * GJB);
-    if (c < b) S[t] = D[j * n + k0 + c];
-}
-
-// Rank-b update on 64x64 tiles with FP64 matrix cores: the four wavefronts of
-// a block each own 16 rows of the tile and accumulate four 16x16 blocks with
-// v_mfma_f64_16x16x4f64 over the (zero-padded) 64-long inner dimension.
-// Operand layout of that instruction: lane l supplies A[l%16][l/16] and
-// B[l/16][l%16]; result register v of lane l is D[l/16 + 4v][l%16].
+// v_mfma_f64_16x16x4f64: lane l supplies A[l%16][l/16] and B[l/16][l%16];
+// result register v of lane l is D[l/16 + 4v][l%16].
 typedef double rich_d4 __attribute__((ext_vector_type(4)));
-__global__ void __launch_bounds__(256) k_bgj_update(double *__restrict__ D, int64_t n, int64_t k0, int b,
-                                                     const double *__restrict__ R, const double *__restrict__ S) {
-    __shared__ double Ss[GJB][GJB + 1];  // [row in tile][t]
-    __shared__ double Rs[GJB][GJB + 1];  // [t][col in tile]
-    int64_t i0 = (int64_t)blockIdx.y * GJB, j0 = (int64_t)blockIdx.x * GJB;
-    for (int t = threadIdx.x; t < GJB * GJB; t += blockDim.x) {
-        int r = t / GJB, c = t - r * GJB;
-        int64_t gi = i0 + r, gj = j0 + c;
-        Ss[r][c] = (gi < n && c < b) ? S[gi * GJB + c] : 0.0;
-        Rs[r][c] = (r < b && gj < n) ? R[(int64_t)r * n + gj] : 0.0;
+
+// Panel of pivot block K, one workgroup per tile row I: X = D_KI as the step
+// sees it (from the stored tile (I,K) below the pivot, (K,I) before it),
+// R_I = P^{-1} X, S_I = D_IK; the new row and column K go back to D.
+// S (npad x 64) and RT = R^T (npad x 64) are zero where a row is past n.
+__global__ void __launch_bounds__(256) k_bgj_panel(double *__restrict__ D, int64_t n, int K,
+                                                   const double *__restrict__ Pinv, double *__restrict__ S,
+                                                   double *__restrict__ RT) {
+    __shared__ double X[GJB][GJB + 1];  // [t][i]
+    __shared__ double Q[GJB][GJB + 1];  // Pinv, then R [r][i]
+    const int I = blockIdx.x;
+    const int64_t i0 = (int64_t)I * GJB, k0 = (int64_t)K * GJB;
+    // every load of the tile is issued before the first is stored in LDS
+    double pq[16], dq[16];
+    const int64_t rb = I > K ? i0 : k0, cb = I > K ? k0 : i0;  // the stored tile
+#pragma unroll
+    for (int q = 0; q < 16; q++) {
+        const int t = threadIdx.x + 256 * q, a = t / GJB, c = t % GJB;
+        pq[q] = Pinv[t];
+        dq[q] = (I != K && rb + a < n && cb + c < n) ? D[(rb + a) * n + cb + c] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < 16; q++) {
+        const int t = threadIdx.x + 256 * q, a = t / GJB, c = t % GJB;
+        Q[a][c] = pq[q];
+        if (I > K) X[c][a] = dq[q];
+        else X[a][c] = dq[q];
     }
     __syncthreads();
-    const int w = threadIdx.x / 64, l = threadIdx.x % 64;
-    const int li = l % 16, lk = l / 16;
+    if (I == K) {
+        for (int t = threadIdx.x; t < GJB * GJB; t += 256) {
+            const int a = t / GJB, c = t % GJB;
+            if (k0 + a < n && k0 + c < n) D[(k0 + a) * n + k0 + c] = Q[a][c];
+        }
+        return;
+    }
+    const int w = threadIdx.x / 64, l = threadIdx.x % 64, li = l % 16, lk = l / 16;
     rich_d4 acc[4];
 #pragma unroll
     for (int c = 0; c < 4; c++) acc[c] = (rich_d4){0.0, 0.0, 0.0, 0.0};
     for (int t = 0; t < GJB; t += 4) {
-        double a = Ss[16 * w + li][t + lk];
+        const double a = Q[16 * w + li][t + lk];
 #pragma unroll
-        for (int c = 0; c < 4; c++) acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Rs[t + lk][16 * c + li], acc[c], 0, 0, 0);
+        for (int c = 0; c < 4; c++)
+            acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, X[t + lk][16 * c + li], acc[c], 0, 0, 0);
     }
+    __syncthreads();
 #pragma unroll
-    for (int c = 0; c < 4; c++) {
-        int64_t gj = j0 + 16 * c + li;
-        if (gj >= n) continue;
-        bool colK = gj >= k0 && gj < k0 + b;
+    for (int c = 0; c < 4; c++)
+#pragma unroll
+        for (int v = 0; v < 4; v++) Q[16 * w + lk + 4 * v][16 * c + li] = acc[c][v];
+    __syncthreads();
+    const double sg = I > K ? 1.0 : -1.0;
+    for (int t = threadIdx.x; t < GJB * GJB; t += 256) {
+        const int a = t / GJB, c = t % GJB;
+        S[(i0 + a) * GJB + c] = sg * X[c][a];
+        RT[(i0 + a) * GJB + c] = Q[c][a];
+        if (I > K) {
+            if (i0 + a < n && k0 + c < n) D[(i0 + a) * n + k0 + c] = -Q[c][a];
+        } else if (k0 + a < n && i0 + c < n) {
+            D[(k0 + a) * n + i0 + c] = Q[a][c];
+        }
+    }
+}
+
+// Update of the tiles (I, J), I >= J, I and J other than K: D_IJ -= S_I R_J.
+// The tile starts in the accumulators (S enters negated); the 64-long inner
+// index is dealt so that lane group lk takes 16 consecutive entries of its
+// rows, read as 16-byte pairs.  Block 0 takes the next pivot tile (K+1, K+1)
+// and inverts it; the others take the remaining tiles in order.
+__global__ void __launch_bounds__(256) k_bgj_update(double *__restrict__ D, int64_t n, int K, int tiles,
+                                                    const double *__restrict__ S, const double *__restrict__ RT,
+                                                    double *__restrict__ Pinv, int *__restrict__ bad) {
+    __shared__ double B[GJB][GJB + 1];  // RT tile [j][t]; the next pivot's tile
+    __shared__ double rc[4 * GJB];
+    // block 0: the next pivot; block b: the b-th remaining tile of the lower triangle without row and column K
+    const bool last = K == tiles - 1;
+    int I, J;
+    if (blockIdx.x == 0 && !last) {
+        I = J = K + 1;
+    } else {
+        // tile b of a lower triangle of tiles - 1 rows, renumbered past K
+        const int64_t b = (int64_t)blockIdx.x - (last ? 0 : 1);
+        int r = (int)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
+        while ((int64_t)(r + 1) * (r + 2) / 2 <= b) r++;
+        while ((int64_t)r * (r + 1) / 2 > b) r--;
+        const int c = (int)(b - (int64_t)r * (r + 1) / 2);
+        I = r < K ? r : r + 1;
+        J = c < K ? c : c + 1;
+        if (!last && I == K + 1 && J == K + 1) return;  // block 0's
+    }
+    const int64_t i0 = (int64_t)I * GJB, j0 = (int64_t)J * GJB;
+    const int w = threadIdx.x / 64, l = threadIdx.x % 64, li = l % 16, lk = l / 16;
+    const bool piv = blockIdx.x == 0 && !last;
+    rich_d4 acc[4];
+#pragma unroll
+    for (int c = 0; c < 4; c++)
 #pragma unroll
         for (int v = 0; v < 4; v++) {
-            int64_t gi = i0 + 16 * w + lk + 4 * v;
-            if (gi >= n) continue;
-            bool rowK = gi >= k0 && gi < k0 + b;
-            double out;
-            if (rowK) out = R[(gi - k0) * n + gj];
-            else out = (colK ? 0.0 : D[gi * n + gj]) - acc[c][v];
-            D[gi * n + gj] = out;
+            const int64_t gi = i0 + 16 * w + lk + 4 * v, gj = j0 + 16 * c + li;
+            // the pivot tile reads its lower triangle (the upper one is not kept)
+            const int64_t hi = piv && gj > gi ? gj : gi, lo = piv && gj > gi ? gi : gj;
+            acc[c][v] = hi < n && lo < n ? D[hi * n + lo] : (piv && gi == gj ? 1.0 : 0.0);
         }
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    d2 sa[8];
+    const d2 *sp = reinterpret_cast<const d2 *>(S + (i0 + 16 * w + li) * GJB + 16 * lk);
+#pragma unroll
+    for (int s = 0; s < 8; s++) sa[s] = sp[s];
+    double bq[16];
+#pragma unroll
+    for (int q = 0; q < 16; q++) bq[q] = RT[j0 * GJB + threadIdx.x + 256 * q];
+#pragma unroll
+    for (int q = 0; q < 16; q++) {
+        const int t = threadIdx.x + 256 * q;
+        B[t / GJB][t % GJB] = bq[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < 16; s++) {
+        const double a = -(s & 1 ? sa[s / 2].y : sa[s / 2].x);
+#pragma unroll
+        for (int c = 0; c < 4; c++)
+            acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, B[16 * c + li][16 * lk + s], acc[c], 0, 0, 0);
+    }
+    if (piv) {
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < 4; c++)
+#pragma unroll
+            for (int v = 0; v < 4; v++) B[16 * w + lk + 4 * v][16 * c + li] = acc[c][v];
+        __syncthreads();
+        invert_pivot(B, rc, Pinv, bad);
+        return;
+    }
+#pragma unroll
+    for (int c = 0; c < 4; c++)
+#pragma unroll
+        for (int v = 0; v < 4; v++) {
+            const int64_t gi = i0 + 16 * w + lk + 4 * v, gj = j0 + 16 * c + li;
+            if (gi < n && gj < n) D[gi * n + gj] = acc[c][v];
+        }
+}
+
+// The swept matrix is the inverse, its lower triangle stored: copy it to the
+// upper one, in FP64 (in place) or rounded into the FP32 copy Df.
+template <bool F32>
+__global__ void __launch_bounds__(256) k_bgj_mirror(double *__restrict__ D, int64_t n, float *__restrict__ Df) {
+    __shared__ double T[GJB][GJB + 1];
+    const int I = blockIdx.y, J = blockIdx.x;
+    if (J > I) return;
+    const int64_t i0 = (int64_t)I * GJB, j0 = (int64_t)J * GJB;
+    for (int t = threadIdx.x; t < GJB * GJB; t += 256) {
+        const int a = t / GJB, c = t % GJB;
+        if (i0 + a >= n || j0 + c >= n) continue;
+        const double v = D[(i0 + a) * n + j0 + c];
+        T[a][c] = v;
+        if (F32 && (I > J || c <= a)) Df[(i0 + a) * n + j0 + c] = f32_sat(v);
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < GJB * GJB; t += 256) {
+        const int a = t / GJB, c = t % GJB;  // upper entry (j0 + a, i0 + c)
+        if (j0 + a >= n || i0 + c >= n || (I == J && c <= a)) continue;
+        if (F32) Df[(j0 + a) * n + i0 + c] = f32_sat(T[c][a]);
+        else D[(j0 + a) * n + i0 + c] = T[c][a];
     }
 }
 
@@ -1051,27 +1205,32 @@ rich_status compose_agg(int32_t *comp, const int32_t *a, int64_t n, hipStream_t 
     return RICH_OK;
 }
 
-// Inverse of an SPD CSR matrix into a dense row-major n x n buffer, using
-// the workspace of dense_inverse_ws (no allocation: it runs on every refresh).
-int64_t dense_inverse_ws(int64_t n) { return (int64_t)GJB * GJB + 2 * (int64_t)GJB * n + 1; }
+// Inverse of an SPD CSR matrix, dense row-major n x n, using the workspace of
+// dense_inverse_ws (no allocation: it runs on every refresh).  With Df the
+// result is Df, rounded to FP32, and D holds the lower triangle only.
+int64_t dense_inverse_ws(int64_t n) {
+    const int64_t npad = (n + GJB - 1) / GJB * GJB;
+    return (int64_t)GJB * GJB + 2 * (int64_t)GJB * npad + 1;
+}
 
-rich_status dense_inverse(const CsrDev &A, double *D, double *ws, hipStream_t s) {
+rich_status dense_inverse(const CsrDev &A, double *D, float *Df, double *ws, hipStream_t s) {
     int64_t n = A.n;
     if (n == 0) return RICH_OK;
-    double *Pinv = ws, *R = ws + GJB * GJB, *S = R + (int64_t)GJB * n;
-    int *bad = reinterpret_cast<int *>(S + (int64_t)GJB * n);
+    const int tiles = (int)((n + GJB - 1) / GJB);
+    double *Pinv = ws, *S = ws + GJB * GJB, *RT = S + (int64_t)GJB * GJB * tiles;
+    int *bad = reinterpret_cast<int *>(RT + (int64_t)GJB * GJB * tiles);
     HIP_TRY(hipMemsetAsync(bad, 0, sizeof(int), s));
     HIP_TRY(hipMemsetAsync(D, 0, (size_t)n * n * sizeof(double), s));
     k_csr_to_dense<<<nblocks(n), TPB, 0, s>>>(n, A.rowptr, A.col, A.val, D);
+    k_bgj_pivot<<<1, 256, 0, s>>>(D, n, Pinv, bad);
     LAUNCH_CHECK();
-    unsigned tiles = (unsigned)((n + GJB - 1) / GJB);
-    for (int64_t k0 = 0; k0 < n; k0 += GJB) {
-        int b = (int)std::min<int64_t>(GJB, n - k0);
-        k_bgj_pivot<<<1, 1024, 0, s>>>(D, n, k0, b, Pinv, bad);
-        k_bgj_panel_R<<<dim3(nblocks(n), b), TPB, 0, s>>>(D, n, k0, b, Pinv, R);
-        k_bgj_panel_S<<<nblocks(n * GJB), TPB, 0, s>>>(D, n, k0, b, S);
-        k_bgj_update<<<dim3(tiles, tiles), 256, 0, s>>>(D, n, k0, b, R, S);
+    const unsigned rest = (unsigned)((int64_t)(tiles - 1) * tiles / 2);  // tiles off row and column K
+    for (int K = 0; K < tiles; K++) {
+        k_bgj_panel<<<tiles, 256, 0, s>>>(D, n, K, Pinv, S, RT);
+        if (rest) k_bgj_update<<<rest + (K < tiles - 1 ? 1 : 0), 256, 0, s>>>(D, n, K, tiles, S, RT, Pinv, bad);
     }
+    if (Df) k_bgj_mirror<true><<<dim3(tiles, tiles), 256, 0, s>>>(D, n, Df);
+    else k_bgj_mirror<false><<<dim3(tiles, tiles), 256, 0, s>>>(D, n, nullptr);
     LAUNCH_CHECK();
     int hb = 0;
     HIP_TRY(hipMemcpyAsync(&hb, bad, sizeof(int), hipMemcpyDeviceToHost, s));

@@ -1,0 +1,51 @@
+"""Coarse-level kernels of the preconditioner at the edges of their tiles and
+splits, against the oracle or plain linear algebra in FP64."""
+import numpy as np
+import pytest
+import scipy.sparse as sp
+import scipy.sparse.linalg as spla
+
+import synth
+from tests.helpers import box_problem, random_heads, random_ks
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available(), "GPU tests need a GPU"
+    return t
+
+
+@pytest.fixture(scope="module")
+def rich():
+    import paper_2112_05051_amd as r
+    r.load()
+    return r
+
+
+def dev(torch, a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+
+
+# A one-level hierarchy applies the dense inverse of M itself: rows below, at
+# and above the 64-row tiles, one to twelve tiles.  The inverse's error is
+# kappa(M) eps; kappa <= 1e4 on these boxes (dt 10 s), FP32 rounds it to 6e-8
+# per entry (sum of n terms).
+@pytest.mark.parametrize("precision,tol", [(synth.FP64, 1e-10), (synth.MIXED, 1e-5)])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (63, 1, 1), (8, 8, 1), (13, 5, 1), (4, 4, 8), (43, 3, 1), (8, 8, 3),
+                                   (11, 11, 6)])
+def test_dense_inverse_tiles(rich, torch, shape, precision, tol):
+    P = box_problem(*shape, dt=10.0)
+    ks = random_ks(P, 41)
+    s = rich.Solver(P, synth.Options(amg_max_levels=1, precision=precision), dev(torch, ks))
+    for seed in (42, 43):  # set-up, then a refresh
+        s.assemble(dev(torch, random_heads(P.n, seed, -70, -30)))
+        assert s.levels() == 1
+        rp, col, val = s.export_csr(rich.WHICH_A, 0)
+        M = sp.csc_matrix(sp.csr_matrix((val, col, rp), shape=(P.n, P.n)))
+        b = np.random.default_rng(seed).standard_normal(P.n)
+        x = s.apply_prec(dev(torch, b)).cpu().numpy()
+        xo = np.atleast_1d(spla.spsolve(M, b))
+        assert np.linalg.norm(x - xo) <= tol * np.linalg.norm(xo)
