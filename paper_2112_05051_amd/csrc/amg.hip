@@ -341,6 +341,110 @@ __global__ void __launch_bounds__(64) k_gal_numeric(int64_t nc, const int64_t *_
     }
 }
 
+// The numeric product again and again on a fixed pattern (the refreshes): the
+// fine values that make up each coarse entry are listed once at set-up, in the
+// order of k_gal_numeric, so a refresh is one gather-sum per coarse entry: no
+// search, no LDS accumulators (which held k_gal_numeric at six waves a CU), and
+// level 0 reads the stencil arrays themselves instead of a CSR copy of them.
+// Bound by the list and value reads (12 bytes per fine entry).  A refresh at
+// 256^3, five levels: 1.1 ms, against 4.0 with k_gal_numeric and 1.2 for the
+// CSR copy of M.
+// FILL = false counts the sources of each entry, FILL = true lists them; one
+// thread per coarse row, rows of up to GAL_REG entries count in LDS.
+struct StencilIndex {  // value index of CSR entry (i, j): e itself, or its place in the M arrays
+    int nx, ny, nz;    // nx = 0: CSR
+    __device__ uint32_t operator()(int64_t n, int64_t i, int64_t j, int64_t e) const {
+        if (nx == 0) return (uint32_t)e;
+        if (i == j) return (uint32_t)(M_D * n + i);
+        const int64_t lo = i < j ? i : j, d = i < j ? j - i : i - j;
+        // an axis of one cell has no coupling; the others differ in their stride
+        const int t = nx > 1 && d == 1 ? M_XP : ny > 1 && d == nx ? M_YP : M_ZP;
+        return (uint32_t)(t * n + lo);
+    }
+};
+template <bool FILL>
+__global__ void __launch_bounds__(64) k_gal_sources(int64_t nc, int64_t n, StencilIndex ix,
+                                                    const int64_t *__restrict__ mptr, const int32_t *__restrict__ mem,
+                                                    const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col,
+                                                    const int32_t *__restrict__ agg, const int64_t *__restrict__ crow,
+                                                    const int32_t *__restrict__ ccol, int64_t *__restrict__ cnt,
+                                                    const uint32_t *__restrict__ gptr, uint32_t *__restrict__ gsrc) {
+    __shared__ uint32_t cur_s[GAL_REG * 64];
+    __shared__ int32_t cj_s[GAL_REG * 64];
+    const int64_t I = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (I >= nc) return;
+    const int t = threadIdx.x;
+    const int64_t a = crow[I], b = crow[I + 1];
+    const int64_t len = b - a;
+    if (len > GAL_REG) {  // counts (and, filling, the next free places) in memory
+        for (int64_t q = a; q < b; q++) cnt[q] = 0;
+        for (int64_t m = mptr[I]; m < mptr[I + 1]; m++) {
+            const int64_t i = mem[m];
+            for (int64_t e = rowptr[i]; e < rowptr[i + 1]; e++) {
+                const int32_t J = agg[col[e]];
+                int64_t lo = a, hi = b - 1;
+                while (lo < hi) {
+                    const int64_t mid = (lo + hi) >> 1;
+                    if (ccol[mid] < J) lo = mid + 1;
+                    else hi = mid;
+                }
+                if (FILL) gsrc[gptr[lo] + cnt[lo]] = ix(n, i, col[e], e);
+                cnt[lo]++;
+            }
+        }
+        return;
+    }
+    for (int q = 0; q < len; q++) {
+        cj_s[q * 64 + t] = ccol[a + q];
+        cur_s[q * 64 + t] = FILL ? gptr[a + q] : 0u;
+    }
+    for (int64_t m = mptr[I]; m < mptr[I + 1]; m++) {
+        const int64_t i = mem[m];
+        for (int64_t e = rowptr[i]; e < rowptr[i + 1]; e++) {
+            const int32_t J = agg[col[e]];
+            int lo = 0, hi = (int)len - 1;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (cj_s[mid * 64 + t] < J) lo = mid + 1;
+                else hi = mid;
+            }
+            const uint32_t at = cur_s[lo * 64 + t]++;
+            if (FILL) gsrc[at] = ix(n, i, col[e], e);
+        }
+    }
+    if (!FILL)
+        for (int q = 0; q < len; q++) cnt[a + q] = cur_s[q * 64 + t];
+}
+
+__global__ void k_narrow_u32(int64_t n, const int64_t *__restrict__ in, uint32_t *__restrict__ out) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) out[i] = (uint32_t)in[i];
+}
+
+template <bool F32>
+__global__ void __launch_bounds__(256) k_gal_sum(int64_t cnnz, const uint32_t *__restrict__ gptr,
+                                                 const uint32_t *__restrict__ gsrc, const double *__restrict__ val,
+                                                 double *__restrict__ cval, float *__restrict__ cvalf) {
+    const int64_t q = (int64_t)xcd_block() * blockDim.x + threadIdx.x;
+    if (q >= cnnz) return;
+    const uint32_t t0 = gptr[q], t1 = gptr[q + 1];
+    double s = 0.0;
+    // four sources in flight, added in list order
+    for (uint32_t t = t0; t < t1; t += 4) {
+        uint32_t ix[4];
+        double v[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) ix[u] = gsrc[t + u < t1 ? t + u : t1 - 1];
+#pragma unroll
+        for (int u = 0; u < 4; u++) v[u] = val[ix[u]];
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+            if (t + u < t1) s += v[u];
+    }
+    cval[q] = s;
+    if (F32) cvalf[q] = f32_sat(s);
+}
+
 __global__ void k_csr_invd(int64_t n, const int64_t *__restrict__ rowptr, const double *__restrict__ val,
                            double *__restrict__ invd, float *__restrict__ invdf) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1143,6 +1247,38 @@ rich_status galerkin_numeric(const CsrDev &A, const int32_t *agg, const int64_t 
     if (C.n == 0) return RICH_OK;
     k_gal_numeric<<<nblocks(C.n, 64), 64, 0, s>>>(C.n, mptr, mem, A.rowptr, A.col, A.val, agg, C.rowptr, C.col,
                                                   C.val);
+    LAUNCH_CHECK();
+    return RICH_OK;
+}
+
+rich_status galerkin_sources(const CsrDev &A, const int32_t *agg, const int64_t *mptr, const int32_t *mem,
+                             const CsrDev &C, const Grid3 *g, uint32_t *gptr, uint32_t *gsrc, hipStream_t s) {
+    if (C.n == 0) return RICH_OK;
+    DevAlloc tmp;
+    int64_t *cnt, *ptr, *stmp;
+    RICH_TRY(tmp.get(&cnt, C.nnz));
+    RICH_TRY(tmp.get(&ptr, C.nnz + 1));
+    RICH_TRY(tmp.get(&stmp, scan_tmp_size(C.nnz)));
+    const StencilIndex ix{g ? g->nx : 0, g ? g->ny : 0, g ? g->nz : 0};
+    const unsigned nb = nblocks(C.n, 64);
+    k_gal_sources<false><<<nb, 64, 0, s>>>(C.n, A.n, ix, mptr, mem, A.rowptr, A.col, agg, C.rowptr, C.col, cnt,
+                                           nullptr, nullptr);
+    LAUNCH_CHECK();
+    RICH_TRY(scan_exclusive_i64(cnt, ptr, C.nnz, stmp, s));
+    k_narrow_u32<<<nblocks(C.nnz + 1), TPB, 0, s>>>(C.nnz + 1, ptr, gptr);
+    k_gal_sources<true><<<nb, 64, 0, s>>>(C.n, A.n, ix, mptr, mem, A.rowptr, A.col, agg, C.rowptr, C.col, cnt, gptr,
+                                          gsrc);
+    LAUNCH_CHECK();
+    HIP_TRY(hipStreamSynchronize(s));  // tmp is freed on return
+    return RICH_OK;
+}
+
+rich_status galerkin_sum(int64_t cnnz, const uint32_t *gptr, const uint32_t *gsrc, const double *val, double *cval,
+                         float *cvalf, hipStream_t s) {
+    if (cnnz == 0) return RICH_OK;
+    const unsigned nb = xcd_grid(cnnz, 256);
+    if (cvalf) k_gal_sum<true><<<nb, 256, 0, s>>>(cnnz, gptr, gsrc, val, cval, cvalf);
+    else k_gal_sum<false><<<nb, 256, 0, s>>>(cnnz, gptr, gsrc, val, cval, nullptr);
     LAUNCH_CHECK();
     return RICH_OK;
 }

@@ -363,6 +363,11 @@ struct Level {
     int64_t nrb = 0;
     int64_t *rb = nullptr;  // nrb + 1 (first row, its first entry) pairs; nullptr: rows too long, plain CSR kernels
     int sg = 1;             // lanes per row in the kernels' reduction phase
+    // numeric refresh of the next level's matrix (piecewise-constant P): the
+    // values of this level that add up to each coarse entry, in the order they
+    // are added; nullptr: galerkin_numeric refreshes it
+    uint32_t *gptr = nullptr;  // coarse nnz + 1
+    uint32_t *gsrc = nullptr;  // nnz: value indices (level 0: into the M stencil arrays)
 };
 constexpr int STREAM_CHUNK = 1536, STREAM_MAXROW = 512;
 
@@ -409,6 +414,15 @@ rich_status galerkin_symbolic(const CsrDev &A, const int32_t *agg, int64_t nc, c
                               const int32_t *mem, CsrDev *C, DevAlloc &mem_out, hipStream_t s);
 rich_status galerkin_numeric(const CsrDev &A, const int32_t *agg, const int64_t *mptr, const int32_t *mem,
                              const CsrDev &C, hipStream_t s);
+// The source lists (gptr: C.nnz + 1, gsrc: A.nnz) of galerkin_sum.  g set: A is
+// the level-0 matrix of that grid and the sources index the M stencil arrays,
+// else A's values.  Needs A.nnz and 4 A.n below 2^32.
+rich_status galerkin_sources(const CsrDev &A, const int32_t *agg, const int64_t *mptr, const int32_t *mem,
+                             const CsrDev &C, const Grid3 *g, uint32_t *gptr, uint32_t *gsrc, hipStream_t s);
+// cval[q] = sum of val at q's sources, and its FP32 copy when cvalf is set:
+// the values galerkin_numeric gives, bit for bit
+rich_status galerkin_sum(int64_t cnnz, const uint32_t *gptr, const uint32_t *gsrc, const double *val, double *cval,
+                         float *cvalf, hipStream_t s);
 // Fused serving launches (solver.hip): a batcher gathers the preconditioned
 // products of the GMRES solves of the simulations attached to it and its
 // thread issues them as batched launches on its own stream (on the device

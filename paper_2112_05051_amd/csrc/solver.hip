@@ -196,7 +196,7 @@ rich_status build_hierarchy(rich_ctx *h) {
     const Phys &P = h->P;
     int64_t N = h->N;
     DevAlloc tmp;
-    // level-0 CSR of M, kept for the numeric refreshes of the coarse matrices
+    // level-0 CSR of M: the set-up's input (kept only where a refresh needs it, below)
     CsrDev A0;
     A0.n = N;
     int64_t *cnt, *stmp;
@@ -289,6 +289,14 @@ rich_status build_hierarchy(rich_ctx *h) {
         } else {
             RICH_TRY(galerkin_symbolic(levA, comp, nc, Lf.mptr, Lf.mem, &C, H.mem, s));
             RICH_TRY(galerkin_numeric(levA, comp, Lf.mptr, Lf.mem, C, s));
+            // what the refreshes sum (32-bit indices; the M arrays hold 4 N values)
+            if (h->O.amg_refresh && levA.nnz < ((int64_t)1 << 32) && (l > 0 || N < ((int64_t)1 << 30))) {
+                const Grid3 g{P.nx, P.ny, P.nz};
+                RICH_TRY(H.mem.get(&Lf.gptr, C.nnz + 1));
+                RICH_TRY(H.mem.get(&Lf.gsrc, levA.nnz));
+                RICH_TRY(galerkin_sources(levA, comp, Lf.mptr, Lf.mem, C, l == 0 ? &g : nullptr, Lf.gptr, Lf.gsrc,
+                                          s));
+            }
         }
         RICH_TRY(sync(h));
         Level &Lc = H.L[l + 1];
@@ -341,6 +349,15 @@ rich_status build_hierarchy(rich_ctx *h) {
         RICH_TRY(dense_inverse(A, H.cinv, H.cinvf, H.cws, s));
     }
     RICH_TRY(sync(h));
+    // with source lists the refreshes read M itself: its CSR form served the set-up only
+    if (H.L[0].gsrc) {
+        H.mem.release(H.L[0].rowptr);
+        H.mem.release(H.L[0].col);
+        H.mem.release(H.L[0].val);
+        H.L[0].rowptr = nullptr;
+        H.L[0].col = nullptr;
+        H.L[0].val = nullptr;
+    }
     return RICH_OK;
 }
 
@@ -354,16 +371,21 @@ rich_status refresh_hierarchy(rich_ctx *h) {
     hipStream_t s = h->s;
     bool all = h->O.amg_refresh != 0;
     if (!all && H.nlev > 1) return RICH_OK;
-    RICH_TRY(launch_stencil_to_csr(h->P, h->M4, H.L[0].rowptr, H.L[0].col, H.L[0].val, s));
+    if (H.L[0].rowptr) RICH_TRY(launch_stencil_to_csr(h->P, h->M4, H.L[0].rowptr, H.L[0].col, H.L[0].val, s));
     if (all) {
         for (int l = 0; l + 1 < H.nlev; l++) {
             Level &Lf = H.L[l], &Lc = H.L[l + 1];
             CsrDev A{Lf.n, Lf.nnz, Lf.rowptr, Lf.col, Lf.val};
             CsrDev C{Lc.n, Lc.nnz, Lc.rowptr, Lc.col, Lc.val};
-            if (Lf.prow) RICH_TRY(sa_numeric(A, Lf.agg, Lf, C, h->mixed, s));
-            else RICH_TRY(galerkin_numeric(A, Lf.agg, Lf.mptr, Lf.mem, C, s));
+            if (Lf.gsrc) {
+                RICH_TRY(galerkin_sum(Lc.nnz, Lf.gptr, Lf.gsrc, l == 0 ? h->M4 : Lf.val, Lc.val,
+                                      h->mixed ? Lc.valf : nullptr, s));
+            } else {
+                if (Lf.prow) RICH_TRY(sa_numeric(A, Lf.agg, Lf, C, h->mixed, s));
+                else RICH_TRY(galerkin_numeric(A, Lf.agg, Lf.mptr, Lf.mem, C, s));
+                if (h->mixed) RICH_TRY(launch_cast(Lc.val, Lc.valf, Lc.nnz, s));
+            }
             RICH_TRY(csr_invd(C, Lc.invd, Lc.invdf, s));
-            if (h->mixed) RICH_TRY(launch_cast(Lc.val, Lc.valf, Lc.nnz, s));
         }
     }
     if (H.dense) {

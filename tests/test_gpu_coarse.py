@@ -6,7 +6,7 @@ import scipy.sparse as sp
 import scipy.sparse.linalg as spla
 
 import synth
-from tests.helpers import box_problem, random_heads, random_ks
+from tests.helpers import box_problem, csr_close, random_heads, random_ks
 
 pytestmark = pytest.mark.gpu
 
@@ -49,3 +49,32 @@ def test_dense_inverse_tiles(rich, torch, shape, precision, tol):
         x = s.apply_prec(dev(torch, b)).cpu().numpy()
         xo = np.atleast_1d(spla.spsolve(M, b))
         assert np.linalg.norm(x - xo) <= tol * np.linalg.norm(xo)
+
+
+# The refreshed coarse matrices are P^T A P of the refreshed fine ones (same
+# terms; scipy adds them in another order: 1e-12 of the row maximum), on boxes
+# with absent directions (the stencil's strides coincide) and with aggregates
+# large enough that coarse rows pass the 32 entries summed in LDS at set-up.
+@pytest.mark.parametrize("precision", [synth.FP64, synth.MIXED])
+@pytest.mark.parametrize("shape,sweeps", [((40, 1, 1), 1), ((1, 1, 40), 3), ((1, 9, 7), 2), ((9, 1, 7), 3), ((2, 2, 9), 1),
+                                          ((7, 9, 1), 3), ((21, 17, 13), 3), ((40, 37, 33), 6)])
+def test_galerkin_refresh(rich, torch, shape, sweeps, precision):
+    P = box_problem(*shape, dt=10.0)
+    opts = synth.Options(amg_coarse_size=8, coarse_dense_max=8, amg_sweeps=sweeps, precision=precision)
+    s = rich.Solver(P, opts, dev(torch, random_ks(P, 51)))
+    longest = 0
+    for seed in (52, 53, 54):
+        s.assemble(dev(torch, random_heads(P.n, seed, -70, -30)))
+        assert s.levels() >= 2
+        rp, col, val = s.export_csr(rich.WHICH_A, 0)
+        A = sp.csr_matrix((val, col, rp), shape=(P.n, P.n))
+        for l in range(s.levels() - 1):
+            agg, nc = s.export_aggregates(l)
+            Pr = sp.csr_matrix((np.ones(A.shape[0]), (np.arange(A.shape[0]), agg)), shape=(A.shape[0], nc))
+            C = sp.csr_matrix(Pr.T @ A @ Pr)
+            rp, col, val = s.export_csr(rich.WHICH_A, l + 1)
+            csr_close(rp, col, val, C, 1e-12)
+            longest = max(longest, int(np.diff(rp).max()))
+            A = sp.csr_matrix((val, col, rp), shape=(nc, nc))
+    if sweeps == 6:
+        assert longest > 32
