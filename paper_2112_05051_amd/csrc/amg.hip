@@ -790,32 +790,32 @@ __global__ void k_csr_to_dense(int64_t n, const int64_t *__restrict__ rowptr, co
     for (int64_t e = rowptr[i]; e < rowptr[i + 1]; e++) D[i * n + col[e]] = val[e];
 }
 
-// Blocked symmetric Gauss-Jordan (sweep) inversion of an SPD matrix, in
-// place (no pivoting: every leading block of an SPD matrix and every Schur
-// complement stay SPD).  Sweeping the pivot block K: P = D_KK,
-//   D_Kj <- R_j = P^{-1} D_Kj,  D_iK <- -D_iK P^{-1},  D_KK <- P^{-1},
-//   D_ij <- D_ij - D_iK R_j                            otherwise.
-// Between two swept or two unswept blocks the matrix stays symmetric, between
-// a swept and an unswept one antisymmetric, so only the tiles on and below the
-// diagonal are kept: half the operations and half the bytes of a full
-// sweep.  Each step is two launches: a panel (S = D_:K and R for every tile
-// row, the new row and column K), then the update of all other tiles on the
-// FP64 matrix cores; the block of the next pivot tile inverts it right after
-// updating it, beside the other tiles' updates, so the 64 scalar steps of a
-// pivot are not a launch of their own.
-// Bounds: the update moves 8 n^2 bytes a step (n = 3118: 78 MB, resident in
-// the last-level cache) and does 32 n^2 multiply-adds; on small n the pivot's
-// serial chain (64 steps of LDS, barrier, reciprocal).  Measured a step:
-// n = 3118 update 36 and panel 10 us (a full sweep with the pivot as its own
-// launch: 103 + 59 + 18 + 5), n = 517 27 and 8 us (19 + 54 + 16 + 5).
+// Blocked Gauss-Jordan inversion of an SPD matrix (no pivoting: every
+// leading block of an SPD matrix and every Schur complement stay SPD).  For
+// the pivot block K = [k0, k0+64):  P = D_KK,  R_K: = P^{-1} D_K: (with P^{-1}
+// itself in the K columns),  S_:K = D_:K (old), then
+//   D_ij <- R_{i-k0, j}                                  for i in K,
+//   D_ij <- [j not in K] D_ij - sum_t S_it R_tj          otherwise.
+// Two launches a step: a panel (S, R and the new rows K, one workgroup per
+// tile), then the update of all other tiles on the FP64 matrix cores; the block
+// of the next pivot tile inverts it right after updating it, beside the other
+// tiles' updates, so a pivot's 64 scalar steps are no launch of their own.
+// Bounds: the update moves 16 n^2 bytes a step (n = 3118: 156 MB, resident in
+// the last-level cache) and does 64 n^2 multiply-adds; on small n the pivot's
+// serial chain (64 steps of LDS, barrier, division).  Measured a step: n = 3118
+// update 48 and panel 10 us (with the pivot and the panels as launches of their
+// own: 103 + 59 + 18 + 5), n = 517 27 and 9 us (19 + 54 + 16 + 5).  The order of
+// operations is part of the contract: a restarted or repeated GMRES solve in
+// FP64 amplifies the last bits of the preconditioner, so sweeping only half of
+// the tiles (36 us, not the same bits) is not used.
 constexpr int GJB = 64;  // pivot block and tile size
 
-// P^{-1} of the symmetric 64 x 64 block in A, one workgroup of 256 threads.
-// Thread (ti, tj) keeps the entries (ti + 16 a, tj + 16 b) in registers; each
-// of the 64 scalar Gauss-Jordan steps shares its pivot row and column through
+// P^{-1} of the 64 x 64 block in A, one workgroup of 256 threads.  Thread
+// (ti, tj) keeps the entries (ti + 16 a, tj + 16 b) in registers; each of the
+// 64 scalar Gauss-Jordan steps shares its pivot row and column through
 // double-buffered LDS (one barrier a step).  rc: 4 * 64 doubles.
 __device__ __forceinline__ void invert_pivot(const double (*__restrict__ A)[GJB + 1], double *__restrict__ rc,
-                                    double *__restrict__ Pinv, int *__restrict__ bad) {
+                                             double *__restrict__ Pinv, int *__restrict__ bad) {
     const int tid = threadIdx.x, ti = tid >> 4, tj = tid & 15;
     double v[4][4];
 #pragma unroll
@@ -849,10 +849,7 @@ __device__ __forceinline__ void invert_pivot(const double (*__restrict__ A)[GJB 
                 neg = true;
                 p = 1.0;  // keep going; the caller reports the failure
             }
-            // 1/p: hardware estimate and two Newton steps
-            double ip = __builtin_amdgcn_rcp(p);
-            ip = fma(fma(-p, ip, 1.0), ip, ip);
-            ip = fma(fma(-p, ip, 1.0), ip, ip);
+            const double ip = 1.0 / p;
             double r[4], f[4];
 #pragma unroll
             for (int c = 0; c < 4; c++) r[c] = c == ka && tj == kk ? 1.0 : row[tj + 16 * c];
@@ -879,9 +876,7 @@ __global__ void __launch_bounds__(256) k_bgj_pivot(const double *__restrict__ D,
 #pragma unroll
     for (int q = 0; q < 16; q++) {
         const int t = threadIdx.x + 256 * q, i = t / GJB, j = t % GJB;
-        // the lower triangle holds the matrix
-        const int lo = i < j ? i : j, hi = i < j ? j : i;
-        d[q] = hi < n ? D[(int64_t)hi * n + lo] : (i == j ? 1.0 : 0.0);
+        d[q] = (i < n && j < n) ? D[(int64_t)i * n + j] : (i == j ? 1.0 : 0.0);
     }
 #pragma unroll
     for (int q = 0; q < 16; q++) {
@@ -892,142 +887,132 @@ __global__ void __launch_bounds__(256) k_bgj_pivot(const double *__restrict__ D,
     invert_pivot(A, rc, Pinv, bad);
 }
 
-// v_mfma_f64_16x16x4f64: lane l supplies A[l%16][l/16] and B[l/16][l%16];
-// result register v of lane l is D[l/16 + 4v][l%16].
-typedef double rich_d4 __attribute__((ext_vector_type(4)));
-
-// Panel of pivot block K, one workgroup per tile row I: X = D_KI as the step
-// sees it (from the stored tile (I,K) below the pivot, (K,I) before it),
-// R_I = P^{-1} X, S_I = D_IK; the new row and column K go back to D.
-// S (npad x 64) and RT = R^T (npad x 64) are zero where a row is past n.
-__global__ void __launch_bounds__(256) k_bgj_panel(double *__restrict__ D, int64_t n, int K,
+// Panel of pivot block K, one workgroup per tile T: R_T = P^{-1} D_KT (terms
+// added in ascending t), which are also the new rows K of D, and S_T = the old
+// D_TK.  S (npad x 64) and R (64 x npad) are zero past n.
+__global__ void __launch_bounds__(256) k_bgj_panel(double *__restrict__ D, int64_t n, int64_t npad, int K,
                                                    const double *__restrict__ Pinv, double *__restrict__ S,
-                                                   double *__restrict__ RT) {
-    __shared__ double X[GJB][GJB + 1];  // [t][i]
-    __shared__ double Q[GJB][GJB + 1];  // Pinv, then R [r][i]
-    const int I = blockIdx.x;
-    const int64_t i0 = (int64_t)I * GJB, k0 = (int64_t)K * GJB;
-    // every load of the tile is issued before the first is stored in LDS
-    double pq[16], dq[16];
-    const int64_t rb = I > K ? i0 : k0, cb = I > K ? k0 : i0;  // the stored tile
+                                                   double *__restrict__ R) {
+    __shared__ double X[GJB][GJB + 1];  // D_KT [t][j]
+    __shared__ double Q[GJB][GJB + 1];  // Pinv transposed [t][r]
+    const int T = blockIdx.x, tid = threadIdx.x;
+    const int64_t t0 = (int64_t)T * GJB, k0 = (int64_t)K * GJB;
+    // every load is issued before the first is stored in LDS
+    double pq[16], dq[16], sq[16];
 #pragma unroll
     for (int q = 0; q < 16; q++) {
-        const int t = threadIdx.x + 256 * q, a = t / GJB, c = t % GJB;
+        const int t = tid + 256 * q, a = t / GJB, c = t % GJB;
         pq[q] = Pinv[t];
-        dq[q] = (I != K && rb + a < n && cb + c < n) ? D[(rb + a) * n + cb + c] : 0.0;
+        dq[q] = (k0 + a < n && t0 + c < n) ? D[(k0 + a) * n + t0 + c] : 0.0;
+        sq[q] = (t0 + a < n && k0 + c < n) ? D[(t0 + a) * n + k0 + c] : 0.0;
     }
 #pragma unroll
     for (int q = 0; q < 16; q++) {
-        const int t = threadIdx.x + 256 * q, a = t / GJB, c = t % GJB;
-        Q[a][c] = pq[q];
-        if (I > K) X[c][a] = dq[q];
-        else X[a][c] = dq[q];
+        const int t = tid + 256 * q, a = t / GJB, c = t % GJB;
+        Q[c][a] = pq[q];
+        X[a][c] = dq[q];
+        S[(t0 + a) * GJB + c] = sq[q];
     }
     __syncthreads();
-    if (I == K) {
-        for (int t = threadIdx.x; t < GJB * GJB; t += 256) {
-            const int a = t / GJB, c = t % GJB;
-            if (k0 + a < n && k0 + c < n) D[(k0 + a) * n + k0 + c] = Q[a][c];
-        }
-        return;
-    }
-    const int w = threadIdx.x / 64, l = threadIdx.x % 64, li = l % 16, lk = l / 16;
-    rich_d4 acc[4];
+    const int ti = tid >> 4, tj = tid & 15;
+    double v[4][4];
 #pragma unroll
-    for (int c = 0; c < 4; c++) acc[c] = (rich_d4){0.0, 0.0, 0.0, 0.0};
-    for (int t = 0; t < GJB; t += 4) {
-        const double a = Q[16 * w + li][t + lk];
+    for (int a = 0; a < 4; a++)
 #pragma unroll
-        for (int c = 0; c < 4; c++)
-            acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, X[t + lk][16 * c + li], acc[c], 0, 0, 0);
-    }
-    __syncthreads();
+        for (int c = 0; c < 4; c++) v[a][c] = 0.0;
+    if (T == K) {
 #pragma unroll
-    for (int c = 0; c < 4; c++)
+        for (int a = 0; a < 4; a++)
 #pragma unroll
-        for (int v = 0; v < 4; v++) Q[16 * w + lk + 4 * v][16 * c + li] = acc[c][v];
-    __syncthreads();
-    const double sg = I > K ? 1.0 : -1.0;
-    for (int t = threadIdx.x; t < GJB * GJB; t += 256) {
-        const int a = t / GJB, c = t % GJB;
-        S[(i0 + a) * GJB + c] = sg * X[c][a];
-        RT[(i0 + a) * GJB + c] = Q[c][a];
-        if (I > K) {
-            if (i0 + a < n && k0 + c < n) D[(i0 + a) * n + k0 + c] = -Q[c][a];
-        } else if (k0 + a < n && i0 + c < n) {
-            D[(k0 + a) * n + i0 + c] = Q[a][c];
+            for (int c = 0; c < 4; c++) v[a][c] = Q[tj + 16 * c][ti + 16 * a];
+    } else {
+#pragma unroll 4
+        for (int t = 0; t < GJB; t++) {
+            double p[4], x[4];
+#pragma unroll
+            for (int a = 0; a < 4; a++) p[a] = Q[t][ti + 16 * a];
+#pragma unroll
+            for (int c = 0; c < 4; c++) x[c] = X[t][tj + 16 * c];
+#pragma unroll
+            for (int a = 0; a < 4; a++)
+#pragma unroll
+                for (int c = 0; c < 4; c++) v[a][c] = fma(p[a], x[c], v[a][c]);
         }
     }
+#pragma unroll
+    for (int a = 0; a < 4; a++)
+#pragma unroll
+        for (int c = 0; c < 4; c++) {
+            const int r = ti + 16 * a, j = tj + 16 * c;
+            R[r * npad + t0 + j] = v[a][c];
+            if (k0 + r < n && t0 + j < n) D[(k0 + r) * n + t0 + j] = v[a][c];
+        }
 }
 
-// Update of the tiles (I, J), I >= J, I and J other than K: D_IJ -= S_I R_J.
-// The tile starts in the accumulators (S enters negated); the 64-long inner
-// index is dealt so that lane group lk takes 16 consecutive entries of its
-// rows, read as 16-byte pairs.  Block 0 takes the next pivot tile (K+1, K+1)
-// and inverts it; the others take the remaining tiles in order.
-__global__ void __launch_bounds__(256) k_bgj_update(double *__restrict__ D, int64_t n, int K, int tiles,
-                                                    const double *__restrict__ S, const double *__restrict__ RT,
+// Update of the tiles (I, J), I other than K: D_IJ <- [J != K] D_IJ - S_I R_J.
+// The four wavefronts of a block each own 16 rows of the tile and accumulate
+// four 16x16 blocks with v_mfma_f64_16x16x4f64 (lane l supplies A[l%16][l/16]
+// and B[l/16][l%16]; result register v of lane l is D[l/16 + 4v][l%16]).
+// Block 0 takes the next pivot tile (K+1, K+1) and inverts it; the others take
+// the tiles in row order.
+typedef double rich_d4 __attribute__((ext_vector_type(4)));
+__global__ void __launch_bounds__(256) k_bgj_update(double *__restrict__ D, int64_t n, int64_t npad, int K, int tiles,
+                                                    const double *__restrict__ S, const double *__restrict__ R,
                                                     double *__restrict__ Pinv, int *__restrict__ bad) {
-    __shared__ double B[GJB][GJB + 1];  // RT tile [j][t]; the next pivot's tile
-    __shared__ double rc[4 * GJB];
-    // block 0: the next pivot; block b: the b-th remaining tile of the lower triangle without row and column K
-    const bool last = K == tiles - 1;
+    __shared__ double Ss[GJB][GJB + 1];  // [row in tile][t]; the next pivot's tile
+    __shared__ double Rs[GJB][GJB + 1];  // [t][col in tile]
+    const bool last = K == tiles - 1, piv = blockIdx.x == 0 && !last;
     int I, J;
-    if (blockIdx.x == 0 && !last) {
+    if (piv) {
         I = J = K + 1;
     } else {
-        // tile b of a lower triangle of tiles - 1 rows, renumbered past K
-        const int64_t b = (int64_t)blockIdx.x - (last ? 0 : 1);
-        int r = (int)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
-        while ((int64_t)(r + 1) * (r + 2) / 2 <= b) r++;
-        while ((int64_t)r * (r + 1) / 2 > b) r--;
-        const int c = (int)(b - (int64_t)r * (r + 1) / 2);
-        I = r < K ? r : r + 1;
-        J = c < K ? c : c + 1;
+        const int b = (int)blockIdx.x - (last ? 0 : 1);
+        I = b / tiles;
+        J = b - I * tiles;
+        if (I >= K) I++;
         if (!last && I == K + 1 && J == K + 1) return;  // block 0's
     }
     const int64_t i0 = (int64_t)I * GJB, j0 = (int64_t)J * GJB;
-    const int w = threadIdx.x / 64, l = threadIdx.x % 64, li = l % 16, lk = l / 16;
-    const bool piv = blockIdx.x == 0 && !last;
-    rich_d4 acc[4];
+    const int tid = threadIdx.x, w = tid / 64, l = tid % 64, li = l % 16, lk = l / 16;
+    // the tile's own entries are needed last: loaded with the panels
+    double sq[16], rq[16], d[4][4];
+#pragma unroll
+    for (int q = 0; q < 16; q++) {
+        const int t = tid + 256 * q, a = t / GJB, c = t % GJB;
+        sq[q] = S[i0 * GJB + t];
+        rq[q] = R[a * npad + j0 + c];
+    }
 #pragma unroll
     for (int c = 0; c < 4; c++)
 #pragma unroll
         for (int v = 0; v < 4; v++) {
             const int64_t gi = i0 + 16 * w + lk + 4 * v, gj = j0 + 16 * c + li;
-            // the pivot tile reads its lower triangle (the upper one is not kept)
-            const int64_t hi = piv && gj > gi ? gj : gi, lo = piv && gj > gi ? gi : gj;
-            acc[c][v] = hi < n && lo < n ? D[hi * n + lo] : (piv && gi == gj ? 1.0 : 0.0);
+            d[c][v] = J != K && gi < n && gj < n ? D[gi * n + gj] : (piv && gi == gj ? 1.0 : 0.0);
         }
-    typedef double d2 __attribute__((ext_vector_type(2)));
-    d2 sa[8];
-    const d2 *sp = reinterpret_cast<const d2 *>(S + (i0 + 16 * w + li) * GJB + 16 * lk);
-#pragma unroll
-    for (int s = 0; s < 8; s++) sa[s] = sp[s];
-    double bq[16];
-#pragma unroll
-    for (int q = 0; q < 16; q++) bq[q] = RT[j0 * GJB + threadIdx.x + 256 * q];
 #pragma unroll
     for (int q = 0; q < 16; q++) {
-        const int t = threadIdx.x + 256 * q;
-        B[t / GJB][t % GJB] = bq[q];
+        const int t = tid + 256 * q, a = t / GJB, c = t % GJB;
+        Ss[a][c] = sq[q];
+        Rs[a][c] = rq[q];
     }
     __syncthreads();
+    rich_d4 acc[4];
 #pragma unroll
-    for (int s = 0; s < 16; s++) {
-        const double a = -(s & 1 ? sa[s / 2].y : sa[s / 2].x);
+    for (int c = 0; c < 4; c++) acc[c] = (rich_d4){0.0, 0.0, 0.0, 0.0};
+    for (int t = 0; t < GJB; t += 4) {
+        const double a = Ss[16 * w + li][t + lk];
 #pragma unroll
         for (int c = 0; c < 4; c++)
-            acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, B[16 * c + li][16 * lk + s], acc[c], 0, 0, 0);
+            acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Rs[t + lk][16 * c + li], acc[c], 0, 0, 0);
     }
     if (piv) {
         __syncthreads();
 #pragma unroll
         for (int c = 0; c < 4; c++)
 #pragma unroll
-            for (int v = 0; v < 4; v++) B[16 * w + lk + 4 * v][16 * c + li] = acc[c][v];
+            for (int v = 0; v < 4; v++) Ss[16 * w + lk + 4 * v][16 * c + li] = d[c][v] - acc[c][v];
         __syncthreads();
-        invert_pivot(B, rc, Pinv, bad);
+        invert_pivot(Ss, &Rs[0][0], Pinv, bad);
         return;
     }
 #pragma unroll
@@ -1035,32 +1020,8 @@ __global__ void __launch_bounds__(256) k_bgj_update(double *__restrict__ D, int6
 #pragma unroll
         for (int v = 0; v < 4; v++) {
             const int64_t gi = i0 + 16 * w + lk + 4 * v, gj = j0 + 16 * c + li;
-            if (gi < n && gj < n) D[gi * n + gj] = acc[c][v];
+            if (gi < n && gj < n) D[gi * n + gj] = d[c][v] - acc[c][v];
         }
-}
-
-// The swept matrix is the inverse, its lower triangle stored: copy it to the
-// upper one, in FP64 (in place) or rounded into the FP32 copy Df.
-template <bool F32>
-__global__ void __launch_bounds__(256) k_bgj_mirror(double *__restrict__ D, int64_t n, float *__restrict__ Df) {
-    __shared__ double T[GJB][GJB + 1];
-    const int I = blockIdx.y, J = blockIdx.x;
-    if (J > I) return;
-    const int64_t i0 = (int64_t)I * GJB, j0 = (int64_t)J * GJB;
-    for (int t = threadIdx.x; t < GJB * GJB; t += 256) {
-        const int a = t / GJB, c = t % GJB;
-        if (i0 + a >= n || j0 + c >= n) continue;
-        const double v = D[(i0 + a) * n + j0 + c];
-        T[a][c] = v;
-        if (F32 && (I > J || c <= a)) Df[(i0 + a) * n + j0 + c] = f32_sat(v);
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < GJB * GJB; t += 256) {
-        const int a = t / GJB, c = t % GJB;  // upper entry (j0 + a, i0 + c)
-        if (j0 + a >= n || i0 + c >= n || (I == J && c <= a)) continue;
-        if (F32) Df[(j0 + a) * n + i0 + c] = f32_sat(T[c][a]);
-        else D[(j0 + a) * n + i0 + c] = T[c][a];
-    }
 }
 
 }  // namespace
@@ -1341,32 +1302,30 @@ rich_status compose_agg(int32_t *comp, const int32_t *a, int64_t n, hipStream_t 
     return RICH_OK;
 }
 
-// Inverse of an SPD CSR matrix, dense row-major n x n, using the workspace of
-// dense_inverse_ws (no allocation: it runs on every refresh).  With Df the
-// result is Df, rounded to FP32, and D holds the lower triangle only.
+// Inverse of an SPD CSR matrix into a dense row-major n x n buffer, using
+// the workspace of dense_inverse_ws (no allocation: it runs on every refresh).
 int64_t dense_inverse_ws(int64_t n) {
     const int64_t npad = (n + GJB - 1) / GJB * GJB;
     return (int64_t)GJB * GJB + 2 * (int64_t)GJB * npad + 1;
 }
 
-rich_status dense_inverse(const CsrDev &A, double *D, float *Df, double *ws, hipStream_t s) {
+rich_status dense_inverse(const CsrDev &A, double *D, double *ws, hipStream_t s) {
     int64_t n = A.n;
     if (n == 0) return RICH_OK;
     const int tiles = (int)((n + GJB - 1) / GJB);
-    double *Pinv = ws, *S = ws + GJB * GJB, *RT = S + (int64_t)GJB * GJB * tiles;
-    int *bad = reinterpret_cast<int *>(RT + (int64_t)GJB * GJB * tiles);
+    const int64_t npad = (int64_t)tiles * GJB;
+    double *Pinv = ws, *S = ws + GJB * GJB, *R = S + GJB * npad;
+    int *bad = reinterpret_cast<int *>(R + GJB * npad);
     HIP_TRY(hipMemsetAsync(bad, 0, sizeof(int), s));
     HIP_TRY(hipMemsetAsync(D, 0, (size_t)n * n * sizeof(double), s));
     k_csr_to_dense<<<nblocks(n), TPB, 0, s>>>(n, A.rowptr, A.col, A.val, D);
     k_bgj_pivot<<<1, 256, 0, s>>>(D, n, Pinv, bad);
     LAUNCH_CHECK();
-    const unsigned rest = (unsigned)((int64_t)(tiles - 1) * tiles / 2);  // tiles off row and column K
+    const unsigned rest = (unsigned)((tiles - 1) * tiles);  // tiles off row K
     for (int K = 0; K < tiles; K++) {
-        k_bgj_panel<<<tiles, 256, 0, s>>>(D, n, K, Pinv, S, RT);
-        if (rest) k_bgj_update<<<rest + (K < tiles - 1 ? 1 : 0), 256, 0, s>>>(D, n, K, tiles, S, RT, Pinv, bad);
+        k_bgj_panel<<<tiles, 256, 0, s>>>(D, n, npad, K, Pinv, S, R);
+        if (rest) k_bgj_update<<<rest + (K < tiles - 1 ? 1 : 0), 256, 0, s>>>(D, n, npad, K, tiles, S, R, Pinv, bad);
     }
-    if (Df) k_bgj_mirror<true><<<dim3(tiles, tiles), 256, 0, s>>>(D, n, Df);
-    else k_bgj_mirror<false><<<dim3(tiles, tiles), 256, 0, s>>>(D, n, nullptr);
     LAUNCH_CHECK();
     int hb = 0;
     HIP_TRY(hipMemcpyAsync(&hb, bad, sizeof(int), hipMemcpyDeviceToHost, s));

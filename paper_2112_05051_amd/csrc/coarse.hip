@@ -1,0 +1,755 @@
+// Coarse levels of the V-cycle in aggregate order.
+//
+// The rows of a smoothed coarse level are renumbered by the member lists of
+// the next level's aggregates, so the rows of one aggregate are neighbours and
+// a thread block that owns whole aggregates can finish more than its sweep:
+//   down: r = b - A x0 of its rows, then P^T r of its aggregates, which goes
+//         straight to the next level's right-hand side (with x0 = D^{-1} b
+//         there); r is never stored;
+//   up:   x = xt + D^{-1}(b - A xt) of its rows, then xt = x0 + P x of the finer
+//         level's rows they stand for (one contiguous run per row).
+// A level is two launches a cycle instead of four (sweep, restriction,
+// prolongation, sweep).  The products are formed in entry order into LDS and
+// added per row, in the column order of the level's matrix; members are added
+// in ascending order: the sums are those of the separate kernels.
+#include <algorithm>
+#include <cstring>
+#include <type_traits>
+
+#include "common.hpp"
+
+namespace rich {
+
+namespace {
+
+constexpr int TPB = 256;
+inline unsigned nblocks(int64_t n, int tpb = TPB) { return (unsigned)((n + tpb - 1) / tpb); }
+
+// Entries of a level in aggregate order, read in pairs (the entry index is
+// even): FP32 (byte offset of the column's value, value) pairs, FP64 offsets
+// and values apart.  The offsets go into the gathers as they are loaded.
+typedef int i2_t __attribute__((ext_vector_type(2)));
+typedef int i4_t __attribute__((ext_vector_type(4)));
+typedef double d2_t __attribute__((ext_vector_type(2)));
+template <class P, bool NT>
+__device__ __forceinline__ P load_as(const void *p, uint32_t off) {
+    const P *q = reinterpret_cast<const P *>(reinterpret_cast<const char *>(p) + off);
+    return NT ? __builtin_nontemporal_load(q) : *q;
+}
+template <class T>
+struct Entries;
+template <>
+struct Entries<float> {
+    const int2 *e;
+    template <bool NT>
+    __device__ __forceinline__ void pair(int64_t base, uint32_t i, uint32_t *c, float *v) const {
+        const i4_t t = load_as<i4_t, NT>(e + base, i * 8);
+        c[0] = t.x;
+        v[0] = __int_as_float(t.y);
+        c[1] = t.z;
+        v[1] = __int_as_float(t.w);
+    }
+};
+template <>
+struct Entries<double> {
+    const uint32_t *c_;
+    const double *v_;
+    template <bool NT>
+    __device__ __forceinline__ void pair(int64_t base, uint32_t i, uint32_t *c, double *v) const {
+        const i2_t t = load_as<i2_t, NT>(c_ + base, i * 4);
+        const d2_t u = load_as<d2_t, NT>(v_ + base, i * 8);
+        c[0] = t.x;
+        c[1] = t.y;
+        v[0] = u.x;
+        v[1] = u.y;
+    }
+};
+
+// One level's part of a cycle.  blk: first aggregate, row and entry of each
+// block (x, y, z), one more than there are blocks; lds_ent: products held.
+template <class T>
+struct VArgs {
+    const int4 *blk;
+    const int32_t *ptr;  // row starts
+    Entries<T> ent;
+    const T *b, *v;      // right-hand side; x0 (down) or xt (up)
+    // down
+    const int64_t *mptr;  // rows of each aggregate
+    const int32_t *pos;   // next level's place of each aggregate (null: itself)
+    const T *invdc;       // next level: D^{-1} (null at the coarsest), b and x0
+    T *bc, *x0c;
+    // up
+    const T *invd;
+    T *x;               // result (level 1), or
+    const int2 *child;  // the finer level's rows of each row,
+    const T *x0f;       // their x0
+    T *xtf;             // and their prolongated iterate
+    int lds_ent;
+};
+
+// Sum of a row's products [ra, re) as G interleaved partial sums added
+// pairwise: by the G lanes of the row's group, or for G <= 2 by one lane.
+template <int G, class T>
+__device__ __forceinline__ T row_sum(const T *prod, int ra, int re, int lane) {
+    if (G == 1) {
+        T s = 0;
+        for (int e = ra; e < re; e++) s += prod[e];
+        return s;
+    }
+    if (G == 2) {
+        T s0 = 0, s1 = 0;
+        int e = ra;
+        for (; e + 1 < re; e += 2) {
+            s0 += prod[e];
+            s1 += prod[e + 1];
+        }
+        if (e < re) s0 += prod[e];
+        return s0 + s1;
+    }
+    T s = 0;
+    for (int e = ra + lane; e < re; e += G) s += prod[e];
+    return group_sum<G>(s);
+}
+
+// UP = false: down.  A block's entries are taken 512 NP at a time, each wave a
+// run of 128 per step (two per lane).  These kernels are bound by their
+// instruction issue, not by memory: with 8-byte loads under a bounds check
+// each, 64-bit gather addresses and two lanes per row a level-1 sweep at 256^3
+// took about 600 instructions a wave; runs past a block's end are read
+// unmasked instead (the next block's entries, or the padding behind the
+// last) and their products not used.
+template <int NP, int G, class T, bool UP>
+__device__ __forceinline__ void vlevel_body(const VArgs<T> &a, T *__restrict__ prod, int blk) {
+    constexpr int LPR = G <= 2 ? 1 : G;  // lanes per row
+    constexpr bool NT = NP > 2;          // large levels stream past the caches
+    T *rr = prod + a.lds_ent;
+    const int4 b0 = a.blk[blk], b1 = a.blk[blk + 1];
+    const int R0 = b0.y, R1 = b1.y, E0 = b0.z & ~1, E1 = b1.z;
+    if (R0 >= R1) return;
+    const int tid = threadIdx.x, lane = tid % LPR;
+    const int wrun = __builtin_amdgcn_readfirstlane(tid >> 6) * 128;
+    // what the row phase needs of its first row is loaded ahead of the products
+    int row = R0 + tid / LPR;
+    int ra = 0, re = 0;
+    T pb = 0, pd = 0, pv = 0;
+    auto row_in = [&]() {
+        if (row < R1) {
+            ra = a.ptr[row] - E0;
+            re = a.ptr[row + 1] - E0;
+            pb = a.b[row];
+            if (UP) {
+                pd = a.invd[row];
+                pv = a.v[row];
+            }
+        }
+    };
+    row_in();
+    for (int base = E0; base < E1; base += 512 * NP) {
+        uint32_t c[NP][2];
+        T v[NP][2], x[NP][2];
+#pragma unroll
+        for (int q = 0; q < NP; q++) {
+            c[q][0] = c[q][1] = 0;
+            v[q][0] = v[q][1] = 0;
+            if (base + 512 * q + wrun < E1) a.ent.template pair<NT>(base + 512 * q, 2 * tid, c[q], v[q]);
+        }
+#pragma unroll
+        for (int q = 0; q < NP; q++) {
+            x[q][0] = load_as<T, false>(a.v, c[q][0]);
+            x[q][1] = load_as<T, false>(a.v, c[q][1]);
+        }
+#pragma unroll
+        for (int q = 0; q < NP; q++)
+            if (base + 512 * q + wrun < E1) {
+                typedef T t2 __attribute__((ext_vector_type(2)));
+                *reinterpret_cast<t2 *>(prod + (base - E0) + 512 * q + 2 * tid) =
+                    (t2){v[q][0] * x[q][0], v[q][1] * x[q][1]};
+            }
+    }
+    __syncthreads();
+    // every lane of a group runs the same number of row iterations (shuffles)
+    for (int rb = R0; rb < R1; rb += 256 / LPR) {
+        if (rb != R0) {
+            row = rb + tid / LPR;
+            row_in();
+        }
+        const T s = row_sum<G, T>(prod, ra, row < R1 ? re : ra, lane);
+        if (lane == 0 && row < R1) {
+            if (!UP) rr[row - R0] = pb - s;
+            else if (a.child) rr[row - R0] = pv + pd * (pb - s);
+            else a.x[row] = pv + pd * (pb - s);
+        }
+    }
+    if (UP && !a.child) return;
+    __syncthreads();
+    if (UP) {
+        // eight lanes per row for its run on the finer level
+        for (int r = R0 + tid / 8; r < R1; r += 32) {
+            const int2 ch = a.child[r];
+            const T xr = rr[r - R0];
+            for (int t = ch.x + tid % 8; t < ch.y; t += 8) a.xtf[t] = a.x0f[t] + xr;
+        }
+        return;
+    }
+    for (int J = b0.x + tid; J < b1.x; J += 256) {
+        const int m0 = (int)a.mptr[J] - R0, m1 = (int)a.mptr[J + 1] - R0;
+        const int to = a.pos ? a.pos[J] : J;
+        const T d = a.invdc ? a.invdc[to] : (T)0;
+        T s = 0;
+        for (int m = m0; m < m1; m++) s += rr[m];
+        a.bc[to] = s;
+        if (a.invdc) a.x0c[to] = s * d;
+    }
+}
+
+extern __shared__ __align__(16) char vlevel_lds[];
+
+template <int NP, int G, class T, bool UP>
+__global__ void __launch_bounds__(256) k_vlevel(VArgs<T> a) {
+    vlevel_body<NP, G, T, UP>(a, reinterpret_cast<T *>(vlevel_lds), (int)xcd_block());
+}
+
+template <int NP, int G, class T, bool UP>
+__global__ void __launch_bounds__(256) k_vlevel_batch(Batch<VArgs<T>> B) {
+    for_each_block(B, xcd_block(), [&](unsigned L) {
+        const int e = batch_entry(B, L);
+        vlevel_body<NP, G, T, UP>(B.a[e], reinterpret_cast<T *>(vlevel_lds), (int)(L - B.begin[e]));
+    });
+}
+
+// x = Ainv b on the coarsest level, one wavefront per row, prolongated to the
+// finer level's rows (child) or stored (one coarse level only).
+template <class TB, class T>
+struct GemvArgs {
+    const T *Ainv;
+    const TB *b;
+    int64_t n;
+    T *x;
+    const int2 *child;
+    const T *x0f;
+    T *xtf;
+};
+template <class TB, class T>
+__device__ __forceinline__ void gemv_body(const GemvArgs<TB, T> &g, int64_t blk) {
+    const int64_t row = (blk * blockDim.x + threadIdx.x) / 64, n = g.n;
+    const int lane = threadIdx.x % 64;
+    if (row >= n) return;
+    int2 c = make_int2(0, 0);
+    if (g.child) c = g.child[row];
+    // four independent partial sums per lane keep four row segments in flight
+    const T *__restrict__ a = g.Ainv + row * n;
+    const TB *__restrict__ b = g.b;
+    T s0 = 0, s1 = 0, s2 = 0, s3 = 0;
+    int64_t j = lane;
+    for (; j + 192 < n; j += 256) {
+        s0 += a[j] * (T)b[j];
+        s1 += a[j + 64] * (T)b[j + 64];
+        s2 += a[j + 128] * (T)b[j + 128];
+        s3 += a[j + 192] * (T)b[j + 192];
+    }
+    for (; j < n; j += 64) s0 += a[j] * (T)b[j];
+    T s = (s0 + s1) + (s2 + s3);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+    if (g.child) {
+        s = __shfl(s, 0, 64);
+        for (int t = c.x + lane; t < c.y; t += 64) g.xtf[t] = g.x0f[t] + s;
+    } else if (lane == 0) {
+        g.x[row] = s;
+    }
+}
+
+template <class TB, class T>
+__global__ void k_dense_gemv(GemvArgs<TB, T> g) {
+    gemv_body(g, blockIdx.x);
+}
+template <class T>
+__global__ void k_dense_gemv_batch(Batch<GemvArgs<T, T>> B) {
+    for_each_block(B, blockIdx.x, [&](unsigned L) {
+        const int e = batch_entry(B, L);
+        gemv_body(B.a[e], (int64_t)(L - B.begin[e]));
+    });
+}
+
+// xt = x0 + P x on the finer level (the coarsest level without a direct solve)
+template <class T>
+__global__ void k_v_prolong(int64_t n, const T *__restrict__ x, const int2 *__restrict__ child,
+                            const T *__restrict__ x0f, T *__restrict__ xtf) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int2 c = child[i];
+    const T v = x[i];
+    for (int t = c.x; t < c.y; t++) xtf[t] = x0f[t] + v;
+}
+
+// ------------------------------------------------------------------ set-up
+__global__ void k_v_pos(int64_t n, const int32_t *__restrict__ mem, const int64_t *__restrict__ rowptr,
+                        int32_t *__restrict__ pos, int64_t *__restrict__ len) {
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= n) return;
+    const int32_t i = mem[p];
+    pos[i] = (int32_t)p;
+    len[p] = rowptr[i + 1] - rowptr[i];
+}
+
+__global__ void k_v_narrow(int64_t n, const int64_t *__restrict__ in, int32_t *__restrict__ out) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) out[i] = (int32_t)in[i];
+}
+
+// column offsets, and the place of every entry of the level's matrix
+template <bool F32>
+__global__ void k_v_columns(int64_t n, const int32_t *__restrict__ mem, const int64_t *__restrict__ rowptr,
+                            const int32_t *__restrict__ col, const int32_t *__restrict__ pos,
+                            const int32_t *__restrict__ ptr, int32_t *__restrict__ place, int2 *__restrict__ ent,
+                            uint32_t *__restrict__ vcol) {
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= n) return;
+    const int32_t i = mem[p];
+    int32_t o = ptr[p];
+    for (int64_t e = rowptr[i]; e < rowptr[i + 1]; e++, o++) {
+        const int32_t c = pos[col[e]];
+        if (F32) ent[o].x = (int)((uint32_t)c * 4u);
+        else vcol[o] = (uint32_t)c * 8u;
+        place[e] = o;
+    }
+}
+
+template <bool F32>
+__global__ void k_v_values(int64_t nnz, const double *__restrict__ val, const int32_t *__restrict__ place,
+                           int2 *__restrict__ ent, double *__restrict__ vval) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= nnz) return;
+    if (F32) ent[place[e]].y = __float_as_int(f32_sat(val[e]));
+    else vval[place[e]] = val[e];
+}
+
+// block b: the aggregates whose first entry lies in [b chunk, (b+1) chunk);
+// the blocks past the last chunk (grid padding) are empty
+__global__ void k_v_blocks(int64_t nc, int64_t nb, int64_t ngrid, int chunk, const int64_t *__restrict__ mptr,
+                           const int32_t *__restrict__ ptr, int4 *__restrict__ blk) {
+    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (b > ngrid) return;
+    int64_t lo = nc;
+    if (b < nb) {
+        const int64_t target = b * (int64_t)chunk;
+        int64_t hi = nc;
+        lo = 0;
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) >> 1;
+            if (ptr[mptr[mid]] < target) lo = mid + 1;
+            else hi = mid;
+        }
+    }
+    blk[b] = make_int4((int)lo, (int)mptr[lo], ptr[mptr[lo]], 0);
+}
+
+// the most entries and rows of a block
+__global__ void k_v_most(int64_t ngrid, const int4 *__restrict__ blk, int *__restrict__ most) {
+    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (b >= ngrid) return;
+    atomicMax(most, blk[b + 1].z - (blk[b].z & ~1));
+    atomicMax(most + 1, blk[b + 1].y - blk[b].y);
+}
+
+// the most entries of an aggregate
+__global__ void k_v_most_agg(int64_t nc, const int64_t *__restrict__ mptr, const int32_t *__restrict__ ptr,
+                             int *__restrict__ most) {
+    const int64_t J = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    int m = J < nc ? ptr[mptr[J + 1]] - ptr[mptr[J]] : 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_down(m, o, 64));
+    if (threadIdx.x % 64 == 0) atomicMax(most, m);
+}
+
+__global__ void k_v_child(int64_t n, const int32_t *__restrict__ mem, const int64_t *__restrict__ mptrf,
+                          int2 *__restrict__ child) {
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= n) return;
+    const int64_t i = mem ? mem[p] : p;
+    child[p] = make_int2((int)mptrf[i], (int)mptrf[i + 1]);
+}
+
+// fine level: aggregate map in level 1's order, and its member lists, one
+// thread per place of level 1 (mem1: the row there)
+__global__ void k_v_agg(int64_t n, const int32_t *__restrict__ agg, const int32_t *__restrict__ pos,
+                        int32_t *__restrict__ vagg) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) vagg[i] = pos[agg[i]];
+}
+
+__global__ void k_v_count(int64_t n1, const int32_t *__restrict__ mem1, const int64_t *__restrict__ mptr,
+                          int64_t *__restrict__ len) {
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p < n1) len[p] = mptr[mem1[p] + 1] - mptr[mem1[p]];
+}
+
+__global__ void k_v_members(int64_t n1, const int32_t *__restrict__ mem1, const int64_t *__restrict__ mptr,
+                            const int32_t *__restrict__ mem, const int64_t *__restrict__ vmptr,
+                            int32_t *__restrict__ vmem) {
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= n1) return;
+    int64_t o = vmptr[p];
+    for (int64_t t = mptr[mem1[p]]; t < mptr[mem1[p] + 1]; t++) vmem[o++] = mem[t];
+}
+
+// The members of each stretch that a restriction block stages in LDS, put in
+// ascending order (bitonic sort of (member, place in the stretch) keys); longer
+// stretches keep the member lists' order.
+static_assert(RESTRICT_LDS == 2048, "11 bits of place");
+__global__ void __launch_bounds__(256) k_v_sort(int64_t n1, const int64_t *__restrict__ vmptr,
+                                                int32_t *__restrict__ vmem, uint16_t *__restrict__ vslot) {
+    __shared__ unsigned long long key[RESTRICT_LDS];
+    const int64_t I0 = (int64_t)blockIdx.x * RESTRICT_TPB, I1 = I0 + RESTRICT_TPB < n1 ? I0 + RESTRICT_TPB : n1;
+    const int64_t t0 = vmptr[I0];
+    const int64_t len = vmptr[I1] - t0;
+    if (len > RESTRICT_LDS) {
+        for (int64_t t = threadIdx.x; t < len; t += 256) vslot[t0 + t] = 0;  // not read
+        return;
+    }
+    for (int t = threadIdx.x; t < RESTRICT_LDS; t += 256)
+        key[t] = t < len ? ((unsigned long long)(uint32_t)vmem[t0 + t] << 11) | (unsigned)t : ~0ull;
+    __syncthreads();
+    for (int k = 2; k <= RESTRICT_LDS; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int t = threadIdx.x; t < RESTRICT_LDS / 2; t += 256) {
+                const int lo = (t / j) * 2 * j + t % j, hi = lo + j;
+                const unsigned long long x = key[lo], y = key[hi];
+                if ((x > y) == ((lo & k) == 0)) {
+                    key[lo] = y;
+                    key[hi] = x;
+                }
+            }
+            __syncthreads();
+        }
+    for (int t = threadIdx.x; t < len; t += 256) {
+        vmem[t0 + t] = (int32_t)(key[t] >> 11);
+        vslot[t0 + t] = (uint16_t)(key[t] & 2047);
+    }
+}
+
+// l1 inverse diagonal at the rows' places
+template <class T>
+__global__ void k_v_invd(int64_t n, const int64_t *__restrict__ rowptr, const double *__restrict__ val,
+                         const int32_t *__restrict__ pos, T *__restrict__ invd) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    double s = 0.0;
+    for (int64_t e = rowptr[i]; e < rowptr[i + 1]; e++) s += fabs(val[e]);
+    invd[pos[i]] = convert<T>(1.0 / s);
+}
+
+}  // namespace
+
+// Products and row results of a block in LDS: at most this, so that two
+// blocks share a CU at worst; levels with a larger aggregate keep the separate
+// kernels.
+constexpr size_t V_LDS_MAX = 60 << 10;
+// Entries read past the last block (whole 128-entry runs from an even index).
+constexpr int64_t V_PAD = 128;
+
+rich_status vlevel_order(Level &Lv, int64_t nc, bool mixed, DevAlloc &mem, bool *ok, hipStream_t s) {
+    *ok = false;
+    const size_t tsz = mixed ? sizeof(float) : sizeof(double);
+    // 32-bit entry indices and byte offsets
+    if (Lv.n == 0 || nc == 0 || Lv.nnz >= ((int64_t)1 << 31) - 4096 || Lv.n * (int64_t)tsz >= ((int64_t)1 << 32))
+        return RICH_OK;
+    VLevel &V = Lv.V;
+    DevAlloc tmp;
+    int64_t *len, *ptr, *stmp;
+    int *most;
+    int hm[2] = {0, 0};
+    RICH_TRY(tmp.get(&len, Lv.n));
+    RICH_TRY(tmp.get(&ptr, Lv.n + 1));
+    RICH_TRY(tmp.get(&stmp, scan_tmp_size(Lv.n)));
+    RICH_TRY(tmp.get(&most, 2));
+    RICH_TRY(mem.get(&V.pos, Lv.n));
+    RICH_TRY(mem.get(&V.ptr, Lv.n + 1));
+    k_v_pos<<<nblocks(Lv.n), TPB, 0, s>>>(Lv.n, Lv.mem, Lv.rowptr, V.pos, len);
+    LAUNCH_CHECK();
+    RICH_TRY(scan_exclusive_i64(len, ptr, Lv.n, stmp, s));
+    k_v_narrow<<<nblocks(Lv.n + 1), TPB, 0, s>>>(Lv.n + 1, ptr, V.ptr);
+    RICH_TRY(launch_fill_i32(most, 0, 2, s));
+    k_v_most_agg<<<nblocks(nc), TPB, 0, s>>>(nc, Lv.mptr, V.ptr, most);
+    LAUNCH_CHECK();
+    HIP_TRY(hipMemcpyAsync(hm, most, sizeof(int), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    // A block takes whole aggregates from a stretch of `chunk` entries, so that
+    // with the last one's overhang it fills 512 np: np = 4 where that leaves
+    // eight blocks a CU, less on smaller levels, where the blocks are too few
+    // and a block's latency counts.
+    V.np = Lv.nnz >= (int64_t)2048 * 2048 ? 4 : Lv.nnz >= (int64_t)1024 * 2048 ? 2 : 1;
+    const int chunk = std::max(512 * V.np - hm[0] - 1, 256);
+    const int64_t nb = (Lv.nnz + chunk - 1) / chunk, ngrid = xcd_grid(nb, 1);
+    RICH_TRY(mem.get(&V.blk, ngrid + 1));
+    k_v_blocks<<<nblocks(ngrid + 1), TPB, 0, s>>>(nc, nb, ngrid, chunk, Lv.mptr, V.ptr, V.blk);
+    RICH_TRY(launch_fill_i32(most, 0, 2, s));
+    k_v_most<<<nblocks(ngrid), TPB, 0, s>>>(ngrid, V.blk, most);
+    LAUNCH_CHECK();
+    HIP_TRY(hipMemcpyAsync(hm, most, sizeof(hm), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    V.nblk = (int)ngrid;
+    V.lds_ent = (hm[0] + 127) / 128 * 128;
+    V.lds = (unsigned)(((size_t)(V.lds_ent + hm[1]) * tsz + 15) & ~(size_t)15);
+    if (V.lds > V_LDS_MAX) return RICH_OK;
+    const int64_t mean = Lv.nnz / Lv.n;
+    V.g = mean < 8 ? 1 : mean < 16 ? 2 : mean < 32 ? 4 : 8;
+    RICH_TRY(mem.get(&V.place, Lv.nnz));
+    if (mixed) {
+        RICH_TRY(mem.get(&V.ent, Lv.nnz + V_PAD));
+        RICH_TRY(launch_fill_i32((int32_t *)(V.ent + Lv.nnz), 0, 2 * V_PAD, s));
+        k_v_columns<true><<<nblocks(Lv.n), TPB, 0, s>>>(Lv.n, Lv.mem, Lv.rowptr, Lv.col, V.pos, V.ptr, V.place, V.ent,
+                                                        nullptr);
+    } else {
+        RICH_TRY(mem.get(&V.col, Lv.nnz + V_PAD));
+        RICH_TRY(mem.get(&V.val, Lv.nnz + V_PAD));
+        RICH_TRY(launch_fill_i32((int32_t *)(V.col + Lv.nnz), 0, V_PAD, s));
+        RICH_TRY(launch_fill_f64(V.val + Lv.nnz, 0.0, V_PAD, s));
+        k_v_columns<false><<<nblocks(Lv.n), TPB, 0, s>>>(Lv.n, Lv.mem, Lv.rowptr, Lv.col, V.pos, V.ptr, V.place,
+                                                         nullptr, V.col);
+    }
+    LAUNCH_CHECK();
+    if (mixed) RICH_TRY(mem.get((float **)&V.invd, Lv.n));
+    else RICH_TRY(mem.get((double **)&V.invd, Lv.n));
+    HIP_TRY(hipStreamSynchronize(s));  // tmp is freed on return
+    *ok = true;
+    return RICH_OK;
+}
+
+rich_status vlevel_child(Level &Lv, const Level &Lf, bool ordered, DevAlloc &mem, hipStream_t s) {
+    RICH_TRY(mem.get(&Lv.V.child, Lv.n));
+    k_v_child<<<nblocks(Lv.n), TPB, 0, s>>>(Lv.n, ordered ? Lv.mem : nullptr, Lf.mptr, Lv.V.child);
+    LAUNCH_CHECK();
+    return RICH_OK;
+}
+
+rich_status vlevel_fine(Level &L0, const Level &L1, DevAlloc &mem, hipStream_t s) {
+    DevAlloc tmp;
+    int64_t *len, *stmp;
+    RICH_TRY(tmp.get(&len, L1.n));
+    RICH_TRY(tmp.get(&stmp, scan_tmp_size(L1.n)));
+    RICH_TRY(mem.get(&L0.vagg, L0.n));
+    RICH_TRY(mem.get(&L0.vmptr, L1.n + 1));
+    RICH_TRY(mem.get(&L0.vmem, L0.n));
+    k_v_agg<<<nblocks(L0.n), TPB, 0, s>>>(L0.n, L0.agg, L1.V.pos, L0.vagg);
+    k_v_count<<<nblocks(L1.n), TPB, 0, s>>>(L1.n, L1.mem, L0.mptr, len);
+    LAUNCH_CHECK();
+    RICH_TRY(scan_exclusive_i64(len, L0.vmptr, L1.n, stmp, s));
+    k_v_members<<<nblocks(L1.n), TPB, 0, s>>>(L1.n, L1.mem, L0.mptr, L0.mem, L0.vmptr, L0.vmem);
+    RICH_TRY(mem.get(&L0.vslot, L0.n));
+    k_v_sort<<<nblocks(L1.n, RESTRICT_TPB), 256, 0, s>>>(L1.n, L0.vmptr, L0.vmem, L0.vslot);
+    LAUNCH_CHECK();
+    HIP_TRY(hipStreamSynchronize(s));  // tmp is freed on return
+    return RICH_OK;
+}
+
+rich_status vlevel_values(Level &Lv, bool mixed, hipStream_t s) {
+    const VLevel &V = Lv.V;
+    if (mixed) k_v_values<true><<<nblocks(Lv.nnz), TPB, 0, s>>>(Lv.nnz, Lv.val, V.place, V.ent, nullptr);
+    else k_v_values<false><<<nblocks(Lv.nnz), TPB, 0, s>>>(Lv.nnz, Lv.val, V.place, nullptr, V.val);
+    LAUNCH_CHECK();
+    return RICH_OK;
+}
+
+rich_status vlevel_invd(Level &Lv, bool mixed, hipStream_t s) {
+    if (mixed) k_v_invd<float><<<nblocks(Lv.n), TPB, 0, s>>>(Lv.n, Lv.rowptr, Lv.val, Lv.V.pos, (float *)Lv.V.invd);
+    else k_v_invd<double><<<nblocks(Lv.n), TPB, 0, s>>>(Lv.n, Lv.rowptr, Lv.val, Lv.V.pos, (double *)Lv.V.invd);
+    LAUNCH_CHECK();
+    return RICH_OK;
+}
+
+// --------------------------------------------------------------- launchers
+static void entries_of(const VLevel &V, Entries<float> *e) { e->e = V.ent; }
+static void entries_of(const VLevel &V, Entries<double> *e) {
+    e->c_ = V.col;
+    e->v_ = V.val;
+}
+
+template <class T>
+static VArgs<T> down_args(const Level *L, int l, int nlev) {
+    const Level &Lv = L[l], &Lc = L[l + 1];
+    VArgs<T> a;
+    memset(&a, 0, sizeof(a));
+    a.blk = Lv.V.blk;
+    a.ptr = Lv.V.ptr;
+    entries_of(Lv.V, &a.ent);
+    a.b = (const T *)Lv.b;
+    a.v = (const T *)Lv.x;
+    a.mptr = Lv.mptr;
+    a.bc = (T *)Lc.b;
+    if (l + 1 < nlev - 1) {
+        a.pos = Lc.V.pos;
+        a.invdc = (const T *)Lc.V.invd;
+        a.x0c = (T *)Lc.x;
+    }
+    a.lds_ent = Lv.V.lds_ent;
+    return a;
+}
+
+template <class T>
+static VArgs<T> up_args(const Level *L, int l) {
+    const Level &Lv = L[l];
+    VArgs<T> a;
+    memset(&a, 0, sizeof(a));
+    a.blk = Lv.V.blk;
+    a.ptr = Lv.V.ptr;
+    entries_of(Lv.V, &a.ent);
+    a.b = (const T *)Lv.b;
+    a.v = (const T *)Lv.r;
+    a.invd = (const T *)Lv.V.invd;
+    if (l == 1) {
+        a.x = (T *)Lv.x;
+    } else {
+        a.child = Lv.V.child;
+        a.x0f = (const T *)L[l - 1].x;
+        a.xtf = (T *)L[l - 1].r;
+    }
+    a.lds_ent = Lv.V.lds_ent;
+    return a;
+}
+
+// f(np, g) with the level's split as compile-time constants
+template <class F>
+static void with_split(const VLevel &V, F &&f) {
+    auto by_g = [&](auto np) {
+        switch (V.g) {
+        case 1: f(np, std::integral_constant<int, 1>()); break;
+        case 2: f(np, std::integral_constant<int, 2>()); break;
+        case 4: f(np, std::integral_constant<int, 4>()); break;
+        default: f(np, std::integral_constant<int, 8>()); break;
+        }
+    };
+    if (V.np == 4) by_g(std::integral_constant<int, 4>());
+    else if (V.np == 2) by_g(std::integral_constant<int, 2>());
+    else by_g(std::integral_constant<int, 1>());
+}
+
+template <class T, bool UP>
+static void vlevel_launch(const VLevel &V, const VArgs<T> &a, hipStream_t s) {
+    with_split(V, [&](auto np, auto g) {
+        k_vlevel<np(), g(), T, UP><<<(unsigned)V.nblk, 256, V.lds, s>>>(a);
+    });
+}
+
+template <class T>
+rich_status launch_vdown(const Level *L, int l, int nlev, hipStream_t s) {
+    vlevel_launch<T, false>(L[l].V, down_args<T>(L, l, nlev), s);
+    LAUNCH_CHECK();
+    return RICH_OK;
+}
+template <class T>
+rich_status launch_vup(const Level *L, int l, hipStream_t s) {
+    vlevel_launch<T, true>(L[l].V, up_args<T>(L, l), s);
+    LAUNCH_CHECK();
+    return RICH_OK;
+}
+
+template <class T>
+static GemvArgs<T, T> gemv_args(const Level *L, int nlev, const T *Ainv, bool prolong) {
+    const Level &Lc = L[nlev - 1];
+    GemvArgs<T, T> g;
+    memset(&g, 0, sizeof(g));
+    g.Ainv = Ainv;
+    g.b = (const T *)Lc.b;
+    g.n = Lc.n;
+    g.x = (T *)Lc.x;
+    if (prolong) {
+        g.child = Lc.V.child;
+        g.x0f = (const T *)L[nlev - 2].x;
+        g.xtf = (T *)L[nlev - 2].r;
+    }
+    return g;
+}
+
+template <class TB, class T>
+rich_status launch_dense_gemv(const T *Ainv, const TB *b, T *x, int64_t n, hipStream_t s) {
+    if (n == 0) return RICH_OK;
+    k_dense_gemv<TB, T><<<nblocks(n * 64), TPB, 0, s>>>(GemvArgs<TB, T>{Ainv, b, n, x, nullptr, nullptr, nullptr});
+    LAUNCH_CHECK();
+    return RICH_OK;
+}
+template rich_status launch_dense_gemv<double, double>(const double *, const double *, double *, int64_t, hipStream_t);
+template rich_status launch_dense_gemv<double, float>(const float *, const double *, float *, int64_t, hipStream_t);
+template rich_status launch_dense_gemv<float, float>(const float *, const float *, float *, int64_t, hipStream_t);
+
+template <class T>
+rich_status launch_vgemv(const Level *L, int nlev, const T *Ainv, hipStream_t s) {
+    k_dense_gemv<T, T><<<nblocks(L[nlev - 1].n * 64), TPB, 0, s>>>(gemv_args<T>(L, nlev, Ainv, true));
+    LAUNCH_CHECK();
+    return RICH_OK;
+}
+
+template <class T>
+rich_status launch_vprolong(const Level *L, int nlev, hipStream_t s) {
+    const Level &Lc = L[nlev - 1];
+    k_v_prolong<T><<<nblocks(Lc.n), TPB, 0, s>>>(Lc.n, (const T *)Lc.x, Lc.V.child, (const T *)L[nlev - 2].x,
+                                                 (T *)L[nlev - 2].r);
+    LAUNCH_CHECK();
+    return RICH_OK;
+}
+
+template <class T, bool UP>
+static rich_status vlevel_batch(const std::vector<VItem<T>> &v, int l, hipStream_t s, WorkQueue *q) {
+    // one launch for the simulations whose level takes the same split
+    std::vector<char> done(v.size(), 0);
+    for (size_t first = 0; first < v.size(); first++) {
+        if (done[first] || l >= v[first].nlev - 1) continue;
+        const VLevel &V = v[first].L[l].V;
+        std::vector<VArgs<T>> a;
+        std::vector<unsigned> nb;
+        unsigned lds = 0;
+        for (size_t i = first; i < v.size(); i++) {
+            if (done[i] || l >= v[i].nlev - 1) continue;
+            const VLevel &W = v[i].L[l].V;
+            if (W.np != V.np || W.g != V.g) continue;
+            done[i] = 1;
+            if constexpr (UP) a.push_back(up_args<T>(v[i].L, l));
+            else a.push_back(down_args<T>(v[i].L, l, v[i].nlev));
+            nb.push_back((unsigned)W.nblk);
+            lds = std::max(lds, W.lds);
+        }
+        rich_status st = RICH_OK;
+        with_split(V, [&](auto np, auto g) {
+            st = launch_batches(a, nb, [&](const Batch<VArgs<T>> &bt, unsigned grid) {
+                k_vlevel_batch<np(), g(), T, UP><<<grid, 256, lds, s>>>(bt);
+            }, q);
+        });
+        RICH_TRY(st);
+    }
+    return RICH_OK;
+}
+
+template <class T>
+rich_status launch_vdown_batch(const std::vector<VItem<T>> &v, int l, hipStream_t s, WorkQueue *q) {
+    return vlevel_batch<T, false>(v, l, s, q);
+}
+template <class T>
+rich_status launch_vup_batch(const std::vector<VItem<T>> &v, int l, hipStream_t s, WorkQueue *q) {
+    return vlevel_batch<T, true>(v, l, s, q);
+}
+
+template <class T>
+rich_status launch_vgemv_batch(const std::vector<VItem<T>> &v, hipStream_t s, WorkQueue *q) {
+    std::vector<GemvArgs<T, T>> a;
+    std::vector<unsigned> nb;
+    for (const auto &it : v) {
+        a.push_back(gemv_args<T>(it.L, it.nlev, it.Ainv, it.nlev > 2));
+        nb.push_back(nblocks(it.L[it.nlev - 1].n * 64));
+    }
+    return launch_batches(a, nb, [&](const Batch<GemvArgs<T, T>> &bt, unsigned g) {
+        k_dense_gemv_batch<T><<<g, TPB, 0, s>>>(bt);
+    }, q);
+}
+
+#define INST_V(T)                                                                                      \
+    template rich_status launch_vdown<T>(const Level *, int, int, hipStream_t);                        \
+    template rich_status launch_vup<T>(const Level *, int, hipStream_t);                               \
+    template rich_status launch_vgemv<T>(const Level *, int, const T *, hipStream_t);                  \
+    template rich_status launch_vprolong<T>(const Level *, int, hipStream_t);                          \
+    template rich_status launch_vdown_batch<T>(const std::vector<VItem<T>> &, int, hipStream_t, WorkQueue *); \
+    template rich_status launch_vup_batch<T>(const std::vector<VItem<T>> &, int, hipStream_t, WorkQueue *);   \
+    template rich_status launch_vgemv_batch<T>(const std::vector<VItem<T>> &, hipStream_t, WorkQueue *);
+INST_V(double)
+INST_V(float)
+
+}  // namespace rich

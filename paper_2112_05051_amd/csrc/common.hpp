@@ -436,11 +436,10 @@ void batcher_stats(rich_batcher *B, int64_t *flushes, int64_t *items);
 rich_status members(const int32_t *agg, int64_t n, int64_t nc, int64_t *mptr, int32_t *mem,
                     hipStream_t s);
 rich_status csr_invd(const CsrDev &A, double *invd, float *invdf, hipStream_t s);
-// dense row-major inverse of an SPD CSR matrix (blocked symmetric sweeps; RICH_NOT_SPD on a
-// non-positive pivot) in D, or in Df (FP32) when it is set (D then holds the lower triangle
-// only); ws holds dense_inverse_ws(n) doubles
+// dense row-major inverse of an SPD CSR matrix (blocked Gauss-Jordan; RICH_NOT_SPD on a
+// non-positive pivot); ws holds dense_inverse_ws(n) doubles
 int64_t dense_inverse_ws(int64_t n);
-rich_status dense_inverse(const CsrDev &A, double *D, float *Df, double *ws, hipStream_t s);
+rich_status dense_inverse(const CsrDev &A, double *D, double *ws, hipStream_t s);
 rich_status compose_agg(int32_t *comp, const int32_t *a, int64_t n, hipStream_t s);
 // Decoupled greedy aggregation of A over blocks of `block` rows (strength
 // threshold theta); agg (n) receives aggregate ids, *nc their number.

@@ -345,8 +345,11 @@ rich_status build_hierarchy(rich_ctx *h) {
         RICH_TRY(H.mem.get(&H.cinv, Lc.n * Lc.n));
         RICH_TRY(H.mem.get(&H.cws, dense_inverse_ws(Lc.n)));
         CsrDev A{Lc.n, Lc.nnz, Lc.rowptr, Lc.col, Lc.val};
-        if (h->mixed) RICH_TRY(H.mem.get(&H.cinvf, Lc.n * Lc.n));
-        RICH_TRY(dense_inverse(A, H.cinv, H.cinvf, H.cws, s));
+        RICH_TRY(dense_inverse(A, H.cinv, H.cws, s));
+        if (h->mixed) {
+            RICH_TRY(H.mem.get(&H.cinvf, Lc.n * Lc.n));
+            RICH_TRY(launch_cast(H.cinv, H.cinvf, Lc.n * Lc.n, s));
+        }
     }
     RICH_TRY(sync(h));
     // with source lists the refreshes read M itself: its CSR form served the set-up only
@@ -391,7 +394,8 @@ rich_status refresh_hierarchy(rich_ctx *h) {
     if (H.dense) {
         Level &Lc = H.L[H.nlev - 1];
         CsrDev A{Lc.n, Lc.nnz, Lc.rowptr, Lc.col, Lc.val};
-        RICH_TRY(dense_inverse(A, H.cinv, H.cinvf, H.cws, s));
+        RICH_TRY(dense_inverse(A, H.cinv, H.cws, s));
+        if (h->mixed) RICH_TRY(launch_cast(H.cinv, H.cinvf, Lc.n * Lc.n, s));
     }
     return sync(h);
 }
