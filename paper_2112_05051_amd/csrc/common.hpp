@@ -336,6 +336,24 @@ rich_status scan_exclusive_i64(const int64_t *in, int64_t *out, int64_t n, int64
                                hipStream_t s);
 
 // ---------------------------------------------------------------------- AMG
+// A smoothed coarse level in aggregate order (coarse.hip): its rows follow the
+// member lists of the next level's aggregates.
+struct VLevel {
+    int32_t *pos = nullptr;   // place of each row
+    int32_t *ptr = nullptr;   // row starts in that order (n + 1)
+    int32_t *place = nullptr; // place of each entry of the level's matrix
+    int2 *ent = nullptr;      // FP32 cycle: (byte offset of the column's value, value bits)
+    uint32_t *col = nullptr;  // FP64 cycle: byte offsets, values
+    double *val = nullptr;
+    void *invd = nullptr;     // l1 inverse diagonal, the cycle's precision
+    int2 *child = nullptr;    // rows [x, y) of the finer level that each row stands for (also set on the coarsest)
+    int4 *blk = nullptr;      // block table, nblk + 1
+    int nblk = 0, np = 1;     // blocks, of about 512 np entries
+    int g = 1;                // partial sums per row
+    int lds_ent = 0;          // entries of the largest block
+    unsigned lds = 0;         // LDS bytes of a launch
+};
+
 struct Level {
     int64_t n = 0, nnz = 0;
     int64_t *rowptr = nullptr;  // CSR (levels >= 1 only)
@@ -345,6 +363,12 @@ struct Level {
     double *invd = nullptr;     // 1 / sum_j |a_ij|
     float *invdf = nullptr;
     int32_t *agg = nullptr;     // to level+1 (n)
+    // level 0 of an ordered hierarchy: agg, mptr and mem in level 1's order (else those)
+    int32_t *vagg = nullptr;
+    int64_t *vmptr = nullptr;
+    int32_t *vmem = nullptr;    // ascending in each stretch that a restriction block stages
+    uint16_t *vslot = nullptr;  // and the place of each in its stretch
+    VLevel V;
     int64_t *mptr = nullptr;    // members of each coarse row (n_{l+1} + 1)
     int32_t *mem = nullptr;     // (n)
     // V-cycle work vectors, in the cycle's precision
@@ -370,11 +394,14 @@ struct Level {
     uint32_t *gsrc = nullptr;  // nnz: value indices (level 0: into the M stencil arrays)
 };
 constexpr int STREAM_CHUNK = 1536, STREAM_MAXROW = 512;
+// coarse rows of a restriction block, and the members it stages in LDS
+constexpr int RESTRICT_TPB = 256, RESTRICT_LDS = 2048;
 
 struct Hierarchy {
     int nlev = 0;
     Level L[16];
     bool dense = false;          // coarsest solved by dense inverse
+    bool ordered = false;        // levels 1 .. nlev-2 run in aggregate order
     double *cinv = nullptr;      // n_c x n_c inverse (row-major), FP64
     float *cinvf = nullptr;
     double *cws = nullptr;       // workspace of the inverse (kept: refreshes must not allocate)
@@ -419,10 +446,11 @@ rich_status galerkin_numeric(const CsrDev &A, const int32_t *agg, const int64_t 
 // else A's values.  Needs A.nnz and 4 A.n below 2^32.
 rich_status galerkin_sources(const CsrDev &A, const int32_t *agg, const int64_t *mptr, const int32_t *mem,
                              const CsrDev &C, const Grid3 *g, uint32_t *gptr, uint32_t *gsrc, hipStream_t s);
-// cval[q] = sum of val at q's sources, and its FP32 copy when cvalf is set:
-// the values galerkin_numeric gives, bit for bit
-rich_status galerkin_sum(int64_t cnnz, const uint32_t *gptr, const uint32_t *gsrc, const double *val, double *cval,
-                         float *cvalf, hipStream_t s);
+// Values of the next level Lc = sums of val at each entry's sources (the values
+// galerkin_numeric gives, bit for bit), with the copy the cycle reads: in
+// aggregate order when Lc is ordered, else FP32 when mixed.
+rich_status galerkin_sum(const uint32_t *gptr, const uint32_t *gsrc, const double *val, Level &Lc, bool ordered,
+                         bool mixed, hipStream_t s);
 // Fused serving launches (solver.hip): a batcher gathers the preconditioned
 // products of the GMRES solves of the simulations attached to it and its
 // thread issues them as batched launches on its own stream (on the device
@@ -448,19 +476,13 @@ rich_status vmb_aggregate(const CsrDev &A, double theta, int64_t block, int32_t 
 // r = b - A x0 (x0 = D^{-1} b, the pre-smoothed iterate from zero, stored by the restriction)
 template <class TB, class T>
 rich_status launch_csr_pre(const Level &Lv, const T *val, const T *x0, const TB *b, T *r, hipStream_t s);
-// Batched coarse-level V-cycle steps over several simulations (levels with
-// CSR-stream row blocks and a piecewise-constant prolongator only).
-// CsrItem: pre: out = r = b - A x0;  post: out = x = post-smooth(x0 + P xc)
-// (the level's r buffer holds x0 + P xc).
-template <class T>
-struct CsrItem {
-    const Level *Lv;
-    const T *val, *invd, *b, *x0, *xc;
-    T *out;
-};
+// Batched restrictions from the fine level over several simulations
+// (piecewise-constant prolongators only).
 template <class T>
 struct RestrictItem {
-    const Level *Lv;  // the finer level (its members lists)
+    const int64_t *mptr;  // the finer level's members lists
+    const int32_t *mem;
+    const uint16_t *slot;
     const T *r;
     T *bc;
     int64_t nc;
@@ -468,19 +490,44 @@ struct RestrictItem {
     T *x0c;
 };
 template <class T>
-struct GemvItem {
-    const T *Ainv, *b;
-    T *x;
-    int64_t n;
+rich_status launch_restrict_batch(const std::vector<RestrictItem<T>> &items, hipStream_t s, WorkQueue *q = nullptr);
+
+// Coarse levels in aggregate order (coarse.hip).  vlevel_order gives a level
+// its order (nc aggregates), block table and columns, *ok = false when it does
+// not fit the kernels; vlevel_child its rows' runs on the finer level Lf
+// (ordered: Lv itself is in aggregate order); vlevel_fine the fine level's
+// aggregate map and member lists in level 1's order; vlevel_values and vlevel_invd copy the matrix
+// values and the l1 inverse diagonal to their places.
+rich_status vlevel_order(Level &Lv, int64_t nc, bool mixed, DevAlloc &mem, bool *ok, hipStream_t s);
+rich_status vlevel_child(Level &Lv, const Level &Lf, bool ordered, DevAlloc &mem, hipStream_t s);
+rich_status vlevel_fine(Level &L0, const Level &L1, DevAlloc &mem, hipStream_t s);
+rich_status vlevel_values(Level &Lv, bool mixed, hipStream_t s);
+rich_status vlevel_invd(Level &Lv, bool mixed, hipStream_t s);
+// down: sweep from x0 and restriction of level l; up: sweep from xt and, above
+// level 1, prolongation into level l-1's xt (its r buffer); vgemv: the direct
+// coarsest solve and its prolongation; vprolong: the prolongation of the
+// coarsest level's x alone
+template <class T>
+rich_status launch_vdown(const Level *L, int l, int nlev, hipStream_t s);
+template <class T>
+rich_status launch_vup(const Level *L, int l, hipStream_t s);
+template <class T>
+rich_status launch_vgemv(const Level *L, int nlev, const T *Ainv, hipStream_t s);
+template <class T>
+rich_status launch_vprolong(const Level *L, int nlev, hipStream_t s);
+// the same over several simulations' hierarchies
+template <class T>
+struct VItem {
+    const Level *L;
+    int nlev;
+    const T *Ainv;
 };
 template <class T>
-rich_status launch_csr_pre_batch(const std::vector<CsrItem<T>> &items, hipStream_t s, WorkQueue *q = nullptr);
+rich_status launch_vdown_batch(const std::vector<VItem<T>> &items, int l, hipStream_t s, WorkQueue *q = nullptr);
 template <class T>
-rich_status launch_csr_post_batch(const std::vector<CsrItem<T>> &items, hipStream_t s, WorkQueue *q = nullptr);
+rich_status launch_vup_batch(const std::vector<VItem<T>> &items, int l, hipStream_t s, WorkQueue *q = nullptr);
 template <class T>
-rich_status launch_restrict_batch(const std::vector<RestrictItem<T>> &items, hipStream_t s, WorkQueue *q = nullptr);
-template <class T>
-rich_status launch_dense_gemv_batch(const std::vector<GemvItem<T>> &items, hipStream_t s, WorkQueue *q = nullptr);
+rich_status launch_vgemv_batch(const std::vector<VItem<T>> &items, hipStream_t s, WorkQueue *q = nullptr);
 // x = post-smooth(x0 + P xc); the level's r buffer holds the prolongated iterate
 template <class TB, class T>
 rich_status launch_csr_post(const Level &Lv, const T *val, const T *invd, const TB *b, const T *x0,

@@ -314,11 +314,27 @@ rich_status build_hierarchy(rich_ctx *h) {
         l++;
     }
     H.nlev = l + 1;
+    // the smoothed coarse levels in aggregate order, when every one of them
+    // fits those kernels (piecewise-constant transfers, no huge aggregate)
+    H.ordered = H.nlev > 2;
+    for (int t = 0; t < H.nlev - 1; t++) H.ordered = H.ordered && !H.L[t].prow;
+    for (int t = 1; t < H.nlev - 1 && H.ordered; t++)
+        RICH_TRY(vlevel_order(H.L[t], H.L[t + 1].n, h->mixed, H.mem, &H.ordered, s));
+    for (int t = 1; t < H.nlev - 1 && !H.ordered; t++) {
+        VLevel &V = H.L[t].V;
+        for (void *q : {(void *)V.pos, (void *)V.ptr, (void *)V.place, (void *)V.ent, (void *)V.col, (void *)V.val,
+                        V.invd, (void *)V.blk})
+            if (q) H.mem.release(q);
+        V = VLevel{};
+    }
     // smoother data, FP32 copies, work vectors
     size_t esz = h->mixed ? sizeof(float) : sizeof(double);
     for (int t = 0; t < H.nlev; t++) {
         Level &Lv = H.L[t];
-        if (t > 0) {
+        if (t > 0 && H.ordered && t < H.nlev - 1) {
+            RICH_TRY(vlevel_values(Lv, h->mixed, s));
+            RICH_TRY(vlevel_invd(Lv, h->mixed, s));
+        } else if (t > 0) {
             CsrDev A{Lv.n, Lv.nnz, Lv.rowptr, Lv.col, Lv.val};
             RICH_TRY(H.mem.get(&Lv.invd, Lv.n));
             if (h->mixed) {
@@ -330,6 +346,7 @@ rich_status build_hierarchy(rich_ctx *h) {
             // levels smoothed inside the cycle get their CSR-stream row blocks
             if (t < H.nlev - 1) RICH_TRY(stream_blocks(Lv, H.mem, s));
         }
+        if (t > 1 && H.ordered) RICH_TRY(vlevel_child(Lv, H.L[t - 1], t < H.nlev - 1, H.mem, s));
         char *b, *x, *r;
         RICH_TRY(H.mem.get(&b, Lv.n * esz));
         RICH_TRY(H.mem.get(&x, Lv.n * esz));
@@ -338,6 +355,8 @@ rich_status build_hierarchy(rich_ctx *h) {
         Lv.x = x;
         Lv.r = r;
     }
+    H.L[0].vagg = H.L[0].agg;
+    if (H.ordered) RICH_TRY(vlevel_fine(H.L[0], H.L[1], H.mem, s));
     // coarsest solver
     Level &Lc = H.L[H.nlev - 1];
     H.dense = Lc.n <= h->O.coarse_dense_max;
@@ -360,6 +379,12 @@ rich_status build_hierarchy(rich_ctx *h) {
         H.L[0].rowptr = nullptr;
         H.L[0].col = nullptr;
         H.L[0].val = nullptr;
+        if (H.ordered) {  // and so did its member lists in natural order
+            H.mem.release(H.L[0].mptr);
+            H.mem.release(H.L[0].mem);
+            H.L[0].mptr = nullptr;
+            H.L[0].mem = nullptr;
+        }
     }
     return RICH_OK;
 }
@@ -380,15 +405,17 @@ rich_status refresh_hierarchy(rich_ctx *h) {
             Level &Lf = H.L[l], &Lc = H.L[l + 1];
             CsrDev A{Lf.n, Lf.nnz, Lf.rowptr, Lf.col, Lf.val};
             CsrDev C{Lc.n, Lc.nnz, Lc.rowptr, Lc.col, Lc.val};
+            const bool ord = H.ordered && l + 1 < H.nlev - 1;
             if (Lf.gsrc) {
-                RICH_TRY(galerkin_sum(Lc.nnz, Lf.gptr, Lf.gsrc, l == 0 ? h->M4 : Lf.val, Lc.val,
-                                      h->mixed ? Lc.valf : nullptr, s));
+                RICH_TRY(galerkin_sum(Lf.gptr, Lf.gsrc, l == 0 ? h->M4 : Lf.val, Lc, ord, h->mixed, s));
             } else {
                 if (Lf.prow) RICH_TRY(sa_numeric(A, Lf.agg, Lf, C, h->mixed, s));
                 else RICH_TRY(galerkin_numeric(A, Lf.agg, Lf.mptr, Lf.mem, C, s));
-                if (h->mixed) RICH_TRY(launch_cast(Lc.val, Lc.valf, Lc.nnz, s));
+                if (ord) RICH_TRY(vlevel_values(Lc, h->mixed, s));
+                else if (h->mixed) RICH_TRY(launch_cast(Lc.val, Lc.valf, Lc.nnz, s));
             }
-            RICH_TRY(csr_invd(C, Lc.invd, Lc.invdf, s));
+            if (ord) RICH_TRY(vlevel_invd(Lc, h->mixed, s));
+            else RICH_TRY(csr_invd(C, Lc.invd, Lc.invdf, s));
         }
     }
     if (H.dense) {
@@ -450,35 +477,53 @@ rich_status vcycle(rich_ctx *h, const double *b, const double *bs, T *z) {
     // each restriction also stores the next level's pre-smoothed iterate
     // x0 = D^{-1} b in its x buffer, except for the coarsest level
     auto x0_of = [&](int l) { return l < H.nlev - 1 ? (T *)H.L[l].x : nullptr; };
+    const bool ord = H.ordered;
+    const T *invd1 = ord ? (const T *)H.L[1].V.invd : lvinvd<T>(H.L[1]);
     RICH_TRY(timed(h, RICH_K_VC0_RESTRICT, rbytes, [&] {
-        return launch_restrict<T>(H.L[0], (const T *)H.L[0].r, (T *)H.L[1].b, H.L[1].n, lvinvd<T>(H.L[1]), x0_of(1),
-                                  s);
+        return launch_restrict<T>(H.L[0], (const T *)H.L[0].r, (T *)H.L[1].b, H.L[1].n, invd1, x0_of(1), s);
     }));
     for (int l = 1; l < H.nlev - 1; l++) {
         Level &Lv = H.L[l];
+        const int id = l == 1 ? RICH_K_VC1_PRE : RICH_K_COUNT;
+        const double nc = (double)H.L[l + 1].n, low = l + 1 < H.nlev - 1 ? 1.0 : 0.0;
+        if (ord) {
+            const double bytes = (double)Lv.nnz * (4 + t) + (double)Lv.n * (4 + 2 * t) + nc * (8 + t + low * (4 + 2 * t));
+            RICH_TRY(timed(h, id, bytes, [&] { return launch_vdown<T>(H.L, l, H.nlev, s); }));
+            continue;
+        }
         double bytes = (double)Lv.nnz * (4 + t) + (double)Lv.n * (8 + 3 * t);
-        RICH_TRY(timed(h, l == 1 ? RICH_K_VC1_PRE : RICH_K_COUNT, bytes, [&] {
+        RICH_TRY(timed(h, id, bytes, [&] {
             return launch_csr_pre<T, T>(Lv, lvval<T>(Lv), (const T *)Lv.x, (const T *)Lv.b, (T *)Lv.r, s);
         }));
-        charge(h, (double)Lv.n * (t + 4) + (double)H.L[l + 1].n * (8 + t + (l + 1 < H.nlev - 1 ? 2 * t : 0)));
+        charge(h, (double)Lv.n * (t + 4) + nc * (8 + t + low * 2 * t));
         RICH_TRY(launch_restrict<T>(Lv, (const T *)Lv.r, (T *)H.L[l + 1].b, H.L[l + 1].n, lvinvd<T>(H.L[l + 1]),
                                     x0_of(l + 1), s));
     }
     // coarsest
     Level &Lc = H.L[H.nlev - 1];
+    const double pbytes_c = ord ? (double)Lc.n * 8 + (double)H.L[H.nlev - 2].n * 2 * t : 0.0;
     if (H.dense) {
-        charge(h, (double)Lc.n * Lc.n * t + 2.0 * Lc.n * t);
-        RICH_TRY(launch_dense_gemv<T, T>(cinv, (const T *)Lc.b, (T *)Lc.x, Lc.n, s));
+        charge(h, (double)Lc.n * Lc.n * t + 2.0 * Lc.n * t + pbytes_c);
+        if (ord) RICH_TRY(launch_vgemv<T>(H.L, H.nlev, cinv, s));
+        else RICH_TRY(launch_dense_gemv<T, T>(cinv, (const T *)Lc.b, (T *)Lc.x, Lc.n, s));
     } else {
-        charge(h, h->O.coarse_l1_sweeps * ((double)Lc.nnz * (4 + t) + (double)Lc.n * (8 + 4 * t)));
+        charge(h, h->O.coarse_l1_sweeps * ((double)Lc.nnz * (4 + t) + (double)Lc.n * (8 + 4 * t)) + pbytes_c);
         RICH_TRY(launch_csr_sweeps<T, T>(Lc, lvval<T>(Lc), lvinvd<T>(Lc), (const T *)Lc.b, (T *)Lc.x, (T *)Lc.r,
                                          h->O.coarse_l1_sweeps, s));
+        if (ord) RICH_TRY(launch_vprolong<T>(H.L, H.nlev, s));
     }
     // up
     for (int l = H.nlev - 2; l >= 1; l--) {
         Level &Lv = H.L[l];
+        const int id = l == 1 ? RICH_K_VC1_POST : RICH_K_COUNT;
+        if (ord) {
+            const double bytes = (double)Lv.nnz * (4 + t) + (double)Lv.n * (4 + 3 * t) +
+                                 (l == 1 ? (double)Lv.n * t : (double)Lv.n * 8 + (double)H.L[l - 1].n * 2 * t);
+            RICH_TRY(timed(h, id, bytes, [&] { return launch_vup<T>(H.L, l, s); }));
+            continue;
+        }
         double bytes = (double)Lv.nnz * (4 + t) + (double)Lv.n * (12 + 7 * t) + (double)H.L[l + 1].n * t;
-        RICH_TRY(timed(h, l == 1 ? RICH_K_VC1_POST : RICH_K_COUNT, bytes, [&] {
+        RICH_TRY(timed(h, id, bytes, [&] {
             return launch_csr_post<T, T>(Lv, lvval<T>(Lv), lvinvd<T>(Lv), (const T *)Lv.b, (const T *)Lv.x,
                                          (const T *)H.L[l + 1].x, (T *)Lv.x, s);
         }));
@@ -489,7 +534,7 @@ rich_status vcycle(rich_ctx *h, const double *b, const double *bs, T *z) {
             T *xt = (T *)H.L[0].r;
             const T *x0 = (const T *)H.L[0].x, *xc = (const T *)H.L[1].x;
             if (L0.prow) RICH_TRY(launch_sa_prolong<double, T>(L0, invd0, b, bs, x0, xc, xt, s));
-            return launch_gs_post<double, T>(h->P, M4, b, bs, x0, xc, L0.prow ? nullptr : L0.agg, xt, z, s);
+            return launch_gs_post<double, T>(h->P, M4, b, bs, x0, xc, L0.prow ? nullptr : L0.vagg, xt, z, s);
         });
     }
     if (L0.prow) {
@@ -502,7 +547,7 @@ rich_status vcycle(rich_ctx *h, const double *b, const double *bs, T *z) {
         });
     }
     return timed(h, RICH_K_VC0_POST, n0 * (12 + 6 * t) + n1 * t, [&] {
-        return launch_st_post<double, T>(h->P, M4, invd0, b, bs, (const T *)H.L[1].x, H.L[0].agg, z, (T *)H.L[0].r,
+        return launch_st_post<double, T>(h->P, M4, invd0, b, bs, (const T *)H.L[1].x, H.L[0].vagg, z, (T *)H.L[0].r,
                                          s);
     });
 }
@@ -580,74 +625,40 @@ const T *invd0_of(const rich_ctx *h) {
 
 // A simulation can join a batch when its V-cycle has the shape the batched
 // kernels cover: a piecewise-constant hierarchy of two or more levels with a
-// dense coarsest solve and CSR-stream row blocks on every smoothed coarse level.
+// dense coarsest solve, the levels between in aggregate order.
 bool batchable(const rich_ctx *h) {
     const Hierarchy *H = h->H;
     if (!H || H->nlev < 2 || !H->dense || h->O.smoother != RICH_SMOOTH_L1) return false;
-    for (int l = 0; l < H->nlev - 1; l++) {
-        if (H->L[l].prow) return false;
-        if (l >= 1 && !H->L[l].rb) return false;
-    }
-    return true;
+    return H->nlev == 2 ? !H->L[0].prow : H->ordered;
 }
 
 template <class T>
 rich_status apply_batch(const std::vector<BatchReq> &rq, hipStream_t s, WorkQueue *q) {
     if (rq.empty()) return RICH_OK;
-    auto x0_of = [](const Hierarchy &H, int l) { return l < H.nlev - 1 ? (T *)H.L[l].x : nullptr; };
     int maxlev = 0;
     for (const auto &q : rq) maxlev = std::max(maxlev, q.h->H->nlev);
     std::vector<FineItem<double, T>> f;
     std::vector<RestrictItem<T>> ri;
-    std::vector<CsrItem<T>> ci;
-    std::vector<GemvItem<T>> gi;
-    // down: fine pre-smoothing + residual, restriction
+    std::vector<VItem<T>> vi;
+    // down: fine pre-smoothing + residual, restriction, the levels in order
     for (const auto &q : rq) {
         Hierarchy &H = *q.h->H;
-        f.push_back({&q.h->P, m4_of<T>(q.h), invd0_of<T>(q.h), q.b, q.bs, nullptr, nullptr, nullptr, (T *)H.L[0].r});
-        ri.push_back({&H.L[0], (const T *)H.L[0].r, (T *)H.L[1].b, H.L[1].n, lvinvd<T>(H.L[1]), x0_of(H, 1)});
+        const Level &L0 = H.L[0], &L1 = H.L[1];
+        f.push_back({&q.h->P, m4_of<T>(q.h), invd0_of<T>(q.h), q.b, q.bs, nullptr, nullptr, nullptr, (T *)L0.r});
+        ri.push_back({L0.vmptr ? L0.vmptr : L0.mptr, L0.vmem ? L0.vmem : L0.mem, L0.vslot, (const T *)L0.r, (T *)L1.b, L1.n,
+                      (const T *)L1.V.invd, H.nlev > 2 ? (T *)L1.x : nullptr});
+        vi.push_back({H.L, H.nlev, q.h->mixed ? (const T *)(const void *)H.cinvf : (const T *)(const void *)H.cinv});
     }
     RICH_TRY(launch_st_pre_batch<double, T>(f, s, q));
     RICH_TRY(launch_restrict_batch<T>(ri, s, q));
-    for (int l = 1; l < maxlev - 1; l++) {
-        ci.clear();
-        ri.clear();
-        for (const auto &q : rq) {
-            Hierarchy &H = *q.h->H;
-            if (l >= H.nlev - 1) continue;
-            Level &Lv = H.L[l];
-            ci.push_back({&Lv, lvval<T>(Lv), nullptr, (const T *)Lv.b, (const T *)Lv.x, nullptr, (T *)Lv.r});
-            ri.push_back({&Lv, (const T *)Lv.r, (T *)H.L[l + 1].b, H.L[l + 1].n, lvinvd<T>(H.L[l + 1]),
-                          x0_of(H, l + 1)});
-        }
-        RICH_TRY(launch_csr_pre_batch<T>(ci, s, q));
-        RICH_TRY(launch_restrict_batch<T>(ri, s, q));
-    }
-    // coarsest
-    for (const auto &q : rq) {
-        Hierarchy &H = *q.h->H;
-        Level &Lc = H.L[H.nlev - 1];
-        const T *cinv = q.h->mixed ? (const T *)(const void *)H.cinvf : (const T *)(const void *)H.cinv;
-        gi.push_back({cinv, (const T *)Lc.b, (T *)Lc.x, Lc.n});
-    }
-    RICH_TRY(launch_dense_gemv_batch<T>(gi, s, q));
-    // up: prolongation + post-smoothing
-    for (int l = maxlev - 2; l >= 1; l--) {
-        ci.clear();
-        for (const auto &q : rq) {
-            Hierarchy &H = *q.h->H;
-            if (l >= H.nlev - 1) continue;
-            Level &Lv = H.L[l];
-            ci.push_back({&Lv, lvval<T>(Lv), lvinvd<T>(Lv), (const T *)Lv.b, (const T *)Lv.x,
-                          (const T *)H.L[l + 1].x, (T *)Lv.x});
-        }
-        RICH_TRY(launch_csr_post_batch<T>(ci, s, q));
-    }
+    for (int l = 1; l < maxlev - 1; l++) RICH_TRY(launch_vdown_batch<T>(vi, l, s, q));
+    RICH_TRY(launch_vgemv_batch<T>(vi, s, q));
+    for (int l = maxlev - 2; l >= 1; l--) RICH_TRY(launch_vup_batch<T>(vi, l, s, q));
     f.clear();
     std::vector<SpmvItem<T>> sp;
     for (const auto &q : rq) {
         Hierarchy &H = *q.h->H;
-        f.push_back({&q.h->P, m4_of<T>(q.h), invd0_of<T>(q.h), q.b, q.bs, (const T *)H.L[1].x, H.L[0].agg,
+        f.push_back({&q.h->P, m4_of<T>(q.h), invd0_of<T>(q.h), q.b, q.bs, (const T *)H.L[1].x, H.L[0].vagg,
                      (T *)H.L[0].r, (T *)q.h->z});
         if (q.w) {
             SpmvItem<T> it{&q.h->P, q.h->J7, (const T *)q.h->z, q.w};

@@ -78,3 +78,30 @@ def test_galerkin_refresh(rich, torch, shape, sweeps, precision):
             A = sp.csr_matrix((val, col, rp), shape=(nc, nc))
     if sweeps == 6:
         assert longest > 32
+
+
+# One V-cycle against the oracle's on the GPU's own M: coarse levels of every
+# split of the aggregate-order kernels (short and long rows, aggregates of 2 to
+# 64 rows, levels of one block up to several thousand, the l1-sweep coarsest
+# level) and, where an aggregate outgrows their LDS, the separate kernels.
+# FP64: the dense inverse's kappa eps; FP32: sums of a few hundred rounded terms.
+@pytest.mark.parametrize("precision,tol", [(synth.FP64, 1e-10), (synth.MIXED, 1e-5)])
+@pytest.mark.parametrize("shape,kw", [
+    ((37, 5, 3), dict(amg_coarse_size=8, coarse_dense_max=8, amg_sweeps=1)),
+    ((60, 1, 1), dict(amg_coarse_size=4, coarse_dense_max=8, amg_sweeps=2)),
+    ((21, 17, 13), dict(amg_coarse_size=8, coarse_dense_max=64)),
+    ((40, 37, 33), dict(amg_coarse_size=8, coarse_dense_max=8, amg_sweeps=6)),
+    ((33, 31, 29), dict(amg_coarse_size=8, coarse_dense_max=8, amg_aggregation=1, amg_block=997)),
+    ((150, 140, 130), dict()), ((150, 140, 130), dict(amg_max_levels=5))])
+def test_vcycle_splits(rich, torch, orc, shape, kw, precision, tol):
+    P = box_problem(*shape, dt=10.0)
+    opts = synth.Options(precision=precision, **kw)
+    s = rich.Solver(P, opts, dev(torch, random_ks(P, 61)))
+    s.assemble(dev(torch, random_heads(P.n, 62, -70, -30)))
+    rp, col, val = s.export_csr(rich.WHICH_A, 0)
+    amg = orc.AMG(opts, sp.csr_matrix((val, col, rp), shape=(P.n, P.n)))
+    assert s.levels() == amg.levels >= 3
+    b = np.random.default_rng(63).standard_normal(P.n)
+    x = s.apply_prec(dev(torch, b)).cpu().numpy()
+    xo = amg.apply(b)
+    assert np.linalg.norm(x - xo) <= tol * np.linalg.norm(xo)
