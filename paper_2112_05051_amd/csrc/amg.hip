@@ -347,7 +347,7 @@ __global__ void __launch_bounds__(64) k_gal_numeric(int64_t nc, const int64_t *_
 // search, no LDS accumulators (which held k_gal_numeric at six waves a CU), and
 // level 0 reads the stencil arrays themselves instead of a CSR copy of them.
 // Bound by the list and value reads (12 bytes per fine entry).  A refresh at
-// 256^3, five levels: 1.1 ms, against 4.0 with k_gal_numeric and 1.2 for the
+// 256^3, five levels: 0.7 ms, against 4.0 with k_gal_numeric and 1.2 for the
 // CSR copy of M.
 // FILL = false counts the sources of each entry, FILL = true lists them; one
 // thread per coarse row, rows of up to GAL_REG entries count in LDS.
@@ -424,44 +424,93 @@ __global__ void k_narrow_u32(int64_t n, const int64_t *__restrict__ in, uint32_t
 // COPY: what else the value goes to: GS_F32 an FP32 copy, GS_ENT / GS_VAL the
 // FP32 / FP64 cycle's entry at its place in aggregate order.
 enum { GS_NONE = 0, GS_F32, GS_ENT, GS_VAL };
+// A block's entries have one contiguous stretch of sources: its threads gather
+// them into LDS with coalesced list reads, all in flight at once, and each
+// thread adds its entry's from there.  (A thread walking its own list waits
+// for two dependent loads per four sources, and a wave for its longest list, a
+// diagonal's of about 26: 1200 us for the five levels at 256^3, now 690.)
+constexpr int GS_TPB = 256, GS_PER = 6, GS_PIECE = GS_TPB * GS_PER;
 template <int COPY>
-__global__ void __launch_bounds__(256) k_gal_sum(int64_t cnnz, const uint32_t *__restrict__ gptr,
-                                                 const uint32_t *__restrict__ gsrc, const double *__restrict__ val,
-                                                 double *__restrict__ cval, float *__restrict__ cvalf,
-                                                 const int32_t *__restrict__ place, int2 *__restrict__ ent,
-                                                 double *__restrict__ vval) {
-    const int64_t q = (int64_t)xcd_block() * blockDim.x + threadIdx.x;
-    if (q >= cnnz) return;
-    const uint32_t t0 = gptr[q], t1 = gptr[q + 1];
+__global__ void __launch_bounds__(GS_TPB) k_gal_sum(int64_t cnnz, const uint32_t *__restrict__ gptr,
+                                                    const uint32_t *__restrict__ gsrc, const double *__restrict__ val,
+                                                    double *__restrict__ cval, float *__restrict__ cvalf,
+                                                    const int32_t *__restrict__ place, const uint32_t *__restrict__ off,
+                                                    int2 *__restrict__ ent, double *__restrict__ vval) {
+    __shared__ double sv[GS_PIECE];
+    const int64_t q0 = (int64_t)xcd_block() * GS_TPB, q = q0 + threadIdx.x;
+    if (q0 >= cnnz) return;
+    const uint32_t t0 = gptr[q0], t1 = gptr[q0 + GS_TPB < cnnz ? q0 + GS_TPB : cnnz];
+    uint32_t a = t1, b = t1, of = 0;
     int32_t pl = 0;
-    if (COPY == GS_ENT || COPY == GS_VAL) pl = place[q];
-    double s = 0.0;
-    // four sources in flight, added in list order
-    for (uint32_t t = t0; t < t1; t += 4) {
-        uint32_t ix[4];
-        double v[4];
-#pragma unroll
-        for (int u = 0; u < 4; u++) ix[u] = gsrc[t + u < t1 ? t + u : t1 - 1];
-#pragma unroll
-        for (int u = 0; u < 4; u++) v[u] = val[ix[u]];
-#pragma unroll
-        for (int u = 0; u < 4; u++)
-            if (t + u < t1) s += v[u];
+    if (q < cnnz) {
+        a = gptr[q];
+        b = gptr[q + 1];
+        if (COPY == GS_ENT || COPY == GS_VAL) pl = place[q];
+        if (COPY == GS_ENT) of = off[q];
     }
+    double s = 0.0;
+    for (uint32_t base = t0; base < t1; base += GS_PIECE) {
+        uint32_t ix[GS_PER];
+        double v[GS_PER];
+#pragma unroll
+        for (int u = 0; u < GS_PER; u++) {
+            const uint32_t t = base + threadIdx.x + GS_TPB * u;
+            ix[u] = t < t1 ? __builtin_nontemporal_load(gsrc + t) : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < GS_PER; u++) v[u] = val[ix[u]];
+        if (base != t0) __syncthreads();  // the previous piece is summed
+#pragma unroll
+        for (int u = 0; u < GS_PER; u++) sv[threadIdx.x + GS_TPB * u] = v[u];
+        __syncthreads();
+        const uint32_t lo = a > base ? a - base : 0u;
+        const uint32_t hi = b <= base ? 0u : b - base < GS_PIECE ? b - base : GS_PIECE;
+        for (uint32_t t = lo; t < hi; t++) s += sv[t];
+    }
+    if (q >= cnnz) return;
     cval[q] = s;
     if (COPY == GS_F32) cvalf[q] = f32_sat(s);
-    if (COPY == GS_ENT) ent[pl].y = __float_as_int(f32_sat(s));
+    if (COPY == GS_ENT) ent[pl] = make_int2((int)of, __float_as_int(f32_sat(s)));
     if (COPY == GS_VAL) vval[pl] = s;
 }
 
-__global__ void k_csr_invd(int64_t n, const int64_t *__restrict__ rowptr, const double *__restrict__ val,
-                           double *__restrict__ invd, float *__restrict__ invdf) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+// l1 inverse diagonals 1 / sum_j |a_ij|, each row's terms added in order: a
+// block's rows have one stretch of values, staged in LDS as above (a thread
+// walking its own row strides across the others': five levels at 256^3 250 us,
+// now 95).
+// pos: place of each row in the results (null: itself).
+constexpr int L1_PIECE = 2048;
+__global__ void __launch_bounds__(256) k_row_l1(int64_t n, const int64_t *__restrict__ rowptr,
+                                                const double *__restrict__ val, const int32_t *__restrict__ pos,
+                                                double *__restrict__ invd, float *__restrict__ invdf) {
+    __shared__ double sv[L1_PIECE];
+    const int64_t r0 = (int64_t)blockIdx.x * 256, i = r0 + threadIdx.x;
+    const int64_t t0 = rowptr[r0], t1 = rowptr[r0 + 256 < n ? r0 + 256 : n];
+    int64_t a = t1, b = t1, to = i;
+    if (i < n) {
+        a = rowptr[i];
+        b = rowptr[i + 1];
+        if (pos) to = pos[i];
+    }
     double s = 0.0;
-    for (int64_t e = rowptr[i]; e < rowptr[i + 1]; e++) s += fabs(val[e]);
-    if (invd) invd[i] = 1.0 / s;
-    if (invdf) invdf[i] = f32_sat(1.0 / s);
+    for (int64_t base = t0; base < t1; base += L1_PIECE) {
+        double v[L1_PIECE / 256];
+#pragma unroll
+        for (int u = 0; u < L1_PIECE / 256; u++) {
+            const int64_t t = base + threadIdx.x + 256 * u;
+            v[u] = t < t1 ? val[t] : 0.0;
+        }
+        if (base != t0) __syncthreads();
+#pragma unroll
+        for (int u = 0; u < L1_PIECE / 256; u++) sv[threadIdx.x + 256 * u] = v[u];
+        __syncthreads();
+        const int lo = a > base ? (int)(a - base < L1_PIECE ? a - base : L1_PIECE) : 0;
+        const int hi = b <= base ? 0 : b - base < L1_PIECE ? (int)(b - base) : L1_PIECE;
+        for (int t = lo; t < hi; t++) s += fabs(sv[t]);
+    }
+    if (i >= n) return;
+    if (invd) invd[to] = 1.0 / s;
+    if (invdf) invdf[to] = f32_sat(1.0 / s);
 }
 
 __global__ void k_compose(int64_t n, int32_t *__restrict__ comp, const int32_t *__restrict__ a) {
@@ -1195,16 +1244,16 @@ rich_status galerkin_sources(const CsrDev &A, const int32_t *agg, const int64_t 
 rich_status galerkin_sum(const uint32_t *gptr, const uint32_t *gsrc, const double *val, Level &Lc, bool ordered,
                          bool mixed, hipStream_t s) {
     if (Lc.nnz == 0) return RICH_OK;
-    const unsigned nb = xcd_grid(Lc.nnz, 256);
+    const unsigned nb = xcd_grid(Lc.nnz, GS_TPB);
     const VLevel &V = Lc.V;
     if (ordered && mixed)
-        k_gal_sum<GS_ENT><<<nb, 256, 0, s>>>(Lc.nnz, gptr, gsrc, val, Lc.val, nullptr, V.place, V.ent, nullptr);
+        k_gal_sum<GS_ENT><<<nb, GS_TPB, 0, s>>>(Lc.nnz, gptr, gsrc, val, Lc.val, nullptr, V.place, V.off, V.ent, nullptr);
     else if (ordered)
-        k_gal_sum<GS_VAL><<<nb, 256, 0, s>>>(Lc.nnz, gptr, gsrc, val, Lc.val, nullptr, V.place, nullptr, V.val);
+        k_gal_sum<GS_VAL><<<nb, GS_TPB, 0, s>>>(Lc.nnz, gptr, gsrc, val, Lc.val, nullptr, V.place, nullptr, nullptr, V.val);
     else if (mixed)
-        k_gal_sum<GS_F32><<<nb, 256, 0, s>>>(Lc.nnz, gptr, gsrc, val, Lc.val, Lc.valf, nullptr, nullptr, nullptr);
+        k_gal_sum<GS_F32><<<nb, GS_TPB, 0, s>>>(Lc.nnz, gptr, gsrc, val, Lc.val, Lc.valf, nullptr, nullptr, nullptr, nullptr);
     else
-        k_gal_sum<GS_NONE><<<nb, 256, 0, s>>>(Lc.nnz, gptr, gsrc, val, Lc.val, nullptr, nullptr, nullptr, nullptr);
+        k_gal_sum<GS_NONE><<<nb, GS_TPB, 0, s>>>(Lc.nnz, gptr, gsrc, val, Lc.val, nullptr, nullptr, nullptr, nullptr, nullptr);
     LAUNCH_CHECK();
     return RICH_OK;
 }
@@ -1249,9 +1298,9 @@ rich_status stream_blocks(Level &Lv, DevAlloc &mem, hipStream_t s) {
     return RICH_OK;
 }
 
-rich_status csr_invd(const CsrDev &A, double *invd, float *invdf, hipStream_t s) {
+rich_status csr_invd(const CsrDev &A, const int32_t *pos, double *invd, float *invdf, hipStream_t s) {
     if (A.n == 0) return RICH_OK;
-    k_csr_invd<<<nblocks(A.n), TPB, 0, s>>>(A.n, A.rowptr, A.val, invd, invdf);
+    k_row_l1<<<nblocks(A.n, 256), 256, 0, s>>>(A.n, A.rowptr, A.val, pos, invd, invdf);
     LAUNCH_CHECK();
     return RICH_OK;
 }

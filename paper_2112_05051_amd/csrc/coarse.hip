@@ -301,15 +301,15 @@ __global__ void k_v_narrow(int64_t n, const int64_t *__restrict__ in, int32_t *_
 template <bool F32>
 __global__ void k_v_columns(int64_t n, const int32_t *__restrict__ mem, const int64_t *__restrict__ rowptr,
                             const int32_t *__restrict__ col, const int32_t *__restrict__ pos,
-                            const int32_t *__restrict__ ptr, int32_t *__restrict__ place, int2 *__restrict__ ent,
-                            uint32_t *__restrict__ vcol) {
+                            const int32_t *__restrict__ ptr, int32_t *__restrict__ place, uint32_t *__restrict__ off,
+                            int2 *__restrict__ ent, uint32_t *__restrict__ vcol) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
     const int32_t i = mem[p];
     int32_t o = ptr[p];
     for (int64_t e = rowptr[i]; e < rowptr[i + 1]; e++, o++) {
         const int32_t c = pos[col[e]];
-        if (F32) ent[o].x = (int)((uint32_t)c * 4u);
+        if (F32) ent[o].x = (int)(off[e] = (uint32_t)c * 4u);
         else vcol[o] = (uint32_t)c * 8u;
         place[e] = o;
     }
@@ -428,17 +428,6 @@ __global__ void __launch_bounds__(256) k_v_sort(int64_t n1, const int64_t *__res
     }
 }
 
-// l1 inverse diagonal at the rows' places
-template <class T>
-__global__ void k_v_invd(int64_t n, const int64_t *__restrict__ rowptr, const double *__restrict__ val,
-                         const int32_t *__restrict__ pos, T *__restrict__ invd) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    double s = 0.0;
-    for (int64_t e = rowptr[i]; e < rowptr[i + 1]; e++) s += fabs(val[e]);
-    invd[pos[i]] = convert<T>(1.0 / s);
-}
-
 }  // namespace
 
 // Products and row results of a block in LDS: at most this, so that two
@@ -498,15 +487,16 @@ rich_status vlevel_order(Level &Lv, int64_t nc, bool mixed, DevAlloc &mem, bool 
     if (mixed) {
         RICH_TRY(mem.get(&V.ent, Lv.nnz + V_PAD));
         RICH_TRY(launch_fill_i32((int32_t *)(V.ent + Lv.nnz), 0, 2 * V_PAD, s));
-        k_v_columns<true><<<nblocks(Lv.n), TPB, 0, s>>>(Lv.n, Lv.mem, Lv.rowptr, Lv.col, V.pos, V.ptr, V.place, V.ent,
-                                                        nullptr);
+        RICH_TRY(mem.get(&V.off, Lv.nnz));
+        k_v_columns<true><<<nblocks(Lv.n), TPB, 0, s>>>(Lv.n, Lv.mem, Lv.rowptr, Lv.col, V.pos, V.ptr, V.place, V.off,
+                                                        V.ent, nullptr);
     } else {
         RICH_TRY(mem.get(&V.col, Lv.nnz + V_PAD));
         RICH_TRY(mem.get(&V.val, Lv.nnz + V_PAD));
         RICH_TRY(launch_fill_i32((int32_t *)(V.col + Lv.nnz), 0, V_PAD, s));
         RICH_TRY(launch_fill_f64(V.val + Lv.nnz, 0.0, V_PAD, s));
         k_v_columns<false><<<nblocks(Lv.n), TPB, 0, s>>>(Lv.n, Lv.mem, Lv.rowptr, Lv.col, V.pos, V.ptr, V.place,
-                                                         nullptr, V.col);
+                                                         nullptr, nullptr, V.col);
     }
     LAUNCH_CHECK();
     if (mixed) RICH_TRY(mem.get((float **)&V.invd, Lv.n));
@@ -547,13 +537,6 @@ rich_status vlevel_values(Level &Lv, bool mixed, hipStream_t s) {
     const VLevel &V = Lv.V;
     if (mixed) k_v_values<true><<<nblocks(Lv.nnz), TPB, 0, s>>>(Lv.nnz, Lv.val, V.place, V.ent, nullptr);
     else k_v_values<false><<<nblocks(Lv.nnz), TPB, 0, s>>>(Lv.nnz, Lv.val, V.place, nullptr, V.val);
-    LAUNCH_CHECK();
-    return RICH_OK;
-}
-
-rich_status vlevel_invd(Level &Lv, bool mixed, hipStream_t s) {
-    if (mixed) k_v_invd<float><<<nblocks(Lv.n), TPB, 0, s>>>(Lv.n, Lv.rowptr, Lv.val, Lv.V.pos, (float *)Lv.V.invd);
-    else k_v_invd<double><<<nblocks(Lv.n), TPB, 0, s>>>(Lv.n, Lv.rowptr, Lv.val, Lv.V.pos, (double *)Lv.V.invd);
     LAUNCH_CHECK();
     return RICH_OK;
 }

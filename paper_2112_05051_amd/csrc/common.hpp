@@ -342,6 +342,7 @@ struct VLevel {
     int32_t *pos = nullptr;   // place of each row
     int32_t *ptr = nullptr;   // row starts in that order (n + 1)
     int32_t *place = nullptr; // place of each entry of the level's matrix
+    uint32_t *off = nullptr;  // FP32 cycle: byte offset of its column's value, by entry
     int2 *ent = nullptr;      // FP32 cycle: (byte offset of the column's value, value bits)
     uint32_t *col = nullptr;  // FP64 cycle: byte offsets, values
     double *val = nullptr;
@@ -463,7 +464,8 @@ void batcher_stats(rich_batcher *B, int64_t *flushes, int64_t *items);
 
 rich_status members(const int32_t *agg, int64_t n, int64_t nc, int64_t *mptr, int32_t *mem,
                     hipStream_t s);
-rich_status csr_invd(const CsrDev &A, double *invd, float *invdf, hipStream_t s);
+// l1 inverse diagonals (either may be null), row i's at pos[i] (null: at i)
+rich_status csr_invd(const CsrDev &A, const int32_t *pos, double *invd, float *invdf, hipStream_t s);
 // dense row-major inverse of an SPD CSR matrix (blocked Gauss-Jordan; RICH_NOT_SPD on a
 // non-positive pivot); ws holds dense_inverse_ws(n) doubles
 int64_t dense_inverse_ws(int64_t n);
@@ -496,13 +498,12 @@ rich_status launch_restrict_batch(const std::vector<RestrictItem<T>> &items, hip
 // its order (nc aggregates), block table and columns, *ok = false when it does
 // not fit the kernels; vlevel_child its rows' runs on the finer level Lf
 // (ordered: Lv itself is in aggregate order); vlevel_fine the fine level's
-// aggregate map and member lists in level 1's order; vlevel_values and vlevel_invd copy the matrix
-// values and the l1 inverse diagonal to their places.
+// aggregate map and member lists in level 1's order; vlevel_values copies the
+// matrix values to their places.
 rich_status vlevel_order(Level &Lv, int64_t nc, bool mixed, DevAlloc &mem, bool *ok, hipStream_t s);
 rich_status vlevel_child(Level &Lv, const Level &Lf, bool ordered, DevAlloc &mem, hipStream_t s);
 rich_status vlevel_fine(Level &L0, const Level &L1, DevAlloc &mem, hipStream_t s);
 rich_status vlevel_values(Level &Lv, bool mixed, hipStream_t s);
-rich_status vlevel_invd(Level &Lv, bool mixed, hipStream_t s);
 // down: sweep from x0 and restriction of level l; up: sweep from xt and, above
 // level 1, prolongation into level l-1's xt (its r buffer); vgemv: the direct
 // coarsest solve and its prolongation; vprolong: the prolongation of the

@@ -188,6 +188,13 @@ rich_status timed(rich_ctx *h, int id, double bytes, F &&f) {
 }
 
 // ------------------------------------------------------------- hierarchy
+// the l1 inverse diagonal of a level in aggregate order
+rich_status level_invd(rich_ctx *h, Level &Lv) {
+    const CsrDev A{Lv.n, Lv.nnz, Lv.rowptr, Lv.col, Lv.val};
+    return csr_invd(A, Lv.V.pos, h->mixed ? nullptr : (double *)Lv.V.invd, h->mixed ? (float *)Lv.V.invd : nullptr,
+                    h->s);
+}
+
 rich_status build_hierarchy(rich_ctx *h) {
     delete h->H;
     h->H = new Hierarchy();
@@ -322,7 +329,7 @@ rich_status build_hierarchy(rich_ctx *h) {
         RICH_TRY(vlevel_order(H.L[t], H.L[t + 1].n, h->mixed, H.mem, &H.ordered, s));
     for (int t = 1; t < H.nlev - 1 && !H.ordered; t++) {
         VLevel &V = H.L[t].V;
-        for (void *q : {(void *)V.pos, (void *)V.ptr, (void *)V.place, (void *)V.ent, (void *)V.col, (void *)V.val,
+        for (void *q : {(void *)V.pos, (void *)V.ptr, (void *)V.place, (void *)V.off, (void *)V.ent, (void *)V.col, (void *)V.val,
                         V.invd, (void *)V.blk})
             if (q) H.mem.release(q);
         V = VLevel{};
@@ -333,7 +340,7 @@ rich_status build_hierarchy(rich_ctx *h) {
         Level &Lv = H.L[t];
         if (t > 0 && H.ordered && t < H.nlev - 1) {
             RICH_TRY(vlevel_values(Lv, h->mixed, s));
-            RICH_TRY(vlevel_invd(Lv, h->mixed, s));
+            RICH_TRY(level_invd(h, Lv));
         } else if (t > 0) {
             CsrDev A{Lv.n, Lv.nnz, Lv.rowptr, Lv.col, Lv.val};
             RICH_TRY(H.mem.get(&Lv.invd, Lv.n));
@@ -342,7 +349,7 @@ rich_status build_hierarchy(rich_ctx *h) {
                 RICH_TRY(H.mem.get(&Lv.valf, Lv.nnz));
                 RICH_TRY(launch_cast(Lv.val, Lv.valf, Lv.nnz, s));
             }
-            RICH_TRY(csr_invd(A, Lv.invd, Lv.invdf, s));
+            RICH_TRY(csr_invd(A, nullptr, Lv.invd, Lv.invdf, s));
             // levels smoothed inside the cycle get their CSR-stream row blocks
             if (t < H.nlev - 1) RICH_TRY(stream_blocks(Lv, H.mem, s));
         }
@@ -414,8 +421,8 @@ rich_status refresh_hierarchy(rich_ctx *h) {
                 if (ord) RICH_TRY(vlevel_values(Lc, h->mixed, s));
                 else if (h->mixed) RICH_TRY(launch_cast(Lc.val, Lc.valf, Lc.nnz, s));
             }
-            if (ord) RICH_TRY(vlevel_invd(Lc, h->mixed, s));
-            else RICH_TRY(csr_invd(C, Lc.invd, Lc.invdf, s));
+            if (ord) RICH_TRY(level_invd(h, Lc));
+            else RICH_TRY(csr_invd(C, nullptr, Lc.invd, Lc.invdf, s));
         }
     }
     if (H.dense) {
