@@ -809,18 +809,20 @@ __global__ void k_csr_to_dense(int64_t n, const int64_t *__restrict__ rowptr, co
 // tiles' updates, so a pivot's 64 scalar steps are no launch of their own.
 // Bounds: the update moves 16 n^2 bytes a step (n = 3118: 156 MB, resident in
 // the last-level cache) and does 64 n^2 multiply-adds; on small n the pivot's
-// serial chain (64 steps of LDS, barrier, division).  Measured a step: n = 3118
-// update 48 and panel 10 us (with the pivot and the panels as launches of their
-// own: 103 + 59 + 18 + 5), n = 517 27 and 9 us (19 + 54 + 16 + 5).  The order of
+// serial chain (32 pairs of scalar steps: LDS, barrier, two divisions).  Measured a
+// step: n = 3118 update 43 and panel 10 us (with the pivot and the panels as
+// launches of their own: 103 + 59 + 18 + 5), n = 517 25 and 9 us (19 + 54 + 16 + 5).  The order of
 // operations is part of the contract: a restarted or repeated GMRES solve in
 // FP64 amplifies the last bits of the preconditioner, so sweeping only half of
 // the tiles (36 us, not the same bits) is not used.
 constexpr int GJB = 64;  // pivot block and tile size
 
 // P^{-1} of the 64 x 64 block in A, one workgroup of 256 threads.  Thread
-// (ti, tj) keeps the entries (ti + 16 a, tj + 16 b) in registers; each of the
-// 64 scalar Gauss-Jordan steps shares its pivot row and column through
-// double-buffered LDS (one barrier a step).  rc: 4 * 64 doubles.
+// (ti, tj) keeps the entries (ti + 16 a, tj + 16 b) in registers; the 64 scalar
+// Gauss-Jordan steps go in pairs that share their two rows and columns through
+// double-buffered LDS, one barrier a pair: row and column k + 1 are read as they
+// are before step k, and every thread takes its part of them through that
+// step itself (the same operations as their owners').  rc: 8 * 64 doubles.
 __device__ __forceinline__ void invert_pivot(const double (*__restrict__ A)[GJB + 1], double *__restrict__ rc,
                                              double *__restrict__ Pinv, int *__restrict__ bad) {
     const int tid = threadIdx.x, ti = tid >> 4, tj = tid & 15;
@@ -830,42 +832,72 @@ __device__ __forceinline__ void invert_pivot(const double (*__restrict__ A)[GJB 
 #pragma unroll
         for (int c = 0; c < 4; c++) v[a][c] = A[ti + 16 * a][tj + 16 * c];
     bool neg = false;
+    auto inverse = [&](double p) {
+        if (!(p > 0.0)) {
+            neg = true;
+            p = 1.0;  // keep going; the caller reports the failure
+        }
+        return 1.0 / p;
+    };
+    // row and column k are cleared where they are kept: with f_k = -1/p and
+    // r_k = 1 the one update of a step serves every entry
 #pragma unroll
     for (int ka = 0; ka < 4; ka++)
 #pragma unroll 1
-        for (int kk = 0; kk < 16; kk++) {
+        for (int kk = 0; kk < 16; kk += 2) {
             const int k = 16 * ka + kk;
-            double *row = rc + (k & 1) * 2 * GJB, *col = row + GJB;
-            // the owners hand out row and column k and clear them: with
-            // f_k = -1/p and r_k = 1 the one update below serves every entry
+            double *row0 = rc + (kk & 2) * 2 * GJB, *row1 = row0 + GJB, *col0 = row1 + GJB, *col1 = col0 + GJB;
             if (ti == kk)
 #pragma unroll
-                for (int c = 0; c < 4; c++) {
-                    row[tj + 16 * c] = v[ka][c];
-                    if (c != ka || tj != kk) v[ka][c] = 0.0;
-                }
+                for (int c = 0; c < 4; c++) row0[tj + 16 * c] = v[ka][c];
+            if (ti == kk + 1)
+#pragma unroll
+                for (int c = 0; c < 4; c++) row1[tj + 16 * c] = v[ka][c];
             if (tj == kk)
 #pragma unroll
                 for (int a = 0; a < 4; a++) {
-                    if (a != ka || ti != kk) col[ti + 16 * a] = v[a][ka];
+                    col0[ti + 16 * a] = v[a][ka];
                     v[a][ka] = 0.0;
                 }
+            if (tj == kk + 1)
+#pragma unroll
+                for (int a = 0; a < 4; a++) col1[ti + 16 * a] = v[a][ka];
+            if (ti == kk)
+#pragma unroll
+                for (int c = 0; c < 4; c++) v[ka][c] = 0.0;
             __syncthreads();
-            double p = row[k];
-            if (!(p > 0.0)) {
-                neg = true;
-                p = 1.0;  // keep going; the caller reports the failure
+            // step k
+            double r[4], f[4], r1[4], f1[4];
+            const double ip0 = inverse(row0[k]), x01 = row0[k + 1], f10 = col0[k + 1] * ip0;
+#pragma unroll
+            for (int c = 0; c < 4; c++) {
+                r[c] = c == ka && tj == kk ? 1.0 : row0[tj + 16 * c];
+                r1[c] = fma(-f10, r[c], c == ka && tj == kk ? 0.0 : row1[tj + 16 * c]);
             }
-            const double ip = 1.0 / p;
-            double r[4], f[4];
 #pragma unroll
-            for (int c = 0; c < 4; c++) r[c] = c == ka && tj == kk ? 1.0 : row[tj + 16 * c];
-#pragma unroll
-            for (int a = 0; a < 4; a++) f[a] = a == ka && ti == kk ? -ip : col[ti + 16 * a] * ip;
+            for (int a = 0; a < 4; a++) {
+                f[a] = a == ka && ti == kk ? -ip0 : col0[ti + 16 * a] * ip0;
+                f1[a] = fma(-f[a], x01, a == ka && ti == kk ? 0.0 : col1[ti + 16 * a]);
+            }
 #pragma unroll
             for (int a = 0; a < 4; a++)
 #pragma unroll
                 for (int c = 0; c < 4; c++) v[a][c] = fma(-f[a], r[c], v[a][c]);
+            // step k + 1
+            const double ip1 = inverse(fma(-f10, x01, row1[k + 1]));
+            if (ti == kk + 1)
+#pragma unroll
+                for (int c = 0; c < 4; c++) v[ka][c] = 0.0;
+            if (tj == kk + 1)
+#pragma unroll
+                for (int a = 0; a < 4; a++) v[a][ka] = 0.0;
+            if (tj == kk + 1) r1[ka] = 1.0;
+#pragma unroll
+            for (int a = 0; a < 4; a++) f1[a] = a == ka && ti == kk + 1 ? -ip1 : f1[a] * ip1;
+#pragma unroll
+            for (int a = 0; a < 4; a++)
+#pragma unroll
+                for (int c = 0; c < 4; c++) v[a][c] = fma(-f1[a], r1[c], v[a][c]);
         }
     if (neg && tid == 0) *bad = 1;
 #pragma unroll
@@ -878,7 +910,7 @@ __device__ __forceinline__ void invert_pivot(const double (*__restrict__ A)[GJB 
 // then diag(P^{-1}, I)).
 __global__ void __launch_bounds__(256) k_bgj_pivot(const double *__restrict__ D, int64_t n,
                                                    double *__restrict__ Pinv, int *__restrict__ bad) {
-    __shared__ double A[GJB][GJB + 1], rc[4 * GJB];
+    __shared__ double A[GJB][GJB + 1], rc[8 * GJB];
     double d[16];
 #pragma unroll
     for (int q = 0; q < 16; q++) {
@@ -918,7 +950,8 @@ __global__ void __launch_bounds__(256) k_bgj_panel(double *__restrict__ D, int64
         const int t = tid + 256 * q, a = t / GJB, c = t % GJB;
         Q[c][a] = pq[q];
         X[a][c] = dq[q];
-        S[(t0 + a) * GJB + c] = sq[q];
+        // in the order of the update's A operands: column t of S at 16 (t % 4) + t / 4
+        S[(t0 + a) * GJB + 16 * (c & 3) + (c >> 2)] = sq[q];
     }
     __syncthreads();
     const int ti = tid >> 4, tj = tid & 15;
@@ -963,11 +996,11 @@ __global__ void __launch_bounds__(256) k_bgj_panel(double *__restrict__ D, int64
 // Block 0 takes the next pivot tile (K+1, K+1) and inverts it; the others take
 // the tiles in row order.
 typedef double rich_d4 __attribute__((ext_vector_type(4)));
-__global__ void __launch_bounds__(256) k_bgj_update(double *__restrict__ D, int64_t n, int64_t npad, int K, int tiles,
+__global__ void __launch_bounds__(256, 3) k_bgj_update(double *__restrict__ D, int64_t n, int64_t npad, int K, int tiles,
                                                     const double *__restrict__ S, const double *__restrict__ R,
                                                     double *__restrict__ Pinv, int *__restrict__ bad) {
-    __shared__ double Ss[GJB][GJB + 1];  // [row in tile][t]; the next pivot's tile
-    __shared__ double Rs[GJB][GJB + 1];  // [t][col in tile]
+    __shared__ double Rs[GJB][GJB + 1];  // [t][col in tile]; the next pivot's tile
+    __shared__ double rc[8 * GJB];
     const bool last = K == tiles - 1, piv = blockIdx.x == 0 && !last;
     int I, J;
     if (piv) {
@@ -981,14 +1014,19 @@ __global__ void __launch_bounds__(256) k_bgj_update(double *__restrict__ D, int6
     }
     const int64_t i0 = (int64_t)I * GJB, j0 = (int64_t)J * GJB;
     const int tid = threadIdx.x, w = tid / 64, l = tid % 64, li = l % 16, lk = l / 16;
-    // the tile's own entries are needed last: loaded with the panels
-    double sq[16], rq[16], d[4][4];
+    // a wave's rows of S go straight into its A operands; R is shared through
+    // LDS (35 KB: three blocks a CU); the tile's own entries are needed last
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    d2 sq[8], rq[8];
+    double d[4][4];
 #pragma unroll
-    for (int q = 0; q < 16; q++) {
-        const int t = tid + 256 * q, a = t / GJB, c = t % GJB;
-        sq[q] = S[i0 * GJB + t];
-        rq[q] = R[a * npad + j0 + c];
+    for (int q = 0; q < 8; q++) {
+        const int t = tid + 256 * q, a = t / (GJB / 2), c = t % (GJB / 2);
+        rq[q] = *reinterpret_cast<const d2 *>(R + a * npad + j0 + 2 * c);
     }
+    const d2 *sp = reinterpret_cast<const d2 *>(S + (i0 + 16 * w + li) * GJB + 16 * lk);
+#pragma unroll
+    for (int q = 0; q < 8; q++) sq[q] = sp[q];
 #pragma unroll
     for (int c = 0; c < 4; c++)
 #pragma unroll
@@ -997,29 +1035,29 @@ __global__ void __launch_bounds__(256) k_bgj_update(double *__restrict__ D, int6
             d[c][v] = J != K && gi < n && gj < n ? D[gi * n + gj] : (piv && gi == gj ? 1.0 : 0.0);
         }
 #pragma unroll
-    for (int q = 0; q < 16; q++) {
-        const int t = tid + 256 * q, a = t / GJB, c = t % GJB;
-        Ss[a][c] = sq[q];
-        Rs[a][c] = rq[q];
+    for (int q = 0; q < 8; q++) {
+        const int t = tid + 256 * q, a = t / (GJB / 2), c = t % (GJB / 2);
+        Rs[a][2 * c] = rq[q].x;
+        Rs[a][2 * c + 1] = rq[q].y;
     }
     __syncthreads();
     rich_d4 acc[4];
 #pragma unroll
     for (int c = 0; c < 4; c++) acc[c] = (rich_d4){0.0, 0.0, 0.0, 0.0};
-    for (int t = 0; t < GJB; t += 4) {
-        const double a = Ss[16 * w + li][t + lk];
+#pragma unroll
+    for (int q = 0; q < 16; q++)
 #pragma unroll
         for (int c = 0; c < 4; c++)
-            acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Rs[t + lk][16 * c + li], acc[c], 0, 0, 0);
-    }
+            acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(q & 1 ? sq[q / 2].y : sq[q / 2].x,
+                                                          Rs[4 * q + lk][16 * c + li], acc[c], 0, 0, 0);
     if (piv) {
         __syncthreads();
 #pragma unroll
         for (int c = 0; c < 4; c++)
 #pragma unroll
-            for (int v = 0; v < 4; v++) Ss[16 * w + lk + 4 * v][16 * c + li] = d[c][v] - acc[c][v];
+            for (int v = 0; v < 4; v++) Rs[16 * w + lk + 4 * v][16 * c + li] = d[c][v] - acc[c][v];
         __syncthreads();
-        invert_pivot(Ss, &Rs[0][0], Pinv, bad);
+        invert_pivot(Rs, rc, Pinv, bad);
         return;
     }
 #pragma unroll
