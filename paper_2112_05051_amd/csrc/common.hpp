@@ -364,8 +364,7 @@ struct Level {
     double *invd = nullptr;     // 1 / sum_j |a_ij|
     float *invdf = nullptr;
     int32_t *agg = nullptr;     // to level+1 (n)
-    // level 0 of an ordered hierarchy: agg, mptr and mem in level 1's order (else those)
-    int32_t *vagg = nullptr;
+    // level 0 of an ordered hierarchy: mptr and mem in level 1's order
     int64_t *vmptr = nullptr;
     int32_t *vmem = nullptr;    // ascending in each stretch that a restriction block stages
     uint16_t *vslot = nullptr;  // and the place of each in its stretch
@@ -498,7 +497,7 @@ rich_status launch_restrict_batch(const std::vector<RestrictItem<T>> &items, hip
 // its order (nc aggregates), block table and columns, *ok = false when it does
 // not fit the kernels; vlevel_child its rows' runs on the finer level Lf
 // (ordered: Lv itself is in aggregate order); vlevel_fine the fine level's
-// aggregate map and member lists in level 1's order; vlevel_values copies the
+// member lists in level 1's order; vlevel_values copies the
 // matrix values to their places.
 rich_status vlevel_order(Level &Lv, int64_t nc, bool mixed, DevAlloc &mem, bool *ok, hipStream_t s);
 rich_status vlevel_child(Level &Lv, const Level &Lf, bool ordered, DevAlloc &mem, hipStream_t s);

@@ -362,7 +362,6 @@ rich_status build_hierarchy(rich_ctx *h) {
         Lv.x = x;
         Lv.r = r;
     }
-    H.L[0].vagg = H.L[0].agg;
     if (H.ordered) RICH_TRY(vlevel_fine(H.L[0], H.L[1], H.mem, s));
     // coarsest solver
     Level &Lc = H.L[H.nlev - 1];
@@ -541,7 +540,7 @@ rich_status vcycle(rich_ctx *h, const double *b, const double *bs, T *z) {
             T *xt = (T *)H.L[0].r;
             const T *x0 = (const T *)H.L[0].x, *xc = (const T *)H.L[1].x;
             if (L0.prow) RICH_TRY(launch_sa_prolong<double, T>(L0, invd0, b, bs, x0, xc, xt, s));
-            return launch_gs_post<double, T>(h->P, M4, b, bs, x0, xc, L0.prow ? nullptr : L0.vagg, xt, z, s);
+            return launch_gs_post<double, T>(h->P, M4, b, bs, x0, xc, L0.prow ? nullptr : L0.agg, xt, z, s);
         });
     }
     if (L0.prow) {
@@ -554,7 +553,7 @@ rich_status vcycle(rich_ctx *h, const double *b, const double *bs, T *z) {
         });
     }
     return timed(h, RICH_K_VC0_POST, n0 * (12 + 6 * t) + n1 * t, [&] {
-        return launch_st_post<double, T>(h->P, M4, invd0, b, bs, (const T *)H.L[1].x, H.L[0].vagg, z, (T *)H.L[0].r,
+        return launch_st_post<double, T>(h->P, M4, invd0, b, bs, (const T *)H.L[1].x, H.L[0].agg, z, (T *)H.L[0].r,
                                          s);
     });
 }
@@ -665,7 +664,7 @@ rich_status apply_batch(const std::vector<BatchReq> &rq, hipStream_t s, WorkQueu
     std::vector<SpmvItem<T>> sp;
     for (const auto &q : rq) {
         Hierarchy &H = *q.h->H;
-        f.push_back({&q.h->P, m4_of<T>(q.h), invd0_of<T>(q.h), q.b, q.bs, (const T *)H.L[1].x, H.L[0].vagg,
+        f.push_back({&q.h->P, m4_of<T>(q.h), invd0_of<T>(q.h), q.b, q.bs, (const T *)H.L[1].x, H.L[0].agg,
                      (T *)H.L[0].r, (T *)q.h->z});
         if (q.w) {
             SpmvItem<T> it{&q.h->P, q.h->J7, (const T *)q.h->z, q.w};
