@@ -685,9 +685,6 @@ __global__ void k_st_post(Phys P, uint32_t n, const T *__restrict__ M4, const T 
 #define ST25_TY 8
 #endif
 constexpr int T25X = 64, T25Y = ST25_TY;
-#ifndef ST25_MIN_BLOCKS
-#define ST25_MIN_BLOCKS 2048
-#endif
 enum { ST25_PRE = 0, ST25_POST = 1, ST25_XT = 2 };
 
 // The inputs of u at one cell as loaded (u is formed when it is used).
@@ -898,15 +895,48 @@ __global__ void k_spmv_J_batch(Batch<SpmvArgs<TX>> B) {
 
 // The 64-wide tile needs rows of at least about that length to keep its lanes busy.
 inline bool use25(const Phys &P) { return P.nx >= 48 && P.ny >= T25Y && P.nz >= 4; }
-// Planes per block: the fewest chunks of at most 16 planes that give at least
-// ST25_MIN_BLOCKS blocks, with the planes spread evenly over the chunks (a
-// short last chunk leaves its blocks' share of the sweep idle).
-inline int kz25(const Phys &P) {
+// Planes per block, at most 16: the chunks that cost the fewest planes in a row.
+// The blocks run in rounds of `fit` (what the chip holds at once); a block
+// walks its planes after a start worth about two more (the planes below and
+// above its chunk).  Measured post-smoother us, chosen depth against the one
+// that gives at least 2048 blocks: 199 x 199 x 38 mixed 4 planes 22.7 (2: 28.4),
+// 96^3 3 planes 14.8 (2: 18.3), 128^3 4 planes 22.5 (2: 25.0), 160^3 10 planes
+// 39.6 (5: 42.5; 8, which starts a second round with a fifth of its blocks:
+// 52.6), 128^3 FP64 8 planes 34.5 (2: 39.7); the pre-smoother changes by less
+// than 1 us but for 128^3 FP64 (6 planes 31, 2: 28).
+inline int kz25(const Phys &P, int fit) {
     if (P.tile_kz > 0) return P.tile_kz < P.nz ? P.tile_kz : P.nz;
-    int64_t tiles = (int64_t)((P.nx + T25X - 1) / T25X) * ((P.ny + T25Y - 1) / T25Y);
-    int64_t chunks = std::max<int64_t>((ST25_MIN_BLOCKS + tiles - 1) / tiles, (P.nz + 15) / 16);
-    chunks = std::min<int64_t>(chunks, P.nz);
+    const int64_t tiles = (int64_t)((P.nx + T25X - 1) / T25X) * ((P.ny + T25Y - 1) / T25Y);
+    int best = 1;
+    int64_t cost = INT64_MAX;
+    for (int kz = 1; kz <= 16 && kz <= P.nz; kz++) {
+        const int64_t blocks = tiles * ((P.nz + kz - 1) / kz);
+        const int64_t c = (blocks + fit - 1) / fit * (kz + 2);
+        if (c < cost) {
+            cost = c;
+            best = kz;
+        }
+    }
+    const int64_t chunks = (P.nz + best - 1) / best;  // spread evenly
     return (int)((P.nz + chunks - 1) / chunks);
+}
+// Blocks of a tiled kernel that the chip holds at once (a constant of the
+// compiled kernel and the chip, asked once).
+template <class K>
+inline int blocks_at_once(K kernel) {
+    int dev = 0, cus = 256, per = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, T25X * T25Y, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        per = 2;
+    }
+    return std::max(1, per) * std::max(1, cus);
+}
+template <class TB, class T, int MODE>
+inline int kz25_of(const Phys &P) {
+    static const int fit = blocks_at_once(k_st25<TB, T, MODE>);
+    return kz25(P, fit);
 }
 inline int64_t tiles25(const Phys &P, int kz) {
     return (int64_t)((P.nx + T25X - 1) / T25X) * ((P.ny + T25Y - 1) / T25Y) * ((P.nz + kz - 1) / kz);
@@ -1134,7 +1164,7 @@ rich_status launch_st_pre(const Phys &P, const T *M4, const T *invd, const TB *b
                           hipStream_t s) {
     uint32_t n = ncells(P);
     if (use25(P)) {
-        int kz = kz25(P);
+        int kz = kz25_of<TB, T, ST25_PRE>(P);
         k_st25<TB, T, ST25_PRE><<<grid25(P, kz), dim3(T25X, T25Y), 0, s>>>(P, M4, invd, b, bs, nullptr, nullptr, r, kz);
     } else {
         k_st_pre<TB, T><<<nblocks(n), TPB, 0, s>>>(P, n, M4, invd, b, bs, r);
@@ -1148,7 +1178,7 @@ rich_status launch_st_post(const Phys &P, const T *M4, const T *invd, const TB *
                            const int32_t *agg, T *x, T *xt, hipStream_t s) {
     uint32_t n = ncells(P);
     if (use25(P)) {
-        int kz = kz25(P);
+        int kz = kz25_of<TB, T, ST25_POST>(P);
         k_st25<TB, T, ST25_POST><<<grid25(P, kz), dim3(T25X, T25Y), 0, s>>>(P, M4, invd, b, bs, xc, agg, x, kz);
     } else {
         k_st_prolong<TB, T><<<nblocks(n), TPB, 0, s>>>(n, invd, b, bs, xc, agg, xt);
@@ -1164,7 +1194,7 @@ rich_status launch_st_post_from(const Phys &P, const T *M4, const T *invd, const
                                 const T *xt, T *x, hipStream_t s) {
     uint32_t n = ncells(P);
     if (use25(P)) {
-        int kz = kz25(P);
+        int kz = kz25_of<TB, T, ST25_XT>(P);
         k_st25<TB, T, ST25_XT><<<grid25(P, kz), dim3(T25X, T25Y), 0, s>>>(P, M4, invd, b, bs, xt, nullptr, x, kz);
     } else {
         k_st_post<TB, T><<<nblocks(n), TPB, 0, s>>>(P, n, M4, invd, b, bs, xt, x);
@@ -1235,13 +1265,13 @@ static StArgs<TB, T> st_args(const FineItem<TB, T> &it, int kz) {
 }
 
 // Split the items into those on the tiled kernel and those on the plain one.
-template <class TB, class T>
+template <int MODE, class TB, class T>
 static void st_split(const std::vector<FineItem<TB, T>> &v, std::vector<StArgs<TB, T>> &a25,
                      std::vector<unsigned> &b25, std::vector<StArgs<TB, T>> &a1, std::vector<unsigned> &b1) {
     for (const auto &it : v) {
         const Phys &P = *it.P;
         if (use25(P)) {
-            int kz = kz25(P);
+            int kz = kz25_of<TB, T, MODE>(P);
             a25.push_back(st_args(it, kz));
             b25.push_back((unsigned)tiles25(P, kz));
         } else {
@@ -1255,7 +1285,7 @@ template <class TB, class T>
 rich_status launch_st_pre_batch(const std::vector<FineItem<TB, T>> &v, hipStream_t s, WorkQueue *q) {
     std::vector<StArgs<TB, T>> a25, a1;
     std::vector<unsigned> b25, b1;
-    st_split(v, a25, b25, a1, b1);
+    st_split<ST25_PRE>(v, a25, b25, a1, b1);
     using B = Batch<StArgs<TB, T>>;
     RICH_TRY(launch_batches(a25, b25, [&](const B &bt, unsigned g) {
         k_st25_batch<TB, T, ST25_PRE><<<g, dim3(T25X, T25Y), 0, s>>>(bt);
@@ -1267,7 +1297,7 @@ template <class TB, class T>
 rich_status launch_st_post_batch(const std::vector<FineItem<TB, T>> &v, hipStream_t s, WorkQueue *q) {
     std::vector<StArgs<TB, T>> a25, a1;
     std::vector<unsigned> b25, b1;
-    st_split(v, a25, b25, a1, b1);
+    st_split<ST25_POST>(v, a25, b25, a1, b1);
     using B = Batch<StArgs<TB, T>>;
     RICH_TRY(launch_batches(a25, b25, [&](const B &bt, unsigned g) {
         k_st25_batch<TB, T, ST25_POST><<<g, dim3(T25X, T25Y), 0, s>>>(bt);
