@@ -277,18 +277,21 @@ constexpr int RED_THREADS = 256;
 constexpr int GMRES_BLOCK_MAX = 10; // largest round of the s-step GMRES
 constexpr int BLK_BUF = 1024;       // doubles per s-step result or coefficient buffer (>= 65 * 10 + 100)
 
+// The reductions below leave their results in device memory (out) and, where
+// host is set, also in pinned host memory, for the host to poll.
 // Basis vectors are stored unnormalised: the true V_i is vs[i] * stored V_i.
 // out[i] = V_i . w (i < k), out[k] = w . w; reduced in fixed order.
 rich_status launch_multidot(const double *V, int64_t ldv, int k, const double *vs, const double *w, int64_t n,
-                            double *partial, double *out, hipStream_t s);
+                            double *partial, double *out, double *host, hipStream_t s);
 // w -= sum_i h_i V_i (i < k, h and vs on device); out[0] = ||w||^2 (after update)
 rich_status launch_update_norm(const double *V, int64_t ldv, int k, const double *h, const double *vs, double *w,
-                               int64_t n, double *partial, double *out, hipStream_t s);
-// Block Gram-Schmidt of the s-step GMRES (S <= 6 raw block vectors Q_k at
+                               int64_t n, double *partial, double *out, double *host, hipStream_t s);
+// Block Gram-Schmidt of the s-step GMRES (S <= 10 raw block vectors Q_k at
 // stride ldv, nv <= 66 basis vectors with device scales vs).
 // launch_block_dot: out[i*S + k] = (vs_i V_i) . Q_k (i < nv, k < S), then the
-// upper triangle of Q^T Q by rows (S(S+1)/2 values); partial needs
-// RED_BLOCKS * block_partial_size(nv, S) doubles.  Deterministic.
+// upper triangle of Q^T Q by rows (S(S+1)/2 values), to pinned host memory
+// (out); partial needs RED_BLOCKS * block_partial_size(nv, S) doubles.
+// Deterministic.
 rich_status launch_block_dot(const double *V, int64_t ldv, int nv, const double *vs, const double *Q, int S,
                              int64_t n, double *partial, double *out, hipStream_t s);
 int block_partial_size(int nv, int S);
@@ -299,13 +302,13 @@ rich_status launch_block_update(const double *V, int64_t ldv, int nv, const doub
 // vs[0] = 1 / sqrt(ww[0]) on the device
 rich_status launch_set_scale(double *vs, const double *ww, hipStream_t s);
 // out[0] = x.y (deterministic)
-rich_status launch_dot(const double *x, const double *y, int64_t n, double *partial, double *out,
+rich_status launch_dot(const double *x, const double *y, int64_t n, double *partial, double *out, double *host,
                        hipStream_t s);
 // out[0] = max |x_i| (NaN propagates), out[1] = sum x_i, out[2] = x.x
-rich_status launch_norms(const double *x, int64_t n, double *partial, double *out, hipStream_t s);
+rich_status launch_norms(const double *x, int64_t n, double *partial, double *out, double *host, hipStream_t s);
 // out[0] = max_i |a*d_i| / max(|u_i|, 1)
 rich_status launch_rel_length(const double *d, const double *u, int64_t n, double *partial,
-                              double *out, hipStream_t s);
+                              double *out, double *host, hipStream_t s);
 rich_status launch_scale(double *x, double a, int64_t n, hipStream_t s);
 rich_status launch_scale_dev(double *x, const double *inv_of, int64_t n, hipStream_t s);
 // y = a*x + b*y

@@ -119,16 +119,23 @@ __global__ void __launch_bounds__(RED_THREADS) k_multidot_small(const double *__
     multidot_body<K>(V, ldv, w, n, partial);
 }
 
+// A result that the host also waits for: its copy goes straight to pinned host
+// memory (host, may be null), so that no copy command follows the reduction.
+__device__ inline void put(double *out, double *host, double v) {
+    *out = v;
+    if (host) __hip_atomic_store(host, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // out[i] = sum_b partial[b*(m) + i], b ascending (one block per output),
 // times scale[i] for i < nscale (basis vectors stored with a scale factor).
-__global__ void k_reduce_partials(const double *__restrict__ partial, int m, int nb, double *__restrict__ out,
+__global__ void k_reduce_partials(const double *__restrict__ partial, int m, int nb, double *out, double *host,
                                   const double *__restrict__ scale = nullptr, int nscale = 0) {
     __shared__ double sh[RED_THREADS / WAVE];
     int i = blockIdx.x;
     double a = 0.0;
     for (int b = threadIdx.x; b < nb; b += blockDim.x) a += partial[(size_t)b * m + i];
     double r = block_sum(a, sh);
-    if (threadIdx.x == 0) out[i] = (i < nscale) ? r * scale[i] : r;
+    if (threadIdx.x == 0) put(out + i, host ? host + i : nullptr, (i < nscale) ? r * scale[i] : r);
 }
 
 // vs[0] = 1/sqrt(ww[0]) (0 for a zero vector): the scale of a new basis vector.
@@ -136,15 +143,23 @@ __global__ void k_set_scale(double *__restrict__ vs, const double *__restrict__ 
     if (threadIdx.x == 0 && blockIdx.x == 0) vs[0] = ww[0] > 0.0 ? 1.0 / sqrt(ww[0]) : 0.0;
 }
 
-__global__ void k_reduce_max(const double *__restrict__ partial, int m, int nb, double *__restrict__ out) {
+// out[0] = max_b partial[b*m] (block 0), out[i] = sum_b partial[b*m + i] (block i > 0)
+__global__ void k_reduce_max(const double *__restrict__ partial, int m, int nb, double *out, double *host) {
     __shared__ double sh[RED_THREADS / WAVE];
+    const int i = blockIdx.x;
     double a = 0.0;
+    if (i > 0) {
+        for (int b = threadIdx.x; b < nb; b += blockDim.x) a += partial[(size_t)b * m + i];
+        const double r = block_sum(a, sh);
+        if (threadIdx.x == 0) put(out + i, host ? host + i : nullptr, r);
+        return;
+    }
     for (int b = threadIdx.x; b < nb; b += blockDim.x) {
         double v = partial[(size_t)b * m];
         a = (v > a || v != v) ? v : a;
     }
     double r = block_max(a, sh);
-    if (threadIdx.x == 0) out[0] = r;
+    if (threadIdx.x == 0) put(out, host, r);
 }
 
 // w -= sum_i h_i (vs_i V_i) and the partial sums of ||w||^2, K compile-time, row pairs.
@@ -445,19 +460,16 @@ __global__ void __launch_bounds__(RED_THREADS) k_block_dot_wide_small(const doub
 // out_c[j] = vs[j / S] * sum_b partial[b*m + j] for j < nvs (the C entries),
 // out_g[j - nvs] = sum_b partial[b*m + j] after (the Gram matrix); b ascending.
 __global__ void k_reduce_block(const double *__restrict__ partial, int m, int nb, int S, int nvs,
-                               const double *__restrict__ vs, double *__restrict__ out_c,
-                               double *__restrict__ out_g) {
+                               const double *__restrict__ vs, double *out_c, double *out_g) {
     __shared__ double sh[RED_THREADS / WAVE];
     const int j = blockIdx.x;
     double a = 0.0;
     for (int b = threadIdx.x; b < nb; b += blockDim.x) a += partial[(size_t)b * m + j];
     const double r = block_sum(a, sh);
-    if (threadIdx.x == 0) {
-        if (j < nvs)
-            out_c[j] = r * vs[j / S];
-        else
-            out_g[j - nvs] = r;
-    }
+    // the results go to the host (pinned memory)
+    if (threadIdx.x == 0)
+        __hip_atomic_store(j < nvs ? out_c + j : out_g + (j - nvs), j < nvs ? r * vs[j / S] : r, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // The block vectors orthonormalised in place:
@@ -767,7 +779,7 @@ __global__ void k_scan_final(const int64_t *__restrict__ in, int64_t n, const in
     X(54) X(55) X(56) X(57) X(58) X(59) X(60) X(61) X(62) X(63) X(64)
 
 rich_status launch_multidot(const double *V, int64_t ldv, int k, const double *vs, const double *w, int64_t n,
-                            double *partial, double *out, hipStream_t s) {
+                            double *partial, double *out, double *host, hipStream_t s) {
     if (k < 1 || k > 64 || (ldv & 1)) return RICH_EINVAL;
     switch (k) {
 #define X(K)                                                                         \
@@ -781,13 +793,13 @@ rich_status launch_multidot(const double *V, int64_t ldv, int k, const double *v
 #undef X
     }
     LAUNCH_CHECK();
-    k_reduce_partials<<<k + 1, RED_THREADS, 0, s>>>(partial, k + 1, RED_BLOCKS, out, vs, k);
+    k_reduce_partials<<<k + 1, RED_THREADS, 0, s>>>(partial, k + 1, RED_BLOCKS, out, host, vs, k);
     LAUNCH_CHECK();
     return RICH_OK;
 }
 
 rich_status launch_update_norm(const double *V, int64_t ldv, int k, const double *h, const double *vs, double *w,
-                               int64_t n, double *partial, double *out, hipStream_t s) {
+                               int64_t n, double *partial, double *out, double *host, hipStream_t s) {
     if (k < 1 || k > 64 || (ldv & 1)) return RICH_EINVAL;
     switch (k) {
 #define X(K)                                                                            \
@@ -801,7 +813,7 @@ rich_status launch_update_norm(const double *V, int64_t ldv, int k, const double
 #undef X
     }
     LAUNCH_CHECK();
-    k_reduce_partials<<<1, RED_THREADS, 0, s>>>(partial, 1, RED_BLOCKS, out);
+    k_reduce_partials<<<1, RED_THREADS, 0, s>>>(partial, 1, RED_BLOCKS, out, host);
     LAUNCH_CHECK();
     return RICH_OK;
 }
@@ -875,29 +887,28 @@ rich_status launch_block_update(const double *V, int64_t ldv, int nv, const doub
 
 int block_partial_size(int nv, int S) { return nv * S + S * (S + 1) / 2; }
 
-rich_status launch_dot(const double *x, const double *y, int64_t n, double *partial, double *out, hipStream_t s) {
+rich_status launch_dot(const double *x, const double *y, int64_t n, double *partial, double *out, double *host,
+                       hipStream_t s) {
     k_dot<<<RED_BLOCKS, RED_THREADS, 0, s>>>(x, y, n, partial);
     LAUNCH_CHECK();
-    k_reduce_partials<<<1, RED_THREADS, 0, s>>>(partial, 1, RED_BLOCKS, out);
+    k_reduce_partials<<<1, RED_THREADS, 0, s>>>(partial, 1, RED_BLOCKS, out, host);
     LAUNCH_CHECK();
     return RICH_OK;
 }
 
-rich_status launch_norms(const double *x, int64_t n, double *partial, double *out, hipStream_t s) {
+rich_status launch_norms(const double *x, int64_t n, double *partial, double *out, double *host, hipStream_t s) {
     k_norms<<<RED_BLOCKS, RED_THREADS, 0, s>>>(x, n, partial);
     LAUNCH_CHECK();
-    k_reduce_max<<<1, RED_THREADS, 0, s>>>(partial, 3, RED_BLOCKS, out);
-    LAUNCH_CHECK();
-    k_reduce_partials<<<2, RED_THREADS, 0, s>>>(partial + 1, 3, RED_BLOCKS, out + 1);
+    k_reduce_max<<<3, RED_THREADS, 0, s>>>(partial, 3, RED_BLOCKS, out, host);
     LAUNCH_CHECK();
     return RICH_OK;
 }
 
 rich_status launch_rel_length(const double *d, const double *u, int64_t n, double *partial, double *out,
-                              hipStream_t s) {
+                              double *host, hipStream_t s) {
     k_rel_length<<<RED_BLOCKS, RED_THREADS, 0, s>>>(d, u, n, partial);
     LAUNCH_CHECK();
-    k_reduce_max<<<1, RED_THREADS, 0, s>>>(partial, 1, RED_BLOCKS, out);
+    k_reduce_max<<<1, RED_THREADS, 0, s>>>(partial, 1, RED_BLOCKS, out, host);
     LAUNCH_CHECK();
     return RICH_OK;
 }

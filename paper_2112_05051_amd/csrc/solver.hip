@@ -56,16 +56,18 @@ struct rich_ctx {
     double *partial = nullptr; // RED_BLOCKS * (m + 2)
     double *dres = nullptr;    // device scalars (m + 8)
     double *dres2 = nullptr;
-    double *hres = nullptr;    // pinned host mirror (2 * (m + 8))
+    double *hres = nullptr;    // pinned: results of reductions (2 (m + 8)), then uploads (hy, m)
+    double *hy = nullptr;
     double *vs = nullptr;      // device scale of every stored basis vector (m + 1)
+    bool vs_set = false;       // s-step rounds: a scale behind the first is not 1
     double *one = nullptr;     // device constant 1.0
     double *hbuf = nullptr;    // device Arnoldi results, one row of (m + 4) per iteration
     double *hall = nullptr;    // pinned host mirror of hbuf
-    double *dblk = nullptr;    // s-step rounds: block dots [0, BLK_BUF), coefficients [BLK_BUF, 2 BLK_BUF)
+    double *dblk = nullptr;    // s-step rounds: coefficients (BLK_BUF)
     double shifts[GMRES_BLOCK_MAX] = {};  // s-step basis shifts sigma_t, in the order they are used
     int scap = 1;                          // s-step round size cap (gmres_block at first)
     int sgood = 0;                         // rounds taken whole since the cap last changed
-    double *hblk = nullptr;    // pinned host mirror of dblk
+    double *hblk = nullptr;    // pinned: block dots [0, BLK_BUF), coefficients [BLK_BUF, 2 BLK_BUF)
     double *bsc = nullptr;     // N: scaled right-hand side for a one-level hierarchy
     std::vector<hipEvent_t> iter_ev;  // one per Arnoldi iteration
     // fused serving launches: the batcher this simulation posts its
@@ -117,24 +119,70 @@ rich_status sync(rich_ctx *h) {
     return RICH_OK;
 }
 
-// read n device doubles into the pinned mirror
-rich_status readback(rich_ctx *h, const double *dev, int n, double *out) {
-    HIP_TRY(hipMemcpyAsync(h->hres, dev, n * sizeof(double), hipMemcpyDeviceToHost, h->s));
-    HIP_TRY(hipStreamSynchronize(h->s));
-    memcpy(out, h->hres, n * sizeof(double));
+// Results that a reduction stores in pinned host memory.  expect() marks the
+// places before the launch (the mark is a signalling NaN, which no arithmetic
+// gives); arrived() waits until no mark is left, which takes the store's own
+// few microseconds instead of a copy and a stream wait (26 -> 14 us for the norms
+// of a small vector).  The wait ends at the latest with the stream itself: after
+// POLL_S it waits for that, and the values are what the kernels stored.  Values
+// stored earlier on the same stream have been read before (every launch with a
+// host result is followed by its arrived()).
+constexpr uint64_t NOT_YET = 0x7ff4a5c3e1d20b96ull;
+constexpr double POLL_S = 1e-3, POLL_YIELD_S = 5e-5;
+
+void expect(double *host, int n) {
+    for (int i = 0; i < n; i++) __atomic_store_n(reinterpret_cast<uint64_t *>(host + i), NOT_YET, __ATOMIC_RELEASE);
+}
+
+rich_status arrived(rich_ctx *h, const double *host, int n) {
+    const uint64_t *p = reinterpret_cast<const uint64_t *>(host);
+    double t0 = 0.0;
+    int spins = 0;
+    for (int i = 0; i < n;) {
+        if (__atomic_load_n(p + i, __ATOMIC_ACQUIRE) != NOT_YET) {
+            i++;
+            continue;
+        }
+        __builtin_ia32_pause();
+        if (++spins % 64) continue;
+        const double t = now_s();
+        if (t0 == 0.0) t0 = t;
+        if (t - t0 > POLL_S) return sync(h);
+        if (t - t0 > POLL_YIELD_S) std::this_thread::yield();
+    }
     return RICH_OK;
 }
 
 // ||x||_inf, sum x, ||x||_2^2
 rich_status norms(rich_ctx *h, const double *x, double out[3]) {
-    RICH_TRY(launch_norms(x, h->N, h->partial, h->dres, h->s));
-    return readback(h, h->dres, 3, out);
+    expect(h->hres, 3);
+    RICH_TRY(launch_norms(x, h->N, h->partial, h->dres, h->hres, h->s));
+    RICH_TRY(arrived(h, h->hres, 3));
+    memcpy(out, h->hres, 3 * sizeof(double));
+    return RICH_OK;
 }
 
 rich_status dotp(rich_ctx *h, const double *x, const double *y, double *out) {
-    RICH_TRY(launch_dot(x, y, h->N, h->partial, h->dres, h->s));
-    return readback(h, h->dres, 1, out);
+    expect(h->hres, 1);
+    RICH_TRY(launch_dot(x, y, h->N, h->partial, h->dres, h->hres, h->s));
+    RICH_TRY(arrived(h, h->hres, 1));
+    *out = h->hres[0];
+    return RICH_OK;
 }
+
+// max_i |d_i| / max(|u_i|, 1)
+rich_status rel_length(rich_ctx *h, const double *d, const double *u, double *out) {
+    expect(h->hres, 1);
+    RICH_TRY(launch_rel_length(d, u, h->N, h->partial, h->dres, h->hres, h->s));
+    RICH_TRY(arrived(h, h->hres, 1));
+    *out = h->hres[0];
+    return RICH_OK;
+}
+
+// One classical Gram-Schmidt pass of w against V_0..V_{k-1}: w's new norm
+// squared in ww (and dres2), the dots in hres[0..k-1], ||w||^2 before in hres[k].
+// ids: the profiled kernels of the dots and the update.
+rich_status gs_pass(rich_ctx *h, int k, double *w, int id_dot, int id_update, double *ww);
 
 // ---------------------------------------------------------- profiling
 // Collect the elapsed time of every pending (start, stop) event pair.
@@ -185,6 +233,22 @@ rich_status timed(rich_ctx *h, int id, double bytes, F &&f) {
     k.bytes += bytes;
     if (k.pending.size() >= 2048) RICH_TRY(prof_harvest(h));
     return st;
+}
+
+rich_status gs_pass(rich_ctx *h, int k, double *w, int id_dot, int id_update, double *ww) {
+    double *hw = h->hres + h->m + 8;
+    expect(h->hres, k + 1);
+    expect(hw, 1);
+    RICH_TRY(timed(h, id_dot, 8.0 * h->N * (k + 1), [&] {
+        return launch_multidot(h->V, h->ldv, k, h->vs, w, h->N, h->partial, h->dres, h->hres, h->s);
+    }));
+    RICH_TRY(timed(h, id_update, 8.0 * h->N * (k + 2), [&] {
+        return launch_update_norm(h->V, h->ldv, k, h->dres, h->vs, w, h->N, h->partial, h->dres2, hw, h->s);
+    }));
+    RICH_TRY(arrived(h, h->hres, k + 1));
+    RICH_TRY(arrived(h, hw, 1));
+    *ww = *hw;
+    return RICH_OK;
 }
 
 // ------------------------------------------------------------- hierarchy
@@ -803,9 +867,9 @@ rich_status gmres_classic(rich_ctx *h, const double *b, double *x, int *its_out,
         double *hb = h->hbuf + (size_t)j * W;
         RICH_TRY(prec_product(h, vj, h->vs + j, w));
         RICH_TRY(timed(h, RICH_K_MULTIDOT, (double)N * 8 * (j + 2),
-                       [&] { return launch_multidot(h->V, ld, j + 1, h->vs, w, N, h->partial, hb, s); }));
+                       [&] { return launch_multidot(h->V, ld, j + 1, h->vs, w, N, h->partial, hb, nullptr, s); }));
         RICH_TRY(timed(h, RICH_K_UPDATE, (double)N * 8 * (j + 3), [&] {
-            return launch_update_norm(h->V, ld, j + 1, hb, h->vs, w, N, h->partial, hb + j + 2, s);
+            return launch_update_norm(h->V, ld, j + 1, hb, h->vs, w, N, h->partial, hb + j + 2, nullptr, s);
         }));
         RICH_TRY(launch_set_scale(h->vs + j + 1, hb + j + 2, s));
         HIP_TRY(hipMemcpyAsync(h->hall + (size_t)j * W, hb, (j + 3) * sizeof(double), hipMemcpyDeviceToHost, s));
@@ -823,10 +887,12 @@ rich_status gmres_classic(rich_ctx *h, const double *b, double *x, int *its_out,
             RICH_TRY(launch_b_minus(b, h->V, N, s));
             charge(h, 72.0 * N + 24.0 * N);
         }
-        charge(h, 8.0 * N);  // norms of V_0
+        double rn[3] = {nb[0], nb[1], nb[2]};  // V_0 = b at first: the norms just taken
+        if (!first) {
+            charge(h, 8.0 * N);
+            RICH_TRY(norms(h, h->V, rn));
+        }
         first = false;
-        double rn[3];
-        RICH_TRY(norms(h, h->V, rn));
         double beta = std::sqrt(rn[2]);
         if (!std::isfinite(beta)) return RICH_NONFINITE;
         relres = beta / bnorm;
@@ -868,14 +934,9 @@ rich_status gmres_classic(rich_ctx *h, const double *b, double *x, int *its_out,
                 // the once-orthogonalised vector and is redone
                 double *w = h->V + (size_t)(j + 1) * ld;
                 RICH_TRY(sync(h));
-                RICH_TRY(launch_multidot(h->V, ld, j + 1, h->vs, w, N, h->partial, h->dres, s));
-                RICH_TRY(launch_update_norm(h->V, ld, j + 1, h->dres, h->vs, w, N, h->partial, h->dres2, s));
+                RICH_TRY(gs_pass(h, j + 1, w, RICH_K_COUNT, RICH_K_COUNT, &ww1));
                 RICH_TRY(launch_set_scale(h->vs + j + 1, h->dres2, s));
-                HIP_TRY(hipMemcpyAsync(h->hres, h->dres, (j + 1) * sizeof(double), hipMemcpyDeviceToHost, s));
-                HIP_TRY(hipMemcpyAsync(h->hres + (m + 8), h->dres2, sizeof(double), hipMemcpyDeviceToHost, s));
-                RICH_TRY(sync(h));
                 for (int i = 0; i <= j; i++) hv[i] += h->hres[i];
-                ww1 = h->hres[m + 8];
                 queued = j;
             }
             double hn = std::sqrt(ww1);
@@ -904,13 +965,13 @@ rich_status gmres_classic(rich_ctx *h, const double *b, double *x, int *its_out,
             for (int t = i + 1; t < k; t++) sum -= Hm[i * m + t] * y[t];
             y[i] = sum / Hm[i * m + i];
         }
-        memcpy(h->hres, y.data(), k * sizeof(double));
-        HIP_TRY(hipMemcpyAsync(h->dres, h->hres, k * sizeof(double), hipMemcpyHostToDevice, s));
+        // (the previous cycle's upload is over: norms have been read since)
+        memcpy(h->hy, y.data(), k * sizeof(double));
+        HIP_TRY(hipMemcpyAsync(h->dres, h->hy, k * sizeof(double), hipMemcpyHostToDevice, s));
         RICH_TRY(launch_lincomb(h->V, ld, k, h->dres, h->vs, h->work, N, s));
         RICH_TRY(prec_product(h, h->work, h->one, nullptr));
         RICH_TRY(add_z(h, x));
         charge(h, 8.0 * (k + 1) * N + (16.0 + (h->mixed ? 4 : 8)) * N);
-        RICH_TRY(sync(h));  // hres is reused before the next read
     }
     *its_out = total;
     *relres_out = relres;
@@ -967,8 +1028,7 @@ rich_status gmres_sstep(rich_ctx *h, const double *b, double *x, int *its_out, d
     }
     if (!std::isfinite(bnorm)) return RICH_NONFINITE;
     BatchScope batch_scope(h);
-    double *dout = h->dblk, *dcf = h->dblk + BLK_BUF;
-    double *hout = h->hblk, *hcf = h->hblk + BLK_BUF;
+    double *dcf = h->dblk, *hout = h->hblk, *hcf = h->hblk + BLK_BUF;
     bool first = true;
     for (;;) {
         // true residual into V_0 (stored unnormalised, scale 1/beta on the device)
@@ -980,10 +1040,12 @@ rich_status gmres_sstep(rich_ctx *h, const double *b, double *x, int *its_out, d
             RICH_TRY(launch_b_minus(b, h->V, N, s));
             charge(h, 72.0 * N + 24.0 * N);
         }
-        charge(h, 8.0 * N);  // norms of V_0
+        double rn[3] = {nb[0], nb[1], nb[2]};  // V_0 = b at first: the norms just taken
+        if (!first) {
+            charge(h, 8.0 * N);
+            RICH_TRY(norms(h, h->V, rn));
+        }
         first = false;
-        double rn[3];
-        RICH_TRY(norms(h, h->V, rn));
         const double beta = std::sqrt(rn[2]);
         if (!std::isfinite(beta)) return RICH_NONFINITE;
         relres = beta / bnorm;
@@ -993,6 +1055,9 @@ rich_status gmres_sstep(rich_ctx *h, const double *b, double *x, int *its_out, d
         }
         if (total >= h->O.gmres_maxit) break;
         RICH_TRY(launch_set_scale(h->vs, h->dres + 2, s));  // dres[2] = ||V_0||^2 from norms()
+        // every other scale is 1 but where an earlier cycle finished a round vector by vector
+        if (h->vs_set) RICH_TRY(launch_fill_f64(h->vs + 1, 1.0, m, s));
+        h->vs_set = false;
         std::fill(g.begin(), g.end(), 0.0);
         std::fill(Hr.begin(), Hr.end(), 0.0);
         g[0] = beta;
@@ -1029,21 +1094,14 @@ rich_status gmres_sstep(rich_ctx *h, const double *b, double *x, int *its_out, d
                 std::vector<double> hv(j + 1, 0.0);
                 double ww0 = 0.0, ww = 0.0;
                 for (int pass = 0; pass < 2; pass++) {
-                    RICH_TRY(timed(h, pass ? RICH_K_COUNT : RICH_K_MULTIDOT, 8.0 * N * (j + 2), [&] {
-                        return launch_multidot(h->V, ld, j + 1, h->vs, w, N, h->partial, h->dres, s);
-                    }));
-                    RICH_TRY(timed(h, pass ? RICH_K_COUNT : RICH_K_UPDATE, 8.0 * N * (j + 3), [&] {
-                        return launch_update_norm(h->V, ld, j + 1, h->dres, h->vs, w, N, h->partial, h->dres2, s);
-                    }));
-                    HIP_TRY(hipMemcpyAsync(h->hres, h->dres, (j + 2) * sizeof(double), hipMemcpyDeviceToHost, s));
-                    HIP_TRY(hipMemcpyAsync(h->hres + (m + 8), h->dres2, sizeof(double), hipMemcpyDeviceToHost, s));
-                    RICH_TRY(sync(h));
+                    RICH_TRY(gs_pass(h, j + 1, w, pass ? RICH_K_COUNT : RICH_K_MULTIDOT,
+                                     pass ? RICH_K_COUNT : RICH_K_UPDATE, &ww));
                     for (int i = 0; i <= j; i++) hv[i] += h->hres[i];
                     if (pass == 0) ww0 = h->hres[j + 1];
-                    ww = h->hres[m + 8];
                     if (!(std::sqrt(ww) < h->O.gmres_reorth * std::sqrt(ww0))) break;
                 }
                 RICH_TRY(launch_set_scale(h->vs + j + 1, h->dres2, s));
+                h->vs_set = true;
                 const double hn = std::sqrt(ww);
                 if (!std::isfinite(hn)) return RICH_NONFINITE;
                 for (int i = 0; i <= j; i++) Hr[(size_t)i * m + j] = hv[i];
@@ -1058,16 +1116,15 @@ rich_status gmres_sstep(rich_ctx *h, const double *b, double *x, int *its_out, d
             double *Q = h->V + (size_t)nv * ld;
             const double g_start = std::fabs(g[j0]);
             // the power basis: raw vectors (scale 1) in slots nv .. nv+ss-1
-            RICH_TRY(launch_fill_f64(h->vs + nv, 1.0, ss, s));
             for (int t = 0; t < ss; t++)
                 RICH_TRY(prec_product(h, h->V + (size_t)(j0 + t) * ld, h->vs + j0 + t,
                                       h->V + (size_t)(j0 + t + 1) * ld, sig[t]));
             const int nout = block_partial_size(nv, ss);
+            expect(hout, nout);
             RICH_TRY(timed(h, RICH_K_BLOCK_DOT, 8.0 * N * (nv + ss), [&] {
-                return launch_block_dot(h->V, ld, nv, h->vs, Q, ss, N, h->partial, dout, s);
+                return launch_block_dot(h->V, ld, nv, h->vs, Q, ss, N, h->partial, hout, s);
             }));
-            HIP_TRY(hipMemcpyAsync(hout, dout, nout * sizeof(double), hipMemcpyDeviceToHost, s));
-            RICH_TRY(sync(h));
+            RICH_TRY(arrived(h, hout, nout));
             bool finite = true;
             for (int t = 0; t < nout; t++) finite = finite && std::isfinite(hout[t]);
             if (!finite) {
@@ -1146,20 +1203,12 @@ rich_status gmres_sstep(rich_ctx *h, const double *b, double *x, int *its_out, d
                     double *w = h->V + (size_t)slot * ld;
                     double ww = 0.0;
                     for (int pass = 0; pass < 2; pass++) {
-                        RICH_TRY(timed(h, RICH_K_COUNT, 8.0 * N * (slot + 1), [&] {
-                            return launch_multidot(h->V, ld, slot, h->vs, w, N, h->partial, h->dres, s);
-                        }));
-                        RICH_TRY(timed(h, RICH_K_COUNT, 8.0 * N * (slot + 2), [&] {
-                            return launch_update_norm(h->V, ld, slot, h->dres, h->vs, w, N, h->partial, h->dres2, s);
-                        }));
-                        HIP_TRY(hipMemcpyAsync(h->hres, h->dres, slot * sizeof(double), hipMemcpyDeviceToHost, s));
-                        HIP_TRY(hipMemcpyAsync(h->hres + (m + 8), h->dres2, sizeof(double), hipMemcpyDeviceToHost, s));
-                        RICH_TRY(sync(h));
+                        RICH_TRY(gs_pass(h, slot, w, RICH_K_COUNT, RICH_K_COUNT, &ww));
                         for (int i = 0; i < nv; i++) C[i * sw + t] += h->hres[i];
                         for (int r = 0; r < t; r++) R[r * sw + t] += h->hres[nv + r];
-                        ww = h->hres[m + 8];
                     }
                     RICH_TRY(launch_set_scale(h->vs + slot, h->dres2, s));
+                    h->vs_set = true;
                     R[t * sw + t] = std::sqrt(ww);
                     if (!std::isfinite(R[t * sw + t])) {
                         overflow = true;
@@ -1228,13 +1277,13 @@ rich_status gmres_sstep(rich_ctx *h, const double *b, double *x, int *its_out, d
             for (int t = i + 1; t < k; t++) sum -= Hm[(size_t)i * m + t] * y[t];
             y[i] = sum / Hm[(size_t)i * m + i];
         }
-        memcpy(h->hres, y.data(), k * sizeof(double));
-        HIP_TRY(hipMemcpyAsync(h->dres, h->hres, k * sizeof(double), hipMemcpyHostToDevice, s));
+        // (the previous cycle's upload is over: norms have been read since)
+        memcpy(h->hy, y.data(), k * sizeof(double));
+        HIP_TRY(hipMemcpyAsync(h->dres, h->hy, k * sizeof(double), hipMemcpyHostToDevice, s));
         RICH_TRY(launch_lincomb(h->V, ld, k, h->dres, h->vs, h->work, N, s));
         RICH_TRY(prec_product(h, h->work, h->one, nullptr));
         RICH_TRY(add_z(h, x));
         charge(h, 8.0 * (k + 1) * N + (16.0 + (h->mixed ? 4 : 8)) * N);
-        RICH_TRY(sync(h));  // hres is reused before the next read
     }
     *its_out = total;
     *relres_out = relres;
@@ -1301,13 +1350,15 @@ rich_status rebuild(rich_ctx *h, const double *u) {
     return RICH_OK;
 }
 
-// f = 0.5 ||F||^2 and ||F||_inf
-rich_status fnorms(rich_ctx *h, const double *F, double *f_half, double *finf) {
+// f = 0.5 ||F||^2, ||F||_inf and sum F
+struct FNorms {
+    double f = 0.0, inf = 0.0, sum = 0.0;
+};
+rich_status fnorms(rich_ctx *h, const double *F, FNorms *o) {
     double n3[3];
     charge(h, 8.0 * h->N);
     RICH_TRY(norms(h, F, n3));
-    *f_half = 0.5 * n3[2];
-    *finf = n3[0];
+    *o = {0.5 * n3[2], n3[0], n3[1]};
     return RICH_OK;
 }
 
@@ -1370,41 +1421,40 @@ struct Backtrack {
 // scsteptol / max_i(|d_i| / max(|u_i|, 1)) it gives up.  A full step that
 // was not truncated and beats the beta = 0.9 bound of the linear model is
 // doubled while the doubled step keeps the Armijo condition and stays within
-// the maximum step (at most ten times).  On success ut/Ft hold the point.
+// the maximum step (at most ten times).  On success ut/Ft hold the point and
+// *acc the norms of Ft.
 rich_status line_search(rich_ctx *h, double f0, double slope, double mxstep, bool truncated, double dnorm,
-                        rich_newton_event_t *ev, double *lam_out) {
+                        rich_newton_event_t *ev, double *lam_out, FNorms *acc) {
     const int64_t N = h->N;
     const double alpha = h->O.ls_alpha, beta = 0.9;
     charge(h, 16.0 * N);
-    RICH_TRY(launch_rel_length(h->d, h->u, N, h->partial, h->dres, h->s));
-    RICH_TRY(readback(h, h->dres, 1, &ev->rel_d));
+    RICH_TRY(rel_length(h, h->d, h->u, &ev->rel_d));
     const double lam_min = ev->rel_d > 0.0 ? h->O.scsteptol / ev->rel_d : 0.0;
     auto armijo = [&](double lam, double f) { return std::isfinite(f) && f <= f0 + alpha * lam * slope; };
-    auto trial = [&](double lam, double *x, double *Fx, double *f) -> rich_status {
+    auto trial = [&](double lam, double *x, double *Fx, FNorms *o) -> rich_status {
         charge(h, 24.0 * N);
         RICH_TRY(launch_xpay_to(h->u, lam, h->d, x, N, h->s));
         RICH_TRY(feval(h, x, Fx));
-        double finf;
-        RICH_TRY(fnorms(h, Fx, f, &finf));
-        record_trial(ev, lam, *f);
+        RICH_TRY(fnorms(h, Fx, o));
+        record_trial(ev, lam, o->f);
         return RICH_OK;
     };
     Backtrack model{f0, slope};
-    double lam = 1.0, ft;
+    double lam = 1.0;
     for (;;) {
-        RICH_TRY(trial(lam, h->ut, h->Ft, &ft));
-        if (armijo(lam, ft)) break;
+        RICH_TRY(trial(lam, h->ut, h->Ft, acc));
+        if (armijo(lam, acc->f)) break;
         if (lam < lam_min) return RICH_LINESEARCH_FAIL;
-        lam = model.next(lam, ft);
+        lam = model.next(lam, acc->f);
         ev->nback++;
     }
     if (lam == 1.0 && !truncated) {
-        for (int k = 0; k < 10 && ft < f0 + beta * lam * slope && 2.0 * lam * dnorm <= mxstep; k++) {
-            double fb;
+        for (int k = 0; k < 10 && acc->f < f0 + beta * lam * slope && 2.0 * lam * dnorm <= mxstep; k++) {
+            FNorms fb;
             RICH_TRY(trial(2.0 * lam, h->ub, h->Fb, &fb));
-            if (!armijo(2.0 * lam, fb)) break;
+            if (!armijo(2.0 * lam, fb.f)) break;
             lam *= 2.0;
-            ft = fb;
+            *acc = fb;
             std::swap(h->ut, h->ub);
             std::swap(h->Ft, h->Fb);
         }
@@ -1455,8 +1505,9 @@ rich_status newton_step(rich_ctx *h, rich_step_stats_t *st) {
     HIP_TRY(hipMemcpyAsync(h->u, h->p, N * sizeof(double), hipMemcpyDeviceToDevice, s));
     charge(h, 8.0 * N + 16.0 * N + 16.0 * N);
     RICH_TRY(feval(h, h->u, h->F));
-    double f0, fnorm;
-    RICH_TRY(fnorms(h, h->F, &f0, &fnorm));
+    FNorms at;  // of F
+    RICH_TRY(fnorms(h, h->F, &at));
+    double f0 = at.f, fnorm = at.inf;
     if (!std::isfinite(fnorm)) return st->status = RICH_NONFINITE;
     double mxstep = h->O.mxnewtstep;
     if (!(mxstep > 0.0)) mxstep = 1000.0 * std::max(std::sqrt(pn[2]), 1.0);
@@ -1545,7 +1596,8 @@ rich_status newton_step(rich_ctx *h, rich_step_stats_t *st) {
             break;
         }
         double lam;
-        rich_status rc = line_search(h, f0, ev.slope, mxstep, ev.truncated != 0, dn, &ev, &lam);
+        FNorms acc;
+        rich_status rc = line_search(h, f0, ev.slope, mxstep, ev.truncated != 0, dn, &ev, &lam, &acc);
         st->ls_backtracks += ev.nback;
         if (rc == RICH_LINESEARCH_FAIL) {
             if (!fresh) {
@@ -1562,14 +1614,15 @@ rich_status newton_step(rich_ctx *h, rich_step_stats_t *st) {
         ev.lam = lam;
         ev.step_inf = lam * ev.dnorminf;
         charge(h, 16.0 * N);
-        RICH_TRY(launch_rel_length(h->d, h->ut, N, h->partial, h->dres, s));
-        RICH_TRY(readback(h, h->dres, 1, &ev.step_rel));
+        RICH_TRY(rel_length(h, h->d, h->ut, &ev.step_rel));
         ev.step_rel *= lam;
         std::swap(h->u, h->ut);
         std::swap(h->F, h->Ft);
         st->newton_its++;
         h->since_build++;
-        RICH_TRY(fnorms(h, h->F, &f0, &fnorm));
+        at = acc;
+        f0 = at.f;
+        fnorm = at.inf;
         ev.f_acc = f0;
         ev.fnorm_inf = fnorm;
         if (!std::isfinite(fnorm)) {
@@ -1596,10 +1649,8 @@ rich_status newton_step(rich_ctx *h, rich_step_stats_t *st) {
     st->fnorm_inf = fnorm;
     if (status == RICH_OK || status == RICH_STEP_TOO_SMALL) {
         HIP_TRY(hipMemcpyAsync(h->p, h->u, N * sizeof(double), hipMemcpyDeviceToDevice, s));
-        double fn[3];
-        charge(h, 16.0 * N + 8.0 * N);
-        RICH_TRY(norms(h, h->F, fn));
-        st->mass_residual = h->P.dt * fn[1];
+        charge(h, 16.0 * N);
+        st->mass_residual = h->P.dt * at.sum;
     }
     if (h->H) {
         st->levels = h->H->nlev;
@@ -1804,15 +1855,16 @@ rich_status rich_create(const rich_problem_t *prob, const rich_solver_opts_t *op
     h->z = z;
     h->ztmp = zt;
     G(&h->partial, (size_t)RED_BLOCKS * std::max(3 * (h->m + 2), block_partial_size(h->m + 1, GMRES_BLOCK_MAX)));
-    G(&h->dblk, 2 * BLK_BUF);
+    G(&h->dblk, BLK_BUF);
     G(&h->dres, h->m + 8);
     G(&h->dres2, 8);
     G(&h->vs, h->m + 2);
     G(&h->one, 1);
     G(&h->hbuf, (size_t)(h->m + 1) * (h->m + 4));
     G(&h->bsc, N);
-    if (st == RICH_OK && hipHostMalloc((void **)&h->hres, 2 * (h->m + 8) * sizeof(double)) != hipSuccess)
+    if (st == RICH_OK && hipHostMalloc((void **)&h->hres, (2 * (h->m + 8) + h->m) * sizeof(double)) != hipSuccess)
         st = RICH_ENOMEM;
+    if (st == RICH_OK) h->hy = h->hres + 2 * (h->m + 8);
     if (st == RICH_OK &&
         hipHostMalloc((void **)&h->hall, (size_t)(h->m + 1) * (h->m + 4) * sizeof(double)) != hipSuccess)
         st = RICH_ENOMEM;
