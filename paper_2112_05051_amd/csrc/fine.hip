@@ -160,10 +160,21 @@ __device__ inline void mean_of(const Phys &P, int axis, int dir, double pc, cons
     }
 }
 
+// Theta of C cells per thread, all C heads loaded before the first law: at
+// 256^3 one cell a thread took 95 us, four take 82 (67 us of FP64 issue, 54 us
+// of bytes).
+template <int C>
 __global__ void k_theta(Phys P, uint32_t n, const double *__restrict__ p, double *__restrict__ th) {
-    uint32_t c = xcd_block() * blockDim.x + threadIdx.x;
-    if (c >= n) return;
-    th[c] = laws(P, p[c], 1.0).th;
+    uint32_t c[C];
+    double v[C];
+#pragma unroll
+    for (int t = 0; t < C; t++) {
+        c[t] = (xcd_block() * C + t) * blockDim.x + threadIdx.x;
+        v[t] = c[t] < n ? p[c[t]] : 0.0;
+    }
+#pragma unroll
+    for (int t = 0; t < C; t++)
+        if (c[t] < n) th[c[t]] = laws(P, v[t], 1.0).th;
 }
 
 // eq. (dynamic_of_the_problem), f = 0: time term plus, per face, the
@@ -257,7 +268,8 @@ __global__ void k_assemble(Phys P, uint32_t n, const double *__restrict__ Ks, co
 }
 
 // ------------------------------------ plane-tiled residual and assembly
-// A block owns an FT_X x FT_Y tile of (x, y) columns and a run of z planes.
+// For the integral mean, whose faces take 16 law evaluations each: every face
+// once.  A block owns an FT_X x FT_Y tile of (x, y) columns and a run of z planes.
 // For each plane it stages the tile and a one-cell ring around it in LDS
 // (heads, K_s and the laws of every cell, each evaluated once; the tile's own
 // cells carry their laws over from the plane below, where they were the upper
@@ -287,7 +299,7 @@ __device__ inline int ring_pos(int t) {
     return r * FT_RX + ((t & 1) ? FT_RX - 1 : 0);
 }
 
-template <bool JAC, bool INTEG>
+template <bool JAC>
 __global__ void __launch_bounds__(FT_TPB) k_faces_tiled(Phys P, int kz, const double *__restrict__ Ks,
                                                         const double *__restrict__ p,
                                                         const double *__restrict__ th_old, double *__restrict__ F,
@@ -324,7 +336,7 @@ __global__ void __launch_bounds__(FT_TPB) k_faces_tiled(Phys P, int kz, const do
             const double ksd = Ks[cd];
             const Law Ld = laws(P, pd, ksd);
             double Kf, dL, dU;
-            mean_of<INTEG>(P, 2, 1, pd, Ld, ksd, pc, Lc, ksc, Kf, dL, dU);
+            mean_of<true>(P, 2, 1, pd, Ld, ksd, pc, Lc, ksc, Kf, dL, dU);
             q_dn = -Kf * (pc - pd) / hz2;
             g_dn = -(Ld.K + Lc.K) / (2.0 * P.hz);
             m_dn = {Kf, dL, dU};
@@ -360,7 +372,7 @@ __global__ void __launch_bounds__(FT_TPB) k_faces_tiled(Phys P, int kz, const do
             ksu = Ks[cu];
             Lu = laws(P, pu, ksu);
             double Kf, dL, dU;
-            mean_of<INTEG>(P, 2, 1, pc, Lc, ksc, pu, Lu, ksu, Kf, dL, dU);
+            mean_of<true>(P, 2, 1, pc, Lc, ksc, pu, Lu, ksu, Kf, dL, dU);
             q_up = -Kf * (pu - pc) / hz2;
             g_up = -(Lc.K + Lu.K) / (2.0 * P.hz);
             m_up = {Kf, dL, dU};
@@ -374,7 +386,7 @@ __global__ void __launch_bounds__(FT_TPB) k_faces_tiled(Phys P, int kz, const do
                 const int a = (r + 1) * FT_RX + f, b = a + 1;
                 Law La{0.0, 0.0, sK[a], JAC ? sdK[a] : 0.0}, Lb{0.0, 0.0, sK[b], JAC ? sdK[b] : 0.0};
                 double Kf, dL, dU;
-                mean_of<INTEG>(P, 0, 1, sp[a], La, sks[a], sp[b], Lb, sks[b], Kf, dL, dU);
+                mean_of<true>(P, 0, 1, sp[a], La, sks[a], sp[b], Lb, sks[b], Kf, dL, dU);
                 if constexpr (JAC) {
                     fx[0][t] = Kf;
                     fx[1][t] = dL;
@@ -392,7 +404,7 @@ __global__ void __launch_bounds__(FT_TPB) k_faces_tiled(Phys P, int kz, const do
                 const int a = g * FT_RX + c + 1, b = a + FT_RX;
                 Law La{0.0, 0.0, sK[a], JAC ? sdK[a] : 0.0}, Lb{0.0, 0.0, sK[b], JAC ? sdK[b] : 0.0};
                 double Kf, dL, dU;
-                mean_of<INTEG>(P, 1, 1, sp[a], La, sks[a], sp[b], Lb, sks[b], Kf, dL, dU);
+                mean_of<true>(P, 1, 1, sp[a], La, sks[a], sp[b], Lb, sks[b], Kf, dL, dU);
                 if constexpr (JAC) {
                     fy[0][t] = Kf;
                     fy[1][t] = dL;
@@ -433,7 +445,7 @@ __global__ void __launch_bounds__(FT_TPB) k_faces_tiled(Phys P, int kz, const do
                     Law Ln = laws(P, fc.pn, fc.Ksn);
                     double Kf, dcc, dnn;
                     int dir = (f & 1) ? 1 : -1;
-                    mean_of<INTEG>(P, f >> 1, dir, pc, Lc, ksc, fc.pn, Ln, fc.Ksn, Kf, dcc, dnn);
+                    mean_of<true>(P, f >> 1, dir, pc, Lc, ksc, fc.pn, Ln, fc.Ksn, Kf, dcc, dnn);
                     acc += -Kf * (fc.pn - pc) / (fc.h * fc.h);
                     if ((f >> 1) == 2) acc += dir * (-(Lc.K + Ln.K) / (2.0 * P.hz));
                 }
@@ -475,7 +487,7 @@ __global__ void __launch_bounds__(FT_TPB) k_faces_tiled(Phys P, int kz, const do
                         if (fc.kind == 0) continue;
                         interior = false;
                         Law Ln = laws(P, fc.pn, fc.Ksn);
-                        mean_of<INTEG>(P, axis, dir, pc, Lc, ksc, fc.pn, Ln, fc.Ksn, Kf, dcc, dnn);
+                        mean_of<true>(P, axis, dir, pc, Lc, ksc, fc.pn, Ln, fc.Ksn, Kf, dcc, dnn);
                         pn = fc.pn;
                         dKn = Ln.dK;
                         h2 = fc.h * fc.h;
@@ -532,6 +544,279 @@ __global__ void __launch_bounds__(FT_TPB) k_faces_tiled(Phys P, int kz, const do
             Lc = Lu;
         }
         __syncthreads();  // the staged plane and faces are overwritten next
+    }
+}
+
+// ------------------------------------ plane-marching residual and assembly
+// The means without a quadrature.  A block owns an F_X x F_Y tile of (x, y)
+// columns and marches up a run of z planes: per plane it stages the heads, K
+// (and K') of the tile and of the ring around it in LDS (each evaluated once;
+// the tile's own come up from the plane below, where they were the upper
+// neighbours), and each cell takes its four lateral faces from there, its z
+// faces from its column's registers.  Both cells of a lateral face form it
+// from the same values in the same order (lower cell first), so they agree
+// bitwise.  Each cell adds its faces in the order -x, +x, -y, +y, -z, +z.
+// Bounds: FP64 issue (a log, two exp and the divisions of a cell: about 180 us
+// of a residual at 256^3) and the loads' latency, against 97 us for the
+// residual's bytes.  So the next plane's heads, K_s and theta are loaded a plane
+// ahead; the planes alternate between two LDS buffers, one barrier each; the
+// 64 ring cells (no corners) are one wave's work, each plane another wave's;
+// and divisions by the grid's constants go through their reciprocals.
+// Measured at 256^3: MARCHUS.
+constexpr int F_X = 16, F_Y = 16, F_TPB = F_X * F_Y;
+constexpr int F_RX = F_X + 2, F_RING = F_RX * (F_Y + 2);
+static_assert(2 * (F_X + F_Y) == 64, "the ring is one wave's");
+
+// a / b for a constant b with y = 1 / b rounded: two Newton corrections of
+// a * y with exact remainders (Markstein's division), which give the rounded
+// quotient as the division instruction sequence does, short of subnormals.
+struct Recip {
+    double b, y;
+    __device__ explicit Recip(double v) : b(v), y(1.0 / v) {}
+    __device__ __forceinline__ double div(double a) const {
+        const double q0 = a * y;
+        const double q1 = fma(fma(-q0, b, a), y, q0);
+        const double q2 = fma(fma(-q1, b, a), y, q1);
+        return isfinite(q0) ? q2 : q0;
+    }
+};
+
+template <bool JAC>
+__global__ void __launch_bounds__(F_TPB, JAC ? 3 : 4) k_faces_march(Phys P, int kz, const double *__restrict__ Ks,
+                                                       const double *__restrict__ p,
+                                                       const double *__restrict__ th_old, double *__restrict__ F,
+                                                       double *__restrict__ J7, double *__restrict__ M4,
+                                                       float *__restrict__ M4f, double *__restrict__ invd,
+                                                       float *__restrict__ invdf, int dflux) {
+    __shared__ double sp[2][F_RING], sK[2][F_RING], sdK[JAC ? 2 : 1][JAC ? F_RING : 1];
+    const int tid = threadIdx.x, tx = tid % F_X, ty = tid / F_X;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int i0 = blockIdx.x * F_X, j0 = blockIdx.y * F_Y;
+    const int k0 = blockIdx.z * kz, k1 = min(k0 + kz, P.nz);
+    const int i = i0 + tx, j = j0 + ty;
+    const bool own = i < P.nx && j < P.ny;
+    const uint32_t nxy = (uint32_t)P.nx * (uint32_t)P.ny, n = nxy * (uint32_t)P.nz;
+    const int me = (ty + 1) * F_RX + (tx + 1);
+    const Recip dx2(P.hx * P.hx), dy2(P.hy * P.hy), dz2(P.hz * P.hz), d2z(2.0 * P.hz), ddt(P.dt);
+    // ring cell of this lane: the row below, the row above, the left and right columns
+    const int rs = lane >> 4, rt = lane & 15;
+    const int gi = rs < 2 ? i0 + rt : rs == 2 ? i0 - 1 : i0 + F_X, gj = rs >= 2 ? j0 + rt : rs == 0 ? j0 - 1 : j0 + F_Y;
+    const int rpos = (gj - j0 + 1) * F_RX + (gi - i0 + 1);
+    const bool ring = gi >= 0 && gi < P.nx && gj >= 0 && gj < P.ny;
+    const uint32_t rcol = ring ? (uint32_t)gi + (uint32_t)P.nx * (uint32_t)gj : 0u;
+    const uint32_t col = own ? (uint32_t)i + (uint32_t)P.nx * (uint32_t)j : 0u;
+    // the own column: current plane (c), the one above (u) and the face below
+    double pc = 0.0, ksc = 0.0, pu = 0.0, ksu = 0.0, th = 0.0, rp = 0.0, rk = 0.0;
+    Law Lc{}, Lu{};
+    double q_dn = 0.0, g_dn = 0.0;   // residual: diffusive flux and gravity term of the face below, as they
+                                     // enter the lower cell's row (the upper cell takes their negatives)
+    FaceMean m_dn{}, m_up{};         // Jacobian: means of the z faces
+    double pd = 0.0, dKd = 0.0;      // Jacobian: head and K' of the cell below
+    uint32_t c = col + nxy * (uint32_t)k0;
+    if (ring && wave == (k0 & 3)) {
+        rp = p[rcol + nxy * (uint32_t)k0];
+        rk = Ks[rcol + nxy * (uint32_t)k0];
+    }
+    if (own) {
+        pc = p[c];
+        ksc = Ks[c];
+        if (k0 + 1 < P.nz) {
+            pu = p[c + nxy];
+            ksu = Ks[c + nxy];
+        }
+        if (!JAC) th = th_old[c];
+        double ksd = 0.0;
+        if (k0 > 0) {
+            pd = p[c - nxy];
+            ksd = Ks[c - nxy];
+        }
+        Lc = laws(P, pc, ksc);
+        if (k0 > 0) {
+            const Law Ld = laws(P, pd, ksd);
+            double Kf, dL, dU;
+            mean_of<false>(P, 2, 1, pd, Ld, ksd, pc, Lc, ksc, Kf, dL, dU);
+            q_dn = dz2.div(-Kf * (pc - pd));
+            g_dn = d2z.div(-(Ld.K + Lc.K));
+            m_dn = {Kf, dL, dU};
+            dKd = Ld.dK;
+        }
+    }
+    for (int k = k0; k < k1; k++, c += nxy) {
+        const int b = k & 1;
+        // the next plane's loads
+        double p2 = 0.0, ks2 = 0.0, th1 = 0.0, rp1 = 0.0, rk1 = 0.0;
+        if (k + 1 < k1) {
+            if (own) {
+                if (k + 2 < P.nz) {
+                    p2 = p[c + 2 * nxy];
+                    ks2 = Ks[c + 2 * nxy];
+                }
+                if (!JAC) th1 = th_old[c + nxy];
+            }
+            if (ring && wave == ((k + 1) & 3)) {
+                rp1 = p[rcol + nxy * (uint32_t)(k + 1)];
+                rk1 = Ks[rcol + nxy * (uint32_t)(k + 1)];
+            }
+        }
+        if (own) {
+            sp[b][me] = pc;
+            sK[b][me] = Lc.K;
+            if constexpr (JAC) sdK[b][me] = Lc.dK;
+        }
+        if (ring && wave == (k & 3)) {
+            const Law L = laws(P, rp, rk);
+            sp[b][rpos] = rp;
+            sK[b][rpos] = L.K;
+            if constexpr (JAC) sdK[b][rpos] = L.dK;
+        }
+        // the own column's cell above and the face between
+        const bool up = own && k + 1 < P.nz;
+        double q_up = 0.0, g_up = 0.0;
+        if (up) {
+            Lu = laws(P, pu, ksu);
+            double Kf, dL, dU;
+            mean_of<false>(P, 2, 1, pc, Lc, ksc, pu, Lu, ksu, Kf, dL, dU);
+            if constexpr (JAC) {
+                m_up = {Kf, dL, dU};
+            } else {
+                q_up = dz2.div(-Kf * (pu - pc));
+                g_up = d2z.div(-(Lc.K + Lu.K));
+            }
+        }
+        __syncthreads();  // plane k is staged (the other buffer is written next)
+        if (own) {
+            const Cell q{i, j, k};
+            // whether face f has a neighbour in the domain, and that neighbour's LDS slot (x, y faces)
+            auto inside = [&](int f) {
+                return f == 0 ? i > 0 : f == 1 ? i + 1 < P.nx : f == 2 ? j > 0 : f == 3 ? j + 1 < P.ny
+                     : f == 4 ? k > 0 : k + 1 < P.nz;
+            };
+            auto slot = [&](int f) { return f == 0 ? me - 1 : f == 1 ? me + 1 : f == 2 ? me - F_RX : me + F_RX; };
+            // mean of the lateral face f, its lower-index cell first
+            auto lateral = [&](int f, double pn) {
+                const int s = slot(f);
+                const Law Ln{0.0, 0.0, sK[b][s], JAC ? sdK[JAC ? b : 0][JAC ? s : 0] : 0.0};
+                FaceMean m;
+                if (f & 1) mean_of<false>(P, f >> 1, 1, pc, Lc, ksc, pn, Ln, 0.0, m.Kf, m.dL, m.dU);
+                else mean_of<false>(P, f >> 1, 1, pn, Ln, 0.0, pc, Lc, ksc, m.Kf, m.dL, m.dU);
+                return m;
+            };
+            if constexpr (!JAC) {
+                double acc = ddt.div(Lc.th - th);
+#pragma unroll
+                for (int f = 0; f < 6; f++) {
+                    if (inside(f)) {
+                        // the cell is the lower one on its + faces
+                        double v;
+                        if (f < 4) {
+                            const double pn = sp[b][slot(f)];
+                            const FaceMean m = lateral(f, pn);
+                            v = (f < 2 ? dx2 : dy2).div(-m.Kf * ((f & 1) ? pn - pc : pc - pn));
+                        } else {
+                            v = f == 4 ? q_dn : q_up;
+                        }
+                        acc += (f & 1) ? v : -v;
+                        if (f == 4) acc += -g_dn;
+                        if (f == 5) acc += g_up;
+                        continue;
+                    }
+                    Face fc = face(P, q, c, f, p, Ks);
+                    if (fc.kind == 0) continue;
+                    Law Ln = laws(P, fc.pn, fc.Ksn);
+                    double Kf, dcc, dnn;
+                    int dir = (f & 1) ? 1 : -1;
+                    mean_of<false>(P, f >> 1, dir, pc, Lc, ksc, fc.pn, Ln, fc.Ksn, Kf, dcc, dnn);
+                    acc += -Kf * (fc.pn - pc) / (fc.h * fc.h);
+                    if ((f >> 1) == 2) acc += dir * (-(Lc.K + Ln.K) / (2.0 * P.hz));
+                }
+                F[c] = acc;
+            } else {
+                const double dtm = ddt.div(Lc.dth);
+                double jd = dtm, md = dtm;
+                double joff[6] = {0, 0, 0, 0, 0, 0}, moff[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll
+                for (int f = 0; f < 6; f++) {
+                    const int axis = f >> 1, dir = (f & 1) ? 1 : -1;
+                    const Recip &h2 = axis == 0 ? dx2 : axis == 1 ? dy2 : dz2;
+                    double Kf, dcc, dnn, pn, dKn;
+                    bool interior;
+                    if (inside(f)) {
+                        interior = true;
+                        FaceMean m;
+                        if (f < 4) {
+                            pn = sp[b][slot(f)];
+                            dKn = sdK[b][slot(f)];
+                            m = lateral(f, pn);
+                        } else {
+                            m = f == 4 ? m_dn : m_up;
+                            pn = f == 4 ? pd : pu;
+                            dKn = f == 4 ? dKd : Lu.dK;
+                        }
+                        Kf = m.Kf;
+                        // the cell is the lower one on its + faces
+                        dcc = dir > 0 ? m.dL : m.dU;
+                        dnn = dir > 0 ? m.dU : m.dL;
+                    } else {
+                        Face fc = face(P, q, c, f, p, Ks);
+                        if (fc.kind == 0) continue;
+                        interior = false;
+                        Law Ln = laws(P, fc.pn, fc.Ksn);
+                        mean_of<false>(P, axis, dir, pc, Lc, ksc, fc.pn, Ln, fc.Ksn, Kf, dcc, dnn);
+                        pn = fc.pn;
+                        dKn = Ln.dK;
+                    }
+                    const double Kh = h2.div(Kf), dh = h2.div(pn - pc);
+                    const bool zf = axis == 2;
+                    jd += Kh - dh * dcc;
+                    if (zf) jd += d2z.div(-dir * Lc.dK);
+                    md += Kh;
+                    if (dflux) md += -dh * dcc;
+                    if (interior) {
+                        double v = -Kh - dh * dnn;
+                        if (zf) v += d2z.div(-dir * dKn);
+                        joff[f] = v;
+                        moff[f] = -Kh;
+                    }
+                }
+                J7[(size_t)J_D * n + c] = jd;
+                J7[(size_t)J_XM * n + c] = joff[0];
+                J7[(size_t)J_XP * n + c] = joff[1];
+                J7[(size_t)J_YM * n + c] = joff[2];
+                J7[(size_t)J_YP * n + c] = joff[3];
+                J7[(size_t)J_ZM * n + c] = joff[4];
+                J7[(size_t)J_ZP * n + c] = joff[5];
+                M4[(size_t)M_D * n + c] = md;
+                M4[(size_t)M_XP * n + c] = moff[1];
+                M4[(size_t)M_YP * n + c] = moff[3];
+                M4[(size_t)M_ZP * n + c] = moff[5];
+                double l1 = md;
+#pragma unroll
+                for (int f = 0; f < 6; f++) l1 += fabs(moff[f]);
+                if (M4f) {
+                    M4f[(size_t)M_D * n + c] = f32_sat(md);
+                    M4f[(size_t)M_XP * n + c] = f32_sat(moff[1]);
+                    M4f[(size_t)M_YP * n + c] = f32_sat(moff[3]);
+                    M4f[(size_t)M_ZP * n + c] = f32_sat(moff[5]);
+                }
+                const double il1 = 1.0 / l1;
+                if (invd) invd[c] = il1;
+                if (invdf) invdf[c] = f32_sat(il1);
+            }
+        }
+        // carry the column up one plane
+        pd = pc;
+        dKd = Lc.dK;
+        m_dn = m_up;
+        q_dn = q_up;
+        g_dn = g_up;
+        pc = pu;
+        ksc = ksu;
+        Lc = Lu;
+        pu = p2;
+        ksu = ks2;
+        th = th1;
+        rp = rp1;
+        rk = rk1;
     }
 }
 
@@ -895,7 +1180,7 @@ __global__ void k_spmv_J_batch(Batch<SpmvArgs<TX>> B) {
 
 // The 64-wide tile needs rows of at least about that length to keep its lanes busy.
 inline bool use25(const Phys &P) { return P.nx >= 48 && P.ny >= T25Y && P.nz >= 4; }
-// Planes per block, at most 16: the chunks that cost the fewest planes in a row.
+// Planes per block, at most `most`: the chunks that cost the fewest planes in a row.
 // The blocks run in rounds of `fit` (what the chip holds at once); a block
 // walks its planes after a start worth about two more (the planes below and
 // above its chunk).  Measured post-smoother us, chosen depth against the one
@@ -904,30 +1189,32 @@ inline bool use25(const Phys &P) { return P.nx >= 48 && P.ny >= T25Y && P.nz >= 
 // 39.6 (5: 42.5; 8, which starts a second round with a fifth of its blocks:
 // 52.6), 128^3 FP64 8 planes 34.5 (2: 39.7); the pre-smoother changes by less
 // than 1 us but for 128^3 FP64 (6 planes 31, 2: 28).
-inline int kz25(const Phys &P, int fit) {
-    if (P.tile_kz > 0) return P.tile_kz < P.nz ? P.tile_kz : P.nz;
-    const int64_t tiles = (int64_t)((P.nx + T25X - 1) / T25X) * ((P.ny + T25Y - 1) / T25Y);
+inline int planes_per_block(int64_t tiles, int nz, int most, int fit) {
     int best = 1;
     int64_t cost = INT64_MAX;
-    for (int kz = 1; kz <= 16 && kz <= P.nz; kz++) {
-        const int64_t blocks = tiles * ((P.nz + kz - 1) / kz);
+    for (int kz = 1; kz <= most && kz <= nz; kz++) {
+        const int64_t blocks = tiles * ((nz + kz - 1) / kz);
         const int64_t c = (blocks + fit - 1) / fit * (kz + 2);
         if (c < cost) {
             cost = c;
             best = kz;
         }
     }
-    const int64_t chunks = (P.nz + best - 1) / best;  // spread evenly
-    return (int)((P.nz + chunks - 1) / chunks);
+    const int64_t chunks = (nz + best - 1) / best;  // spread evenly
+    return (int)((nz + chunks - 1) / chunks);
 }
-// Blocks of a tiled kernel that the chip holds at once (a constant of the
-// compiled kernel and the chip, asked once).
+inline int kz25(const Phys &P, int fit) {
+    if (P.tile_kz > 0) return P.tile_kz < P.nz ? P.tile_kz : P.nz;
+    return planes_per_block((int64_t)((P.nx + T25X - 1) / T25X) * ((P.ny + T25Y - 1) / T25Y), P.nz, 16, fit);
+}
+// Blocks of a kernel that the chip holds at once (a constant of the compiled
+// kernel and the chip, asked once).
 template <class K>
-inline int blocks_at_once(K kernel) {
+inline int blocks_at_once(K kernel, int threads) {
     int dev = 0, cus = 256, per = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, T25X * T25Y, 0) != hipSuccess) {
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, threads, 0) != hipSuccess) {
         (void)hipGetLastError();
         per = 2;
     }
@@ -935,7 +1222,7 @@ inline int blocks_at_once(K kernel) {
 }
 template <class TB, class T, int MODE>
 inline int kz25_of(const Phys &P) {
-    static const int fit = blocks_at_once(k_st25<TB, T, MODE>);
+    static const int fit = blocks_at_once(k_st25<TB, T, MODE>, T25X * T25Y);
     return kz25(P, fit);
 }
 inline int64_t tiles25(const Phys &P, int kz) {
@@ -1077,19 +1364,24 @@ static inline uint32_t ncells(const Phys &P) { return (uint32_t)((int64_t)P.nx *
 
 rich_status launch_theta(const Phys &P, const double *p, double *theta, hipStream_t s) {
     uint32_t n = ncells(P);
-    k_theta<<<nblocks(n), TPB, 0, s>>>(P, n, p, theta);
+    // four cells a thread once that leaves every CU a full set of wavefronts
+    // (2048 threads x 256 CUs x 4); below, one: 16^3 took 1.5 us longer with four
+    if (n >= (1u << 21))
+        k_theta<4><<<nblocks(((int64_t)n + 3) / 4), TPB, 0, s>>>(P, n, p, theta);
+    else
+        k_theta<1><<<nblocks(n), TPB, 0, s>>>(P, n, p, theta);
     LAUNCH_CHECK();
     return RICH_OK;
+}
+
+static bool has_integral(const Phys &P) {
+    return P.mean == RICH_MEAN_INTEGRAL || P.mean_vertical == RICH_MEAN_INTEGRAL;
 }
 
 // Grid of the plane-tiled kernels: FT_X x FT_Y columns per block and enough
 // planes per block that the launch has about 2048 blocks; false when the
 // (x, y) tiling does not fit the launch limits (the one-thread-per-cell
 // kernels take those grids).
-static bool has_integral(const Phys &P) {
-    return P.mean == RICH_MEAN_INTEGRAL || P.mean_vertical == RICH_MEAN_INTEGRAL;
-}
-
 static bool faces_grid(const Phys &P, dim3 *g, int *kz) {
     const int64_t tx = (P.nx + FT_X - 1) / FT_X, ty = (P.ny + FT_Y - 1) / FT_Y;
     if (tx > 0x7fffffff || ty > 65535) return false;
@@ -1103,19 +1395,33 @@ static bool faces_grid(const Phys &P, dim3 *g, int *kz) {
     return true;
 }
 
+// The same for the marching kernels: planes per block (at most 64) by the
+// rounds the blocks run in, as in kz25.
+template <bool JAC>
+static bool march_grid(const Phys &P, dim3 *g, int *kz) {
+    static const int fit = blocks_at_once(k_faces_march<JAC>, F_TPB);
+    const int64_t tx = (P.nx + F_X - 1) / F_X, ty = (P.ny + F_Y - 1) / F_Y;
+    if (tx > 0x7fffffff || ty > 65535) return false;
+    const int z = planes_per_block(tx * ty, P.nz, 64, fit);
+    const int64_t tz = (P.nz + z - 1) / z;
+    if (tz > 65535) return false;
+    *g = dim3((unsigned)tx, (unsigned)ty, (unsigned)tz);
+    *kz = z;
+    return true;
+}
+
 rich_status launch_residual(const Phys &P, const double *Ks, const double *p, const double *theta_old,
                             double *F, hipStream_t s) {
     uint32_t n = ncells(P);
     dim3 g;
     int kz;
-    if (faces_grid(P, &g, &kz)) {
-        if (has_integral(P))
-            k_faces_tiled<false, true><<<g, FT_TPB, 0, s>>>(P, kz, Ks, p, theta_old, F, nullptr, nullptr, nullptr,
-                                                            nullptr, nullptr, 0);
-        else
-            k_faces_tiled<false, false><<<g, FT_TPB, 0, s>>>(P, kz, Ks, p, theta_old, F, nullptr, nullptr, nullptr,
-                                                             nullptr, nullptr, 0);
-    } else
+    if (has_integral(P) && faces_grid(P, &g, &kz))
+        k_faces_tiled<false><<<g, FT_TPB, 0, s>>>(P, kz, Ks, p, theta_old, F, nullptr, nullptr, nullptr, nullptr,
+                                                  nullptr, 0);
+    else if (!has_integral(P) && march_grid<false>(P, &g, &kz))
+        k_faces_march<false><<<g, F_TPB, 0, s>>>(P, kz, Ks, p, theta_old, F, nullptr, nullptr, nullptr, nullptr,
+                                                 nullptr, 0);
+    else
         k_residual<<<nblocks(n), TPB, 0, s>>>(P, n, Ks, p, theta_old, F);
     LAUNCH_CHECK();
     return RICH_OK;
@@ -1126,14 +1432,11 @@ rich_status launch_assemble(const Phys &P, const double *Ks, const double *p, do
     uint32_t n = ncells(P);
     dim3 g;
     int kz;
-    if (faces_grid(P, &g, &kz)) {
-        if (has_integral(P))
-            k_faces_tiled<true, true><<<g, FT_TPB, 0, s>>>(P, kz, Ks, p, nullptr, nullptr, J7, M4, M4f, invd, invdf,
-                                                           dflux);
-        else
-            k_faces_tiled<true, false><<<g, FT_TPB, 0, s>>>(P, kz, Ks, p, nullptr, nullptr, J7, M4, M4f, invd,
-                                                            invdf, dflux);
-    } else
+    if (has_integral(P) && faces_grid(P, &g, &kz))
+        k_faces_tiled<true><<<g, FT_TPB, 0, s>>>(P, kz, Ks, p, nullptr, nullptr, J7, M4, M4f, invd, invdf, dflux);
+    else if (!has_integral(P) && march_grid<true>(P, &g, &kz))
+        k_faces_march<true><<<g, F_TPB, 0, s>>>(P, kz, Ks, p, nullptr, nullptr, J7, M4, M4f, invd, invdf, dflux);
+    else
         k_assemble<<<nblocks(n), TPB, 0, s>>>(P, n, Ks, p, J7, M4, M4f, invd, invdf, dflux);
     LAUNCH_CHECK();
     return RICH_OK;
