@@ -421,9 +421,10 @@ __global__ void k_narrow_u32(int64_t n, const int64_t *__restrict__ in, uint32_t
     if (i < n) out[i] = (uint32_t)in[i];
 }
 
-// COPY: what else the value goes to: GS_F32 an FP32 copy, GS_ENT / GS_VAL the
-// FP32 / FP64 cycle's entry at its place in aggregate order.
-enum { GS_NONE = 0, GS_F32, GS_ENT, GS_VAL };
+// COPY: what else the value goes to: GS_F32 an FP32 copy; at the entry's place
+// in aggregate order GS_ENT the FP32 cycle's pair, GS_VALF / GS_VAL its FP32 /
+// FP64 value.
+enum { GS_NONE = 0, GS_F32, GS_ENT, GS_VALF, GS_VAL };
 // A block's entries have one contiguous stretch of sources: its threads gather
 // them into LDS with coalesced list reads, all in flight at once, and each
 // thread adds its entry's from there.  (A thread walking its own list waits
@@ -445,7 +446,7 @@ __global__ void __launch_bounds__(GS_TPB) k_gal_sum(int64_t cnnz, const uint32_t
     if (q < cnnz) {
         a = gptr[q];
         b = gptr[q + 1];
-        if (COPY == GS_ENT || COPY == GS_VAL) pl = place[q];
+        if (COPY >= GS_ENT) pl = place[q];
         if (COPY == GS_ENT) of = off[q];
     }
     double s = 0.0;
@@ -471,6 +472,7 @@ __global__ void __launch_bounds__(GS_TPB) k_gal_sum(int64_t cnnz, const uint32_t
     cval[q] = s;
     if (COPY == GS_F32) cvalf[q] = f32_sat(s);
     if (COPY == GS_ENT) ent[pl] = make_int2((int)of, __float_as_int(f32_sat(s)));
+    if (COPY == GS_VALF) cvalf[pl] = f32_sat(s);
     if (COPY == GS_VAL) vval[pl] = s;
 }
 
@@ -1284,10 +1286,12 @@ rich_status galerkin_sum(const uint32_t *gptr, const uint32_t *gsrc, const doubl
     if (Lc.nnz == 0) return RICH_OK;
     const unsigned nb = xcd_grid(Lc.nnz, GS_TPB);
     const VLevel &V = Lc.V;
-    if (ordered && mixed)
+    if (ordered && mixed && !V.ent)
+        k_gal_sum<GS_VALF><<<nb, GS_TPB, 0, s>>>(Lc.nnz, gptr, gsrc, val, Lc.val, (float *)V.val, V.place, nullptr, nullptr, nullptr);
+    else if (ordered && mixed)
         k_gal_sum<GS_ENT><<<nb, GS_TPB, 0, s>>>(Lc.nnz, gptr, gsrc, val, Lc.val, nullptr, V.place, V.off, V.ent, nullptr);
     else if (ordered)
-        k_gal_sum<GS_VAL><<<nb, GS_TPB, 0, s>>>(Lc.nnz, gptr, gsrc, val, Lc.val, nullptr, V.place, nullptr, nullptr, V.val);
+        k_gal_sum<GS_VAL><<<nb, GS_TPB, 0, s>>>(Lc.nnz, gptr, gsrc, val, Lc.val, nullptr, V.place, nullptr, nullptr, (double *)V.val);
     else if (mixed)
         k_gal_sum<GS_F32><<<nb, GS_TPB, 0, s>>>(Lc.nnz, gptr, gsrc, val, Lc.val, Lc.valf, nullptr, nullptr, nullptr, nullptr);
     else

@@ -44,9 +44,8 @@ struct Entries;
 template <>
 struct Entries<float> {
     const int2 *e;
-    template <bool NT>
     __device__ __forceinline__ void pair(int64_t base, uint32_t i, uint32_t *c, float *v) const {
-        const i4_t t = load_as<i4_t, NT>(e + base, i * 8);
+        const i4_t t = load_as<i4_t, false>(e + base, i * 8);
         c[0] = t.x;
         v[0] = __int_as_float(t.y);
         c[1] = t.z;
@@ -57,10 +56,9 @@ template <>
 struct Entries<double> {
     const uint32_t *c_;
     const double *v_;
-    template <bool NT>
     __device__ __forceinline__ void pair(int64_t base, uint32_t i, uint32_t *c, double *v) const {
-        const i2_t t = load_as<i2_t, NT>(c_ + base, i * 4);
-        const d2_t u = load_as<d2_t, NT>(v_ + base, i * 8);
+        const i2_t t = load_as<i2_t, false>(c_ + base, i * 4);
+        const d2_t u = load_as<d2_t, false>(v_ + base, i * 8);
         c[0] = t.x;
         c[1] = t.y;
         v[0] = u.x;
@@ -68,13 +66,35 @@ struct Entries<double> {
     }
 };
 
+// Large levels: 16-bit places in the block's column list and values, read four
+// entries at a time.
+typedef float f4_t __attribute__((ext_vector_type(4)));
+typedef uint16_t u16x4_t __attribute__((ext_vector_type(4)));
+template <class T>
+struct Locals {
+    const uint16_t *i_;
+    const T *v_;
+    __device__ __forceinline__ void four(int64_t base, uint32_t i, u16x4_t *c, T *v) const {
+        *c = load_as<u16x4_t, true>(i_ + base, i * 2);
+        if constexpr (sizeof(T) == 4) {
+            *reinterpret_cast<f4_t *>(v) = load_as<f4_t, true>(v_ + base, i * 4);
+        } else {
+            *reinterpret_cast<d2_t *>(v) = load_as<d2_t, true>(v_ + base, i * 8);
+            *reinterpret_cast<d2_t *>(v + 2) = load_as<d2_t, true>(v_ + base, i * 8 + 16);
+        }
+    }
+};
+
 // One level's part of a cycle.  blk: first aggregate, row and entry of each
-// block (x, y, z), one more than there are blocks; lds_ent: products held.
+// block (x, y, z), one more than there are blocks, and (w) the columns it
+// lists; lds_ent: products held.
 template <class T>
 struct VArgs {
     const int4 *blk;
     const int32_t *ptr;  // row starts
     Entries<T> ent;
+    Locals<T> loc;
+    const uint32_t *list;  // byte offsets of a block's columns, from its first entry's index
     const T *b, *v;      // right-hand side; x0 (down) or xt (up)
     // down
     const int64_t *mptr;  // rows of each aggregate
@@ -88,8 +108,11 @@ struct VArgs {
     const int2 *child;  // the finer level's rows of each row,
     const T *x0f;       // their x0
     T *xtf;             // and their prolongated iterate
-    int lds_ent;
+    int lds_ent, lds_row;
 };
+
+// The split that lists its blocks' columns, at most V_SORT entries a block.
+constexpr int V_LOCAL = 4, V_SORT = 512 * V_LOCAL;
 
 // Sum of a row's products [ra, re) as G interleaved partial sums added
 // pairwise: by the G lanes of the row's group, or for G <= 2 by one lane.
@@ -115,23 +138,30 @@ __device__ __forceinline__ T row_sum(const T *prod, int ra, int re, int lane) {
     return group_sum<G>(s);
 }
 
-// UP = false: down.  A block's entries are taken 512 NP at a time, each wave a
-// run of 128 per step (two per lane).  These kernels are bound by their
-// instruction issue, not by memory: with 8-byte loads under a bounds check
-// each, 64-bit gather addresses and two lanes per row a level-1 sweep at 256^3
-// took about 600 instructions a wave (82 + 78 us; now 71 + 67); runs past a block's end are read
-// unmasked instead (the next block's entries, or the padding behind the
-// last) and their products not used.
+// UP = false: down.  These kernels are bound by how their loads are issued, not
+// by memory: with 8-byte loads under a bounds check each, 64-bit gather
+// addresses and two lanes per row a level-1 sweep at 256^3 took about 600
+// instructions a wave (82 + 78 us, then 71 + 67).  What was left was the
+// gather, one L1 access per entry (30 M a sweep, about one a cycle and CU).
+// NP = 4 (large levels): a block's distinct columns, about a third of its
+// entries, are listed at set-up and their values staged in LDS first; entries
+// are 16-bit places in that list and values (6 bytes in FP32, not 8).  Half the
+// L1 accesses; level 1 at 256^3 70 + 72 us, now 62 + 57 (51 us of bytes each).
+// NP <= 2: 256 NP pairs at a time, each wave a run of 128 entries per step,
+// gathered from memory: one dependent load less, which is what counts where the
+// blocks are few.
+// Runs past a block's end are read unmasked (the next block's entries, or the
+// padding behind the last) and their products not used.
 template <int NP, int G, class T, bool UP>
 __device__ __forceinline__ void vlevel_body(const VArgs<T> &a, T *__restrict__ prod, int blk) {
     constexpr int LPR = G <= 2 ? 1 : G;  // lanes per row
-    constexpr bool NT = NP > 2;          // large levels stream past the caches
+    constexpr bool LOC = NP == V_LOCAL;
     T *rr = prod + a.lds_ent;
     const int4 b0 = a.blk[blk], b1 = a.blk[blk + 1];
-    const int R0 = b0.y, R1 = b1.y, E0 = b0.z & ~1, E1 = b1.z;
+    const int R0 = b0.y, R1 = b1.y, E0 = b0.z & (LOC ? ~3 : ~1), E1 = b1.z;
     if (R0 >= R1) return;
     const int tid = threadIdx.x, lane = tid % LPR;
-    const int wrun = __builtin_amdgcn_readfirstlane(tid >> 6) * 128;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // what the row phase needs of its first row is loaded ahead of the products
     int row = R0 + tid / LPR;
     int ra = 0, re = 0;
@@ -149,28 +179,65 @@ __device__ __forceinline__ void vlevel_body(const VArgs<T> &a, T *__restrict__ p
             }
         }
     };
-    row_in();
-    for (int base = E0; base < E1; base += 512 * NP) {
-        uint32_t c[NP][2];
-        T v[NP][2], x[NP][2];
+    if constexpr (LOC) {
+        T *xs = rr + a.lds_row;
+        constexpr int QL = 4, QE = 512 * NP / 1024;
+        const int nu = b0.w;
+        const uint32_t *list = a.list + b0.z;
+        uint32_t o[QL];
 #pragma unroll
-        for (int q = 0; q < NP; q++) {
-            c[q][0] = c[q][1] = 0;
-            v[q][0] = v[q][1] = 0;
-            if (base + 512 * q + wrun < E1) a.ent.template pair<NT>(base + 512 * q, 2 * tid, c[q], v[q]);
+        for (int q = 0; q < QL; q++) o[q] = tid + 256 * q < nu ? list[tid + 256 * q] : 0u;
+        u16x4_t c[QE];
+        T v[QE][4];
+#pragma unroll
+        for (int q = 0; q < QE; q++) {
+            c[q] = (u16x4_t){0, 0, 0, 0};
+            if (E0 + 1024 * q + 256 * wave < E1) a.loc.four(E0 + 1024 * q, 4 * tid, &c[q], v[q]);
         }
 #pragma unroll
-        for (int q = 0; q < NP; q++) {
-            x[q][0] = load_as<T, false>(a.v, c[q][0]);
-            x[q][1] = load_as<T, false>(a.v, c[q][1]);
-        }
+        for (int q = 0; q < QL; q++)
+            if (tid + 256 * q < nu) xs[tid + 256 * q] = load_as<T, false>(a.v, o[q]);
+        for (int u = tid + 256 * QL; u < nu; u += 256) xs[u] = load_as<T, false>(a.v, list[u]);
+        row_in();
+        __syncthreads();
 #pragma unroll
-        for (int q = 0; q < NP; q++)
-            if (base + 512 * q + wrun < E1) {
-                typedef T t2 __attribute__((ext_vector_type(2)));
-                *reinterpret_cast<t2 *>(prod + (base - E0) + 512 * q + 2 * tid) =
-                    (t2){v[q][0] * x[q][0], v[q][1] * x[q][1]};
+        for (int q = 0; q < QE; q++)
+            if (E0 + 1024 * q + 256 * wave < E1) {
+                T *to = prod + 1024 * q + 4 * tid;
+                const T t0 = v[q][0] * xs[c[q].x], t1 = v[q][1] * xs[c[q].y];
+                const T t2 = v[q][2] * xs[c[q].z], t3 = v[q][3] * xs[c[q].w];
+                if constexpr (sizeof(T) == 4) {
+                    *reinterpret_cast<f4_t *>(to) = (f4_t){t0, t1, t2, t3};
+                } else {
+                    *reinterpret_cast<d2_t *>(to) = (d2_t){t0, t1};
+                    *reinterpret_cast<d2_t *>(to + 2) = (d2_t){t2, t3};
+                }
             }
+    } else {
+        const int wrun = wave * 128;
+        row_in();
+        for (int base = E0; base < E1; base += 512 * NP) {
+            uint32_t c[NP][2];
+            T v[NP][2], x[NP][2];
+#pragma unroll
+            for (int q = 0; q < NP; q++) {
+                c[q][0] = c[q][1] = 0;
+                v[q][0] = v[q][1] = 0;
+                if (base + 512 * q + wrun < E1) a.ent.pair(base + 512 * q, 2 * tid, c[q], v[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < NP; q++) {
+                x[q][0] = load_as<T, false>(a.v, c[q][0]);
+                x[q][1] = load_as<T, false>(a.v, c[q][1]);
+            }
+#pragma unroll
+            for (int q = 0; q < NP; q++)
+                if (base + 512 * q + wrun < E1) {
+                    typedef T t2 __attribute__((ext_vector_type(2)));
+                    *reinterpret_cast<t2 *>(prod + (base - E0) + 512 * q + 2 * tid) =
+                        (t2){v[q][0] * x[q][0], v[q][1] * x[q][1]};
+                }
+        }
     }
     __syncthreads();
     // every lane of a group runs the same number of row iterations (shuffles)
@@ -303,31 +370,92 @@ __global__ void k_v_narrow(int64_t n, const int64_t *__restrict__ in, int32_t *_
     if (i < n) out[i] = (int32_t)in[i];
 }
 
-// column offsets, and the place of every entry of the level's matrix
-template <bool F32>
-__global__ void k_v_columns(int64_t n, const int32_t *__restrict__ mem, const int64_t *__restrict__ rowptr,
-                            const int32_t *__restrict__ col, const int32_t *__restrict__ pos,
-                            const int32_t *__restrict__ ptr, int32_t *__restrict__ place, uint32_t *__restrict__ off,
-                            int2 *__restrict__ ent, uint32_t *__restrict__ vcol) {
+// column offsets (with ent: there and by entry; otherwise in vcol, in aggregate
+// order) and the place of every entry of the level's matrix
+__global__ void k_v_columns(int64_t n, uint32_t tsz, const int32_t *__restrict__ mem,
+                            const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col,
+                            const int32_t *__restrict__ pos, const int32_t *__restrict__ ptr,
+                            int32_t *__restrict__ place, uint32_t *__restrict__ off, int2 *__restrict__ ent,
+                            uint32_t *__restrict__ vcol) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
     const int32_t i = mem[p];
     int32_t o = ptr[p];
     for (int64_t e = rowptr[i]; e < rowptr[i + 1]; e++, o++) {
-        const int32_t c = pos[col[e]];
-        if (F32) ent[o].x = (int)(off[e] = (uint32_t)c * 4u);
-        else vcol[o] = (uint32_t)c * 8u;
+        const uint32_t c = (uint32_t)pos[col[e]] * tsz;
+        if (ent) ent[o].x = (int)(off[e] = c);
+        else vcol[o] = c;
         place[e] = o;
     }
 }
 
-template <bool F32>
+// Bitonic sort of N keys in LDS, ascending.
+template <int N>
+__device__ inline void sort_keys(unsigned long long *key) {
+    for (int k = 2; k <= N; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int t = threadIdx.x; t < N / 2; t += 256) {
+                const int lo = (t / j) * 2 * j + t % j, hi = lo + j;
+                const unsigned long long x = key[lo], y = key[hi];
+                if ((x > y) == ((lo & k) == 0)) {
+                    key[lo] = y;
+                    key[hi] = x;
+                }
+            }
+            __syncthreads();
+        }
+}
+
+// A block's column list: its entries' offsets (vcol, from the block's first
+// entry on) become the distinct ones, ascending, and idx the place of each
+// entry's in that list; their number goes to blk.w, the largest to most.
+static_assert(V_SORT == 2048, "11 bits of place, eight keys a thread");
+__global__ void __launch_bounds__(256) k_v_local(int4 *__restrict__ blk, uint32_t *__restrict__ vcol,
+                                                 uint16_t *__restrict__ idx, int *__restrict__ most) {
+    __shared__ unsigned long long key[V_SORT];
+    __shared__ int wsum[4];
+    const int E0 = blk[blockIdx.x].z, len = blk[blockIdx.x + 1].z - E0, tid = threadIdx.x;
+    for (int t = tid; t < V_SORT; t += 256)
+        key[t] = t < len ? ((unsigned long long)vcol[E0 + t] << 11) | (unsigned)t : ~0ull;
+    __syncthreads();
+    sort_keys<V_SORT>(key);
+    // a thread's eight keys: how many start a new column, and the ones before them
+    auto first = [&](int t) { return t < len && (t == 0 || (key[t] >> 11) != (key[t - 1] >> 11)); };
+    int mine = 0;
+    for (int u = 0; u < 8; u++) mine += first(8 * tid + u);
+    int incl = mine;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int up = __shfl_up(incl, o, 64);
+        if (tid % 64 >= o) incl += up;
+    }
+    if (tid % 64 == 63) wsum[tid / 64] = incl;
+    __syncthreads();
+    int rank = incl - mine, all = 0;
+    for (int w = 0; w < 4; w++) {
+        if (w < tid / 64) rank += wsum[w];
+        all += wsum[w];
+    }
+    for (int u = 0; u < 8; u++) {
+        const int t = 8 * tid + u;
+        if (t >= len) break;
+        if (first(t)) vcol[E0 + rank++] = (uint32_t)(key[t] >> 11);
+        idx[E0 + (int)(key[t] & 2047)] = (uint16_t)(rank - 1);
+    }
+    if (tid == 0) {
+        blk[blockIdx.x].w = all;
+        atomicMax(most, all);
+    }
+}
+
+// values at their places (ent: in the pairs)
+template <class T>
 __global__ void k_v_values(int64_t nnz, const double *__restrict__ val, const int32_t *__restrict__ place,
-                           int2 *__restrict__ ent, double *__restrict__ vval) {
+                           int2 *__restrict__ ent, T *__restrict__ vval) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= nnz) return;
-    if (F32) ent[place[e]].y = __float_as_int(f32_sat(val[e]));
-    else vval[place[e]] = val[e];
+    const T v = sizeof(T) == 4 ? (T)f32_sat(val[e]) : (T)val[e];
+    if (ent) ent[place[e]].y = __float_as_int((float)v);
+    else vval[place[e]] = v;
 }
 
 // block b: the aggregates whose first entry lies in [b chunk, (b+1) chunk);
@@ -351,10 +479,10 @@ __global__ void k_v_blocks(int64_t nc, int64_t nb, int64_t ngrid, int chunk, con
 }
 
 // the most entries and rows of a block
-__global__ void k_v_most(int64_t ngrid, const int4 *__restrict__ blk, int *__restrict__ most) {
+__global__ void k_v_most(int64_t ngrid, int align, const int4 *__restrict__ blk, int *__restrict__ most) {
     const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= ngrid) return;
-    atomicMax(most, blk[b + 1].z - (blk[b].z & ~1));
+    atomicMax(most, blk[b + 1].z - (blk[b].z & ~(align - 1)));
     atomicMax(most + 1, blk[b + 1].y - blk[b].y);
 }
 
@@ -410,18 +538,7 @@ __global__ void __launch_bounds__(256) k_v_sort(int64_t n1, const int64_t *__res
     for (int t = threadIdx.x; t < RESTRICT_LDS; t += 256)
         key[t] = t < len ? ((unsigned long long)(uint32_t)vmem[t0 + t] << 11) | (unsigned)t : ~0ull;
     __syncthreads();
-    for (int k = 2; k <= RESTRICT_LDS; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int t = threadIdx.x; t < RESTRICT_LDS / 2; t += 256) {
-                const int lo = (t / j) * 2 * j + t % j, hi = lo + j;
-                const unsigned long long x = key[lo], y = key[hi];
-                if ((x > y) == ((lo & k) == 0)) {
-                    key[lo] = y;
-                    key[hi] = x;
-                }
-            }
-            __syncthreads();
-        }
+    sort_keys<RESTRICT_LDS>(key);
     for (int t = threadIdx.x; t < len; t += 256) {
         vmem[t0 + t] = (int32_t)(key[t] >> 11);
         vslot[t0 + t] = (uint16_t)(key[t] & 2047);
@@ -434,8 +551,9 @@ __global__ void __launch_bounds__(256) k_v_sort(int64_t n1, const int64_t *__res
 // blocks share a CU at worst; levels with a larger aggregate keep the separate
 // kernels.
 constexpr size_t V_LDS_MAX = 60 << 10;
-// Entries read past the last block (whole 128-entry runs from an even index).
-constexpr int64_t V_PAD = 128;
+// Entries read past the last block (whole 128-entry runs from an even index;
+// 256-entry ones from a multiple of four).
+constexpr int64_t V_PAD = 256;
 
 rich_status vlevel_order(Level &Lv, int64_t nc, bool mixed, DevAlloc &mem, bool *ok, hipStream_t s) {
     *ok = false;
@@ -447,11 +565,11 @@ rich_status vlevel_order(Level &Lv, int64_t nc, bool mixed, DevAlloc &mem, bool 
     DevAlloc tmp;
     int64_t *len, *ptr, *stmp;
     int *most;
-    int hm[2] = {0, 0};
+    int hm[3] = {0, 0, 0};
     RICH_TRY(tmp.get(&len, Lv.n));
     RICH_TRY(tmp.get(&ptr, Lv.n + 1));
     RICH_TRY(tmp.get(&stmp, scan_tmp_size(Lv.n)));
-    RICH_TRY(tmp.get(&most, 2));
+    RICH_TRY(tmp.get(&most, 3));
     RICH_TRY(mem.get(&V.pos, Lv.n));
     RICH_TRY(mem.get(&V.ptr, Lv.n + 1));
     k_v_pos<<<nblocks(Lv.n), TPB, 0, s>>>(Lv.n, Lv.mem, Lv.rowptr, V.pos, len);
@@ -468,36 +586,47 @@ rich_status vlevel_order(Level &Lv, int64_t nc, bool mixed, DevAlloc &mem, bool 
     // eight blocks a CU, less on smaller levels, where the blocks are too few
     // and a block's latency counts.
     V.np = Lv.nnz >= (int64_t)2048 * 2048 ? 4 : Lv.nnz >= (int64_t)1024 * 2048 ? 2 : 1;
-    const int chunk = std::max(512 * V.np - hm[0] - 1, 256);
+    // Where a large level's blocks would not fit the column sort, two.
+    if (V.np == V_LOCAL && hm[0] + 3 > V_SORT - 256) V.np = 2;
+    const int align = V.np == V_LOCAL ? 4 : 2, run = V.np == V_LOCAL ? 256 : 128;
+    const int chunk = std::max(512 * V.np - hm[0] - align + 1, 256);
     const int64_t nb = (Lv.nnz + chunk - 1) / chunk, ngrid = xcd_grid(nb, 1);
     RICH_TRY(mem.get(&V.blk, ngrid + 1));
     k_v_blocks<<<nblocks(ngrid + 1), TPB, 0, s>>>(nc, nb, ngrid, chunk, Lv.mptr, V.ptr, V.blk);
-    RICH_TRY(launch_fill_i32(most, 0, 2, s));
-    k_v_most<<<nblocks(ngrid), TPB, 0, s>>>(ngrid, V.blk, most);
+    RICH_TRY(launch_fill_i32(most, 0, 3, s));
+    k_v_most<<<nblocks(ngrid), TPB, 0, s>>>(ngrid, align, V.blk, most);
     LAUNCH_CHECK();
-    HIP_TRY(hipMemcpyAsync(hm, most, sizeof(hm), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    V.nblk = (int)ngrid;
-    V.lds_ent = (hm[0] + 127) / 128 * 128;
-    V.lds = (unsigned)(((size_t)(V.lds_ent + hm[1]) * tsz + 15) & ~(size_t)15);
-    if (V.lds > V_LDS_MAX) return RICH_OK;
-    const int64_t mean = Lv.nnz / Lv.n;
-    V.g = mean < 8 ? 1 : mean < 16 ? 2 : mean < 32 ? 4 : 8;
     RICH_TRY(mem.get(&V.place, Lv.nnz));
-    if (mixed) {
+    const bool pairs = mixed && V.np != V_LOCAL;
+    if (pairs) {
         RICH_TRY(mem.get(&V.ent, Lv.nnz + V_PAD));
         RICH_TRY(launch_fill_i32((int32_t *)(V.ent + Lv.nnz), 0, 2 * V_PAD, s));
         RICH_TRY(mem.get(&V.off, Lv.nnz));
-        k_v_columns<true><<<nblocks(Lv.n), TPB, 0, s>>>(Lv.n, Lv.mem, Lv.rowptr, Lv.col, V.pos, V.ptr, V.place, V.off,
-                                                        V.ent, nullptr);
     } else {
         RICH_TRY(mem.get(&V.col, Lv.nnz + V_PAD));
-        RICH_TRY(mem.get(&V.val, Lv.nnz + V_PAD));
         RICH_TRY(launch_fill_i32((int32_t *)(V.col + Lv.nnz), 0, V_PAD, s));
-        RICH_TRY(launch_fill_f64(V.val + Lv.nnz, 0.0, V_PAD, s));
-        k_v_columns<false><<<nblocks(Lv.n), TPB, 0, s>>>(Lv.n, Lv.mem, Lv.rowptr, Lv.col, V.pos, V.ptr, V.place,
-                                                         nullptr, nullptr, V.col);
+        if (mixed) RICH_TRY(mem.get((float **)&V.val, Lv.nnz + V_PAD));
+        else RICH_TRY(mem.get((double **)&V.val, Lv.nnz + V_PAD));
+        RICH_TRY(launch_fill_i32((int32_t *)((char *)V.val + Lv.nnz * tsz), 0, V_PAD * (int64_t)(tsz / 4), s));
     }
+    k_v_columns<<<nblocks(Lv.n), TPB, 0, s>>>(Lv.n, (uint32_t)tsz, Lv.mem, Lv.rowptr, Lv.col, V.pos, V.ptr, V.place,
+                                              V.off, V.ent, V.col);
+    LAUNCH_CHECK();
+    if (V.np == V_LOCAL) {
+        RICH_TRY(mem.get(&V.idx, Lv.nnz + V_PAD));
+        RICH_TRY(launch_fill_i32((int32_t *)(V.idx + (Lv.nnz & ~(int64_t)1)), 0, V_PAD / 2, s));
+        k_v_local<<<(unsigned)ngrid, 256, 0, s>>>(V.blk, V.col, V.idx, most + 2);
+        LAUNCH_CHECK();
+    }
+    HIP_TRY(hipMemcpyAsync(hm, most, sizeof(hm), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    V.nblk = (int)ngrid;
+    V.lds_ent = (hm[0] + run - 1) / run * run;
+    V.lds_row = hm[1];
+    V.lds = (unsigned)(((size_t)(V.lds_ent + hm[1] + hm[2]) * tsz + 15) & ~(size_t)15);
+    if (V.lds > V_LDS_MAX) return RICH_OK;
+    const int64_t mean = Lv.nnz / Lv.n;
+    V.g = mean < 8 ? 1 : mean < 16 ? 2 : mean < 32 ? 4 : 8;
     LAUNCH_CHECK();
     if (mixed) RICH_TRY(mem.get((float **)&V.invd, Lv.n));
     else RICH_TRY(mem.get((double **)&V.invd, Lv.n));
@@ -533,17 +662,24 @@ rich_status vlevel_fine(Level &L0, const Level &L1, DevAlloc &mem, hipStream_t s
 
 rich_status vlevel_values(Level &Lv, bool mixed, hipStream_t s) {
     const VLevel &V = Lv.V;
-    if (mixed) k_v_values<true><<<nblocks(Lv.nnz), TPB, 0, s>>>(Lv.nnz, Lv.val, V.place, V.ent, nullptr);
-    else k_v_values<false><<<nblocks(Lv.nnz), TPB, 0, s>>>(Lv.nnz, Lv.val, V.place, nullptr, V.val);
+    if (mixed) k_v_values<float><<<nblocks(Lv.nnz), TPB, 0, s>>>(Lv.nnz, Lv.val, V.place, V.ent, (float *)V.val);
+    else k_v_values<double><<<nblocks(Lv.nnz), TPB, 0, s>>>(Lv.nnz, Lv.val, V.place, nullptr, (double *)V.val);
     LAUNCH_CHECK();
     return RICH_OK;
 }
 
 // --------------------------------------------------------------- launchers
-static void entries_of(const VLevel &V, Entries<float> *e) { e->e = V.ent; }
-static void entries_of(const VLevel &V, Entries<double> *e) {
-    e->c_ = V.col;
-    e->v_ = V.val;
+static void entries_of(const VLevel &V, VArgs<float> *a) { a->ent.e = V.ent; }
+static void entries_of(const VLevel &V, VArgs<double> *a) { a->ent = {V.col, (const double *)V.val}; }
+template <class T>
+static void set_level(const VLevel &V, VArgs<T> *a) {
+    a->blk = V.blk;
+    a->ptr = V.ptr;
+    entries_of(V, a);
+    a->loc = {V.idx, (const T *)V.val};
+    a->list = V.col;
+    a->lds_ent = V.lds_ent;
+    a->lds_row = V.lds_row;
 }
 
 template <class T>
@@ -551,9 +687,7 @@ static VArgs<T> down_args(const Level *L, int l, int nlev) {
     const Level &Lv = L[l], &Lc = L[l + 1];
     VArgs<T> a;
     memset(&a, 0, sizeof(a));
-    a.blk = Lv.V.blk;
-    a.ptr = Lv.V.ptr;
-    entries_of(Lv.V, &a.ent);
+    set_level(Lv.V, &a);
     a.b = (const T *)Lv.b;
     a.v = (const T *)Lv.x;
     a.mptr = Lv.mptr;
@@ -563,7 +697,6 @@ static VArgs<T> down_args(const Level *L, int l, int nlev) {
         a.invdc = (const T *)Lc.V.invd;
         a.x0c = (T *)Lc.x;
     }
-    a.lds_ent = Lv.V.lds_ent;
     return a;
 }
 
@@ -572,9 +705,7 @@ static VArgs<T> up_args(const Level *L, int l) {
     const Level &Lv = L[l];
     VArgs<T> a;
     memset(&a, 0, sizeof(a));
-    a.blk = Lv.V.blk;
-    a.ptr = Lv.V.ptr;
-    entries_of(Lv.V, &a.ent);
+    set_level(Lv.V, &a);
     a.b = (const T *)Lv.b;
     a.v = (const T *)Lv.r;
     a.invd = (const T *)Lv.V.invd;
@@ -586,7 +717,6 @@ static VArgs<T> up_args(const Level *L, int l) {
         a.x0f = (const T *)L[l - 1].x;
         a.xtf = (T *)L[l - 1].r;
     }
-    a.lds_ent = Lv.V.lds_ent;
     return a;
 }
 

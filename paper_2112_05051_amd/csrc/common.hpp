@@ -345,16 +345,18 @@ struct VLevel {
     int32_t *pos = nullptr;   // place of each row
     int32_t *ptr = nullptr;   // row starts in that order (n + 1)
     int32_t *place = nullptr; // place of each entry of the level's matrix
-    uint32_t *off = nullptr;  // FP32 cycle: byte offset of its column's value, by entry
-    int2 *ent = nullptr;      // FP32 cycle: (byte offset of the column's value, value bits)
-    uint32_t *col = nullptr;  // FP64 cycle: byte offsets, values
-    double *val = nullptr;
+    uint32_t *off = nullptr;  // FP32 cycle, np < 4: byte offset of its column's value, by entry,
+    int2 *ent = nullptr;      // and (that, value bits)
+    uint32_t *col = nullptr;  // otherwise: byte offsets (np = 4: of each block's distinct columns)
+    uint16_t *idx = nullptr;  // np = 4: places in the block's list
+    void *val = nullptr;      // and values, the cycle's precision
     void *invd = nullptr;     // l1 inverse diagonal, the cycle's precision
     int2 *child = nullptr;    // rows [x, y) of the finer level that each row stands for (also set on the coarsest)
     int4 *blk = nullptr;      // block table, nblk + 1
     int nblk = 0, np = 1;     // blocks, of about 512 np entries
     int g = 1;                // partial sums per row
-    int lds_ent = 0;          // entries of the largest block
+    int lds_ent = 0;          // entries and rows of the largest blocks
+    int lds_row = 0;
     unsigned lds = 0;         // LDS bytes of a launch
 };
 

@@ -562,7 +562,8 @@ __global__ void __launch_bounds__(FT_TPB) k_faces_tiled(Phys P, int kz, const do
 // ahead; the planes alternate between two LDS buffers, one barrier each; the
 // 64 ring cells (no corners) are one wave's work, each plane another wave's;
 // and divisions by the grid's constants go through their reciprocals.
-// Measured at 256^3: MARCHUS.
+// At 256^3 the residual takes 255-275 us (345 with a barrier for every stage and
+// full divisions), the assembly 590 (870; 450 us of bytes).
 constexpr int F_X = 16, F_Y = 16, F_TPB = F_X * F_Y;
 constexpr int F_RX = F_X + 2, F_RING = F_RX * (F_Y + 2);
 static_assert(2 * (F_X + F_Y) == 64, "the ring is one wave's");
