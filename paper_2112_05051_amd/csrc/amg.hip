@@ -40,14 +40,20 @@ __device__ inline double find_entry(const int64_t *__restrict__ rowptr, const in
     return 0.0;
 }
 
+// Eight lanes per row: a thread walking its row alone waits for one dependent
+// load after another (the weights of a set-up's 18 sweeps at 256^3 10.3 ms, now
+// 4.4).
+constexpr int ROW_LANES = 8;
 __global__ void k_diag(int64_t n, const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col,
                        const double *__restrict__ val, double *__restrict__ diag) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / ROW_LANES;
+    const int lane = threadIdx.x % ROW_LANES;
     double d = 0.0;
-    for (int64_t e = rowptr[i]; e < rowptr[i + 1]; e++)
-        if (col[e] == i) d = val[e];
-    diag[i] = d;
+    if (i < n)
+        for (int64_t e = rowptr[i] + lane; e < rowptr[i + 1]; e += ROW_LANES)
+            if (col[e] == i) d = val[e];
+    d = group_sum<ROW_LANES>(d);  // the other lanes hold zeros
+    if (i < n && lane == 0) diag[i] = d;
 }
 
 // The edge weights of a sweep, once: w[e] = 1 - 2 a_lo,hi / (d_lo + d_hi) for
@@ -58,9 +64,9 @@ __global__ void k_diag(int64_t n, const int64_t *__restrict__ rowptr, const int3
 __global__ void k_match_weights(int64_t n, const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col,
                                 const double *__restrict__ val, const double *__restrict__ diag,
                                 double *__restrict__ w) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / ROW_LANES;
     if (i >= n) return;
-    for (int64_t e = rowptr[i]; e < rowptr[i + 1]; e++) {
+    for (int64_t e = rowptr[i] + threadIdx.x % ROW_LANES; e < rowptr[i + 1]; e += ROW_LANES) {
         int32_t j = col[e];
         double we = __builtin_nan("");
         if (j != i) {
@@ -74,31 +80,43 @@ __global__ void k_match_weights(int64_t n, const int64_t *__restrict__ rowptr, c
 }
 
 // One matching round: every free row proposes its free neighbour of largest
-// weight (ties to the smaller (lo, hi) pair); -1 when there is none.
+// weight (ties to the smaller (lo, hi) pair); -1 when there is none.  Rows that
+// are no longer free leave their cand as it was: k_commit reads it only for free
+// rows.  Four entries' loads are in flight at a time (a set-up's 388 rounds at
+// 256^3 18.5 ms, now 10.1).
 __global__ void k_candidates(int64_t n, const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col,
                              const double *__restrict__ w, const int32_t *__restrict__ mate,
                              int32_t *__restrict__ cand) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    if (mate[i] != -1) {
-        cand[i] = -1;
-        return;
-    }
+    if (i >= n || mate[i] != -1) return;
     int32_t best = -1;
     double bw = 0.0;
     int64_t blo = 0, bhi = 0;
-    for (int64_t e = rowptr[i]; e < rowptr[i + 1]; e++) {
-        int32_t j = col[e];
-        if (j == i || mate[j] != -1) continue;
-        double we = w[e];
-        if (!isfinite(we)) continue;
-        int64_t lo = j < i ? j : i, hi = j < i ? i : j;
-        bool better = best < 0 || we > bw || (we == bw && (lo < blo || (lo == blo && hi < bhi)));
-        if (better) {
-            best = j;
-            bw = we;
-            blo = lo;
-            bhi = hi;
+    const int64_t e1 = rowptr[i + 1];
+    for (int64_t e0 = rowptr[i]; e0 < e1; e0 += 4) {
+        int32_t js[4], ms[4];
+        double ws[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            const int64_t e = e0 + u < e1 ? e0 + u : e1 - 1;
+            js[u] = col[e];
+            ws[u] = w[e];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; u++) ms[u] = mate[js[u]];
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            const int32_t j = js[u];
+            const double we = ws[u];
+            if (e0 + u >= e1 || j == i || ms[u] != -1 || !isfinite(we)) continue;
+            int64_t lo = j < i ? j : i, hi = j < i ? i : j;
+            bool better = best < 0 || we > bw || (we == bw && (lo < blo || (lo == blo && hi < bhi)));
+            if (better) {
+                best = j;
+                bw = we;
+                blo = lo;
+                bhi = hi;
+            }
         }
     }
     cand[i] = best;
@@ -252,27 +270,71 @@ __global__ void k_seg_len(int64_t nc, const int64_t *__restrict__ mptr, const in
     seg[I] = s;
 }
 
-__global__ void k_sym_collect(int64_t nc, const int64_t *__restrict__ mptr, const int32_t *__restrict__ mem,
-                              const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col,
-                              const int32_t *__restrict__ agg, const int64_t *__restrict__ segptr,
-                              int32_t *__restrict__ scratch, int64_t *__restrict__ cnt) {
-    int64_t I = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (I >= nc) return;
-    int32_t *buf = scratch + segptr[I];
-    int64_t len = 0;
-    for (int64_t t = mptr[I]; t < mptr[I + 1]; t++) {
-        int32_t i = mem[t];
-        for (int64_t e = rowptr[i]; e < rowptr[i + 1]; e++) {
-            // insert agg[col] into the sorted unique prefix buf[0..len)
-            int32_t J = agg[col[e]];
-            int64_t u = len;
-            while (u > 0 && buf[u - 1] > J) u--;
-            if (u > 0 && buf[u - 1] == J) continue;
-            for (int64_t v = len; v > u; v--) buf[v] = buf[v - 1];
-            buf[u] = J;
-            len++;
+// One thread per coarse row; up to SYM_REG columns are held in LDS (column-major
+// over the block's threads, as in k_gal_numeric), longer lists in the segment.
+// (Inserting in the segment itself: 23 products of a set-up at 256^3 20.8 ms,
+// now 5.0.)
+// f(e, i, j, J): entry e = (i, j) of a member row and its coarse column J, in
+// order; the loads of four entries are in flight at a time.
+template <class F>
+__device__ __forceinline__ void member_entries(int64_t m0, int64_t m1, const int32_t *__restrict__ mem,
+                                               const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col,
+                                               const int32_t *__restrict__ agg, F &&f) {
+    for (int64_t t = m0; t < m1; t++) {
+        const int32_t i = mem[t];
+        const int64_t e1 = rowptr[i + 1];
+        for (int64_t e0 = rowptr[i]; e0 < e1; e0 += 4) {
+            int32_t j[4], J[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) j[u] = col[e0 + u < e1 ? e0 + u : e1 - 1];
+#pragma unroll
+            for (int u = 0; u < 4; u++) J[u] = agg[j[u]];
+            f(e0, e1, i, j, J);
         }
     }
+}
+constexpr int SYM_REG = 32;
+__global__ void __launch_bounds__(64) k_sym_collect(int64_t nc, const int64_t *__restrict__ mptr,
+                                                    const int32_t *__restrict__ mem, const int64_t *__restrict__ rowptr,
+                                                    const int32_t *__restrict__ col, const int32_t *__restrict__ agg,
+                                                    const int64_t *__restrict__ segptr, int32_t *__restrict__ scratch,
+                                                    int64_t *__restrict__ cnt) {
+    __shared__ int32_t s_[SYM_REG * 64];
+    const int64_t I = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (I >= nc) return;
+    int32_t *buf = scratch + segptr[I], *reg = s_ + threadIdx.x;
+    int64_t len = 0;
+    bool spilled = false;
+    // insert J into the sorted unique prefix of a list with stride k
+    auto insert = [&](int32_t *b, int k, int32_t J) {
+        int64_t lo = 0, hi = len;
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) >> 1;
+            if (b[mid * k] < J) lo = mid + 1;
+            else hi = mid;
+        }
+        if (lo < len && b[lo * k] == J) return true;
+        if (b == reg && len == SYM_REG) return false;
+        for (int64_t v = len; v > lo; v--) b[v * k] = b[(v - 1) * k];
+        b[lo * k] = J;
+        len++;
+        return true;
+    };
+    member_entries(mptr[I], mptr[I + 1], mem, rowptr, col, agg,
+                   [&](int64_t e0, int64_t e1, int32_t, const int32_t *, const int32_t *J) {
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            if (e0 + u >= e1) continue;
+            if (!spilled && insert(reg, 64, J[u])) continue;
+            if (!spilled) {
+                for (int v = 0; v < SYM_REG; v++) buf[v] = reg[v * 64];
+                spilled = true;
+            }
+            insert(buf, 1, J[u]);
+        }
+    });
+    if (!spilled)
+        for (int64_t v = 0; v < len; v++) buf[v] = reg[v * 64];
     cnt[I] = len;
 }
 
@@ -309,19 +371,23 @@ __global__ void __launch_bounds__(64) k_gal_numeric(int64_t nc, const int64_t *_
             cj_s[e * 64 + t] = ccol[a + e];
             acc_s[e * 64 + t] = 0.0;
         }
-        for (int64_t q = mptr[I]; q < mptr[I + 1]; q++) {
-            int32_t i = mem[q];
-            for (int64_t e = rowptr[i]; e < rowptr[i + 1]; e++) {
-                int32_t J = agg[col[e]];
+        member_entries(mptr[I], mptr[I + 1], mem, rowptr, col, agg,
+                       [&](int64_t e0, int64_t e1, int32_t, const int32_t *, const int32_t *J) {
+            double v[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) v[u] = val[e0 + u < e1 ? e0 + u : e1 - 1];
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                if (e0 + u >= e1) continue;
                 int lo = 0, hi = len - 1;
                 while (lo < hi) {
                     int mid = (lo + hi) >> 1;
-                    if (cj_s[mid * 64 + t] < J) lo = mid + 1;
+                    if (cj_s[mid * 64 + t] < J[u]) lo = mid + 1;
                     else hi = mid;
                 }
-                acc_s[lo * 64 + t] += val[e];
+                acc_s[lo * 64 + t] += v[u];
             }
-        }
+        });
         for (int e = 0; e < len; e++) cval[a + e] = acc_s[e * 64 + t];
         return;
     }
@@ -398,20 +464,21 @@ __global__ void __launch_bounds__(64) k_gal_sources(int64_t nc, int64_t n, Stenc
         cj_s[q * 64 + t] = ccol[a + q];
         cur_s[q * 64 + t] = FILL ? gptr[a + q] : 0u;
     }
-    for (int64_t m = mptr[I]; m < mptr[I + 1]; m++) {
-        const int64_t i = mem[m];
-        for (int64_t e = rowptr[i]; e < rowptr[i + 1]; e++) {
-            const int32_t J = agg[col[e]];
+    member_entries(mptr[I], mptr[I + 1], mem, rowptr, col, agg,
+                   [&](int64_t e0, int64_t e1, int32_t i, const int32_t *j, const int32_t *J) {
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            if (e0 + u >= e1) continue;
             int lo = 0, hi = (int)len - 1;
             while (lo < hi) {
                 const int mid = (lo + hi) >> 1;
-                if (cj_s[mid * 64 + t] < J) lo = mid + 1;
+                if (cj_s[mid * 64 + t] < J[u]) lo = mid + 1;
                 else hi = mid;
             }
             const uint32_t at = cur_s[lo * 64 + t]++;
-            if (FILL) gsrc[at] = ix(n, i, col[e], e);
+            if (FILL) gsrc[at] = ix(n, i, j[u], e0 + u);
         }
-    }
+    });
     if (!FILL)
         for (int q = 0; q < len; q++) cnt[a + q] = cur_s[q * 64 + t];
 }
@@ -1110,10 +1177,10 @@ rich_status match_sweep_ws(int64_t n, const int64_t *rowptr, const int32_t *col,
         *nc_out = 0;
         return RICH_OK;
     }
-    k_diag<<<nblocks(n), TPB, 0, s>>>(n, rowptr, col, val, w.diag);
+    k_diag<<<nblocks(n * ROW_LANES), TPB, 0, s>>>(n, rowptr, col, val, w.diag);
     LAUNCH_CHECK();
     // the weights do not change between rounds: computed once
-    k_match_weights<<<nblocks(n), TPB, 0, s>>>(n, rowptr, col, val, w.diag, w.wts);
+    k_match_weights<<<nblocks(n * ROW_LANES), TPB, 0, s>>>(n, rowptr, col, val, w.diag, w.wts);
     LAUNCH_CHECK();
     RICH_TRY(launch_fill_i32(w.mate, -1, n, s));
     for (int64_t round = 0;; round++) {
