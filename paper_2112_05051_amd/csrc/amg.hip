@@ -872,15 +872,16 @@ __global__ void k_csr_to_dense(int64_t n, const int64_t *__restrict__ rowptr, co
 // itself in the K columns),  S_:K = D_:K (old), then
 //   D_ij <- R_{i-k0, j}                                  for i in K,
 //   D_ij <- [j not in K] D_ij - sum_t S_it R_tj          otherwise.
-// Two launches a step: a panel (S, R and the new rows K, one workgroup per
-// tile), then the update of all other tiles on the FP64 matrix cores; the block
+// Two launches a step: a panel (S and R), then the update (the rows K, and all
+// other tiles on the FP64 matrix cores); the block
 // of the next pivot tile inverts it right after updating it, beside the other
 // tiles' updates, so a pivot's 64 scalar steps are no launch of their own.
 // Bounds: the update moves 16 n^2 bytes a step (n = 3118: 156 MB, resident in
 // the last-level cache) and does 64 n^2 multiply-adds; on small n the pivot's
-// serial chain (32 pairs of scalar steps: LDS, barrier, two divisions).  Measured a
-// step: n = 3118 update 43 and panel 10 us (with the pivot and the panels as
-// launches of their own: 103 + 59 + 18 + 5), n = 517 25 and 9 us (19 + 54 + 16 + 5).  The order of
+// serial chain (32 pairs of scalar steps: LDS, barrier, two divisions; fours,
+// or single steps that hand the next row over early, take the same).  Measured a
+// step: n = 3118 update 44 and panel 7 us (with the pivot and the panels as
+// launches of their own: 103 + 59 + 18 + 5), n = 517 23 and 6 us (19 + 54 + 16 + 5).  The order of
 // operations is part of the contract: a restarted or repeated GMRES solve in
 // FP64 amplifies the last bits of the preconditioner, so sweeping only half of
 // the tiles (36 us, not the same bits) is not used.
@@ -995,70 +996,59 @@ __global__ void __launch_bounds__(256) k_bgj_pivot(const double *__restrict__ D,
     invert_pivot(A, rc, Pinv, bad);
 }
 
-// Panel of pivot block K, one workgroup per tile T: R_T = P^{-1} D_KT (terms
-// added in ascending t), which are also the new rows K of D, and S_T = the old
-// D_TK.  S (npad x 64) and R (64 x npad) are zero past n.
-__global__ void __launch_bounds__(256) k_bgj_panel(double *__restrict__ D, int64_t n, int64_t npad, int K,
+// Panel of pivot block K, four workgroups per tile T, 16 of its rows each:
+// R_T = P^{-1} D_KT (terms added in ascending t) and S_T = the old D_TK.  S
+// (npad x 64) and R (64 x npad) are zero past n.  R is also the new rows K of
+// D, which the update writes (here the other workgroups of T still read them).
+// Bound by latency: with one workgroup a tile n = 3118 10.7 us a step and
+// n = 517 9.4, now 6.9 and 5.5.
+__global__ void __launch_bounds__(256) k_bgj_panel(const double *__restrict__ D, int64_t n, int64_t npad, int K,
                                                    const double *__restrict__ Pinv, double *__restrict__ S,
                                                    double *__restrict__ R) {
     __shared__ double X[GJB][GJB + 1];  // D_KT [t][j]
-    __shared__ double Q[GJB][GJB + 1];  // Pinv transposed [t][r]
-    const int T = blockIdx.x, tid = threadIdx.x;
+    __shared__ double Q[GJB][17];       // rows r0.. of Pinv, transposed [t][r]
+    const int T = blockIdx.x / 4, r0 = 16 * (blockIdx.x % 4), tid = threadIdx.x;
     const int64_t t0 = (int64_t)T * GJB, k0 = (int64_t)K * GJB;
     // every load is issued before the first is stored in LDS
-    double pq[16], dq[16], sq[16];
+    double pq[4], dq[16], sq[4];
 #pragma unroll
     for (int q = 0; q < 16; q++) {
         const int t = tid + 256 * q, a = t / GJB, c = t % GJB;
-        pq[q] = Pinv[t];
         dq[q] = (k0 + a < n && t0 + c < n) ? D[(k0 + a) * n + t0 + c] : 0.0;
-        sq[q] = (t0 + a < n && k0 + c < n) ? D[(t0 + a) * n + k0 + c] : 0.0;
+        if (q < 4) {
+            pq[q] = Pinv[(r0 + a) * GJB + c];
+            sq[q] = (t0 + r0 + a < n && k0 + c < n) ? D[(t0 + r0 + a) * n + k0 + c] : 0.0;
+        }
     }
 #pragma unroll
     for (int q = 0; q < 16; q++) {
         const int t = tid + 256 * q, a = t / GJB, c = t % GJB;
-        Q[c][a] = pq[q];
         X[a][c] = dq[q];
-        // in the order of the update's A operands: column t of S at 16 (t % 4) + t / 4
-        S[(t0 + a) * GJB + 16 * (c & 3) + (c >> 2)] = sq[q];
+        if (q < 4) {
+            Q[c][a] = pq[q];
+            // in the order of the update's A operands: column t of S at 16 (t % 4) + t / 4
+            S[(t0 + r0 + a) * GJB + 16 * (c & 3) + (c >> 2)] = sq[q];
+        }
     }
     __syncthreads();
     const int ti = tid >> 4, tj = tid & 15;
-    double v[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; a++)
-#pragma unroll
-        for (int c = 0; c < 4; c++) v[a][c] = 0.0;
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
     if (T == K) {
 #pragma unroll
-        for (int a = 0; a < 4; a++)
-#pragma unroll
-            for (int c = 0; c < 4; c++) v[a][c] = Q[tj + 16 * c][ti + 16 * a];
+        for (int c = 0; c < 4; c++) v[c] = Q[tj + 16 * c][ti];
     } else {
-#pragma unroll 4
+#pragma unroll 8
         for (int t = 0; t < GJB; t++) {
-            double p[4], x[4];
+            const double p = Q[t][ti];
 #pragma unroll
-            for (int a = 0; a < 4; a++) p[a] = Q[t][ti + 16 * a];
-#pragma unroll
-            for (int c = 0; c < 4; c++) x[c] = X[t][tj + 16 * c];
-#pragma unroll
-            for (int a = 0; a < 4; a++)
-#pragma unroll
-                for (int c = 0; c < 4; c++) v[a][c] = fma(p[a], x[c], v[a][c]);
+            for (int c = 0; c < 4; c++) v[c] = fma(p, X[t][tj + 16 * c], v[c]);
         }
     }
 #pragma unroll
-    for (int a = 0; a < 4; a++)
-#pragma unroll
-        for (int c = 0; c < 4; c++) {
-            const int r = ti + 16 * a, j = tj + 16 * c;
-            R[r * npad + t0 + j] = v[a][c];
-            if (k0 + r < n && t0 + j < n) D[(k0 + r) * n + t0 + j] = v[a][c];
-        }
+    for (int c = 0; c < 4; c++) R[(r0 + ti) * npad + t0 + tj + 16 * c] = v[c];
 }
 
-// Update of the tiles (I, J), I other than K: D_IJ <- [J != K] D_IJ - S_I R_J.
+// Update: the rows K of D are R; the other tiles D_IJ <- [J != K] D_IJ - S_I R_J.
 // The four wavefronts of a block each own 16 rows of the tile and accumulate
 // four 16x16 blocks with v_mfma_f64_16x16x4f64 (lane l supplies A[l%16][l/16]
 // and B[l/16][l%16]; result register v of lane l is D[l/16 + 4v][l%16]).
@@ -1078,10 +1068,16 @@ __global__ void __launch_bounds__(256, 3) k_bgj_update(double *__restrict__ D, i
         const int b = (int)blockIdx.x - (last ? 0 : 1);
         I = b / tiles;
         J = b - I * tiles;
-        if (I >= K) I++;
         if (!last && I == K + 1 && J == K + 1) return;  // block 0's
     }
     const int64_t i0 = (int64_t)I * GJB, j0 = (int64_t)J * GJB;
+    if (I == K) {
+        for (int t = threadIdx.x; t < GJB * GJB; t += 256) {
+            const int64_t gi = i0 + t / GJB, gj = j0 + t % GJB;
+            if (gi < n && gj < n) D[gi * n + gj] = R[(t / GJB) * npad + gj];
+        }
+        return;
+    }
     const int tid = threadIdx.x, w = tid / 64, l = tid % 64, li = l % 16, lk = l / 16;
     // a wave's rows of S go straight into its A operands; R is shared through
     // LDS (35 KB: three blocks a CU); the tile's own entries are needed last
@@ -1444,10 +1440,9 @@ rich_status dense_inverse(const CsrDev &A, double *D, double *ws, hipStream_t s)
     k_csr_to_dense<<<nblocks(n), TPB, 0, s>>>(n, A.rowptr, A.col, A.val, D);
     k_bgj_pivot<<<1, 256, 0, s>>>(D, n, Pinv, bad);
     LAUNCH_CHECK();
-    const unsigned rest = (unsigned)((tiles - 1) * tiles);  // tiles off row K
     for (int K = 0; K < tiles; K++) {
-        k_bgj_panel<<<tiles, 256, 0, s>>>(D, n, npad, K, Pinv, S, R);
-        if (rest) k_bgj_update<<<rest + (K < tiles - 1 ? 1 : 0), 256, 0, s>>>(D, n, npad, K, tiles, S, R, Pinv, bad);
+        k_bgj_panel<<<4 * tiles, 256, 0, s>>>(D, n, npad, K, Pinv, S, R);
+        k_bgj_update<<<tiles * tiles + (K < tiles - 1 ? 1 : 0), 256, 0, s>>>(D, n, npad, K, tiles, S, R, Pinv, bad);
     }
     LAUNCH_CHECK();
     int hb = 0;
