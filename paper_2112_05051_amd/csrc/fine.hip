@@ -953,6 +953,28 @@ __global__ void k_st_post(Phys P, uint32_t n, const T *__restrict__ M4, const T 
     st_post_at(P, n, M4, invd, b, bsp, xt, x, xcd_block() * blockDim.x + threadIdx.x);
 }
 
+// Both in one pass: xt is formed at the cell and its neighbours from b, D^{-1}
+// and the gathered coarse correction (the same operations, so the same bits).
+template <class TB, class T, class G>
+__device__ __forceinline__ void st_correct_at(const G &P, uint32_t n, const T *__restrict__ M4,
+                                              const T *__restrict__ invd, const TB *__restrict__ b,
+                                              const double *__restrict__ bsp, const T *__restrict__ xc,
+                                              const int32_t *__restrict__ agg, T *__restrict__ x, uint32_t c) {
+    if (c >= n) return;
+    const TB bs = (TB)bsp[0];
+    Cell q = cell_of(P, c);
+    auto xt = [&](uint32_t t) -> T { return (T)(b[t] * bs) * invd[t] + xc[agg[t]]; };
+    T s = mstencil<T>(P, q, c, n, M4, xt);
+    x[c] = xt(c) + invd[c] * ((T)(b[c] * bs) - s);
+}
+
+template <class TB, class T>
+__global__ void k_st_correct(Phys P, uint32_t n, const T *__restrict__ M4, const T *__restrict__ invd,
+                             const TB *__restrict__ b, const double *__restrict__ bsp, const T *__restrict__ xc,
+                             const int32_t *__restrict__ agg, T *__restrict__ x) {
+    st_correct_at(P, n, M4, invd, b, bsp, xc, agg, x, xcd_block() * blockDim.x + threadIdx.x);
+}
+
 // 2.5-D versions of the fine-level V-cycle stencils.  A block of 64 x 8
 // threads owns a 64 x 8 column tile and walks a chunk of kz planes upward:
 // the stencil input u of the planes below and above stays in registers, the
@@ -1146,7 +1168,8 @@ __global__ void __launch_bounds__(T25X * T25Y) k_st25_batch(Batch<StArgs<TB, T>>
     });
 }
 
-// MODE 0: pre-smoothing + residual, 1: prolongation into xt, 2: post-smoothing from xt
+// MODE 0: pre-smoothing + residual, 1: prolongation into xt, 2: post-smoothing
+// from xt, 3: both
 template <class TB, class T, int MODE>
 __global__ void k_st1_batch(Batch<StArgs<TB, T>> B) {
     for_each_block(B, xcd_block(), [&](unsigned L) {
@@ -1156,6 +1179,7 @@ __global__ void k_st1_batch(Batch<StArgs<TB, T>> B) {
         if (MODE == 0) st_pre_at(a.g, a.n, a.M4, a.invd, a.b, a.bs, a.out, c);
         if (MODE == 1) st_prolong_at(a.n, a.invd, a.b, a.bs, a.xc, a.agg, a.xt, c);
         if (MODE == 2) st_post_at(a.g, a.n, a.M4, a.invd, a.b, a.bs, a.xt, a.out, c);
+        if (MODE == 3) st_correct_at(a.g, a.n, a.M4, a.invd, a.b, a.bs, a.xc, a.agg, a.out, c);
     });
 }
 
@@ -1179,6 +1203,12 @@ __global__ void k_spmv_J_batch(Batch<SpmvArgs<TX>> B) {
     });
 }
 
+// Up to this many cells the fine level is prolongated and post-smoothed by one
+// launch: us in mixed precision, one against the two kernels' sum without the gap
+// between them (about 1.5): 16^3 3.1 / 5.1, 40^3 3.3 / 5.2, 47 x 64^2 (193 k)
+// 4.8 / 5.8, 47 x 100^2 (470 k) 8.5 / 7.3, 40 x 200^2 19.3 / 16.4; FP64 193 k
+// 5.7 / 6.8, 470 k 10.8 / 10.6.
+constexpr uint32_t CORRECT_MAX = 1u << 18;
 // The 64-wide tile needs rows of at least about that length to keep its lanes busy.
 inline bool use25(const Phys &P) { return P.nx >= 48 && P.ny >= T25Y && P.nz >= 4; }
 // Planes per block, at most `most`: the chunks that cost the fewest planes in a row.
@@ -1484,6 +1514,8 @@ rich_status launch_st_post(const Phys &P, const T *M4, const T *invd, const TB *
     if (use25(P)) {
         int kz = kz25_of<TB, T, ST25_POST>(P);
         k_st25<TB, T, ST25_POST><<<grid25(P, kz), dim3(T25X, T25Y), 0, s>>>(P, M4, invd, b, bs, xc, agg, x, kz);
+    } else if (n <= CORRECT_MAX) {
+        k_st_correct<TB, T><<<nblocks(n), TPB, 0, s>>>(P, n, M4, invd, b, bs, xc, agg, x);
     } else {
         k_st_prolong<TB, T><<<nblocks(n), TPB, 0, s>>>(n, invd, b, bs, xc, agg, xt);
         LAUNCH_CHECK();
@@ -1606,9 +1638,25 @@ rich_status launch_st_post_batch(const std::vector<FineItem<TB, T>> &v, hipStrea
     RICH_TRY(launch_batches(a25, b25, [&](const B &bt, unsigned g) {
         k_st25_batch<TB, T, ST25_POST><<<g, dim3(T25X, T25Y), 0, s>>>(bt);
     }, q));
-    RICH_TRY(launch_batches(a1, b1, [&](const B &bt, unsigned g) { k_st1_batch<TB, T, 1><<<g, TPB, 0, s>>>(bt); },
-                            q));
-    return launch_batches(a1, b1, [&](const B &bt, unsigned g) { k_st1_batch<TB, T, 2><<<g, TPB, 0, s>>>(bt); }, q);
+    std::vector<StArgs<TB, T>> a2;
+    std::vector<unsigned> b2;
+    for (size_t i = 0; i < a1.size(); i++)
+        if (a1[i].n > CORRECT_MAX) {
+            a2.push_back(a1[i]);
+            b2.push_back(b1[i]);
+        }
+    if (!a2.empty()) {
+        RICH_TRY(launch_batches(a2, b2, [&](const B &bt, unsigned g) { k_st1_batch<TB, T, 1><<<g, TPB, 0, s>>>(bt); },
+                                q));
+        RICH_TRY(launch_batches(a2, b2, [&](const B &bt, unsigned g) { k_st1_batch<TB, T, 2><<<g, TPB, 0, s>>>(bt); },
+                                q));
+        for (size_t i = a1.size(); i-- > 0;)
+            if (a1[i].n > CORRECT_MAX) {
+                a1.erase(a1.begin() + i);
+                b1.erase(b1.begin() + i);
+            }
+    }
+    return launch_batches(a1, b1, [&](const B &bt, unsigned g) { k_st1_batch<TB, T, 3><<<g, TPB, 0, s>>>(bt); }, q);
 }
 
 template <class TX>
