@@ -792,6 +792,7 @@ __device__ __forceinline__ void restrict_block(int64_t nc, const int64_t *__rest
     // its index one at a time would serialise eight round trips to memory);
     // a slot past the stretch reads member t0 and is not stored
     const int64_t a = I < nc ? mptr[I] : 0, e = I < nc ? mptr[I + 1] : 0;
+    const T dI = x0c && I < nc ? invdc[I] : (T)0;  // ahead of the gather
     if (staged && t1 > t0) {
         constexpr int PER = RESTRICT_LDS / RESTRICT_TPB;
         int32_t m[PER];
@@ -824,7 +825,7 @@ __device__ __forceinline__ void restrict_block(int64_t nc, const int64_t *__rest
     else
         for (int64_t t = a; t < e; t++) s += r[mem[t]];
     bc[I] = s;
-    if (x0c) x0c[I] = s * invdc[I];
+    if (x0c) x0c[I] = s * dI;
 }
 
 template <class T>

@@ -162,7 +162,17 @@ __device__ __forceinline__ void vlevel_body(const VArgs<T> &a, T *__restrict__ p
     if (R0 >= R1) return;
     const int tid = threadIdx.x, lane = tid % LPR;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // what the row phase needs of its first row is loaded ahead of the products
+    // what the row phase needs of its first row, and (up) what the last phase needs
+    // of its first rows, eight lanes each, is loaded ahead of the products: on
+    // small levels each of these loads is a step in the chain that a launch
+    // consists of (up at 64^3 3.92, now 3.84 us; down, the same for its aggregates
+    // takes longer, 4.23 for 4.08: more loads before the entries')
+    int2 ch = make_int2(0, 0);
+    T pc = 0;
+    if (UP && a.child && R0 + tid / 8 < R1) ch = a.child[R0 + tid / 8];
+    auto last_in = [&]() {
+        if (UP && ch.x + tid % 8 < ch.y) pc = a.x0f[ch.x + tid % 8];
+    };
     int row = R0 + tid / LPR;
     int ra = 0, re = 0;
     int32_t pm = 0;
@@ -199,6 +209,7 @@ __device__ __forceinline__ void vlevel_body(const VArgs<T> &a, T *__restrict__ p
             if (tid + 256 * q < nu) xs[tid + 256 * q] = load_as<T, false>(a.v, o[q]);
         for (int u = tid + 256 * QL; u < nu; u += 256) xs[u] = load_as<T, false>(a.v, list[u]);
         row_in();
+        last_in();
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < QE; q++)
@@ -230,6 +241,7 @@ __device__ __forceinline__ void vlevel_body(const VArgs<T> &a, T *__restrict__ p
                 x[q][0] = load_as<T, false>(a.v, c[q][0]);
                 x[q][1] = load_as<T, false>(a.v, c[q][1]);
             }
+            if (base == E0) last_in();
 #pragma unroll
             for (int q = 0; q < NP; q++)
                 if (base + 512 * q + wrun < E1) {
@@ -258,9 +270,13 @@ __device__ __forceinline__ void vlevel_body(const VArgs<T> &a, T *__restrict__ p
     if (UP) {
         // eight lanes per row for its run on the finer level
         for (int r = R0 + tid / 8; r < R1; r += 32) {
-            const int2 ch = a.child[r];
+            if (r >= R0 + 32) {
+                ch = a.child[r];
+                if (ch.x + tid % 8 < ch.y) pc = a.x0f[ch.x + tid % 8];
+            }
             const T xr = rr[r - R0];
-            for (int t = ch.x + tid % 8; t < ch.y; t += 8) a.xtf[t] = a.x0f[t] + xr;
+            if (ch.x + tid % 8 < ch.y) a.xtf[ch.x + tid % 8] = pc + xr;
+            for (int t = ch.x + tid % 8 + 8; t < ch.y; t += 8) a.xtf[t] = a.x0f[t] + xr;
         }
         return;
     }
@@ -308,7 +324,11 @@ __device__ __forceinline__ void gemv_body(const GemvArgs<TB, T> &g, int64_t blk)
     const int lane = threadIdx.x % 64;
     if (row >= n) return;
     int2 c = make_int2(0, 0);
-    if (g.child) c = g.child[row];
+    T x0 = 0;
+    if (g.child) {
+        c = g.child[row];
+        if (c.x + lane < c.y) x0 = g.x0f[c.x + lane];
+    }
     // four independent partial sums per lane keep four row segments in flight
     const T *__restrict__ a = g.Ainv + row * n;
     const TB *__restrict__ b = g.b;
@@ -326,7 +346,8 @@ __device__ __forceinline__ void gemv_body(const GemvArgs<TB, T> &g, int64_t blk)
     for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
     if (g.child) {
         s = __shfl(s, 0, 64);
-        for (int t = c.x + lane; t < c.y; t += 64) g.xtf[t] = g.x0f[t] + s;
+        if (c.x + lane < c.y) g.xtf[c.x + lane] = x0 + s;
+        for (int t = c.x + lane + 64; t < c.y; t += 64) g.xtf[t] = g.x0f[t] + s;
     } else if (lane == 0) {
         g.x[row] = s;
     }
