@@ -573,7 +573,12 @@ static_assert(2 * (F_X + F_Y) == 64, "the ring is one wave's");
 // quotient as the division instruction sequence does, short of subnormals.
 struct Recip {
     double b, y;
-    __device__ explicit Recip(double v) : b(v), y(1.0 / v) {}
+    // (the same in every lane: kept in scalar registers)
+    __device__ explicit Recip(double v) : b(uniform(v)), y(uniform(1.0 / v)) {}
+    static __device__ double uniform(double v) {
+        return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                                __builtin_amdgcn_readfirstlane(__double2loint(v)));
+    }
     __device__ __forceinline__ double div(double a) const {
         const double q0 = a * y;
         const double q1 = fma(fma(-q0, b, a), y, q0);
