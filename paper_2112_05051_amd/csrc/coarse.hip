@@ -429,7 +429,7 @@ __device__ inline void sort_keys(unsigned long long *key) {
 
 // A block's column list: its entries' offsets (vcol, from the block's first
 // entry on) become the distinct ones, ascending, and idx the place of each
-// entry's in that list; their number goes to blk.w, the largest to most.
+// entry's in that list; their number goes to blk.w, the largest and the sum to most.
 static_assert(V_SORT == 2048, "11 bits of place, eight keys a thread");
 __global__ void __launch_bounds__(256) k_v_local(int4 *__restrict__ blk, uint32_t *__restrict__ vcol,
                                                  uint16_t *__restrict__ idx, int *__restrict__ most) {
@@ -465,6 +465,7 @@ __global__ void __launch_bounds__(256) k_v_local(int4 *__restrict__ blk, uint32_
     if (tid == 0) {
         blk[blockIdx.x].w = all;
         atomicMax(most, all);
+        atomicAdd(most + 1, all);
     }
 }
 
@@ -586,11 +587,11 @@ rich_status vlevel_order(Level &Lv, int64_t nc, bool mixed, DevAlloc &mem, bool 
     DevAlloc tmp;
     int64_t *len, *ptr, *stmp;
     int *most;
-    int hm[3] = {0, 0, 0};
+    int hm[4] = {0, 0, 0, 0};
     RICH_TRY(tmp.get(&len, Lv.n));
     RICH_TRY(tmp.get(&ptr, Lv.n + 1));
     RICH_TRY(tmp.get(&stmp, scan_tmp_size(Lv.n)));
-    RICH_TRY(tmp.get(&most, 3));
+    RICH_TRY(tmp.get(&most, 4));
     RICH_TRY(mem.get(&V.pos, Lv.n));
     RICH_TRY(mem.get(&V.ptr, Lv.n + 1));
     k_v_pos<<<nblocks(Lv.n), TPB, 0, s>>>(Lv.n, Lv.mem, Lv.rowptr, V.pos, len);
@@ -614,7 +615,7 @@ rich_status vlevel_order(Level &Lv, int64_t nc, bool mixed, DevAlloc &mem, bool 
     const int64_t nb = (Lv.nnz + chunk - 1) / chunk, ngrid = xcd_grid(nb, 1);
     RICH_TRY(mem.get(&V.blk, ngrid + 1));
     k_v_blocks<<<nblocks(ngrid + 1), TPB, 0, s>>>(nc, nb, ngrid, chunk, Lv.mptr, V.ptr, V.blk);
-    RICH_TRY(launch_fill_i32(most, 0, 3, s));
+    RICH_TRY(launch_fill_i32(most, 0, 4, s));
     k_v_most<<<nblocks(ngrid), TPB, 0, s>>>(ngrid, align, V.blk, most);
     LAUNCH_CHECK();
     RICH_TRY(mem.get(&V.place, Lv.nnz));
@@ -644,6 +645,7 @@ rich_status vlevel_order(Level &Lv, int64_t nc, bool mixed, DevAlloc &mem, bool 
     V.nblk = (int)ngrid;
     V.lds_ent = (hm[0] + run - 1) / run * run;
     V.lds_row = hm[1];
+    V.nlist = hm[3];
     V.lds = (unsigned)(((size_t)(V.lds_ent + hm[1] + hm[2]) * tsz + 15) & ~(size_t)15);
     if (V.lds > V_LDS_MAX) return RICH_OK;
     const int64_t mean = Lv.nnz / Lv.n;

@@ -225,10 +225,10 @@ rich_status launch_stencil_rowcounts(const Phys &P, int64_t *rowptr_plus1, hipSt
 template <class TB, class T>
 rich_status launch_st_pre(const Phys &P, const T *M4, const T *invd, const TB *b, const double *bs, T *r,
                           hipStream_t s);
-// xt (scratch, N) receives the prolongated iterate before post-smoothing
-template <class TB, class T>
+// xt (scratch, N) may receive the prolongated iterate before post-smoothing
+template <class TB, class T, class TX>
 rich_status launch_st_post(const Phys &P, const T *M4, const T *invd, const TB *b, const double *bs, const T *xc,
-                           const int32_t *agg, T *x, T *xt, hipStream_t s);
+                           const int32_t *agg, TX *x, T *xt, hipStream_t s);
 // Multicolour Gauss-Seidel fine level: x0 = one backward sweep from zero on
 // M x = bs b, r = bs b - M x0; post: xt = x0 + P xc (when agg is set; else xt
 // already holds the prolongated iterate), one forward sweep from xt into x
@@ -355,9 +355,12 @@ struct VLevel {
     int4 *blk = nullptr;      // block table, nblk + 1
     int nblk = 0, np = 1;     // blocks, of about 512 np entries
     int g = 1;                // partial sums per row
+    int nlist = 0;            // np = 4: columns of all lists
     int lds_ent = 0;          // entries and rows of the largest blocks
     int lds_row = 0;
     unsigned lds = 0;         // LDS bytes of a launch
+    // bytes of a sweep's entries (t: of a value)
+    double entry_bytes(int64_t nnz, double t) const { return (double)nnz * ((idx ? 2 : 4) + t) + 4.0 * nlist; }
 };
 
 struct Level {

@@ -940,43 +940,46 @@ __global__ void k_st_prolong(uint32_t n, const T *__restrict__ invd, const TB *_
 }
 
 // V-cycle, fine level, post-smoothing: x = xt + D^{-1}(b - M xt).
-template <class TB, class T, class G>
+// TX: the result's type (the applied preconditioner stores doubles).
+template <class TB, class T, class TX, class G>
 __device__ __forceinline__ void st_post_at(const G &P, uint32_t n, const T *__restrict__ M4,
                                            const T *__restrict__ invd, const TB *__restrict__ b,
                                            const double *__restrict__ bsp, const T *__restrict__ xt,
-                                           T *__restrict__ x, uint32_t c) {
+                                           TX *__restrict__ x, uint32_t c) {
     if (c >= n) return;
     Cell q = cell_of(P, c);
     T s = mstencil<T>(P, q, c, n, M4, [&](uint32_t t) { return xt[t]; });
-    x[c] = xt[c] + invd[c] * ((T)(b[c] * (TB)bsp[0]) - s);
+    const T v = xt[c] + invd[c] * ((T)(b[c] * (TB)bsp[0]) - s);
+    x[c] = v;
 }
 
-template <class TB, class T>
+template <class TB, class T, class TX>
 __global__ void k_st_post(Phys P, uint32_t n, const T *__restrict__ M4, const T *__restrict__ invd,
                           const TB *__restrict__ b, const double *__restrict__ bsp, const T *__restrict__ xt,
-                          T *__restrict__ x) {
+                          TX *__restrict__ x) {
     st_post_at(P, n, M4, invd, b, bsp, xt, x, xcd_block() * blockDim.x + threadIdx.x);
 }
 
 // Both in one pass: xt is formed at the cell and its neighbours from b, D^{-1}
 // and the gathered coarse correction (the same operations, so the same bits).
-template <class TB, class T, class G>
+template <class TB, class T, class TX, class G>
 __device__ __forceinline__ void st_correct_at(const G &P, uint32_t n, const T *__restrict__ M4,
                                               const T *__restrict__ invd, const TB *__restrict__ b,
                                               const double *__restrict__ bsp, const T *__restrict__ xc,
-                                              const int32_t *__restrict__ agg, T *__restrict__ x, uint32_t c) {
+                                              const int32_t *__restrict__ agg, TX *__restrict__ x, uint32_t c) {
     if (c >= n) return;
     const TB bs = (TB)bsp[0];
     Cell q = cell_of(P, c);
     auto xt = [&](uint32_t t) -> T { return (T)(b[t] * bs) * invd[t] + xc[agg[t]]; };
     T s = mstencil<T>(P, q, c, n, M4, xt);
-    x[c] = xt(c) + invd[c] * ((T)(b[c] * bs) - s);
+    const T v = xt(c) + invd[c] * ((T)(b[c] * bs) - s);
+    x[c] = v;
 }
 
-template <class TB, class T>
+template <class TB, class T, class TX>
 __global__ void k_st_correct(Phys P, uint32_t n, const T *__restrict__ M4, const T *__restrict__ invd,
                              const TB *__restrict__ b, const double *__restrict__ bsp, const T *__restrict__ xc,
-                             const int32_t *__restrict__ agg, T *__restrict__ x) {
+                             const int32_t *__restrict__ agg, TX *__restrict__ x) {
     st_correct_at(P, n, M4, invd, b, bsp, xc, agg, x, xcd_block() * blockDim.x + threadIdx.x);
 }
 
@@ -1008,11 +1011,11 @@ struct St25In {
 };
 
 // L: the tile (virtual block) this block computes.
-template <class TB, class T, int MODE, class G>
+template <class TB, class T, int MODE, class TX, class G>
 __device__ __forceinline__ void st25_body(const G &P, const T *__restrict__ M4, const T *__restrict__ invd,
                                           const TB *__restrict__ b, const double *__restrict__ bsp,
                                           const T *__restrict__ xc, const int32_t *__restrict__ agg,
-                                          T *__restrict__ out, int kz, unsigned L) {
+                                          TX *__restrict__ out, int kz, unsigned L) {
     constexpr bool POST = MODE != ST25_PRE;
     __shared__ T us[2][T25Y + 2][T25X + 2];
     __shared__ T xps[2][T25Y][T25X + 1];
@@ -1124,7 +1127,8 @@ __device__ __forceinline__ void st25_body(const G &P, const T *__restrict__ M4, 
             if (k < nz - 1) s += m_zp * u_nxt;
             const T bc = MODE == ST25_XT ? b_of(c) : bval(c0);
             const T dc = MODE == ST25_XT ? invd[c] : c0.d;
-            out[c] = POST ? u_cur + dc * (bc - s) : bc - s;
+            const T o = POST ? u_cur + dc * (bc - s) : bc - s;
+            out[c] = o;
         }
         // rotate (the other LDS buffer is written next: no second barrier)
         u_prev = u_cur;
@@ -1142,12 +1146,12 @@ __device__ __forceinline__ void st25_body(const G &P, const T *__restrict__ M4, 
     }
 }
 
-template <class TB, class T, int MODE>
+template <class TB, class T, int MODE, class TX = T>
 __global__ void __launch_bounds__(T25X * T25Y) k_st25(Phys P, const T *__restrict__ M4, const T *__restrict__ invd,
                                                      const TB *__restrict__ b, const double *__restrict__ bsp,
                                                      const T *__restrict__ xc, const int32_t *__restrict__ agg,
-                                                     T *__restrict__ out, int kz) {
-    st25_body<TB, T, MODE>(P, M4, invd, b, bsp, xc, agg, out, kz, xcd_block());
+                                                     TX *__restrict__ out, int kz) {
+    st25_body<TB, T, MODE, TX>(P, M4, invd, b, bsp, xc, agg, out, kz, xcd_block());
 }
 
 // Batched forms: one launch over the fine levels of several simulations.
@@ -1169,7 +1173,7 @@ __global__ void __launch_bounds__(T25X * T25Y) k_st25_batch(Batch<StArgs<TB, T>>
     for_each_block(B, xcd_block(), [&](unsigned L) {
         const int e = batch_entry(B, L);
         const StArgs<TB, T> &a = B.a[e];
-        st25_body<TB, T, MODE>(a.g, a.M4, a.invd, a.b, a.bs, a.xc, a.agg, a.out, a.kz, L - B.begin[e]);
+        st25_body<TB, T, MODE, T>(a.g, a.M4, a.invd, a.b, a.bs, a.xc, a.agg, a.out, a.kz, L - B.begin[e]);
     });
 }
 
@@ -1512,19 +1516,19 @@ rich_status launch_st_pre(const Phys &P, const T *M4, const T *invd, const TB *b
     return RICH_OK;
 }
 
-template <class TB, class T>
+template <class TB, class T, class TX>
 rich_status launch_st_post(const Phys &P, const T *M4, const T *invd, const TB *b, const double *bs, const T *xc,
-                           const int32_t *agg, T *x, T *xt, hipStream_t s) {
+                           const int32_t *agg, TX *x, T *xt, hipStream_t s) {
     uint32_t n = ncells(P);
     if (use25(P)) {
         int kz = kz25_of<TB, T, ST25_POST>(P);
-        k_st25<TB, T, ST25_POST><<<grid25(P, kz), dim3(T25X, T25Y), 0, s>>>(P, M4, invd, b, bs, xc, agg, x, kz);
+        k_st25<TB, T, ST25_POST, TX><<<grid25(P, kz), dim3(T25X, T25Y), 0, s>>>(P, M4, invd, b, bs, xc, agg, x, kz);
     } else if (n <= CORRECT_MAX) {
-        k_st_correct<TB, T><<<nblocks(n), TPB, 0, s>>>(P, n, M4, invd, b, bs, xc, agg, x);
+        k_st_correct<TB, T, TX><<<nblocks(n), TPB, 0, s>>>(P, n, M4, invd, b, bs, xc, agg, x);
     } else {
         k_st_prolong<TB, T><<<nblocks(n), TPB, 0, s>>>(n, invd, b, bs, xc, agg, xt);
         LAUNCH_CHECK();
-        k_st_post<TB, T><<<nblocks(n), TPB, 0, s>>>(P, n, M4, invd, b, bs, xt, x);
+        k_st_post<TB, T, TX><<<nblocks(n), TPB, 0, s>>>(P, n, M4, invd, b, bs, xt, x);
     }
     LAUNCH_CHECK();
     return RICH_OK;
@@ -1538,7 +1542,7 @@ rich_status launch_st_post_from(const Phys &P, const T *M4, const T *invd, const
         int kz = kz25_of<TB, T, ST25_XT>(P);
         k_st25<TB, T, ST25_XT><<<grid25(P, kz), dim3(T25X, T25Y), 0, s>>>(P, M4, invd, b, bs, xt, nullptr, x, kz);
     } else {
-        k_st_post<TB, T><<<nblocks(n), TPB, 0, s>>>(P, n, M4, invd, b, bs, xt, x);
+        k_st_post<TB, T, T><<<nblocks(n), TPB, 0, s>>>(P, n, M4, invd, b, bs, xt, x);
     }
     LAUNCH_CHECK();
     return RICH_OK;
@@ -1683,8 +1687,8 @@ template rich_status launch_spmv_J_batch<float>(const std::vector<SpmvItem<float
 #define INST_ST(TB, T)                                                                                    \
     template rich_status launch_st_pre<TB, T>(const Phys &, const T *, const T *, const TB *, const double *, T *, \
                                               hipStream_t);                                                     \
-    template rich_status launch_st_post<TB, T>(const Phys &, const T *, const T *, const TB *, const double *,   \
-                                               const T *, const int32_t *, T *, T *, hipStream_t);              \
+    template rich_status launch_st_post<TB, T, T>(const Phys &, const T *, const T *, const TB *, const double *, \
+                                                  const T *, const int32_t *, T *, T *, hipStream_t);            \
     template rich_status launch_st_post_from<TB, T>(const Phys &, const T *, const T *, const TB *,              \
                                                     const double *, const T *, T *, hipStream_t);               \
     template rich_status launch_st_sweeps<TB, T>(const Phys &, const T *, const T *, const TB *, T *, T *, int, \
@@ -1699,6 +1703,9 @@ template rich_status launch_spmv_J_batch<float>(const std::vector<SpmvItem<float
 INST_ST(double, double)
 INST_ST(double, float)
 INST_ST(float, float)
+template rich_status launch_st_post<double, float, double>(const Phys &, const float *, const float *, const double *,
+                                                           const double *, const float *, const int32_t *, double *,
+                                                           float *, hipStream_t);
 
 rich_status launch_stencil_rowcounts(const Phys &P, int64_t *cnt, hipStream_t s) {
     uint32_t n = ncells(P);
