@@ -1365,7 +1365,7 @@ rich_status galerkin_sum(const uint32_t *gptr, const uint32_t *gsrc, const doubl
 }
 
 rich_status galerkin(const CsrDev &A, const int32_t *agg, int64_t nc, CsrDev *C, DevAlloc &mem_out,
-                     hipStream_t s) {
+                     hipStream_t s, bool values) {
     DevAlloc tmp;
     int64_t *mptr;
     int32_t *mem;
@@ -1373,7 +1373,7 @@ rich_status galerkin(const CsrDev &A, const int32_t *agg, int64_t nc, CsrDev *C,
     RICH_TRY(tmp.get(&mem, A.n));
     RICH_TRY(members(agg, A.n, nc, mptr, mem, s));
     RICH_TRY(galerkin_symbolic(A, agg, nc, mptr, mem, C, mem_out, s));
-    RICH_TRY(galerkin_numeric(A, agg, mptr, mem, *C, s));
+    if (values) RICH_TRY(galerkin_numeric(A, agg, mptr, mem, *C, s));
     HIP_TRY(hipStreamSynchronize(s));
     return RICH_OK;
 }

@@ -190,6 +190,12 @@ struct DevAlloc {
                 q = nullptr;
             }
     }
+    void absorb(DevAlloc &o) {  // o's allocations become this one's
+        ptrs.insert(ptrs.end(), o.ptrs.begin(), o.ptrs.end());
+        bytes += o.bytes;
+        o.ptrs.clear();
+        o.bytes = 0;
+    }
     ~DevAlloc() {
         for (void *p : ptrs)
             if (p) (void)hipFree(p);
@@ -443,7 +449,7 @@ struct CsrDev {
     double *val = nullptr;
 };
 rich_status galerkin(const CsrDev &A, const int32_t *agg, int64_t nc, CsrDev *C, DevAlloc &mem,
-                     hipStream_t s);
+                     hipStream_t s, bool values);
 // pattern of P^T A P given the members of every coarse row; values by galerkin_numeric
 rich_status galerkin_symbolic(const CsrDev &A, const int32_t *agg, int64_t nc, const int64_t *mptr,
                               const int32_t *mem, CsrDev *C, DevAlloc &mem_out, hipStream_t s);

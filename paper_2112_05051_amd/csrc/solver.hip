@@ -320,7 +320,8 @@ rich_status build_hierarchy(rich_ctx *h) {
             }
             DevAlloc *nm = new DevAlloc();
             CsrDev nxt;
-            st = galerkin(cur, a, nc, &nxt, *nm, s);
+            // the last sweep's product gives the coarse pattern only
+            st = galerkin(cur, a, nc, &nxt, *nm, s, sw + 1 < h->O.amg_sweeps);
             if (st == RICH_OK) st = compose_agg(comp, a, levA.n, s);
             if (st == RICH_OK) st = sync(h);
             delete am;
@@ -339,13 +340,23 @@ rich_status build_hierarchy(rich_ctx *h) {
             break;
         }
         int64_t nc = h->O.amg_aggregation == RICH_AGG_VMB ? nc_vmb : cur.n;
-        delete cur_mem;  // the pairwise products served the matching only
         // a level that keeps more than half of the rows is not worth its cost
         // once the current level fits the dense coarsest solver: stop here
         if (2 * nc > levA.n && levA.n <= h->O.coarse_dense_max) {
+            delete cur_mem;
             H.mem.release(comp);
             break;
         }
+        // The pattern of the product with the composed aggregates is that of the
+        // pairwise products in turn: the last one's is kept (two short rows
+        // merged per coarse row, not eight).
+        CsrDev C;
+        const bool pattern = cur_mem && l >= h->O.amg_smoothed;
+        if (pattern) {
+            C = cur;
+            H.mem.absorb(*cur_mem);
+        }
+        delete cur_mem;
         Level &Lf = H.L[l];
         Lf.agg = comp;
         RICH_TRY(H.mem.get(&Lf.mptr, nc + 1));
@@ -353,13 +364,11 @@ rich_status build_hierarchy(rich_ctx *h) {
         RICH_TRY(members(comp, levA.n, nc, Lf.mptr, Lf.mem, s));
         // the coarse matrix: Galerkin product with the composed aggregates,
         // through the piecewise-constant or the smoothed prolongator
-        CsrDev C;
         if (l < h->O.amg_smoothed) {
             RICH_TRY(sa_symbolic(levA, comp, nc, Lf.mptr, Lf.mem, Lf, &C, h->mixed, H.mem, s));
             RICH_TRY(sa_numeric(levA, comp, Lf, C, h->mixed, s));
         } else {
-            RICH_TRY(galerkin_symbolic(levA, comp, nc, Lf.mptr, Lf.mem, &C, H.mem, s));
-            RICH_TRY(galerkin_numeric(levA, comp, Lf.mptr, Lf.mem, C, s));
+            if (!pattern) RICH_TRY(galerkin_symbolic(levA, comp, nc, Lf.mptr, Lf.mem, &C, H.mem, s));
             // what the refreshes sum (32-bit indices; the M arrays hold 4 N values)
             if (h->O.amg_refresh && levA.nnz < ((int64_t)1 << 32) && (l > 0 || N < ((int64_t)1 << 30))) {
                 const Grid3 g{P.nx, P.ny, P.nz};
@@ -367,6 +376,12 @@ rich_status build_hierarchy(rich_ctx *h) {
                 RICH_TRY(H.mem.get(&Lf.gsrc, levA.nnz));
                 RICH_TRY(galerkin_sources(levA, comp, Lf.mptr, Lf.mem, C, l == 0 ? &g : nullptr, Lf.gptr, Lf.gsrc,
                                           s));
+                Level V;  // the values as a refresh sums them
+                V.nnz = C.nnz;
+                V.val = C.val;
+                RICH_TRY(galerkin_sum(Lf.gptr, Lf.gsrc, l == 0 ? h->M4 : levA.val, V, false, false, s));
+            } else {
+                RICH_TRY(galerkin_numeric(levA, comp, Lf.mptr, Lf.mem, C, s));
             }
         }
         RICH_TRY(sync(h));
