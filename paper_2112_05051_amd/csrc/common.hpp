@@ -359,6 +359,7 @@ struct VLevel {
     void *invd = nullptr;     // l1 inverse diagonal, the cycle's precision
     int2 *child = nullptr;    // rows [x, y) of the finer level that each row stands for (also set on the coarsest)
     int4 *blk = nullptr;      // block table, nblk + 1
+    void *slab[2] = {nullptr, nullptr};  // the allocations that hold all of these but child
     int nblk = 0, np = 1;     // blocks, of about 512 np entries
     int g = 1;                // partial sums per row
     int nlist = 0;            // np = 4: columns of all lists

@@ -408,8 +408,7 @@ rich_status build_hierarchy(rich_ctx *h) {
         RICH_TRY(vlevel_order(H.L[t], H.L[t + 1].n, h->mixed, H.mem, &H.ordered, s));
     for (int t = 1; t < H.nlev - 1 && !H.ordered; t++) {
         VLevel &V = H.L[t].V;
-        for (void *q : {(void *)V.pos, (void *)V.ptr, (void *)V.place, (void *)V.off, (void *)V.ent, (void *)V.col, (void *)V.idx, V.val,
-                        V.invd, (void *)V.blk})
+        for (void *q : V.slab)
             if (q) H.mem.release(q);
         V = VLevel{};
     }
