@@ -201,13 +201,13 @@ FAMILIES = {
     "block_dot": (("k_block_dot<", "k_block_dot_wide<", "k_block_dot_wide_small<"), "la.hip"),
     "block_update": ("k_block_update<", "la.hip"),
     "spmv_J": ("k_spmv_J<float>", "fine.hip"),
-    "vc0_pre": ("k_st25<double, float, 0>", "fine.hip"),
-    "vc0_post": ("k_st25<double, float, 1>", "fine.hip"),
+    "vc0_pre": ("k_st25<double, float, 0", "fine.hip"),
+    "vc0_post": ("k_st25<double, float, 1", "fine.hip"),
     "restrict": ("k_restrict<float>", "amg.hip"),
     "csr_pre": ("k_csr_stream<2, float, float, false>", "amg.hip"),
     "csr_post": ("k_csr_stream<2, float, float, true>", "amg.hip"),
-    "residual": ("k_faces_tiled<false", "fine.hip"),
-    "assembly": ("k_faces_tiled<true", "fine.hip"),
+    "residual": ("k_faces_march<false", "fine.hip"),
+    "assembly": ("k_faces_march<true", "fine.hip"),
 }
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "traffic_c3_256cube_mixed.md")
 
@@ -237,15 +237,15 @@ def algorithmic_bytes(name, n, blocks=None, levels=None, mixed=True, shifted=Tru
         return 8 * n * (k + 1) + (8 * n if m.group(1) == "update_norm" else 0)
     if "k_spmv_J<float>" in name:
         return (76 if shifted else 68) * n
-    if "k_st25<double, float, 0>" in name or "k_st_pre<double, float>" in name:
+    if "k_st25<double, float, 0" in name or "k_st_pre<double, float>" in name:
         return 8 * n + 6 * t * n
-    if "k_faces_tiled<false" in name or "k_residual" in name:
+    if re.search(r"k_faces_(march|tiled)<false", name) or "k_residual" in name:
         return 32 * n
-    if "k_faces_tiled<true" in name:
+    if re.search(r"k_faces_(march|tiled)<true", name):
         return n * (16 + 56 + 32 + 8 + (20 if mixed else 0))
     if not levels or blocks is None:
         return None
-    if "k_st25<double, float, 1>" in name:
+    if "k_st25<double, float, 1" in name:
         return 8 * n + 6 * t * n + 4 * n + t * levels[1][0]
     if "k_restrict<" in name:
         for l in range(len(levels) - 1):
