@@ -569,12 +569,15 @@ constexpr int F_RX = F_X + 2, F_RING = F_RX * (F_Y + 2);
 static_assert(2 * (F_X + F_Y) == 64, "the ring is one wave's");
 
 // a / b for a constant b with y = 1 / b rounded: two Newton corrections of
-// a * y with exact remainders (Markstein's division), which give the rounded
-// quotient as the division instruction sequence does, short of subnormals.
+// a * y with exact remainders (Markstein's division).  The quotient is the
+// division instruction sequence's, but for the last bit where the remainder
+// underflows (|a| below about 1e-291) and for the sign of a zero.
+// Of an infinite b (y = 0) the quotient of a finite a is the zero a * y: the
+// remainder must not form 0 * inf, so b is then kept as 0.
 struct Recip {
     double b, y;
     // (the same in every lane: kept in scalar registers)
-    __device__ explicit Recip(double v) : b(uniform(v)), y(uniform(1.0 / v)) {}
+    __device__ explicit Recip(double v) : b(uniform(isinf(v) ? 0.0 : v)), y(uniform(1.0 / v)) {}
     static __device__ double uniform(double v) {
         return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
                                 __builtin_amdgcn_readfirstlane(__double2loint(v)));

@@ -88,3 +88,38 @@ def test_vcycle_result(rich, torch, orc, shape, precision, tol):
         bd[:P.n] = dev(torch, b)
         assert s._L.rich_apply_prec(s._h, bd.data_ptr(), xd.data_ptr()) == rich.OK
         assert np.array_equal(xd[:P.n].cpu().numpy(), x)
+
+
+def same_values(g, o, rtol):
+    """Not-numbers and infinities in the same places, finite values within rtol of the largest."""
+    assert np.array_equal(np.isnan(g), np.isnan(o))
+    inf = np.isinf(o)
+    assert np.array_equal(np.isinf(g), inf) and np.array_equal(g[inf], o[inf])
+    ok = np.isfinite(o)
+    if ok.any():
+        assert np.max(np.abs(g[ok] - o[ok])) <= rtol * max(np.max(np.abs(o[ok])), 1e-300)
+
+
+def check_constants(rich, torch, orc, P, p, p_old):
+    """Residual, J and M of the marching kernels where the grid's constants leave the usual range."""
+    ks = random_ks(P, 74)
+    th = orc.theta(P, p_old)
+    s = rich.Solver(P, synth.Options(amg_max_levels=1, coarse_dense_max=0), dev(torch, ks))
+    same_values(s.residual(dev(torch, p), dev(torch, th)).cpu().numpy(), orc.residual(P, ks, p, th), 1e-12)
+    s.assemble(dev(torch, p))
+    for which, ref in ((rich.WHICH_J, orc.jacobian), (rich.WHICH_A, orc.auxiliary)):
+        rp, col, val = s.export_csr(which)
+        R = sp.csr_matrix(ref(P, ks, p))
+        R.sort_indices()
+        assert np.array_equal(rp, R.indptr) and np.array_equal(col, R.indices)
+        same_values(val, R.data, 1e-12)
+
+
+# An infinite time step is the steady operator, and spacings whose square overflows
+# switch a direction off: what is divided by them is zero.
+@pytest.mark.parametrize("mean", [synth.ARITH, synth.UPSTREAM, synth.HARMONIC, synth.GEOMETRIC, synth.INTEGRAL])
+@pytest.mark.parametrize("name", ["dt", "hx", "hy"])
+def test_infinite_constants(rich, torch, orc, mean, name):
+    P = box_problem(18, 17, 5, mean=mean, dt=7.0)
+    setattr(P, name, np.inf if name == "dt" else 1e200)
+    check_constants(rich, torch, orc, P, random_heads(P.n, 72, saturated_fraction=0.05), random_heads(P.n, 73))
