@@ -548,7 +548,7 @@ __global__ void __launch_bounds__(FT_TPB) k_faces_tiled(Phys P, int kz, const do
 }
 
 // ------------------------------------ plane-marching residual and assembly
-// The means without a quadrature.  A block owns an F_X x F_Y tile of (x, y)
+// The means without a quadrature.  A block owns an FX x FY tile of (x, y)
 // columns and marches up a run of z planes: per plane it stages the heads, K
 // (and K') of the tile and of the ring around it in LDS (each evaluated once;
 // the tile's own come up from the plane below, where they were the upper
@@ -564,9 +564,11 @@ __global__ void __launch_bounds__(FT_TPB) k_faces_tiled(Phys P, int kz, const do
 // and divisions by the grid's constants go through their reciprocals.
 // At 256^3 the residual takes 255-275 us (345 with a barrier for every stage and
 // full divisions), the assembly 590 (870; 450 us of bytes).
-constexpr int F_X = 16, F_Y = 16, F_TPB = F_X * F_Y;
-constexpr int F_RX = F_X + 2, F_RING = F_RX * (F_Y + 2);
-static_assert(2 * (F_X + F_Y) == 64, "the ring is one wave's");
+// Tiles: 16 x 16, and 32 x 8 for grids of up to eight rows (one tile spans y, so
+// its ring is two columns of eight), where a 16 x 16 tile has half of its threads
+// or more outside the grid: 300 x 6 x 300 residual 18.2 us (16 x 16: 23.4),
+// assembly 28.1 (36.0); 2000 x 8 x 60 24.7 (28.2) and 36.0 (43.9).
+constexpr int F_TPB = 256;
 
 // a / b for a constant b with y = 1 / b rounded: two Newton corrections of
 // a * y with exact remainders (Markstein's division).  The quotient is the
@@ -590,28 +592,31 @@ struct Recip {
     }
 };
 
-template <bool JAC>
+template <bool JAC, int FX, int FY>
 __global__ void __launch_bounds__(F_TPB, JAC ? 3 : 4) k_faces_march(Phys P, int kz, const double *__restrict__ Ks,
                                                        const double *__restrict__ p,
                                                        const double *__restrict__ th_old, double *__restrict__ F,
                                                        double *__restrict__ J7, double *__restrict__ M4,
                                                        float *__restrict__ M4f, double *__restrict__ invd,
                                                        float *__restrict__ invdf, int dflux) {
+    static_assert(FX * FY == F_TPB && (FY == 8 || (FX == 16 && FY == 16)), "the ring is one wave's");
+    constexpr int F_RX = FX + 2, F_RING = F_RX * (FY + 2);
     __shared__ double sp[2][F_RING], sK[2][F_RING], sdK[JAC ? 2 : 1][JAC ? F_RING : 1];
-    const int tid = threadIdx.x, tx = tid % F_X, ty = tid / F_X;
+    const int tid = threadIdx.x, tx = tid % FX, ty = tid / FX;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int i0 = blockIdx.x * F_X, j0 = blockIdx.y * F_Y;
+    const int i0 = blockIdx.x * FX, j0 = blockIdx.y * FY;
     const int k0 = blockIdx.z * kz, k1 = min(k0 + kz, P.nz);
     const int i = i0 + tx, j = j0 + ty;
     const bool own = i < P.nx && j < P.ny;
     const uint32_t nxy = (uint32_t)P.nx * (uint32_t)P.ny, n = nxy * (uint32_t)P.nz;
     const int me = (ty + 1) * F_RX + (tx + 1);
     const Recip dx2(P.hx * P.hx), dy2(P.hy * P.hy), dz2(P.hz * P.hz), d2z(2.0 * P.hz), ddt(P.dt);
-    // ring cell of this lane: the row below, the row above, the left and right columns
-    const int rs = lane >> 4, rt = lane & 15;
-    const int gi = rs < 2 ? i0 + rt : rs == 2 ? i0 - 1 : i0 + F_X, gj = rs >= 2 ? j0 + rt : rs == 0 ? j0 - 1 : j0 + F_Y;
+    // ring cell of this lane: the row below, the row above, the left and right
+    // columns; with eight rows the columns alone (lanes past them have none)
+    const int rs = FY == 8 ? 2 + (lane >> 3) : lane >> 4, rt = FY == 8 ? lane & 7 : lane & 15;
+    const int gi = rs < 2 ? i0 + rt : rs == 2 ? i0 - 1 : i0 + FX, gj = rs >= 2 ? j0 + rt : rs == 0 ? j0 - 1 : j0 + FY;
     const int rpos = (gj - j0 + 1) * F_RX + (gi - i0 + 1);
-    const bool ring = gi >= 0 && gi < P.nx && gj >= 0 && gj < P.ny;
+    const bool ring = rs < 4 && gi >= 0 && gi < P.nx && gj >= 0 && gj < P.ny;
     const uint32_t rcol = ring ? (uint32_t)gi + (uint32_t)P.nx * (uint32_t)gj : 0u;
     const uint32_t col = own ? (uint32_t)i + (uint32_t)P.nx * (uint32_t)j : 0u;
     // the own column: current plane (c), the one above (u) and the face below
@@ -1438,19 +1443,35 @@ static bool faces_grid(const Phys &P, dim3 *g, int *kz) {
     return true;
 }
 
-// The same for the marching kernels: planes per block (at most 64) by the
-// rounds the blocks run in, as in kz25.
-template <bool JAC>
-static bool march_grid(const Phys &P, dim3 *g, int *kz) {
-    static const int fit = blocks_at_once(k_faces_march<JAC>, F_TPB);
-    const int64_t tx = (P.nx + F_X - 1) / F_X, ty = (P.ny + F_Y - 1) / F_Y;
+// The marching kernels' launch: planes per block (at most 64) by the rounds the
+// blocks run in, as in kz25; false when the grid does not fit the launch limits.
+template <bool JAC, int FX, int FY, class... Args>
+static bool march(const Phys &P, hipStream_t s, Args... args) {
+    static const int fit = blocks_at_once(k_faces_march<JAC, FX, FY>, F_TPB);
+    const int64_t tx = (P.nx + FX - 1) / FX, ty = (P.ny + FY - 1) / FY;
     if (tx > 0x7fffffff || ty > 65535) return false;
-    const int z = planes_per_block(tx * ty, P.nz, 64, fit);
-    const int64_t tz = (P.nz + z - 1) / z;
+    const int kz = planes_per_block(tx * ty, P.nz, 64, fit);
+    const int64_t tz = (P.nz + kz - 1) / kz;
     if (tz > 65535) return false;
-    *g = dim3((unsigned)tx, (unsigned)ty, (unsigned)tz);
-    *kz = z;
+    k_faces_march<JAC, FX, FY><<<dim3((unsigned)tx, (unsigned)ty, (unsigned)tz), F_TPB, 0, s>>>(P, kz, args...);
     return true;
+}
+
+// Slices of one or two cells along x or y leave a tile nearly empty whatever its
+// shape, and there the kernels of one thread per cell win, although they
+// evaluate each law up to seven times.  Residual, us, against the better tile:
+// 100 x 1 x 400 6.6 / 10.1, 2 x 100 x 360 9.0 / 20.7, 300 x 2 x 720 20.7 / 21.7
+// (assembly 30.3 / 35.9).  On fewer cells the chain of a cell's laws is the time:
+// 100 x 1 x 90 6.4 / 7.0, but 100 x 2 x 90 7.6 / 7.2 and 100 x 2 x 180 7.8 / 8.1.
+static bool thin(const Phys &P) {
+    const uint32_t w = (uint32_t)std::min(P.nx, P.ny);
+    return w <= 2 && ncells(P) >= 8192u * w * w;
+}
+
+template <bool JAC, class... Args>
+static bool launch_march(const Phys &P, hipStream_t s, Args... args) {
+    if (has_integral(P) || thin(P)) return false;
+    return P.ny <= 8 && P.nx > 16 ? march<JAC, 32, 8>(P, s, args...) : march<JAC, 16, 16>(P, s, args...);
 }
 
 rich_status launch_residual(const Phys &P, const double *Ks, const double *p, const double *theta_old,
@@ -1461,10 +1482,7 @@ rich_status launch_residual(const Phys &P, const double *Ks, const double *p, co
     if (has_integral(P) && faces_grid(P, &g, &kz))
         k_faces_tiled<false><<<g, FT_TPB, 0, s>>>(P, kz, Ks, p, theta_old, F, nullptr, nullptr, nullptr, nullptr,
                                                   nullptr, 0);
-    else if (!has_integral(P) && march_grid<false>(P, &g, &kz))
-        k_faces_march<false><<<g, F_TPB, 0, s>>>(P, kz, Ks, p, theta_old, F, nullptr, nullptr, nullptr, nullptr,
-                                                 nullptr, 0);
-    else
+    else if (!launch_march<false>(P, s, Ks, p, theta_old, F, nullptr, nullptr, nullptr, nullptr, nullptr, 0))
         k_residual<<<nblocks(n), TPB, 0, s>>>(P, n, Ks, p, theta_old, F);
     LAUNCH_CHECK();
     return RICH_OK;
@@ -1477,9 +1495,7 @@ rich_status launch_assemble(const Phys &P, const double *Ks, const double *p, do
     int kz;
     if (has_integral(P) && faces_grid(P, &g, &kz))
         k_faces_tiled<true><<<g, FT_TPB, 0, s>>>(P, kz, Ks, p, nullptr, nullptr, J7, M4, M4f, invd, invdf, dflux);
-    else if (!has_integral(P) && march_grid<true>(P, &g, &kz))
-        k_faces_march<true><<<g, F_TPB, 0, s>>>(P, kz, Ks, p, nullptr, nullptr, J7, M4, M4f, invd, invdf, dflux);
-    else
+    else if (!launch_march<true>(P, s, Ks, p, nullptr, nullptr, J7, M4, M4f, invd, invdf, dflux))
         k_assemble<<<nblocks(n), TPB, 0, s>>>(P, n, Ks, p, J7, M4, M4f, invd, invdf, dflux);
     LAUNCH_CHECK();
     return RICH_OK;

@@ -123,3 +123,24 @@ def test_infinite_constants(rich, torch, orc, mean, name):
     P = box_problem(18, 17, 5, mean=mean, dt=7.0)
     setattr(P, name, np.inf if name == "dt" else 1e200)
     check_constants(rich, torch, orc, P, random_heads(P.n, 72, saturated_fraction=0.05), random_heads(P.n, 73))
+
+
+# Flat grids: 32 x 8 tiles up to eight rows (whole, single and missing columns, more
+# than one run of planes), and one thread per cell from 8192 cells on where x or y
+# has one, from 32768 where it has two.
+@pytest.mark.parametrize("mean", [synth.ARITH, synth.UPSTREAM, synth.HARMONIC, synth.GEOMETRIC])
+@pytest.mark.parametrize("shape", [(32, 8, 5), (33, 7, 70), (17, 3, 1), (8191, 1, 1), (8192, 1, 1), (129, 2, 127), (2, 128, 128),
+                                   (17, 9, 4)])
+def test_flat_residual_and_assembly(rich, torch, orc, shape, mean):
+    P = box_problem(*shape, mean=mean, dt=7.0)
+    P.bc_type, P.bc_value = all_dirichlet()
+    ks = random_ks(P, 75)
+    p = random_heads(P.n, 76, saturated_fraction=0.05)
+    th = orc.theta(P, random_heads(P.n, 77))
+    s = rich.Solver(P, synth.Options(amg_max_levels=1, coarse_dense_max=0), dev(torch, ks))
+    F_o = orc.residual(P, ks, p, th)
+    F_g = s.residual(dev(torch, p), dev(torch, th)).cpu().numpy()
+    assert np.max(np.abs(F_g - F_o)) <= 1e-12 * np.max(np.abs(F_o))
+    s.assemble(dev(torch, p))
+    csr_close(*s.export_csr(rich.WHICH_J), orc.jacobian(P, ks, p), 1e-12)
+    csr_close(*s.export_csr(rich.WHICH_A, 0), orc.auxiliary(P, ks, p), 1e-12)
