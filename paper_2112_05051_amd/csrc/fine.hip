@@ -2,6 +2,7 @@
 // matrix assembly, 7-point stencil products and the fine-level pieces of the
 // AMG V-cycle.  One thread per cell, x-fastest cell order, SoA coefficient
 // arrays (every load and store of a wavefront is one contiguous run).
+#include <cmath>
 #include <algorithm>
 
 #include "common.hpp"
@@ -1468,9 +1469,18 @@ static bool thin(const Phys &P) {
     return w <= 2 && ncells(P) >= 8192u * w * w;
 }
 
+// Whether Recip divides by the grid's constants: their reciprocals are finite.
+// (A time step below 5.6e-309, or a spacing below 7.5e-155, has an infinite one, and
+// 0 / b is then 0 * inf; the kernels of one thread per cell divide.)
+static bool reciprocals(const Phys &P) {
+    for (double b : {P.hx * P.hx, P.hy * P.hy, P.hz * P.hz, 2.0 * P.hz, P.dt})
+        if (!std::isfinite(1.0 / b)) return false;
+    return true;
+}
+
 template <bool JAC, class... Args>
 static bool launch_march(const Phys &P, hipStream_t s, Args... args) {
-    if (has_integral(P) || thin(P)) return false;
+    if (has_integral(P) || thin(P) || !reciprocals(P)) return false;
     return P.ny <= 8 && P.nx > 16 ? march<JAC, 32, 8>(P, s, args...) : march<JAC, 16, 16>(P, s, args...);
 }
 

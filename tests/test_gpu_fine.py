@@ -125,6 +125,17 @@ def test_infinite_constants(rich, torch, orc, mean, name):
     check_constants(rich, torch, orc, P, random_heads(P.n, 72, saturated_fraction=0.05), random_heads(P.n, 73))
 
 
+# Constants so small that their reciprocal overflows: a saturated state that the
+# time step leaves as it is, and heads that do not vary along y, divide to zero.
+@pytest.mark.parametrize("mean", [synth.ARITH, synth.UPSTREAM, synth.HARMONIC, synth.GEOMETRIC, synth.INTEGRAL])
+@pytest.mark.parametrize("name,value", [("dt", 1e-309), ("hy", 3e-155)])
+def test_tiny_constants(rich, torch, orc, mean, name, value):
+    P = box_problem(18, 17, 5, mean=mean, dt=7.0)
+    setattr(P, name, value)
+    p = np.repeat(np.random.default_rng(78).uniform(0.5, 5.0, (5, 1, 18)), 17, axis=1).reshape(-1)
+    check_constants(rich, torch, orc, P, p, p)
+
+
 # Flat grids: 32 x 8 tiles up to eight rows (whole, single and missing columns, more
 # than one run of planes), and one thread per cell from 8192 cells on where x or y
 # has one, from 32768 where it has two.
