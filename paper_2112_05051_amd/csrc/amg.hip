@@ -497,7 +497,6 @@ enum { GS_NONE = 0, GS_F32, GS_ENT, GS_VALF, GS_VAL };
 // thread adds its entry's from there.  (A thread walking its own list waits
 // for two dependent loads per four sources, and a wave for its longest list, a
 // diagonal's of about 26: 1200 us for the five levels at 256^3, now 690.)
-constexpr int GS_TPB = 256, GS_PER = 6, GS_PIECE = GS_TPB * GS_PER;
 template <int COPY>
 __global__ void __launch_bounds__(GS_TPB) k_gal_sum(int64_t cnnz, const uint32_t *__restrict__ gptr,
                                                     const uint32_t *__restrict__ gsrc, const double *__restrict__ val,

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "../../include/richards.h"
+#include "source_walk.hpp"
 
 struct rich_batcher;
 
@@ -458,7 +459,7 @@ rich_status galerkin_numeric(const CsrDev &A, const int32_t *agg, const int64_t 
                              const CsrDev &C, hipStream_t s);
 // The source lists (gptr: C.nnz + 1, gsrc: A.nnz) of galerkin_sum.  g set: A is
 // the level-0 matrix of that grid and the sources index the M stencil arrays,
-// else A's values.  Needs A.nnz and 4 A.n below 2^32.
+// else A's values.  Needs source_lists_fit.
 rich_status galerkin_sources(const CsrDev &A, const int32_t *agg, const int64_t *mptr, const int32_t *mem,
                              const CsrDev &C, const Grid3 *g, uint32_t *gptr, uint32_t *gsrc, hipStream_t s);
 // Values of the next level Lc = sums of val at each entry's sources (the values

@@ -369,8 +369,8 @@ rich_status build_hierarchy(rich_ctx *h) {
             RICH_TRY(sa_numeric(levA, comp, Lf, C, h->mixed, s));
         } else {
             if (!pattern) RICH_TRY(galerkin_symbolic(levA, comp, nc, Lf.mptr, Lf.mem, &C, H.mem, s));
-            // what the refreshes sum (32-bit indices; the M arrays hold 4 N values)
-            if (h->O.amg_refresh && levA.nnz < ((int64_t)1 << 32) && (l > 0 || N < ((int64_t)1 << 30))) {
+            // what the refreshes sum (the M arrays hold 4 N values)
+            if (h->O.amg_refresh && source_lists_fit(levA.nnz, l == 0 ? 4 * N : levA.nnz)) {
                 const Grid3 g{P.nx, P.ny, P.nz};
                 RICH_TRY(H.mem.get(&Lf.gptr, C.nnz + 1));
                 RICH_TRY(H.mem.get(&Lf.gsrc, levA.nnz));
