@@ -42,11 +42,13 @@ __device__ inline double find_entry(const int64_t *__restrict__ rowptr, const in
 
 // Eight lanes per row: a thread walking its row alone waits for one dependent
 // load after another (the weights of a set-up's 18 sweeps at 256^3 10.3 ms, now
-// 4.4).
+// 4.4).  A launch holds fewer than 2^32 threads, so it takes the rows from r0 on,
+// at most ROW_SLICE of them.
 constexpr int ROW_LANES = 8;
-__global__ void k_diag(int64_t n, const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col,
+constexpr int64_t ROW_SLICE = (int64_t)1 << 28;
+__global__ void k_diag(int64_t r0, int64_t n, const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col,
                        const double *__restrict__ val, double *__restrict__ diag) {
-    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / ROW_LANES;
+    const int64_t i = r0 + ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / ROW_LANES;
     const int lane = threadIdx.x % ROW_LANES;
     double d = 0.0;
     if (i < n)
@@ -61,10 +63,10 @@ __global__ void k_diag(int64_t n, const int64_t *__restrict__ rowptr, const int3
 // where the entry can never be a candidate (the diagonal, a coupling missing
 // from the lower row, a zero coupling).  k_candidates skips every entry
 // whose weight is not finite.
-__global__ void k_match_weights(int64_t n, const int64_t *__restrict__ rowptr, const int32_t *__restrict__ col,
-                                const double *__restrict__ val, const double *__restrict__ diag,
-                                double *__restrict__ w) {
-    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / ROW_LANES;
+__global__ void k_match_weights(int64_t r0, int64_t n, const int64_t *__restrict__ rowptr,
+                                const int32_t *__restrict__ col, const double *__restrict__ val,
+                                const double *__restrict__ diag, double *__restrict__ w) {
+    const int64_t i = r0 + ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / ROW_LANES;
     if (i >= n) return;
     for (int64_t e = rowptr[i] + threadIdx.x % ROW_LANES; e < rowptr[i + 1]; e += ROW_LANES) {
         int32_t j = col[e];
@@ -1173,10 +1175,15 @@ rich_status match_sweep_ws(int64_t n, const int64_t *rowptr, const int32_t *col,
         *nc_out = 0;
         return RICH_OK;
     }
-    k_diag<<<nblocks(n * ROW_LANES), TPB, 0, s>>>(n, rowptr, col, val, w.diag);
+    auto sliced = [&](auto &&launch) {
+        for (int64_t r0 = 0; r0 < n; r0 += ROW_SLICE) launch(r0, nblocks(std::min(ROW_SLICE, n - r0) * ROW_LANES));
+    };
+    sliced([&](int64_t r0, unsigned g) { k_diag<<<g, TPB, 0, s>>>(r0, n, rowptr, col, val, w.diag); });
     LAUNCH_CHECK();
     // the weights do not change between rounds: computed once
-    k_match_weights<<<nblocks(n * ROW_LANES), TPB, 0, s>>>(n, rowptr, col, val, w.diag, w.wts);
+    sliced([&](int64_t r0, unsigned g) {
+        k_match_weights<<<g, TPB, 0, s>>>(r0, n, rowptr, col, val, w.diag, w.wts);
+    });
     LAUNCH_CHECK();
     RICH_TRY(launch_fill_i32(w.mate, -1, n, s));
     for (int64_t round = 0;; round++) {

@@ -105,3 +105,27 @@ def test_vcycle_splits(rich, torch, orc, shape, kw, precision, tol):
     x = s.apply_prec(dev(torch, b)).cpu().numpy()
     xo = amg.apply(b)
     assert np.linalg.norm(x - xo) <= tol * np.linalg.norm(xo)
+
+
+# More rows than a launch of eight threads a row can hold (2^29 = 2^32 / 8): of a
+# chain whose couplings (2 k + 1, 2 k + 2) are the strong ones, these match and the
+# ends stay alone.
+def test_match_sweep_many_rows(rich, torch):
+    n = 2**29 + 4098
+    e = torch.arange(3 * n, dtype=torch.int32, device="cuda")
+    row, at = e // 3, e % 3 - 1
+    del e
+    strong = (at == 1) & (row % 2 == 1) | (at == -1) & (row % 2 == 0)
+    val = torch.full((3 * n,), -0.1, dtype=torch.float64, device="cuda")
+    val[strong] = -1.0
+    val[at == 0] = 3.0
+    row += at
+    rowptr = torch.arange(n + 1, dtype=torch.int64, device="cuda").mul_(3).sub_(1)
+    rowptr[0], rowptr[n] = 0, 3 * n - 2
+    agg, nc = rich.match_sweep(rowptr, row[1:-1].clone(), val[1:-1].clone())
+    assert nc == n // 2 + 1
+    want = torch.arange(1, n + 1, dtype=torch.int32, device="cuda") // 2
+    same = torch.equal(agg, want)
+    del row, at, strong, val, rowptr, agg, want
+    torch.cuda.empty_cache()
+    assert same
