@@ -245,7 +245,8 @@ typedef struct rich_ctx *rich_handle_t;
 
 /* Device bytes a handle for (prob, opts) will hold, before the AMG
  * hierarchy (whose size depends on the matrix) -- plus an upper bound for
- * the hierarchy assuming operator complexity <= 3. */
+ * the hierarchy and its set-up assuming operator complexity <= 3 and at most
+ * 2 N rows on the coarse levels. */
 rich_status rich_query_bytes(const rich_problem_t *prob, const rich_solver_opts_t *opts,
                              size_t *bytes);
 

@@ -266,18 +266,20 @@ rich_status build_hierarchy(rich_ctx *h) {
     hipStream_t s = h->s;
     const Phys &P = h->P;
     int64_t N = h->N;
-    DevAlloc tmp;
     // level-0 CSR of M: the set-up's input (kept only where a refresh needs it, below)
     CsrDev A0;
     A0.n = N;
-    int64_t *cnt, *stmp;
-    RICH_TRY(tmp.get(&cnt, N));
-    RICH_TRY(tmp.get(&stmp, scan_tmp_size(N)));
     RICH_TRY(H.mem.get(&A0.rowptr, N + 1));
-    RICH_TRY(launch_stencil_rowcounts(P, cnt, s));
-    RICH_TRY(scan_exclusive_i64(cnt, A0.rowptr, N, stmp, s));
-    HIP_TRY(hipMemcpyAsync(&A0.nnz, A0.rowptr + N, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    RICH_TRY(sync(h));
+    {
+        DevAlloc tmp;
+        int64_t *cnt, *stmp;
+        RICH_TRY(tmp.get(&cnt, N));
+        RICH_TRY(tmp.get(&stmp, scan_tmp_size(N)));
+        RICH_TRY(launch_stencil_rowcounts(P, cnt, s));
+        RICH_TRY(scan_exclusive_i64(cnt, A0.rowptr, N, stmp, s));
+        HIP_TRY(hipMemcpyAsync(&A0.nnz, A0.rowptr + N, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+        RICH_TRY(sync(h));
+    }
     RICH_TRY(H.mem.get(&A0.col, A0.nnz));
     RICH_TRY(H.mem.get(&A0.val, A0.nnz));
     RICH_TRY(launch_stencil_to_csr(P, h->M4, A0.rowptr, A0.col, A0.val, s));
@@ -397,6 +399,12 @@ rich_status build_hierarchy(rich_ctx *h) {
         levA.rowptr = Lc.rowptr;
         levA.col = Lc.col;
         levA.val = Lc.val;
+        if (l == 0 && Lf.gsrc) {  // the refreshes read M itself: its CSR form has served
+            for (void *q : {(void *)Lf.rowptr, (void *)Lf.col, (void *)Lf.val}) H.mem.release(q);
+            Lf.rowptr = nullptr;
+            Lf.col = nullptr;
+            Lf.val = nullptr;
+        }
         l++;
     }
     H.nlev = l + 1;
@@ -455,20 +463,11 @@ rich_status build_hierarchy(rich_ctx *h) {
         }
     }
     RICH_TRY(sync(h));
-    // with source lists the refreshes read M itself: its CSR form served the set-up only
-    if (H.L[0].gsrc) {
-        H.mem.release(H.L[0].rowptr);
-        H.mem.release(H.L[0].col);
-        H.mem.release(H.L[0].val);
-        H.L[0].rowptr = nullptr;
-        H.L[0].col = nullptr;
-        H.L[0].val = nullptr;
-        if (H.ordered) {  // and so did its member lists in natural order
-            H.mem.release(H.L[0].mptr);
-            H.mem.release(H.L[0].mem);
-            H.L[0].mptr = nullptr;
-            H.L[0].mem = nullptr;
-        }
+    if (H.L[0].gsrc && H.ordered) {  // its member lists in natural order served the set-up only
+        H.mem.release(H.L[0].mptr);
+        H.mem.release(H.L[0].mem);
+        H.L[0].mptr = nullptr;
+        H.L[0].mem = nullptr;
     }
     return RICH_OK;
 }
@@ -1718,6 +1717,43 @@ rich_status validate(const rich_problem_t *P, const rich_solver_opts_t *O) {
     return RICH_OK;
 }
 
+// Upper bound of the hierarchy's device bytes at operator complexity <= 3 (14 N
+// entries on the coarse levels) and twice the fine level's rows on the coarse
+// ones.  The set-up's scratch stays below what the bound leaves for levels that
+// are not there yet: at its largest, on the fine level, about 320 N bytes (its CSR
+// form 92 N, two pairwise products 12 bytes an entry each, 16 per entry of the
+// product for its source lists).
+size_t hierarchy_bytes(size_t N, const rich_solver_opts_t &O) {
+    const bool mixed = O.precision == RICH_PREC_MIXED;
+    const size_t t = mixed ? 4 : 8;
+    const bool lists = O.amg_refresh && source_lists_fit(7 * (int64_t)N, 7 * (int64_t)N);
+    const size_t entries = 14 * N, rows = 2 * N;
+    // fine level: aggregates, member lists (in both orders during set-up), vectors;
+    // its CSR form, or the source lists in its place
+    size_t b = N * (4 + 4 + 4 + 2 + 3 * t) + (lists && !O.amg_smoothed ? 28 : 92) * N;
+    // coarse entries: column and value, places, (offset, offset and value) or FP64
+    // offset, value and list place, source lists
+    b += entries * (12 + 4 + (mixed ? 12 : 14) + (lists ? 8 : 0));
+    // blocks of 256 entries or more, 16 bytes each
+    b += entries / 16;
+    // coarse rows: row starts, aggregate, member lists, vectors, l1 diagonal, place and
+    // row start in aggregate order, finer level's rows; the fine level's lists
+    b += rows * (8 + 4 + 8 + 4 + 3 * t + t + 4 + 4 + 8 + 8);
+    b += 16 * (64 << 10);  // roundings, padding and counters of a level
+    if (O.amg_smoothed) {
+        // level 0 dominates: P and PT (~4.2 entries per fine row), Q = A P
+        // (~12 per row), coarse levels about twice as dense, and the scratch
+        // of the symbolic products during set-up
+        b += 2 * (5 * N) * (12 + 8 + t);
+        b += 14 * N * 12;
+        b += 7 * N * (12 + t);
+        b += 200 * N;
+    }
+    const size_t nc = std::min((size_t)O.coarse_dense_max, N);
+    b += nc * nc * (8 + (mixed ? 4 : 0)) + (nc > 0 ? dense_inverse_ws((int64_t)nc) * 8 : 0);
+    return b;
+}
+
 // Gauss-Legendre nodes and weights on [0, 1]: roots of the Legendre
 // polynomial P_n by Newton's method (three-term recurrence, cosine starting
 // values), weights 2 / ((1 - x^2) P_n'(x)^2), both mapped from [-1, 1].
@@ -1809,21 +1845,10 @@ rich_status rich_query_bytes(const rich_problem_t *prob, const rich_solver_opts_
     if (mixed) b += N * 4 * 5;          // FP32 copies
     b += (m + 1) * N * 8;               // Krylov basis
     b += N * 8 * 2;                     // preconditioner output and scratch
-    size_t esz = mixed ? 4 : 8;
-    // hierarchy bound: operator complexity <= 3, 12-byte CSR entries plus value copies
-    size_t nnz0 = 7 * N;
-    b += 2 * nnz0 * (12 + esz) + N * (8 + esz + 3 * esz + 8) * 2;
-    if (opts->amg_smoothed) {
-        // level 0 dominates: P and PT (~4.2 entries per fine row), Q = A P
-        // (~12 per row), coarse levels about twice as dense, and the scratch
-        // of the symbolic products during set-up
-        b += 2 * (5 * N) * (12 + 8 + esz);
-        b += 14 * N * 12;
-        b += nnz0 * (12 + esz);
-        b += 200 * N;
-    }
-    size_t nc = (size_t)(opts->coarse_dense_max);
-    b += nc * nc * (8 + esz);
+    b += (m + 1) * 63 * 8;              // (rounded to whole runs of 64)
+    b += (size_t)RED_BLOCKS * std::max(3 * (m + 2), (size_t)block_partial_size((int)m + 1, GMRES_BLOCK_MAX)) * 8;
+    b += ((m + 1) * (m + 4) + 2 * (m + 8) + BLK_BUF) * 8;
+    b += hierarchy_bytes(N, *opts);
     *bytes = b;
     return RICH_OK;
 }
