@@ -615,10 +615,14 @@ __global__ void k_csr_pre(int64_t n, const int64_t *__restrict__ rowptr, const i
 
 // prolongation: xt = x0 + P xc
 template <class T>
+__device__ __forceinline__ void csr_prolong_at(int64_t n, const T *__restrict__ x0, const T *__restrict__ xc,
+                                               const int32_t *__restrict__ agg, T *__restrict__ xt, int64_t row) {
+    if (row < n) xt[row] = x0[row] + xc[agg[row]];
+}
+template <class T>
 __global__ void k_csr_prolong(int64_t n, const T *__restrict__ x0, const T *__restrict__ xc,
                               const int32_t *__restrict__ agg, T *__restrict__ xt) {
-    const int64_t row = (int64_t)xcd_block() * blockDim.x + threadIdx.x;
-    if (row < n) xt[row] = x0[row] + xc[agg[row]];
+    csr_prolong_at(n, x0, xc, agg, xt, (int64_t)xcd_block() * blockDim.x + threadIdx.x);
 }
 
 // post-smoothing: x = xt + D^{-1}(b - A xt)
@@ -838,14 +842,46 @@ __global__ void __launch_bounds__(RESTRICT_TPB) k_restrict(int64_t nc, const int
     restrict_block(nc, mptr, mem, slot, r, bc, invdc, x0c, xcd_block());
 }
 
-// The restriction from the fine level over several simulations at once (same
-// per-block code as the lone launch above).
+// The restriction, and the sweeps of levels that are not in aggregate order, over
+// several simulations at once (same per-block code as the lone launches above).
 template <class T>
 __global__ void __launch_bounds__(RESTRICT_TPB) k_restrict_batch(Batch<RestrictItem<T>> B) {
     for_each_block(B, xcd_block(), [&](unsigned L) {
         const int e = batch_entry(B, L);
         const RestrictItem<T> &a = B.a[e];
         restrict_block(a.nc, a.mptr, a.mem, a.slot, a.r, a.bc, a.invdc, a.x0c, (int64_t)(L - B.begin[e]));
+    });
+}
+
+template <class T>
+struct StreamArgs {
+    const int64_t *rb, *rowptr;
+    const int32_t *col;
+    const T *val, *invd, *b, *v;
+    T *out;
+};
+template <int G, class T, bool POST>
+__global__ void __launch_bounds__(256) k_csr_stream_batch(Batch<StreamArgs<T>> B) {
+    for_each_block(B, xcd_block(), [&](unsigned L) {
+        const int e = batch_entry(B, L);
+        const StreamArgs<T> &a = B.a[e];
+        csr_stream_body<G, T, T, POST>(a.rb, a.rowptr, a.col, a.val, a.invd, a.b, a.v, a.out, L - B.begin[e]);
+    });
+}
+
+template <class T>
+struct ProlongArgs {
+    int64_t n;
+    const T *x0, *xc;
+    const int32_t *agg;
+    T *xt;
+};
+template <class T>
+__global__ void k_csr_prolong_batch(Batch<ProlongArgs<T>> B) {
+    for_each_block(B, xcd_block(), [&](unsigned L) {
+        const int e = batch_entry(B, L);
+        const ProlongArgs<T> &a = B.a[e];
+        csr_prolong_at(a.n, a.x0, a.xc, a.agg, a.xt, (int64_t)(L - B.begin[e]) * blockDim.x + threadIdx.x);
     });
 }
 
@@ -1552,6 +1588,55 @@ rich_status launch_restrict_batch(const std::vector<RestrictItem<T>> &v, hipStre
         k_restrict_batch<T><<<g, RESTRICT_TPB, 0, s>>>(bt);
     }, q);
 }
+template <class T, bool POST>
+static rich_status stream_batch(const std::vector<CsrItem<T>> &v, hipStream_t s, WorkQueue *q) {
+    for (int G : {1, 2, 4, 8}) {
+        std::vector<StreamArgs<T>> a;
+        std::vector<unsigned> nb;
+        for (const auto &it : v) {
+            const Level &Lv = *it.Lv;
+            if (Lv.sg != G || Lv.n == 0) continue;
+            a.push_back({Lv.rb, Lv.rowptr, Lv.col, it.val, it.invd, it.b, POST ? (const T *)Lv.r : it.x0, it.out});
+            nb.push_back((unsigned)Lv.nrb);
+        }
+        auto launch = [&](const Batch<StreamArgs<T>> &bt, unsigned g) {
+            switch (G) {
+            case 1: k_csr_stream_batch<1, T, POST><<<g, 256, 0, s>>>(bt); break;
+            case 2: k_csr_stream_batch<2, T, POST><<<g, 256, 0, s>>>(bt); break;
+            case 4: k_csr_stream_batch<4, T, POST><<<g, 256, 0, s>>>(bt); break;
+            default: k_csr_stream_batch<8, T, POST><<<g, 256, 0, s>>>(bt); break;
+            }
+        };
+        RICH_TRY(launch_batches(a, nb, launch, q));
+    }
+    return RICH_OK;
+}
+
+template <class T>
+rich_status launch_csr_pre_batch(const std::vector<CsrItem<T>> &v, hipStream_t s, WorkQueue *q) {
+    return stream_batch<T, false>(v, s, q);
+}
+
+template <class T>
+rich_status launch_csr_post_batch(const std::vector<CsrItem<T>> &v, hipStream_t s, WorkQueue *q) {
+    // xt = x0 + P xc into each level's r buffer, then post-smoothing from xt
+    std::vector<ProlongArgs<T>> a;
+    std::vector<unsigned> nb;
+    for (const auto &it : v) {
+        a.push_back({it.Lv->n, it.x0, it.xc, it.Lv->agg, (T *)it.Lv->r});
+        nb.push_back((unsigned)((it.Lv->n + TPB - 1) / TPB));
+    }
+    RICH_TRY(launch_batches(a, nb, [&](const Batch<ProlongArgs<T>> &bt, unsigned g) {
+        k_csr_prolong_batch<T><<<g, TPB, 0, s>>>(bt);
+    }, q));
+    return stream_batch<T, true>(v, s, q);
+}
+
+#define INST_BATCH(T)                                                                                          \
+    template rich_status launch_csr_pre_batch<T>(const std::vector<CsrItem<T>> &, hipStream_t, WorkQueue *);  \
+    template rich_status launch_csr_post_batch<T>(const std::vector<CsrItem<T>> &, hipStream_t, WorkQueue *);
+INST_BATCH(double)
+INST_BATCH(float)
 template rich_status launch_restrict_batch<double>(const std::vector<RestrictItem<double>> &, hipStream_t, WorkQueue *);
 template rich_status launch_restrict_batch<float>(const std::vector<RestrictItem<float>> &, hipStream_t, WorkQueue *);
 

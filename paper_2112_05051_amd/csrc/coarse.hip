@@ -860,13 +860,13 @@ static rich_status vlevel_batch(const std::vector<VItem<T>> &v, int l, hipStream
     // one launch for the simulations whose level takes the same split
     std::vector<char> done(v.size(), 0);
     for (size_t first = 0; first < v.size(); first++) {
-        if (done[first] || l >= v[first].nlev - 1) continue;
+        if (done[first] || !v[first].ordered || l >= v[first].nlev - 1) continue;
         const VLevel &V = v[first].L[l].V;
         std::vector<VArgs<T>> a;
         std::vector<unsigned> nb;
         unsigned lds = 0;
         for (size_t i = first; i < v.size(); i++) {
-            if (done[i] || l >= v[i].nlev - 1) continue;
+            if (done[i] || !v[i].ordered || l >= v[i].nlev - 1) continue;
             const VLevel &W = v[i].L[l].V;
             if (W.np != V.np || W.g != V.g) continue;
             done[i] = 1;
@@ -900,7 +900,7 @@ rich_status launch_vgemv_batch(const std::vector<VItem<T>> &v, hipStream_t s, Wo
     std::vector<GemvArgs<T, T>> a;
     std::vector<unsigned> nb;
     for (const auto &it : v) {
-        a.push_back(gemv_args<T>(it.L, it.nlev, it.Ainv, it.nlev > 2));
+        a.push_back(gemv_args<T>(it.L, it.nlev, it.Ainv, it.ordered));
         nb.push_back(nblocks(it.L[it.nlev - 1].n * 64));
     }
     return launch_batches(a, nb, [&](const Batch<GemvArgs<T, T>> &bt, unsigned g) {

@@ -493,8 +493,20 @@ rich_status vmb_aggregate(const CsrDev &A, double theta, int64_t block, int32_t 
 // r = b - A x0 (x0 = D^{-1} b, the pre-smoothed iterate from zero, stored by the restriction)
 template <class TB, class T>
 rich_status launch_csr_pre(const Level &Lv, const T *val, const T *x0, const TB *b, T *r, hipStream_t s);
-// Batched restrictions from the fine level over several simulations
-// (piecewise-constant prolongators only).
+// Batched V-cycle steps of levels that are not in aggregate order, over several
+// simulations (CSR-stream row blocks and piecewise-constant prolongators only).
+// CsrItem: pre: out = r = b - A x0;  post: out = x = post-smooth(x0 + P xc)
+// (the level's r buffer holds x0 + P xc).
+template <class T>
+struct CsrItem {
+    const Level *Lv;
+    const T *val, *invd, *b, *x0, *xc;
+    T *out;
+};
+template <class T>
+rich_status launch_csr_pre_batch(const std::vector<CsrItem<T>> &items, hipStream_t s, WorkQueue *q = nullptr);
+template <class T>
+rich_status launch_csr_post_batch(const std::vector<CsrItem<T>> &items, hipStream_t s, WorkQueue *q = nullptr);
 template <class T>
 struct RestrictItem {
     const int64_t *mptr;  // the finer level's members lists
@@ -531,11 +543,13 @@ template <class T>
 rich_status launch_vgemv(const Level *L, int nlev, const T *Ainv, hipStream_t s);
 template <class T>
 rich_status launch_vprolong(const Level *L, int nlev, hipStream_t s);
-// the same over several simulations' hierarchies
+// the same over several simulations' hierarchies (those not ordered take part in
+// the coarsest solve only)
 template <class T>
 struct VItem {
     const Level *L;
     int nlev;
+    bool ordered;
     const T *Ainv;
 };
 template <class T>

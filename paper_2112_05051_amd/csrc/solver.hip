@@ -715,11 +715,16 @@ const T *invd0_of(const rich_ctx *h) {
 
 // A simulation can join a batch when its V-cycle has the shape the batched
 // kernels cover: a piecewise-constant hierarchy of two or more levels with a
-// dense coarsest solve, the levels between in aggregate order.
+// dense coarsest solve, the levels between in aggregate order or all with
+// CSR-stream row blocks.
 bool batchable(const rich_ctx *h) {
     const Hierarchy *H = h->H;
     if (!H || H->nlev < 2 || !H->dense || h->O.smoother != RICH_SMOOTH_L1) return false;
-    return H->nlev == 2 ? !H->L[0].prow : H->ordered;
+    for (int l = 0; l < H->nlev - 1; l++) {
+        if (H->L[l].prow) return false;
+        if (l >= 1 && !H->ordered && !H->L[l].rb) return false;
+    }
+    return true;
 }
 
 template <class T>
@@ -730,20 +735,48 @@ rich_status apply_batch(const std::vector<BatchReq> &rq, hipStream_t s, WorkQueu
     std::vector<FineItem<double, T>> f;
     std::vector<RestrictItem<T>> ri;
     std::vector<VItem<T>> vi;
+    std::vector<CsrItem<T>> ci;
+    // the restriction from level l, in natural order below an ordered hierarchy's fine level
+    auto restrict_from = [&](const Hierarchy &H, int l) {
+        const Level &Lf = H.L[l], &Lc = H.L[l + 1];
+        ri.push_back({Lf.vmptr ? Lf.vmptr : Lf.mptr, Lf.vmem ? Lf.vmem : Lf.mem, Lf.vslot, (const T *)Lf.r, (T *)Lc.b, Lc.n,
+                      H.ordered ? (const T *)Lc.V.invd : lvinvd<T>(Lc), l + 1 < H.nlev - 1 ? (T *)Lc.x : nullptr});
+    };
+    // the simulations whose level l takes the separate kernels
+    auto each_plain = [&](int l, auto &&g) {
+        for (const auto &q : rq)
+            if (!q.h->H->ordered && l < q.h->H->nlev - 1) g(*q.h->H, q.h->H->L[l]);
+    };
     // down: fine pre-smoothing + residual, restriction, the levels in order
     for (const auto &q : rq) {
         Hierarchy &H = *q.h->H;
-        const Level &L0 = H.L[0], &L1 = H.L[1];
-        f.push_back({&q.h->P, m4_of<T>(q.h), invd0_of<T>(q.h), q.b, q.bs, nullptr, nullptr, nullptr, (T *)L0.r});
-        ri.push_back({L0.vmptr ? L0.vmptr : L0.mptr, L0.vmem ? L0.vmem : L0.mem, L0.vslot, (const T *)L0.r, (T *)L1.b, L1.n,
-                      (const T *)L1.V.invd, H.nlev > 2 ? (T *)L1.x : nullptr});
-        vi.push_back({H.L, H.nlev, q.h->mixed ? (const T *)(const void *)H.cinvf : (const T *)(const void *)H.cinv});
+        f.push_back({&q.h->P, m4_of<T>(q.h), invd0_of<T>(q.h), q.b, q.bs, nullptr, nullptr, nullptr, (T *)H.L[0].r});
+        restrict_from(H, 0);
+        vi.push_back({H.L, H.nlev, H.ordered, q.h->mixed ? (const T *)(const void *)H.cinvf : (const T *)(const void *)H.cinv});
     }
     RICH_TRY(launch_st_pre_batch<double, T>(f, s, q));
     RICH_TRY(launch_restrict_batch<T>(ri, s, q));
-    for (int l = 1; l < maxlev - 1; l++) RICH_TRY(launch_vdown_batch<T>(vi, l, s, q));
+    for (int l = 1; l < maxlev - 1; l++) {
+        RICH_TRY(launch_vdown_batch<T>(vi, l, s, q));
+        ci.clear();
+        ri.clear();
+        each_plain(l, [&](const Hierarchy &H, const Level &Lv) {
+            ci.push_back({&Lv, lvval<T>(Lv), nullptr, (const T *)Lv.b, (const T *)Lv.x, nullptr, (T *)Lv.r});
+            restrict_from(H, l);
+        });
+        RICH_TRY(launch_csr_pre_batch<T>(ci, s, q));
+        RICH_TRY(launch_restrict_batch<T>(ri, s, q));
+    }
     RICH_TRY(launch_vgemv_batch<T>(vi, s, q));
-    for (int l = maxlev - 2; l >= 1; l--) RICH_TRY(launch_vup_batch<T>(vi, l, s, q));
+    for (int l = maxlev - 2; l >= 1; l--) {
+        RICH_TRY(launch_vup_batch<T>(vi, l, s, q));
+        ci.clear();
+        each_plain(l, [&](const Hierarchy &H, const Level &Lv) {
+            ci.push_back({&Lv, lvval<T>(Lv), lvinvd<T>(Lv), (const T *)Lv.b, (const T *)Lv.x, (const T *)H.L[l + 1].x,
+                          (T *)Lv.x});
+        });
+        RICH_TRY(launch_csr_post_batch<T>(ci, s, q));
+    }
     f.clear();
     std::vector<SpmvItem<T>> sp;
     for (const auto &q : rq) {

@@ -64,3 +64,17 @@ def csr_close(rp1, c1, v1, A2, rtol):
     scale = np.repeat(rowmax, np.diff(A2.indptr))
     err = np.abs(v1 - A2.data)
     assert np.all(err <= rtol * scale), f"max scaled err {np.max(err / np.maximum(scale, 1e-300)):.3e}"
+
+
+def weave_ks(P, scale):
+    """Conductivities of three families of fibres, along z, x and y, that pass each
+    other (each a quarter of the cells), and of the cells between them.  With a
+    harmonic mean the matching follows the fibres, so the coarse levels get long
+    rows and, where the cells between stick to no one, aggregates of thousands of
+    entries."""
+    k, j, i = np.meshgrid(np.arange(P.nz), np.arange(P.ny), np.arange(P.nx), indexing="ij")
+    ks = np.full(k.shape, float(scale[3]))
+    ks[(i % 2 == 0) & (j % 2 == 0)] = scale[0]
+    ks[(j % 2 == 1) & (k % 2 == 0)] = scale[1]
+    ks[(i % 2 == 1) & (k % 2 == 1)] = scale[2]
+    return synth.KS0 * ks.reshape(-1)

@@ -184,3 +184,36 @@ def test_served_results_match_the_oracle(orc):
                 assert sg[f] == s_o[f], (rec.name, f, sg[f], s_o[f])
     assert converged >= 5
     srv.close()
+
+
+@pytest.mark.parametrize("persistent", [False, True])
+def test_fused_large_aggregates(persistent):
+    """Simulations whose coarse aggregates are too large for the aggregate-order
+    kernels (but their rows not too long for the CSR-stream ones) go through the
+    batches, among themselves and together with one in aggregate order; every
+    result equals the lone run bit for bit."""
+    import torch
+
+    import paper_2112_05051_amd as rich
+    from tests.helpers import weave_ks
+    reqs = []
+    for seed, n in ((41, 24), (42, 24), (43, 24)):
+        rec = synth.serving_stream(count=1, seed=seed, sizes=(n,), nsteps=1)[0][1]
+        rec.problem.mean = synth.HARMONIC
+        rec.problem.dt = 10.0
+        rec.options.precision = synth.FP64
+        rec.options.max_newton = 3
+        if seed < 43:
+            rec.options.amg_sweeps, rec.options.amg_max_levels, rec.options.coarse_dense_max = 6, 3, 3200
+            ks = weave_ks(rec.problem, (1e3, 1e1, 1e-1, 1e-3)) * (seed - 40)
+            rec.ks = lambda ks=ks: ks
+        reqs.append(rec)
+    for group in (reqs[:2], reqs):
+        srv = rich.Server(8 << 30, 3, fused=True, persistent=persistent)
+        ids = [srv.submit(rec.problem, rec.options, rec.ks(), rec.p0(), rec.nsteps) for rec in group]
+        srv.run_until_idle()
+        flushes, products = srv.batch_stats()
+        its = sum(t["gmres_its"] for i in ids for t in srv.poll(i)["stats"])
+        assert flushes > 0 and products >= max(flushes, its) > 0, (flushes, products, its)
+        check_alone_equals_mix(rich, torch, srv, group, ids)
+        srv.close()
