@@ -6,7 +6,7 @@ import scipy.sparse as sp
 import scipy.sparse.linalg as spla
 
 import synth
-from tests.helpers import box_problem, csr_close, random_heads, random_ks
+from tests.helpers import box_problem, csr_close, random_heads, random_ks, weave_ks
 
 pytestmark = pytest.mark.gpu
 
@@ -129,3 +129,65 @@ def test_match_sweep_many_rows(rich, torch):
     del row, at, strong, val, rowptr, agg, want
     torch.cuda.empty_cache()
     assert same
+
+
+def level_split(A, agg, nc, tsz):
+    """(np, g, fits) of a smoothed level in aggregate order, from its matrix, aggregates
+    and value size: blocks of np * 512 entries, g partial sums a row, and whether its
+    largest block fits the LDS."""
+    rows = np.diff(A.indptr)
+    ent = np.bincount(agg, weights=rows, minlength=nc).astype(np.int64)
+    most, nnz = int(ent.max()), A.nnz
+    np_ = 4 if nnz >= 2048 * 2048 else 2 if nnz >= 1024 * 2048 else 1
+    if np_ == 4 and most + 3 > 2048 - 256:
+        np_ = 2
+    align, run = (4, 256) if np_ == 4 else (2, 128)
+    chunk = max(512 * np_ - most - align + 1, 256)
+    first = np.concatenate([[0], np.cumsum(ent)])
+    cut = np.append(np.searchsorted(first[:-1], np.arange(-(-nnz // chunk)) * chunk), nc)
+    entries = int((first[cut[1:]] - first[cut[:-1]] // align * align).max())
+    heads = np.concatenate([[0], np.cumsum(np.bincount(agg, minlength=nc))])
+    mean = nnz // A.shape[0]
+    g = 1 if mean < 8 else 2 if mean < 16 else 4 if mean < 32 else 8
+    lds = (-(-entries // run) * run + int(np.diff(heads[cut]).max())) * tsz  # (np = 4: and the lists, at most 16 KB)
+    return np_, g, lds <= 60 << 10
+
+
+# The same on fibre fields, whose long rows and large aggregates reach what the boxes
+# above do not: four and eight partial sums a row (chains of a lane group), blocks of
+# 1024 entries, of 2048 with a column list, of 1024 where an aggregate is too long for
+# the list's sort, and hierarchies that leave the aggregate order because a level does
+# not fit, the first one or one behind others that do.  splits: of the levels smoothed,
+# in FP64 and in FP32; None where one does not fit.
+# One oracle hierarchy serves both precisions (it is built on the FP64 matrix).
+@pytest.mark.parametrize("n,scale,kw,fp64,fp32", [
+    (32, (1, 1e-2, 1e-4, 1e-2), dict(amg_sweeps=4), [(1, 8), (1, 2)], [(1, 8), (1, 2)]),
+    (32, (1, 1e-2, 1e-4, 1e-4), dict(amg_sweeps=4), [(1, 4), (1, 4)], [(1, 4), (1, 4)]),
+    (104, (1, 1e-2, 1e-4, 1e-2), dict(amg_sweeps=4, amg_max_levels=3), [(2, 8)], [(2, 8)]),
+    (128, (1, 1e-2, 1e-4, 1e-2), dict(amg_sweeps=4, amg_max_levels=3), [(4, 8)], [(4, 8)]),
+    (128, (1, 1e-2, 1e-4, 1e-2), dict(amg_sweeps=5, amg_max_levels=3), [(2, 8)], [(2, 8)]),
+    (40, (1, 1e-2, 1e-6, 1e-9), dict(amg_sweeps=5), None, None),
+    (32, (1, 1e-2, 1e-6, 1e-9), dict(amg_sweeps=6), None, [(1, 4), (1, 1)])])
+def test_vcycle_long_rows(rich, torch, orc, n, scale, kw, fp64, fp32):
+    P = box_problem(n, n, n, mean=synth.HARMONIC, dt=1e5)
+    opts = dict(dict(amg_max_levels=4, amg_coarse_size=8, coarse_dense_max=8), **kw)
+    ks, p = dev(torch, weave_ks(P, scale)), dev(torch, np.full(P.n, -50.0))
+    b = np.random.default_rng(64).standard_normal(P.n)
+    amg = None
+    for precision, tol, want in ((synth.FP64, 1e-10, fp64), (synth.MIXED, 1e-5, fp32)):
+        s = rich.Solver(P, synth.Options(precision=precision, **opts), ks)
+        s.assemble(p)
+        if amg is None:
+            rp, col, val = s.export_csr(rich.WHICH_A, 0)
+            amg = orc.AMG(synth.Options(**opts), sp.csr_matrix((val, col, rp), shape=(P.n, P.n)))
+            L = [amg.level(l) for l in range(amg.levels)]
+            xo = amg.apply(b)
+        assert s.levels() == amg.levels
+        got = [level_split(*L[l], L[l + 1][0].shape[0], 8 if precision == synth.FP64 else 4)
+               for l in range(1, amg.levels - 1)]
+        assert got and ([g[:2] for g in got] == want if want else not all(g[2] for g in got)), got
+        x = s.apply_prec(dev(torch, b)).cpu().numpy()
+        assert np.linalg.norm(x - xo) <= tol * np.linalg.norm(xo)
+        s.assemble(p)  # and after a refresh
+        assert np.array_equal(s.apply_prec(dev(torch, b)).cpu().numpy(), x)
+        s.close()
