@@ -204,8 +204,8 @@ FAMILIES = {
     "vc0_pre": ("k_st25<double, float, 0", "fine.hip"),
     "vc0_post": ("k_st25<double, float, 1", "fine.hip"),
     "restrict": ("k_restrict<float>", "amg.hip"),
-    "csr_pre": ("k_csr_stream<2, float, float, false>", "amg.hip"),
-    "csr_post": ("k_csr_stream<2, float, float, true>", "amg.hip"),
+    "vc1_pre": (tuple(f"k_vlevel<{p}, {g}, float, false>" for p in (1, 2, 4) for g in (1, 2, 4, 8)), "coarse.hip"),
+    "vc1_post": (tuple(f"k_vlevel<{p}, {g}, float, true>" for p in (1, 2, 4) for g in (1, 2, 4, 8)), "coarse.hip"),
     "residual": ("k_faces_march<false", "fine.hip"),
     "assembly": ("k_faces_march<true", "fine.hip"),
 }
@@ -220,15 +220,18 @@ def _xcd(blocks):
     return _ceil(blocks, 8) * 8
 
 
-def algorithmic_bytes(name, n, blocks=None, levels=None, mixed=True, shifted=True):
+def algorithmic_bytes(name, n, blocks=None, levels=None, mixed=True, shifted=True, ordered=False):
     """Algorithmic HBM bytes of one launch (the per-row figures of the kernel
     table of the design notes): fine-grid kernels from n alone; the coarse
     kernels of level l from that level's rows and entries, the level found by
     the launch's block count (CSR-stream: one block per 1536 entries, the
     restriction: one block per 256 coarse rows, both padded to a multiple of
     8).  shifted: the J products of GMRES form the s-step power basis (they
-    also read the shift vector).  None when the launch cannot be placed (the
-    block Gram-Schmidt kernels: their basis length is not in the launch)."""
+    also read the shift vector).  ordered: the coarse levels run in aggregate
+    order (the restriction from the fine level also reads each member's 2-byte
+    place).  None when the launch cannot be placed (the block Gram-Schmidt
+    kernels: their basis length is not in the launch; the aggregate-order
+    sweeps: their block count depends on the aggregates)."""
     import re
     t = 4 if mixed else 8
     m = re.search(r"k_(multidot|update_norm)<(\d+)>", name)
@@ -252,7 +255,7 @@ def algorithmic_bytes(name, n, blocks=None, levels=None, mixed=True, shifted=Tru
             nl, nc = levels[l][0], levels[l + 1][0]
             if _xcd(_ceil(nc, 256)) == blocks:
                 x0 = l + 1 < len(levels) - 1  # the coarse pre-smoothed iterate is stored below the coarsest
-                return nl * (t + 4) + nc * (8 + t + (2 * t if x0 else 0))
+                return nl * (t + 4 + (2 if ordered else 0)) + nc * (8 + t + (2 * t if x0 else 0))
         return None
     m = re.search(r"k_csr_stream<\d+, float, float, (true|false)>", name)
     if m:
@@ -285,8 +288,8 @@ def pmc_summary(fetch_csv, write_csv, n, digests=None, levels=None, info=None):
     `digests` are the source digests the profiled run printed, `levels` its
     hierarchy ([rows, entries] per level), `info` its JSON line: its options
     say whether the J products were shifted, and its per-kernel event timings
-    give the block Gram-Schmidt kernels' algorithmic bytes (the library's own
-    count over the same launches)."""
+    give the algorithmic bytes of the block Gram-Schmidt kernels and of level 1's
+    sweeps in aggregate order (the library's own count over the same launches)."""
     digests = digests or source_digests()
     info = info or {}
     shifted = info.get("options", {}).get("gmres_block", 1) > 1
@@ -310,12 +313,23 @@ def pmc_summary(fetch_csv, write_csv, n, digests=None, levels=None, info=None):
              f"{'kernel':52s} {'blocks':>7s} {'launches':>8s} {'fetch MB':>9s} {'write MB':>9s} {'alg MB':>9s} "
              f"{'traffic/alg':>11s}"]
     rows = []
+    kern = info.get("kernels", {})
+    ordered = any("k_vlevel<" in k for k, _ in vals["FETCH_SIZE"])
+    # level 1's sweeps: of each direction the launches of the most blocks
+    level1 = {}
+    for k, grid in vals["FETCH_SIZE"]:
+        for fam in ("vc1_pre", "vc1_post"):
+            if any(p in k for p in FAMILIES[fam][0]) and grid > level1.get(fam, ("", 0))[1]:
+                level1[fam] = (k, grid)
     for (k, grid), lst in vals["FETCH_SIZE"].items():
         w = vals["WRITE_SIZE"].get((k, grid), [0.0])
         f_b = cal["FETCH_SIZE"] * sum(lst) / len(lst)
         w_b = cal["WRITE_SIZE"] * sum(w) / len(w)
         blocks = grid // 256 if grid else None
-        alg = algorithmic_bytes(k, n, blocks, levels, shifted=shifted)
+        alg = algorithmic_bytes(k, n, blocks, levels, shifted=shifted, ordered=ordered)
+        for fam, at in level1.items():
+            if at == (k, grid) and kern.get(fam, {}).get("launches") == len(lst):
+                alg = kern[fam]["bytes_per_launch"]
         rows.append((k, blocks, len(lst), f_b, w_b, alg))
     rows.sort(key=lambda r: -(r[3] + r[4]) * r[2])
     for k, blocks, cnt, f_b, w_b, alg in rows[:45]:
@@ -323,7 +337,6 @@ def pmc_summary(fetch_csv, write_csv, n, digests=None, levels=None, info=None):
         lines.append(f"{short:52s} {blocks if blocks else 0:7d} {cnt:8d} {f_b / 1e6:9.2f} {w_b / 1e6:9.2f} "
                      f"{(alg / 1e6 if alg else float('nan')):9.2f} {((f_b + w_b) / alg if alg else float('nan')):11.3f}")
     lines += ["", "family      launches  traffic/alg  source digest"]
-    kern = info.get("kernels", {})
     for fam, (prefix, src) in FAMILIES.items():
         prefixes = prefix if isinstance(prefix, tuple) else (prefix,)
         named = [r for r in rows if any(p in r[0] for p in prefixes)]

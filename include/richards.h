@@ -351,8 +351,8 @@ rich_status rich_match_sweep_noalloc(int64_t n, const int64_t *rowptr_dev, const
 #define RICH_K_VC0_PRE 1      /* fine level: pre-smooth from zero + residual */
 #define RICH_K_VC0_POST 2     /* fine level: prolongation + post-smooth */
 #define RICH_K_VC0_RESTRICT 3 /* fine -> level 1 restriction */
-#define RICH_K_VC1_PRE 4      /* level 1 (CSR): pre-smooth + residual */
-#define RICH_K_VC1_POST 5     /* level 1 (CSR): prolongation + post-smooth */
+#define RICH_K_VC1_PRE 4      /* level 1: residual of the pre-smoothed iterate; in aggregate order also its restriction */
+#define RICH_K_VC1_POST 5     /* level 1: post-smooth; prolongation too unless in aggregate order (the level below did it) */
 #define RICH_K_MULTIDOT 6     /* Gram-Schmidt dot block V^T w (first pass) */
 #define RICH_K_UPDATE 7       /* w -= V h with ||w||^2 (first pass) */
 #define RICH_K_RESIDUAL 8     /* Phi(p) */

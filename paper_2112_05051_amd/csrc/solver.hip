@@ -560,7 +560,8 @@ rich_status vcycle(rich_ctx *h, const double *b, const double *bs, T *z, double 
     }));
     const Level &L0 = H.L[0];
     // (+ the coarse pre-smoothed iterate and the inverse diagonal it needs, below the coarsest level)
-    double rbytes = (L0.prow ? (double)L0.pnnz * (4 + 2 * t) + n1 * (8 + t) : n0 * (t + 4) + n1 * (8 + t)) +
+    double rbytes = (L0.prow ? (double)L0.pnnz * (4 + 2 * t) + n1 * (8 + t)
+                             : n0 * (t + 4 + (L0.vslot ? 2 : 0)) + n1 * (8 + t)) +
                     (H.nlev > 2 ? 2 * t * n1 : 0.0);
     // each restriction also stores the next level's pre-smoothed iterate
     // x0 = D^{-1} b in its x buffer, except for the coarsest level

@@ -81,6 +81,30 @@ def test_pmc_summary_calibration_and_family_ratio(tmp_path):
     assert fam[0][4] == "fine.hip" and fam[0][5] == bench.source_digest("fine.hip")
 
 
+def test_aggregate_order_sweeps_have_a_family(tmp_path):
+    """Level 1's sweeps in aggregate order take their bytes from the library's count;
+    the launches of the level below stay without; with them the restriction counts
+    2 bytes more a fine row."""
+    n0, n1, n2 = LEVELS[0][0], LEVELS[1][0], LEVELS[2][0]
+    b01 = -(-(-(-n1 // 256)) // 8) * 8
+    name = "k_restrict<float>(x)"
+    assert bench.algorithmic_bytes(name, N, b01, LEVELS, ordered=True) == n0 * 10 + n1 * 20
+    kib = 1024.0
+    rows = [("k_vlevel<4, 2, float, false>(V)", 256 * 1000, 500.0), ("k_vlevel<4, 2, float, false>(V)", 256 * 1000, 500.0),
+            ("k_vlevel<4, 2, float, false>(V)", 256 * 80, 9.0), ("k_vlevel<1, 1, float, true>(V)", 256 * 1000, 300.0),
+            (name, 256 * b01, (n0 * 10 + n1 * 20) / 2 / kib)]
+    _write_counters(tmp_path / "f.csv", "FETCH_SIZE", [("copyBuffer", 0, (1 << 30) / kib)] + rows)
+    _write_counters(tmp_path / "w.csv", "WRITE_SIZE", [("copyBuffer", 0, (1 << 30) / kib)] + rows)
+    info = {"kernels": {"vc1_pre": {"launches": 2, "bytes_per_launch": 800 * kib},
+                        "vc1_post": {"launches": 3, "bytes_per_launch": 600 * kib}}}
+    text = bench.pmc_summary(str(tmp_path / "f.csv"), str(tmp_path / "w.csv"), N, levels=LEVELS, info=info)
+    fam = {ln.split()[1]: ln.split() for ln in text.splitlines() if ln.startswith("family ")}
+    assert fam["vc1_pre"][2] == "2" and float(fam["vc1_pre"][3]) == pytest.approx(1.25, abs=1e-4)
+    assert fam["vc1_pre"][4:] == ["coarse.hip", bench.source_digest("coarse.hip")]
+    assert "vc1_post" not in fam  # the library timed other launches than the run's
+    assert float(fam["restrict"][3]) == pytest.approx(1.0, abs=1e-4)
+
+
 def test_stats_and_gaps_summaries(tmp_path):
     st = tmp_path / "stats.csv"
     with open(st, "w", newline="") as f:
