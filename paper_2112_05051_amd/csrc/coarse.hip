@@ -634,10 +634,17 @@ rich_status vlevel_order(Level &Lv, int64_t nc, bool mixed, DevAlloc &mem, bool 
     HIP_TRY(hipMemcpyAsync(hm, most, sizeof(int), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     // A block takes whole aggregates from a stretch of `chunk` entries, so that
-    // with the last one's overhang it fills 512 np: np = 4 where that leaves
-    // eight blocks a CU, less on smaller levels, where the blocks are too few
-    // and a block's latency counts.
-    V.np = Lv.nnz >= (int64_t)2048 * 2048 ? 4 : Lv.nnz >= (int64_t)1024 * 2048 ? 2 : 1;
+    // with the last one's overhang it fills 512 np.  Small levels have too few
+    // blocks for more than np = 1 (a block's latency counts); the column lists of
+    // np = 4 pay where the gather has outgrown the caches, in FP64 later (its
+    // values' LDS doubles and leaves fewer blocks a CU).  Both sweeps of level 1, us,
+    // by its entries, one np against the next:
+    //   FP32  0.37 M 8.3 / 8.3, 0.56 M 9.0 / 8.9, 0.80 M 10.7 / 9.6, 1.9 M 17.2 / 14.9
+    //   FP64  0.37 M 8.6 / 8.6, 0.56 M 9.3 / 9.7, 0.80 M 11.8 / 10.5, 1.9 M 19.8 / 16.9
+    //   FP32 (2 / 4)  4.5 M 25.0 / 26.0, 10.3 M 44.6 / 46.4, 13.6 M 64.9 / 59.6, 36.6 M 203 / 155
+    //   FP64 (2 / 4)  4.5 M 28.4 / 40.2, 15.4 M 115 / 124, 19.6 M 152 / 153, 24.5 M 193 / 187
+    const int64_t local = (int64_t)(mixed ? 12 : 20) << 20, pairs2 = (int64_t)5 << 17;
+    V.np = Lv.nnz >= local ? V_LOCAL : Lv.nnz >= pairs2 ? 2 : 1;
     // Where a large level's blocks would not fit the column sort, two.
     if (V.np == V_LOCAL && hm[0] + 3 > V_SORT - 256) V.np = 2;
     const int align = V.np == V_LOCAL ? 4 : 2, run = V.np == V_LOCAL ? 256 : 128;

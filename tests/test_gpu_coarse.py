@@ -138,7 +138,7 @@ def level_split(A, agg, nc, tsz):
     rows = np.diff(A.indptr)
     ent = np.bincount(agg, weights=rows, minlength=nc).astype(np.int64)
     most, nnz = int(ent.max()), A.nnz
-    np_ = 4 if nnz >= 2048 * 2048 else 2 if nnz >= 1024 * 2048 else 1
+    np_ = 4 if nnz >= (12 if tsz == 4 else 20) << 20 else 2 if nnz >= 5 << 17 else 1
     if np_ == 4 and most + 3 > 2048 - 256:
         np_ = 2
     align, run = (4, 256) if np_ == 4 else (2, 128)
@@ -163,9 +163,9 @@ def level_split(A, agg, nc, tsz):
 @pytest.mark.parametrize("n,scale,kw,fp64,fp32", [
     (32, (1, 1e-2, 1e-4, 1e-2), dict(amg_sweeps=4), [(1, 8), (1, 2)], [(1, 8), (1, 2)]),
     (32, (1, 1e-2, 1e-4, 1e-4), dict(amg_sweeps=4), [(1, 4), (1, 4)], [(1, 4), (1, 4)]),
-    (104, (1, 1e-2, 1e-4, 1e-2), dict(amg_sweeps=4, amg_max_levels=3), [(2, 8)], [(2, 8)]),
-    (128, (1, 1e-2, 1e-4, 1e-2), dict(amg_sweeps=4, amg_max_levels=3), [(4, 8)], [(4, 8)]),
-    (128, (1, 1e-2, 1e-4, 1e-2), dict(amg_sweeps=5, amg_max_levels=3), [(2, 8)], [(2, 8)]),
+    (72, (1, 1e-2, 1e-4, 1e-2), dict(amg_sweeps=4, amg_max_levels=3), [(2, 8)], [(2, 8)]),
+    (214, (1, 1e-2, 1e-4, 1e-2), dict(amg_sweeps=4, amg_max_levels=3), [(4, 8)], [(4, 8)]),
+    (184, (1, 1e-2, 1e-4, 1e-2), dict(amg_sweeps=5, amg_max_levels=3), [(2, 8)], [(2, 8)]),
     (40, (1, 1e-2, 1e-6, 1e-9), dict(amg_sweeps=5), None, None),
     (32, (1, 1e-2, 1e-6, 1e-9), dict(amg_sweeps=6), None, [(1, 4), (1, 1)])])
 def test_vcycle_long_rows(rich, torch, orc, n, scale, kw, fp64, fp32):
