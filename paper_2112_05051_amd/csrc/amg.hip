@@ -1370,9 +1370,11 @@ rich_status galerkin_sources(const CsrDev &A, const int32_t *agg, const int64_t 
     if (C.n == 0) return RICH_OK;
     DevAlloc tmp;
     int64_t *cnt, *ptr, *stmp;
-    RICH_TRY(tmp.get(&cnt, C.nnz));
-    RICH_TRY(tmp.get(&ptr, C.nnz + 1));
-    RICH_TRY(tmp.get(&stmp, scan_tmp_size(C.nnz)));
+    Slab scratch;
+    scratch.add(&cnt, C.nnz);
+    scratch.add(&ptr, C.nnz + 1);
+    scratch.add(&stmp, scan_tmp_size(C.nnz));
+    RICH_TRY(scratch.get(tmp));
     const StencilIndex ix{g ? g->nx : 0, g ? g->ny : 0, g ? g->nz : 0};
     const unsigned nb = nblocks(C.n, 64);
     k_gal_sources<false><<<nb, 64, 0, s>>>(C.n, A.n, ix, mptr, mem, A.rowptr, A.col, agg, C.rowptr, C.col, cnt,

@@ -18,7 +18,6 @@
 #include <algorithm>
 #include <cstring>
 #include <type_traits>
-#include <utility>
 #include <vector>
 
 #include "common.hpp"
@@ -579,30 +578,6 @@ constexpr size_t V_LDS_MAX = 60 << 10;
 // 256-entry ones from a multiple of four).
 constexpr int64_t V_PAD = 256;
 
-// Arrays of one allocation, each on a 256-byte boundary (a hierarchy's many
-// allocations take up to 50 us each to give back: 0.6 ms less at 64^3).
-class Slab {
-    std::vector<std::pair<void **, size_t>> parts_;
-
-public:
-    template <class T>
-    void add(T **p, int64_t count) {
-        parts_.push_back({(void **)p, ((size_t)count * sizeof(T) + 255) & ~(size_t)255});
-    }
-    rich_status get(DevAlloc &mem, void **slab) {
-        size_t all = 0;
-        for (auto &q : parts_) all += q.second;
-        char *base;
-        RICH_TRY(mem.get(&base, all));
-        *slab = base;
-        for (auto &q : parts_) {
-            *q.first = base;
-            base += q.second;
-        }
-        return RICH_OK;
-    }
-};
-
 rich_status vlevel_order(Level &Lv, int64_t nc, bool mixed, DevAlloc &mem, bool *ok, hipStream_t s) {
     *ok = false;
     const size_t tsz = mixed ? sizeof(float) : sizeof(double);
@@ -614,11 +589,12 @@ rich_status vlevel_order(Level &Lv, int64_t nc, bool mixed, DevAlloc &mem, bool 
     int64_t *len, *ptr, *stmp;
     int *most;
     int hm[4] = {0, 0, 0, 0};
-    RICH_TRY(tmp.get(&len, Lv.n));
-    RICH_TRY(tmp.get(&ptr, Lv.n + 1));
-    RICH_TRY(tmp.get(&stmp, scan_tmp_size(Lv.n)));
-    RICH_TRY(tmp.get(&most, 4));
-    Slab rows, entries;
+    Slab scratch, rows, entries;
+    scratch.add(&len, Lv.n);
+    scratch.add(&ptr, Lv.n + 1);
+    scratch.add(&stmp, scan_tmp_size(Lv.n));
+    scratch.add(&most, 4);
+    RICH_TRY(scratch.get(tmp));
     rows.add(&V.pos, Lv.n);
     rows.add(&V.ptr, Lv.n + 1);
     if (mixed) rows.add((float **)&V.invd, Lv.n);
@@ -707,15 +683,18 @@ rich_status vlevel_child(Level &Lv, const Level &Lf, bool ordered, DevAlloc &mem
 rich_status vlevel_fine(Level &L0, const Level &L1, DevAlloc &mem, hipStream_t s) {
     DevAlloc tmp;
     int64_t *len, *stmp;
-    RICH_TRY(tmp.get(&len, L1.n));
-    RICH_TRY(tmp.get(&stmp, scan_tmp_size(L1.n)));
-    RICH_TRY(mem.get(&L0.vmptr, L1.n + 1));
-    RICH_TRY(mem.get(&L0.vmem, L0.n));
+    Slab scratch, lists;
+    scratch.add(&len, L1.n);
+    scratch.add(&stmp, scan_tmp_size(L1.n));
+    RICH_TRY(scratch.get(tmp));
+    lists.add(&L0.vmptr, L1.n + 1);
+    lists.add(&L0.vmem, L0.n);
+    lists.add(&L0.vslot, L0.n);
+    RICH_TRY(lists.get(mem));
     k_v_count<<<nblocks(L1.n), TPB, 0, s>>>(L1.n, L1.mem, L0.mptr, len);
     LAUNCH_CHECK();
     RICH_TRY(scan_exclusive_i64(len, L0.vmptr, L1.n, stmp, s));
     k_v_members<<<nblocks(L1.n), TPB, 0, s>>>(L1.n, L1.mem, L0.mptr, L0.mem, L0.vmptr, L0.vmem);
-    RICH_TRY(mem.get(&L0.vslot, L0.n));
     k_v_sort<<<nblocks(L1.n, RESTRICT_TPB), 256, 0, s>>>(L1.n, L0.vmptr, L0.vmem, L0.vslot);
     LAUNCH_CHECK();
     HIP_TRY(hipStreamSynchronize(s));  // tmp is freed on return

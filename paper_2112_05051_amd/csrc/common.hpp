@@ -5,6 +5,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/richards.h"
@@ -200,6 +201,30 @@ struct DevAlloc {
     ~DevAlloc() {
         for (void *p : ptrs)
             if (p) (void)hipFree(p);
+    }
+};
+
+// Arrays of one allocation, each on a 256-byte boundary (a hierarchy's many
+// allocations take up to 50 us each to give back: 0.6 ms less at 64^3).
+class Slab {
+    std::vector<std::pair<void **, size_t>> parts_;
+
+public:
+    template <class T>
+    void add(T **p, int64_t count) {
+        parts_.push_back({(void **)p, ((size_t)count * sizeof(T) + 255) & ~(size_t)255});
+    }
+    rich_status get(DevAlloc &mem, void **slab = nullptr) {
+        size_t all = 0;
+        for (auto &q : parts_) all += q.second;
+        char *base;
+        RICH_TRY(mem.get(&base, all));
+        if (slab) *slab = base;
+        for (auto &q : parts_) {
+            *q.first = base;
+            base += q.second;
+        }
+        return RICH_OK;
     }
 };
 
