@@ -161,9 +161,9 @@ __device__ inline void mean_of(const Phys &P, int axis, int dir, double pc, cons
     }
 }
 
-// Theta of C cells per thread, all C heads loaded before the first law: at
-// 256^3 one cell a thread took 95 us, four take 82 (67 us of FP64 issue, 54 us
-// of bytes).
+// Theta of C cells per thread, all C heads loaded before the first law: more
+// bytes in flight on grids that outgrow the last-level cache (at 384^3 four take
+// 271 us, one 293; 184 us of bytes, 226 of FP64 issue).
 template <int C>
 __global__ void k_theta(Phys P, uint32_t n, const double *__restrict__ p, double *__restrict__ th) {
     uint32_t c[C];
@@ -558,7 +558,7 @@ __global__ void __launch_bounds__(FT_TPB) k_faces_tiled(Phys P, int kz, const do
 // from the same values in the same order (lower cell first), so they agree
 // bitwise.  Each cell adds its faces in the order -x, +x, -y, +y, -z, +z.
 // Bounds: FP64 issue (a log, two exp and the divisions of a cell: about 180 us
-// of a residual at 256^3) and the loads' latency, against 97 us for the
+// of a residual at 256^3) and the loads' latency, against 109 us for the
 // residual's bytes.  So the next plane's heads, K_s and theta are loaded a plane
 // ahead; the planes alternate between two LDS buffers, one barrier each; the
 // 64 ring cells (no corners) are one wave's work, each plane another wave's;
@@ -1413,9 +1413,9 @@ static inline uint32_t ncells(const Phys &P) { return (uint32_t)((int64_t)P.nx *
 
 rich_status launch_theta(const Phys &P, const double *p, double *theta, hipStream_t s) {
     uint32_t n = ncells(P);
-    // four cells a thread once that leaves every CU a full set of wavefronts
-    // (2048 threads x 256 CUs x 4); below, one: 16^3 took 1.5 us longer with four
-    if (n >= (1u << 21))
+    // kernel us, one / four cells a thread: 320^3 174 / 163, 384^3 293 / 271, 256^3
+    // 79 / 79; of the call, 160^3 38.1 / 39.1, 128^3 28.6 / 29.6, 16^3 1.5 apart
+    if (n >= (1u << 24))
         k_theta<4><<<nblocks(((int64_t)n + 3) / 4), TPB, 0, s>>>(P, n, p, theta);
     else
         k_theta<1><<<nblocks(n), TPB, 0, s>>>(P, n, p, theta);

@@ -67,6 +67,17 @@ def test_theta_cells_per_thread(rich, torch, orc, shape):
     assert np.max(np.abs(th - th_o)) <= 1e-13 * np.max(np.abs(th_o))
 
 
+# On both sides of the 2^24 cells from which a thread takes four.
+@pytest.mark.parametrize("shape", [(255, 257, 256), (257, 255, 257)])
+def test_theta_on_both_sides(rich, torch, orc, shape):
+    P = box_problem(*shape)
+    p = random_heads(P.n, 82, saturated_fraction=0.05)
+    s = rich.Solver(P, synth.Options(gmres_restart=1), torch.full((P.n,), synth.KS0, dtype=torch.float64, device="cuda"))
+    th = s.theta(dev(torch, p)).cpu().numpy()
+    th_o = orc.theta(P, p)
+    assert np.max(np.abs(th - th_o)) <= 1e-13 * np.max(np.abs(th_o))
+
+
 # Rows too short for the tiled smoother, on both sides of the 2^18 cells up to which
 # one launch prolongates and smooths, and rows long enough for it; the result is
 # stored straight into x, or through scratch where x is b or overlaps it.
