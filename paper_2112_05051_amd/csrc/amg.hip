@@ -1118,7 +1118,8 @@ __global__ void __launch_bounds__(256, 3) k_bgj_update(double *__restrict__ D, i
     }
     const int tid = threadIdx.x, w = tid / 64, l = tid % 64, li = l % 16, lk = l / 16;
     // a wave's rows of S go straight into its A operands; R is shared through
-    // LDS (35 KB: three blocks a CU); the tile's own entries are needed last
+    // LDS (36.5 KB: four blocks would fit a CU, the registers of the launch bounds
+    // hold it at three); the tile's own entries are needed last
     typedef double d2 __attribute__((ext_vector_type(2)));
     d2 sq[8], rq[8];
     double d[4][4];
