@@ -579,12 +579,7 @@ constexpr int F_TPB = 256;
 // remainder must not form 0 * inf, so b is then kept as 0.
 struct Recip {
     double b, y;
-    // (the same in every lane: kept in scalar registers)
-    __device__ explicit Recip(double v) : b(uniform(isinf(v) ? 0.0 : v)), y(uniform(1.0 / v)) {}
-    static __device__ double uniform(double v) {
-        return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
-                                __builtin_amdgcn_readfirstlane(__double2loint(v)));
-    }
+    explicit Recip(double v) : b(std::isinf(v) ? 0.0 : v), y(1.0 / v) {}
     __device__ __forceinline__ double div(double a) const {
         const double q0 = a * y;
         const double q1 = fma(fma(-q0, b, a), y, q0);
@@ -592,9 +587,21 @@ struct Recip {
         return isfinite(q0) ? q2 : q0;
     }
 };
+// The grid's constants, made on the host (kernel arguments: scalar registers).
+struct Recips {
+    Recip dx2, dy2, dz2, d2z, ddt;
+    explicit Recips(const Phys &P)
+        : dx2(P.hx * P.hx), dy2(P.hy * P.hy), dz2(P.hz * P.hz), d2z(2.0 * P.hz), ddt(P.dt) {}
+    // A time step below 5.6e-309, or a spacing below 7.5e-155, has an infinite
+    // reciprocal, and 0 / b would be 0 * inf.
+    bool finite() const {
+        return std::isfinite(dx2.y) && std::isfinite(dy2.y) && std::isfinite(dz2.y) && std::isfinite(d2z.y) &&
+               std::isfinite(ddt.y);
+    }
+};
 
 template <bool JAC, int FX, int FY>
-__global__ void __launch_bounds__(F_TPB, JAC ? 3 : 4) k_faces_march(Phys P, int kz, const double *__restrict__ Ks,
+__global__ void __launch_bounds__(F_TPB, JAC ? 3 : 4) k_faces_march(Phys P, Recips rc, int kz, const double *__restrict__ Ks,
                                                        const double *__restrict__ p,
                                                        const double *__restrict__ th_old, double *__restrict__ F,
                                                        double *__restrict__ J7, double *__restrict__ M4,
@@ -611,7 +618,7 @@ __global__ void __launch_bounds__(F_TPB, JAC ? 3 : 4) k_faces_march(Phys P, int 
     const bool own = i < P.nx && j < P.ny;
     const uint32_t nxy = (uint32_t)P.nx * (uint32_t)P.ny, n = nxy * (uint32_t)P.nz;
     const int me = (ty + 1) * F_RX + (tx + 1);
-    const Recip dx2(P.hx * P.hx), dy2(P.hy * P.hy), dz2(P.hz * P.hz), d2z(2.0 * P.hz), ddt(P.dt);
+    const Recip &dx2 = rc.dx2, &dy2 = rc.dy2, &dz2 = rc.dz2, &d2z = rc.d2z, &ddt = rc.ddt;
     // ring cell of this lane: the row below, the row above, the left and right
     // columns; with eight rows the columns alone (lanes past them have none)
     const int rs = FY == 8 ? 2 + (lane >> 3) : lane >> 4, rt = FY == 8 ? lane & 7 : lane & 15;
@@ -1447,14 +1454,14 @@ static bool faces_grid(const Phys &P, dim3 *g, int *kz) {
 // The marching kernels' launch: planes per block (at most 64) by the rounds the
 // blocks run in, as in kz25; false when the grid does not fit the launch limits.
 template <bool JAC, int FX, int FY, class... Args>
-static bool march(const Phys &P, hipStream_t s, Args... args) {
+static bool march(const Phys &P, const Recips &rc, hipStream_t s, Args... args) {
     static const int fit = blocks_at_once(k_faces_march<JAC, FX, FY>, F_TPB);
     const int64_t tx = (P.nx + FX - 1) / FX, ty = (P.ny + FY - 1) / FY;
     if (tx > 0x7fffffff || ty > 65535) return false;
     const int kz = planes_per_block(tx * ty, P.nz, 64, fit);
     const int64_t tz = (P.nz + kz - 1) / kz;
     if (tz > 65535) return false;
-    k_faces_march<JAC, FX, FY><<<dim3((unsigned)tx, (unsigned)ty, (unsigned)tz), F_TPB, 0, s>>>(P, kz, args...);
+    k_faces_march<JAC, FX, FY><<<dim3((unsigned)tx, (unsigned)ty, (unsigned)tz), F_TPB, 0, s>>>(P, rc, kz, args...);
     return true;
 }
 
@@ -1469,19 +1476,11 @@ static bool thin(const Phys &P) {
     return w <= 2 && ncells(P) >= 8192u * w * w;
 }
 
-// Whether Recip divides by the grid's constants: their reciprocals are finite.
-// (A time step below 5.6e-309, or a spacing below 7.5e-155, has an infinite one, and
-// 0 / b is then 0 * inf; the kernels of one thread per cell divide.)
-static bool reciprocals(const Phys &P) {
-    for (double b : {P.hx * P.hx, P.hy * P.hy, P.hz * P.hz, 2.0 * P.hz, P.dt})
-        if (!std::isfinite(1.0 / b)) return false;
-    return true;
-}
-
 template <bool JAC, class... Args>
 static bool launch_march(const Phys &P, hipStream_t s, Args... args) {
-    if (has_integral(P) || thin(P) || !reciprocals(P)) return false;
-    return P.ny <= 8 && P.nx > 16 ? march<JAC, 32, 8>(P, s, args...) : march<JAC, 16, 16>(P, s, args...);
+    const Recips rc(P);  // (infinite reciprocals: the kernels of one thread per cell divide)
+    if (has_integral(P) || thin(P) || !rc.finite()) return false;
+    return P.ny <= 8 && P.nx > 16 ? march<JAC, 32, 8>(P, rc, s, args...) : march<JAC, 16, 16>(P, rc, s, args...);
 }
 
 rich_status launch_residual(const Phys &P, const double *Ks, const double *p, const double *theta_old,
