@@ -259,9 +259,7 @@ rich_status level_invd(rich_ctx *h, Level &Lv) {
                     h->s);
 }
 
-rich_status build_hierarchy(rich_ctx *h) {
-    delete h->H;
-    h->H = new Hierarchy();
+rich_status build_levels(rich_ctx *h) {
     Hierarchy &H = *h->H;
     hipStream_t s = h->s;
     const Phys &P = h->P;
@@ -464,6 +462,20 @@ rich_status build_hierarchy(rich_ctx *h) {
         H.L[0].mem = nullptr;
     }
     return RICH_OK;
+}
+
+// A set-up that fails (no memory, a matrix that is not positive definite) leaves
+// no hierarchy: a half-built one has arrays missing that a later refresh or cycle
+// would write.
+rich_status build_hierarchy(rich_ctx *h) {
+    delete h->H;
+    h->H = new Hierarchy();
+    const rich_status st = build_levels(h);
+    if (st != RICH_OK) {
+        delete h->H;
+        h->H = nullptr;
+    }
+    return st;
 }
 
 // After a rebuild of M: the fine level's smoother data come with the
@@ -1582,7 +1594,7 @@ rich_status newton_step(rich_ctx *h, rich_step_stats_t *st) {
         ev.since_build = h->since_build;
         ev.mxstep = mxstep;
         ev.f0 = f0;
-        if (!h->have_J) ev.reason |= RICH_RB_NOJ;
+        if (!h->have_J || !h->H) ev.reason |= RICH_RB_NOJ;
         else if (h->since_build >= h->O.msbset) ev.reason |= RICH_RB_MSBSET;
         if (prev_step > 1.5) ev.reason |= RICH_RB_BIGSTEP;
         if (retry) ev.reason |= RICH_RB_RETRY;

@@ -191,3 +191,33 @@ def test_vcycle_long_rows(rich, torch, orc, n, scale, kw, fp64, fp32):
         s.assemble(p)  # and after a refresh
         assert np.array_equal(s.apply_prec(dev(torch, b)).cpu().numpy(), x)
         s.close()
+
+
+# A set-up that fails (here on heads that are not numbers: no positive pivot in the
+# coarsest matrix) leaves the handle without a hierarchy, and the next assembly builds
+# one, as a new handle's does.
+@pytest.mark.parametrize("precision", [synth.FP64, synth.MIXED])
+@pytest.mark.parametrize("kw", [dict(), dict(amg_coarse_size=64), dict(amg_max_levels=1)])
+def test_assembly_after_a_failed_setup(rich, torch, kw, precision):
+    P = box_problem(12, 11, 9, dt=10.0)
+    opts = synth.Options(precision=precision, **kw)
+    ks, p = dev(torch, random_ks(P, 65)), random_heads(P.n, 66, -70, -30)
+    b = dev(torch, np.random.default_rng(67).standard_normal(P.n))
+    bad = p.copy()
+    bad[P.n // 2] = np.nan
+    s, fresh = rich.Solver(P, opts, ks), rich.Solver(P, opts, ks)
+    with pytest.raises(rich.RichError) as e:
+        s.assemble(dev(torch, bad))
+    assert e.value.status == -9  # not positive definite
+    assert s.levels() == 0
+    with pytest.raises(rich.RichError) as e:
+        s.apply_prec(b)
+    assert e.value.status == -11  # not valid in this state
+    for handle in (s, fresh):
+        handle.assemble(dev(torch, p))
+    assert s.levels() == fresh.levels()
+    assert torch.equal(s.apply_prec(b), fresh.apply_prec(b))
+    for handle in (s, fresh):
+        handle.set_state(dev(torch, p))
+    assert [t["gmres_its"] for t in s.step(1)] == [t["gmres_its"] for t in fresh.step(1)]
+    assert torch.equal(s.get_state(), fresh.get_state())
