@@ -1420,9 +1420,11 @@ static inline uint32_t ncells(const Phys &P) { return (uint32_t)((int64_t)P.nx *
 
 rich_status launch_theta(const Phys &P, const double *p, double *theta, hipStream_t s) {
     uint32_t n = ncells(P);
-    // kernel us, one / four cells a thread: 320^3 174 / 163, 384^3 293 / 271, 256^3
-    // 79 / 79; of the call, 160^3 38.1 / 39.1, 128^3 28.6 / 29.6, 16^3 1.5 apart
-    if (n >= (1u << 24))
+    // us of the call, one / four cells a thread, on heads that are not in the caches:
+    // 128^3 25.2 / 26.1, 160^3 35.1 / 35.8, 176^3 42.0 / 42.4, 200^3 56.1 / 54.2,
+    // 232^3 82.8 / 78.5, 250^3 102 / 94 (in the caches one is ahead up to 216^3); 16^3
+    // 1.5 apart
+    if (n >= (1u << 23))
         k_theta<4><<<nblocks(((int64_t)n + 3) / 4), TPB, 0, s>>>(P, n, p, theta);
     else
         k_theta<1><<<nblocks(n), TPB, 0, s>>>(P, n, p, theta);

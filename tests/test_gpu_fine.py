@@ -67,8 +67,8 @@ def test_theta_cells_per_thread(rich, torch, orc, shape):
     assert np.max(np.abs(th - th_o)) <= 1e-13 * np.max(np.abs(th_o))
 
 
-# On both sides of the 2^24 cells from which a thread takes four.
-@pytest.mark.parametrize("shape", [(255, 257, 256), (257, 255, 257)])
+# On both sides of the 2^23 cells from which a thread takes four.
+@pytest.mark.parametrize("shape", [(255, 257, 128), (257, 255, 129)])
 def test_theta_on_both_sides(rich, torch, orc, shape):
     P = box_problem(*shape)
     p = random_heads(P.n, 82, saturated_fraction=0.05)
